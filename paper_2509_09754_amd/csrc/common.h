@@ -50,14 +50,22 @@ inline void discard_stale_error() { (void)hipGetLastError(); }
 const lava_tuning& tuning();
 
 // Order-preserving map float -> uint32 used by the selection (larger score = larger key); -0 and +0
-// coincide.  The selection's first digit is the key's top kSelDigit0Bits bits.
+// coincide.
 __device__ __forceinline__ unsigned int score_key(float f) {
-  unsigned int b = __float_as_uint(f);
-  if ((b << 1) == 0u) b = 0u;
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  const unsigned int b = __float_as_uint(f + 0.0f);          // -0 + 0 = +0; every other value stays as it is
+  return b ^ ((unsigned int)((int)b >> 31) | 0x80000000u);
 }
-constexpr int kSelBins = 2048;
-constexpr int kSelDigit0Shift = 21;
+constexpr int kSelBins = 2048;              // a selection region's histogram area is 3 * kSelBins words
+// The selection's first digit: 1024 bins, each a sixteenth of an octave of the score, for scores from 2^-44
+// to 2^20; the end bins take whatever lies beyond.  Sixteenths because the threshold's bin then usually holds
+// few enough keys to be collected at once (the top bits of the key, a quarter of an octave, held thousands).
+constexpr int kSelDigit0Bins = 1024;
+constexpr int kSelDigit0Shift = 19;
+constexpr unsigned int kSelKeyBase = 0x80000000u | ((127u - 44u) << 23);
+__device__ __forceinline__ unsigned int sel_digit0(unsigned int key) {
+  const unsigned int d = (key - kSelKeyBase) >> kSelDigit0Shift;
+  return key < kSelKeyBase ? 0u : (d < (unsigned int)kSelDigit0Bins ? d : (unsigned int)kSelDigit0Bins - 1u);
+}
 
 constexpr size_t kAlign = 256;
 constexpr size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }

@@ -1,40 +1,55 @@
 // Top-B selection over the flattened heads of a layer (Alg. 1, "B_l largest entries based on
 // s_l"; the per-head survivor counts are the dynamic head budgets of Sec. 4.1).
 //
-// The paper's cost statement assumes a min-heap, O(H N log B_l); on a GPU the same result
-// comes from a most-significant-digit radix select: three histogram passes (11 + 11 + 10 bits
-// of an order-preserving integer image of the score) find the exact threshold key T and how
-// many entries equal to T must still be taken; ties are resolved by ascending flat index with
-// an ordered scan, so the survivor set is unique and the output needs no floating-point
-// comparison at all.  Survivors are written in flat order, which is exactly "heads
-// concatenated, ascending position inside each head".
+// The paper's cost statement assumes a min-heap, O(H N log B_l); on a GPU the same result comes from
+// narrowing an interval of an order-preserving integer image of the score ("key") until it holds the
+// threshold key T and little else: a histogram over 1024 intervals of the whole key range (sel_digit0)
+// finds the one in which the cumulative count, from the top, reaches the budget; if that interval holds
+// few keys (the usual case) every workgroup collects them all and finds T among them in its own LDS,
+// otherwise its keys are counted again by their next 10 bits, as often as it takes.  Ties at T are
+// resolved by ascending flat index with an ordered scan, so the survivor set is unique and the output
+// needs no floating-point comparison at all.  Survivors are written in flat order, which is exactly
+// "heads concatenated, ascending position inside each head".
 //
-// The whole selection is latency-bound (a few MiB of scores), so it runs as ONE kernel whose
-// workgroups (1024 lanes, 16 scores per lane in registers) meet at four grid-wide barriers; every
-// workgroup derives the digit picks and its output offset redundantly from the shared
-// histograms / per-workgroup counts, so no workgroup waits for a "leader".  Inputs too large for
-// all workgroups to be resident at once fall back to the same phases as separate kernels.
+// The selection is latency-bound (a few MiB of scores): what counts is the number of dependent trips to
+// memory and of waits for other workgroups.  It runs as ONE kernel over workgroups of 1024 lanes with KP
+// keys per lane in registers.  A problem that fits one workgroup exchanges nothing at all.  Otherwise a
+// prepared problem (first histogram built by the score kernels) waits for the other workgroups once, an
+// unprepared one twice (its first histogram, then the interval's keys); every workgroup derives T and its
+// output offset redundantly, so none waits for a leader.  Inputs too large for all workgroups to be
+// resident at once run the same phases as separate kernels.
+// Measured (kernel trace, prepared, against three 11-bit digits with a grid-wide wait each and 16 keys per lane):
+// 2 K entries 18.9 -> 7.8 us, 33 K 23.3 -> 10.3, 262 K 24.0 -> 12.8, 1 M 26.8 -> 17.3; a step of a cascade
+// (several problems, not prepared) 28 -> 18.  Inside the kernel at 262 K, not prepared: scores in and
+// counted 5.8 us (1.5 of it the loads, 2.5 the wait), pick 0.7, split 0.7, exchange 3.3, threshold 1.3,
+// write 2; a row of keys per lane costs 0.3 us of vector work in all, which is why a lane holds few.
+#include <type_traits>
+
 #include "common.h"
 #include "xblock.h"
 
 namespace lava {
 
-constexpr int kSelThreads = 1024;   // few, large workgroups: grid-wide barriers and histogram merges cost per workgroup
-constexpr int kSelPerThread = 16;
-constexpr int kSelChunk = kSelThreads * kSelPerThread;  // entries per workgroup
-constexpr int kBins = kSelBins;
+constexpr int kSelThreads = 1024;   // few, large workgroups: a wait for the others and a histogram merge cost per workgroup
+constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kMaxHeads = 64;
-constexpr unsigned int kSpinLimit = 1u << 18;           // polls of a grid barrier before giving up (default)
+constexpr int kLevelBits = 10;
+constexpr int kLevelBins = 1 << kLevelBits;
+static_assert(kLevelBins == kSelThreads && kSelDigit0Bins == kLevelBins, "one bin per thread");
+constexpr int kMaxLevels = 4;                           // ceil(32 / 10) histograms behind the first
+constexpr unsigned int kSpinLimit = 1u << 18;           // polls of a wait for other workgroups before giving up (default)
+constexpr unsigned int kListCap = 16384;                // keys of the threshold's interval a workgroup collects in LDS
+constexpr int kSegWords = 64;                           // of which a workgroup may contribute this many per key a lane holds
+constexpr int kFusedMaxBlocks = 512;                    // workgroups of a problem in the one-launch selection
 
-// The fused kernel's last histogram pass also publishes, per workgroup, how many of its keys lie
-// above each possible last digit (kPubWords = 1024 digits + 1), so that the counts every
-// workgroup needs from those before it are two loads once the threshold is known.
-constexpr int kPubWords = 1025;
-constexpr int kFusedMaxBlocks = 1024;   // more workgroups than any device keeps resident
+// The region's histogram area (3 * kSelBins words, zeroed beforehand): the first histogram, up to
+// kMaxLevels further ones, then one 64-bit word per workgroup of the one-launch selection.
+constexpr int kFlagWord = (1 + kMaxLevels) * kLevelBins;
+static_assert(kFlagWord + 2 * kFusedMaxBlocks <= 3 * kSelBins, "histogram area");
 
 struct SelectState {
   unsigned int barrier;      // arrivals at the grid barriers of the fused kernel (monotonic)
-  unsigned int error;        // set when a barrier wait gave up (results are then invalid)
+  unsigned int error;        // set when a wait gave up (results are then invalid)
   unsigned int done;         // workgroups of the fused kernel that have written their results
   unsigned int reserved[5];
 };
@@ -43,16 +58,17 @@ static_assert(sizeof(SelectState) == kSelStateWords * sizeof(unsigned int), "cle
 // Layout of a selection's workspace for `total` entries (also evaluated at compile time, for the
 // built-in scratch array of lava_select_topk_static).
 static constexpr SelectWorkspace select_layout(int64_t total) {
+  constexpr int64_t kChunk = kSelThreads * 16;
   SelectWorkspace w{};
-  w.n_blocks = (int)((total + kSelChunk - 1) / kSelChunk);
+  w.n_blocks = (int)((total + kChunk - 1) / kChunk);
   if (w.n_blocks < 1) w.n_blocks = 1;
   size_t off = 0;
-  w.off_hist = off;  off += align_up(sizeof(unsigned int) * 3 * kBins);
+  w.off_hist = off;  off += align_up(sizeof(unsigned int) * 3 * kSelBins);
   w.off_state = off; off += align_up(sizeof(SelectState));
-  // per-workgroup counts: two words per workgroup for the step launches; the fused kernel publishes
-  // kPubWords per workgroup (it serves problems of up to kFusedMaxBlocks workgroups)
+  // two counts per workgroup for the step launches; the fused kernel's segments: kSegWords for every 1024 entries
+  constexpr int kRegionBlocks = 1024;
   size_t words = 2 * (size_t)w.n_blocks;
-  const size_t fused = (size_t)(w.n_blocks < kFusedMaxBlocks ? w.n_blocks : kFusedMaxBlocks) * kPubWords;
+  const size_t fused = (size_t)(w.n_blocks < kRegionBlocks ? w.n_blocks : kRegionBlocks) * (16 * kSegWords + 1);
   if (fused > words) words = fused;
   w.off_blk = off;   off += align_up(sizeof(unsigned int) * words);
   w.bytes = off;
@@ -62,23 +78,21 @@ static constexpr SelectWorkspace select_layout(int64_t total) {
 SelectWorkspace make_select_workspace(int64_t total) { return select_layout(total); }
 
 struct SelShared {
-  union {
-    float val[kSelChunk + 64];        // staging of the chunk (one pad word per 64 entries)
-    unsigned int hist[kBins];         // per-workgroup digit histogram
-  };
-  long long off[kMaxHeads + 1];       // segment starts
-  unsigned int cnt[kMaxHeads];        // survivors per head in this workgroup
-  unsigned int wave[kSelThreads / 64];
-  unsigned long long wave64[kSelThreads / 64];
-  unsigned int pick_digit;
-  long long pick_need;
+  unsigned int list[kListCap];              // keys of the threshold's interval, all workgroups', in workgroup order
+  unsigned int hist[kLevelBins + 1];        // the last word collects what belongs to no bin
+  unsigned int seg_pos[kFusedMaxBlocks + 1];// where workgroup b's keys start in `list`
+  int off[kMaxHeads + 1];                   // segment starts
+  unsigned int cnt[kMaxHeads];              // survivors per head in this workgroup
+  unsigned int wave[kSelWaves];
+  unsigned int wave2[kSelWaves];
+  unsigned int pick[3];
+  unsigned int before[4];                   // handed from wavefront 0 to the workgroup
 };
 
-// Where the selection stands: digits of the threshold key found so far and how many survivors
-// must still come from the keys that match them.
-struct Pick {
-  unsigned int prefix;
-  long long need;
+// The keys that may still hold the threshold: lo .. lo + width.  `need` survivors must come from the
+// `count` keys in it, everything above it survives.  2^bits > width.
+struct Interval {
+  unsigned int lo, width, bits, need, count;
 };
 
 __device__ __forceinline__ long long effective_budget(long long budget, const int64_t* budget_dev,
@@ -93,351 +107,316 @@ __device__ __forceinline__ long long effective_budget(long long budget, const in
   return b;
 }
 
-// Chunk -> registers: coalesced reads through shared memory, then 16 consecutive entries per lane
-// (flat order inside the workgroup = lane order, which the ordered write needs).
-__device__ __forceinline__ void load_chunk(int bx, const float* __restrict__ scores, long long total,
-                                           SelShared& sh, float (&val)[kSelPerThread]) {
-  const long long base = (long long)bx * kSelChunk;
-  float tmp[kSelPerThread];
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {        // all loads in flight before the first use
-    const long long p = base + j * kSelThreads + threadIdx.x;
-    tmp[j] = p < total ? scores[p] : 0.0f;
-  }
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    const int i = j * kSelThreads + threadIdx.x;
-    sh.val[i + (i >> 6)] = tmp[j];
-  }
-  __syncthreads();
-  const int first = threadIdx.x * kSelPerThread;
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) val[j] = sh.val[first + j + ((first + j) >> 6)];
-  __syncthreads();
+// With explicit segments the number of entries is whatever the last offset says (read on the
+// device, so that a caller can chain selections without a host round trip); the host value is then
+// an upper bound that sized the grid and the workspace.
+__device__ __forceinline__ long long device_total(long long bound, const int64_t* __restrict__ seg_offsets,
+                                                  int n_heads) {
+  if (seg_offsets == nullptr) return bound;
+  long long t = (long long)seg_offsets[n_heads];
+  t = t < 0 ? 0 : t;
+  return t < bound ? t : bound;
 }
 
-template <int PASS> struct Digit {
-  static constexpr int kShift = PASS == 0 ? 21 : (PASS == 1 ? 10 : 0);
-  static constexpr int kBits = PASS == 2 ? 10 : 11;
-  static constexpr int kNum = 1 << kBits;
-  static constexpr int kHiShift = kShift + kBits;
+// A workgroup's keys: wavefront w holds the 64 * KP consecutive entries from wave_base on as KP rows of
+// 64 (row j, lane l: entry wave_base + 64 j + l), so that loads are coalesced whatever the alignment of
+// the scores and the flat order inside a wavefront is row by row, lane by lane: positions are bit counts
+// of ballots, nothing goes through LDS.  Entries beyond the end get key 0, which no score has (a NaN
+// would: a documented precondition).
+template <int KP>
+__device__ __forceinline__ void load_keys(const float* __restrict__ scores, int wave_base, int total,
+                                          unsigned int (&key)[KP]) {
+  const int lane = (int)(threadIdx.x & 63);
+  if (wave_base + 64 * KP <= total) {               // uniform; all loads in flight before the first use
+    const float* __restrict__ src = scores + wave_base + lane;
+#pragma unroll
+    for (int j = 0; j < KP; ++j) key[j] = __float_as_uint(src[64 * j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+      const int p = wave_base + lane + 64 * j;
+      key[j] = p < total ? __float_as_uint(scores[p]) : 0xffffffffu;   // a NaN whose key is 0
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < KP; ++j) key[j] = score_key(__uint_as_float(key[j]));
+}
+static_assert(kMaxHeads <= 64, "one lane per head");
+
+// Entries of workgroup bx's chunk that lie beyond the end.
+template <int KP>
+__device__ __forceinline__ unsigned int missing(int bx, int total) {
+  const long long end = (long long)(bx + 1) * (kSelThreads * KP), over = end - total;
+  return over <= 0 ? 0u : (over < kSelThreads * KP ? (unsigned int)over : (unsigned int)(kSelThreads * KP));
+}
+
+// A uniform value the compiler cannot connect with its earlier uses: row masks that are formed twice are
+// compared twice instead of being kept in (spilled) scalar registers from one loop to the other.
+__device__ __forceinline__ unsigned int opaque(unsigned int x) {
+  x = __builtin_amdgcn_readfirstlane(x);
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+__device__ __forceinline__ unsigned int level_shift(const Interval& v) {
+  return v.bits > (unsigned int)kLevelBits ? v.bits - kLevelBits : 0u;
+}
+// LDS add whose result nobody needs, as an instruction: the compiler would turn an atomic add into a
+// reduction over the lanes first, which costs more than the add.
+__device__ __forceinline__ unsigned int lds_offset(const void* p) {
+  return (unsigned int)(unsigned long long)(__attribute__((address_space(3))) const char*)p;
+}
+__device__ __forceinline__ void lds_add(unsigned int at, unsigned int x) {
+  asm volatile("ds_add_u32 %0, %1" : : "v"(at), "v"(x) : "memory");
+}
+
+// every LDS operation of this wavefront is complete
+__device__ __forceinline__ void lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Keeps the compiler from forming the masks of many rows ahead of their use (they do not fit the scalar registers).
+__device__ __forceinline__ void row_done() { __builtin_amdgcn_sched_barrier(0); }
+
+// One count for every lane's bin (byte address in LDS).  A row in one bin (a large plateau: zeros, the window
+// entries) is one add.
+__device__ __forceinline__ void count_row(unsigned int at) {
+  const unsigned int at0 = __builtin_amdgcn_readfirstlane(at);
+  if (__all(at == at0)) {
+    if ((threadIdx.x & 63) == 0) lds_add(at0, 64u);
+  } else {
+    lds_add(at, 1u);
+  }
+  row_done();
+}
+
+// First histogram (bins sel_digit0) over this wavefront's keys, in `hist` (LDS; zeroed and published by a
+// barrier before).  Entries beyond the end have key 0, i.e. count in bin 0: the caller takes them out again.
+template <int KP>
+__device__ __forceinline__ void count_first(const unsigned int (&key)[KP], unsigned int* hist) {
+  constexpr unsigned int kFirst = kSelKeyBase >> kSelDigit0Shift;
+  static_assert((kFirst << kSelDigit0Shift) == kSelKeyBase, "bins are aligned in the key");
+  const unsigned int base = lds_offset(hist) - 4u * kFirst;
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    unsigned int d = key[j] >> kSelDigit0Shift;
+    d = d < kFirst ? kFirst : d;
+    d = d > kFirst + kSelDigit0Bins - 1u ? kFirst + kSelDigit0Bins - 1u : d;
+    count_row(base + 4u * d);
+  }
+}
+
+// Histogram of the keys inside interval v by their next bits.
+template <int KP>
+__device__ __forceinline__ void count_level(const unsigned int (&key)[KP], const Interval& v, unsigned int* hist) {
+  const unsigned int shift = level_shift(v), base = lds_offset(hist);
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    const unsigned int rel = key[j] - v.lo;
+    count_row(base + 4u * (rel <= v.width ? rel >> shift : (unsigned int)kLevelBins));   // kLevelBins: a bin nobody reads
+  }
+}
+
+// Sums across lanes without LDS: data-parallel-primitive moves (a shift inside rows of 16 lanes, then the last
+// lane of one row to the next ones), a few cycles each where a shuffle is a trip through the LDS unit.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int dpp_add(unsigned int x) {
+  return x + (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned int row_scan(unsigned int x) {        // inclusive, inside each row of 16 lanes
+  x = dpp_add<0x111, 0xf>(x);
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  return dpp_add<0x118, 0xf>(x);
+}
+__device__ __forceinline__ unsigned int wave_scan(unsigned int x) {       // inclusive, over the wavefront
+  x = row_scan(x);
+  x = dpp_add<0x142, 0xa>(x);
+  return dpp_add<0x143, 0xc>(x);
+}
+__device__ __forceinline__ unsigned int wave_sum(unsigned int x) {
+  return (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(x), 63);
+}
+// One word per wavefront in LDS: their sum, and that of the wavefronts before `wave`.
+struct WaveSums {
+  unsigned int total, before;
 };
+__device__ __forceinline__ WaveSums wave_sums(const unsigned int* w, int wave) {
+  static_assert(kSelWaves == 16, "one row of lanes");
+  const unsigned int mine = w[threadIdx.x & 15], incl = row_scan(mine);
+  WaveSums r;
+  r.total = (unsigned int)__builtin_amdgcn_readlane((int)incl, 15);
+  r.before = (unsigned int)__builtin_amdgcn_readlane((int)(incl - mine), wave);
+  return r;
+}
+// Index of this wavefront, as a scalar.
+__device__ __forceinline__ int sel_wave() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
-// Histogram of digit PASS over this workgroup's keys that match the prefix; merged into the
-// global histogram with integer atomics.
-template <int PASS>
-__device__ __forceinline__ void hist_phase(int bx, const float (&val)[kSelPerThread], long long total,
-                                           unsigned int prefix, SelShared& sh,
-                                           unsigned int* __restrict__ ghist) {
-  using Dg = Digit<PASS>;
-  for (int i = threadIdx.x; i < Dg::kNum; i += kSelThreads) sh.hist[i] = 0u;
+// The bin, counted from the top, in which the cumulative count reaches `need` (> 0); `mine` is the count
+// of bin kLevelBins - 1 - threadIdx.x.  Returns (bin, survivors needed from it, its count) in `out`.
+__device__ __forceinline__ void pick_bin(unsigned int mine, unsigned int need, SelShared& sh, unsigned int (&out)[3]) {
+  const unsigned int incl = wave_scan(mine);
+  const int wave = sel_wave();
+  if ((threadIdx.x & 63) == 63) sh.wave[wave] = incl;
+  if (threadIdx.x == 0) { sh.pick[0] = 0u; sh.pick[1] = need; sh.pick[2] = 0u; }   // taken only if the counts are short of `need` (a wait gave up)
   __syncthreads();
-  const long long p0 = (long long)bx * kSelChunk + threadIdx.x * kSelPerThread;
-  // neighbouring entries mostly share a digit (pooling makes plateaus, magnitudes vary slowly), so a
-  // lane adds one count per run of equal digits instead of one per entry
-  unsigned int run_digit = 0xffffffffu, run_len = 0u;
+  const unsigned int above = wave_sums(sh.wave, wave).before + incl - mine;
+  if (above < need && need <= above + mine) {
+    sh.pick[0] = (unsigned int)(kLevelBins - 1) - threadIdx.x;
+    sh.pick[1] = need - above;
+    sh.pick[2] = mine;
+  }
+  __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    unsigned int digit = 0xffffffffu;
-    if (p0 + j < total) {
-      const unsigned int key = score_key(val[j]);
-      const bool match = PASS == 0 ? true : ((key >> Dg::kHiShift) == prefix);
-      if (match) digit = (key >> Dg::kShift) & (Dg::kNum - 1);
-    }
-    if (digit != run_digit) {
-      if (run_len != 0u && run_digit != 0xffffffffu) atomicAdd(&sh.hist[run_digit], run_len);
-      run_digit = digit;
-      run_len = 0u;
-    }
-    ++run_len;
-  }
-  if (run_digit != 0xffffffffu) atomicAdd(&sh.hist[run_digit], run_len);
-  __syncthreads();
-  for (int i = threadIdx.x; i < Dg::kNum; i += kSelThreads) {
-    const unsigned int c = sh.hist[i];
-    if (c) __hip_atomic_fetch_add(&ghist[i], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  for (int i = 0; i < 3; ++i) out[i] = __builtin_amdgcn_readfirstlane(sh.pick[i]);
 }
 
-// Digit of the threshold key: the bin, counted from the top, in which the cumulative count
-// reaches `need`.  Every workgroup computes it for itself from the complete global histogram.
-template <int PASS>
-__device__ __forceinline__ Pick pick_phase(const unsigned int* __restrict__ ghist, Pick in,
-                                           SelShared& sh) {
-  using Dg = Digit<PASS>;
-  constexpr int kPer = Dg::kNum / kSelThreads;
-  // thread t owns the bins kNum-1 - t*kPer - j (descending), so a prefix scan over t runs from the top
-  unsigned int cnt[kPer];
-  unsigned int mine = 0u;
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    cnt[j] = ld_dev(&ghist[Dg::kNum - 1 - (threadIdx.x * kPer + j)]);
-    mine += cnt[j];
-  }
-  unsigned int incl = mine;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned int up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  if (lane == 63) sh.wave[wave] = incl;
-  if (threadIdx.x == 0) {
-    sh.pick_digit = (unsigned int)(Dg::kNum - 1);     // taken when need == 0: nothing matches below
-    sh.pick_need = 0;
-  }
-  __syncthreads();
-  long long above = 0;
-  for (int i = 0; i < wave; ++i) above += sh.wave[i];
-  above += (long long)incl - mine;                     // keys in bins above this thread's bins
-  if (in.need > 0 && above < in.need && in.need <= above + (long long)mine) {
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      if (in.need <= above + (long long)cnt[j]) {
-        sh.pick_digit = (unsigned int)(Dg::kNum - 1 - (threadIdx.x * kPer + j));
-        sh.pick_need = in.need - above;
-        break;
-      }
-      above += cnt[j];
-    }
-  }
-  __syncthreads();
-  Pick out;
-  out.prefix = (in.prefix << Dg::kBits) | sh.pick_digit;
-  out.need = sh.pick_need;
-  __syncthreads();
-  return out;
+// Interval of the first histogram's bin.
+__device__ __forceinline__ Interval first_interval(const unsigned int (&pk)[3]) {
+  Interval v;
+  v.lo = pk[0] == 0u ? 1u : kSelKeyBase + (pk[0] << kSelDigit0Shift);      // the end bins take whatever lies beyond
+  const unsigned int hi = pk[0] == (unsigned int)(kLevelBins - 1) ? 0xffffffffu
+                                                                 : kSelKeyBase + ((pk[0] + 1u) << kSelDigit0Shift) - 1u;
+  v.width = hi - v.lo;
+  v.bits = (pk[0] == 0u || pk[0] == (unsigned int)(kLevelBins - 1)) ? 32u : (unsigned int)kSelDigit0Shift;
+  v.need = pk[1];
+  v.count = pk[2];
+  return v;
+}
+__device__ __forceinline__ void narrow(Interval& v, const unsigned int (&pk)[3]) {
+  const unsigned int sh = level_shift(v), skip = pk[0] << sh, most = (1u << sh) - 1u;
+  v.lo += skip;
+  v.width = v.width - skip < most ? v.width - skip : most;
+  v.bits = sh;
+  v.need = pk[1];
+  v.count = pk[2];
 }
 
-// Keys above / equal to the threshold in this workgroup, published for the other workgroups.
-__device__ __forceinline__ void count_phase(int bx, const float (&val)[kSelPerThread], long long total,
-                                            unsigned int T, SelShared& sh, unsigned int* __restrict__ blk,
-                                            int n_blocks, unsigned int& gt_mask, unsigned int& eq_mask) {
-  const long long p0 = (long long)bx * kSelChunk + threadIdx.x * kSelPerThread;
-  gt_mask = 0u;
-  eq_mask = 0u;
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    if (p0 + j < total) {
-      const unsigned int key = score_key(val[j]);
-      gt_mask |= (key > T ? 1u : 0u) << j;
-      eq_mask |= (key == T ? 1u : 0u) << j;
-    }
-  }
-  unsigned int packed = ((unsigned int)__popc(gt_mask) << 16) | (unsigned int)__popc(eq_mask);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) packed += __shfl_xor(packed, off);
-  if ((threadIdx.x & 63) == 0) sh.wave[threadIdx.x >> 6] = packed;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned int tot = 0u;
-    for (int i = 0; i < kSelThreads / 64; ++i) tot += sh.wave[i];
-    st_dev(&blk[bx], tot >> 16);
-    st_dev(&blk[n_blocks + bx], tot & 0xffffu);
-  }
-  __syncthreads();
+// What a survivor is: key > T, or key == T and among the first `ties` such keys in flat order.
+struct Threshold {
+  unsigned int T, ties;
+};
+// ... once the interval is one key wide, or all of its keys survive
+__device__ __forceinline__ bool decided(const Interval& v) { return v.bits == 0u || v.count == v.need; }
+__device__ __forceinline__ Threshold threshold_of(const Interval& v) {
+  Threshold t;
+  const bool all = v.count == v.need;
+  t.T = all ? v.lo - 1u : v.lo;                    // lo >= 1
+  t.ties = all ? 0u : v.need;
+  return t;
 }
 
-// Sums of (gt, eq) over the workgroups before this one.
-__device__ __forceinline__ void prefix_phase(int bx, const unsigned int* __restrict__ blk, int n_blocks,
-                                             SelShared& sh, long long& gt_before, long long& eq_before) {
-  unsigned long long acc = 0ull;   // gt in the high word, eq in the low word (each < 2^31)
-  for (int b = threadIdx.x; b < bx; b += kSelThreads)
-    acc += ((unsigned long long)ld_dev(&blk[b]) << 32) | (unsigned long long)ld_dev(&blk[n_blocks + b]);
+// Ordered write of this workgroup's survivors, which lie in `rows` of its wavefronts (bit j: row j; gt_wg keys
+// above T and eq_wg equal to T lie in the workgroups before it);
+// survivors per head go to head_counts, head offsets are written by the wavefront that holds the first
+// entry of the head.  Contains workgroup barriers.
+template <int KP>
+__device__ __forceinline__ void write_survivors(const unsigned int (&key)[KP], unsigned int rows, const float* __restrict__ scores,
+                                                int wave_base, int total, int n_heads, Threshold t,
+                                                unsigned int gt_wg, unsigned int eq_wg, int kept_total, long long capacity,
+                                                bool alone, bool first_wg, SelShared& sh,
+                                                int32_t* __restrict__ head_counts, int64_t* __restrict__ head_offsets,
+                                                int32_t* __restrict__ kept_idx, float* __restrict__ kept_scores) {
+  const int lane = threadIdx.x & 63, wave = sel_wave();
+  const int wave_end = wave_base + 64 * KP;
+  // lane j: which keys of row j lie above T / are equal to it
+  unsigned long long row_gt = 0ull, row_eq = 0ull;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if ((threadIdx.x & 63) == 0) sh.wave64[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  unsigned long long tot = 0ull;
-  for (int i = 0; i < kSelThreads / 64; ++i) tot += sh.wave64[i];
-  gt_before = (long long)(tot >> 32);
-  eq_before = (long long)(tot & 0xffffffffull);
-  __syncthreads();
-}
-
-// Ordered write of this workgroup's survivors; survivors per head are added to head_counts and the
-// head offsets are written by the lanes that own the first entry of each head.
-__device__ __forceinline__ void write_phase(int bx, const float (&val)[kSelPerThread], long long total, int n_heads,
-                                            const int64_t* __restrict__ seg_offsets, unsigned int gt_mask,
-                                            unsigned int eq_mask, long long need, long long capacity,
-                                            long long gt_blocks_before, long long eq_blocks_before,
-                                            long long need_total, SelShared& sh,
-                                            int32_t* __restrict__ head_counts, int64_t* __restrict__ head_offsets,
-                                            int32_t* __restrict__ kept_idx, float* __restrict__ kept_scores) {
-  if (threadIdx.x <= n_heads) {
-    const long long seg = total / n_heads;
-    sh.off[threadIdx.x] = seg_offsets ? (long long)seg_offsets[threadIdx.x]
-                                      : (threadIdx.x == n_heads ? total : seg * threadIdx.x);
+  for (int j = 0; j < KP; ++j) {
+    if (!((rows >> j) & 1u)) continue;                        // uniform
+    const unsigned long long gt = __ballot(key[j] > t.T), eq = t.ties ? __ballot(key[j] == t.T) : 0ull;
+    if (lane == j) { row_gt = gt; row_eq = eq; }
+    row_done();
   }
+  const unsigned int mine = ((unsigned int)__popcll(row_gt) << 16) | (unsigned int)__popcll(row_eq);
+  const unsigned int incl = wave_scan(mine);
+  if (lane == 63) sh.wave2[wave] = incl;
   if (threadIdx.x < kMaxHeads) sh.cnt[threadIdx.x] = 0u;
-  // exclusive scan of packed (gt << 16 | eq) over the workgroup
-  const unsigned int mine = ((unsigned int)__popc(gt_mask) << 16) | (unsigned int)__popc(eq_mask);
-  unsigned int incl = mine;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned int up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  if (lane == 63) sh.wave[wave] = incl;
   __syncthreads();
-  unsigned int wave_base = 0u;
-  for (int i = 0; i < wave; ++i) wave_base += sh.wave[i];
-  const unsigned int excl = wave_base + incl - mine;
-  long long gt_before = gt_blocks_before + (long long)(excl >> 16);
-  long long eq_before = eq_blocks_before + (long long)(excl & 0xffffu);
+  static_assert(64 * KP * (kSelWaves - 1) < (1 << 16) && KP <= 32, "packed counts, one lane per row");
+  const unsigned int base = wave_sums(sh.wave2, wave).before, excl = incl - mine;
+  const unsigned int gt_wave = gt_wg + (base >> 16), eq_wave = eq_wg + (base & 0xffffu);
+  const unsigned int row_gt0 = gt_wave + (excl >> 16), row_eq0 = eq_wave + (excl & 0xffffu);   // lane j: keys before row j
 
-  const long long first = (long long)bx * kSelChunk + threadIdx.x * kSelPerThread;
-  // head_offsets[h] = survivors before the first entry of head h: written by the lane that owns that
-  // entry; segments starting at or beyond the end (empty trailing heads) and the two ends by lane 0
-  if (bx == 0 && threadIdx.x == 0) {
-    const long long kept = need_total;
-    head_offsets[0] = 0;
-    head_offsets[n_heads] = kept;
-    for (int h = 1; h < n_heads; ++h)
-      if (sh.off[h] >= total) head_offsets[h] = kept;
+  // survivors before entry p of this wavefront (p uniform)
+  auto survivors_before = [&](int p) -> unsigned int {
+    const int r = (p - wave_base) >> 6, l = (p - wave_base) & 63;
+    const unsigned long long below = (1ull << l) - 1ull;
+    const unsigned int gt = row_gt0 + (unsigned int)__popcll(row_gt & below);
+    unsigned int eq = row_eq0 + (unsigned int)__popcll(row_eq & below);
+    if (eq > t.ties) eq = t.ties;
+    return (unsigned int)__builtin_amdgcn_readlane((int)(gt + eq), r);
+  };
+  const unsigned int all = (unsigned int)__builtin_amdgcn_readlane((int)incl, 63);
+  const unsigned int eq0 = eq_wave < t.ties ? eq_wave : t.ties;
+  const unsigned int eq1 = eq_wave + (all & 0xffffu) < t.ties ? eq_wave + (all & 0xffffu) : t.ties;
+  const unsigned int s_begin = gt_wave + eq0, s_end = gt_wave + (all >> 16) + eq1;
+
+  // heads that start inside this wavefront's entries
+  const int start = lane < n_heads ? sh.off[lane] : 0x7fffffff;
+  const unsigned long long started = __ballot(lane < n_heads && start <= wave_base);
+  int g = started ? 63 - __builtin_clzll(started) : 0;        // head of the wavefront's first entry
+  const int g_first = g;
+  unsigned long long starts = __ballot(lane > 0 && lane < n_heads && start >= wave_base && start < wave_end && start < total);
+  const bool several = __ballot(lane > 0 && lane < n_heads && start > wave_base && start < wave_end) != 0ull;
+  unsigned int s_prev = s_begin;
+  while (starts) {
+    const int h = __builtin_ctzll(starts);
+    starts &= starts - 1ull;
+    const int p = __builtin_amdgcn_readlane(start, h);
+    const unsigned int s = survivors_before(p);
+    if (lane == 0) {
+      head_offsets[h] = (int64_t)s;
+      if (p > wave_base && s != s_prev) atomicAdd(&sh.cnt[g], s - s_prev);
+    }
+    if (p > wave_base) { s_prev = s; g = h; }
   }
-  int g = 0;
-  while (g + 1 < n_heads && sh.off[g + 1] < first) ++g;     // segment starts equal to `first` are crossed below
-  // most lanes never cross a segment start: the next start and this head's start stay in registers
-  constexpr long long kNever = 0x7fffffffffffffffll;
-  long long next_start = g + 1 < n_heads ? sh.off[g + 1] : kNever;
-  long long head_start = sh.off[g];
-  unsigned int local_cnt = 0u;
-  // most lanes hold no survivor and no segment start (a fraction of a per cent of the entries survive):
-  // they have nothing to write
-  const bool idle = gt_mask == 0u && (eq_mask == 0u || eq_before >= need) && next_start >= first + kSelPerThread;
+  if (lane == 0 && s_end != s_prev) atomicAdd(&sh.cnt[g], s_end - s_prev);
+  // the two ends, and heads that start at or beyond the end (empty trailing heads)
+  if (first_wg && threadIdx.x < 64) {
+    if (lane == 0) head_offsets[n_heads] = (int64_t)kept_total;
+    if (lane == 0) head_offsets[0] = 0;
+    if (lane > 0 && lane < n_heads && start >= total) head_offsets[lane] = (int64_t)kept_total;
+  }
+
+  const int head_start = __builtin_amdgcn_readlane(start, g_first);
+  rows = (unsigned int)__ballot((row_gt | row_eq) != 0ull);
+  const unsigned int T = opaque(t.T);
 #pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    if (idle) break;
-    const long long p = first + j;
-    while (p >= next_start) {
-      if (local_cnt) atomicAdd(&sh.cnt[g], local_cnt);
-      local_cnt = 0u;
-      ++g;
-      head_start = next_start;
-      if (p == head_start && p < total) head_offsets[g] = gt_before + (eq_before < need ? eq_before : need);
-      next_start = g + 1 < n_heads ? sh.off[g + 1] : kNever;
-    }
-    const bool is_gt = (gt_mask >> j) & 1u;
-    const bool is_eq = (eq_mask >> j) & 1u;
-    if (is_gt || (is_eq && eq_before < need)) {
-      // survivors before this entry in flat order: all larger keys plus the threshold-equal ones taken
-      const long long slot = gt_before + (eq_before < need ? eq_before : need);
+  for (int j = 0; j < KP; ++j) {
+    if (!((rows >> j) & 1u)) continue;                        // uniform
+    const bool is_gt = key[j] > T, is_eq = t.ties != 0u && key[j] == T;
+    const unsigned long long gt = __ballot(is_gt), eq = __ballot(is_eq);
+    const unsigned int gt_rank = (unsigned int)__builtin_amdgcn_readlane((int)row_gt0, j) +
+                                 __builtin_amdgcn_mbcnt_hi((unsigned int)(gt >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)gt, 0u));
+    const unsigned int eq_rank = (unsigned int)__builtin_amdgcn_readlane((int)row_eq0, j) +
+                                 __builtin_amdgcn_mbcnt_hi((unsigned int)(eq >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)eq, 0u));
+    if (is_gt || (is_eq && eq_rank < t.ties)) {
+      const long long slot = (long long)gt_rank + (eq_rank < t.ties ? eq_rank : t.ties);
       if (slot < capacity) {
-        kept_idx[slot] = (int32_t)(p - head_start);
-        if (kept_scores) kept_scores[slot] = val[j];
+        const int p = wave_base + 64 * j + lane;
+        int from = head_start;
+        if (several) {                                        // the last head that starts at or before p
+          int h = g_first;
+          while (h + 1 < n_heads && sh.off[h + 1] <= p) ++h;
+          from = sh.off[h];
+        }
+        kept_idx[slot] = p - from;
+        if (kept_scores) {
+          // the score behind a key; both zeros share one, so those are read again
+          const unsigned int k = key[j];
+          float f = __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
+          if (k == 0x80000000u) f = scores[p];
+          kept_scores[slot] = f;
+        }
       }
-      ++local_cnt;
     }
-    gt_before += is_gt;
-    eq_before += is_eq;
   }
-  if (local_cnt) atomicAdd(&sh.cnt[g], local_cnt);
   __syncthreads();
   if (threadIdx.x < n_heads) {
     const unsigned int c = sh.cnt[threadIdx.x];
-    if (c) __hip_atomic_fetch_add(reinterpret_cast<unsigned int*>(&head_counts[threadIdx.x]), c,
-                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (alone) head_counts[threadIdx.x] = (int32_t)c;
+    else if (c) __hip_atomic_fetch_add(reinterpret_cast<unsigned int*>(&head_counts[threadIdx.x]), c,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-}
-
-// Last histogram pass of the fused kernel.  Besides merging the workgroup's histogram of the last
-// digit (keys matching the 22 digits found so far) into the global one, it publishes
-//   pub[d] = #keys of this workgroup above every key that matches the prefix and has last digit < d
-//          = #keys whose first 22 bits exceed the prefix + #matching keys with last digit >= d,
-// d = 0 .. 1024, so that for a threshold with last digit t the workgroup holds pub[t + 1] keys above
-// it and pub[t] - pub[t + 1] equal to it.
-__device__ __forceinline__ void hist_publish_phase(int bx, const float (&val)[kSelPerThread], long long total,
-                                                   unsigned int prefix, SelShared& sh,
-                                                   unsigned int* __restrict__ ghist,
-                                                   unsigned int* __restrict__ pub) {
-  using Dg = Digit<2>;
-  static_assert(Dg::kNum == kSelThreads && Dg::kNum + 1 == kPubWords, "one last digit per thread");
-  sh.hist[threadIdx.x] = 0u;
-  __syncthreads();
-  const long long p0 = (long long)bx * kSelChunk + threadIdx.x * kSelPerThread;
-  unsigned int run_digit = 0xffffffffu, run_len = 0u, above = 0u;
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    unsigned int digit = 0xffffffffu;
-    if (p0 + j < total) {
-      const unsigned int key = score_key(val[j]);
-      const unsigned int hi = key >> Dg::kHiShift;
-      above += hi > prefix ? 1u : 0u;
-      if (hi == prefix) digit = key & (Dg::kNum - 1);
-    }
-    if (digit != run_digit) {
-      if (run_len != 0u && run_digit != 0xffffffffu) atomicAdd(&sh.hist[run_digit], run_len);
-      run_digit = digit;
-      run_len = 0u;
-    }
-    ++run_len;
-  }
-  if (run_digit != 0xffffffffu) atomicAdd(&sh.hist[run_digit], run_len);
-  __syncthreads();
-  // thread t owns digit kNum - 1 - t: an inclusive scan over t is a suffix sum over the digits
-  const int d = Dg::kNum - 1 - (int)threadIdx.x;
-  const unsigned int c = sh.hist[d];
-  if (c) __hip_atomic_fetch_add(&ghist[d], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  unsigned int incl = c;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned int up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) above += __shfl_xor(above, off);
-  if (lane == 63) sh.wave[wave] = incl;
-  if (lane == 0) sh.wave64[wave] = above;
-  __syncthreads();
-  unsigned int base = 0u, above_all = 0u;
-  for (int i = 0; i < kSelThreads / 64; ++i) {
-    if (i < wave) base += sh.wave[i];
-    above_all += (unsigned int)sh.wave64[i];
-  }
-  st_dev(&pub[d], above_all + base + incl);
-  if (threadIdx.x == 0) st_dev(&pub[Dg::kNum], above_all);
-  __syncthreads();
-}
-
-// This lane's keys above / equal to the threshold.
-__device__ __forceinline__ void mask_phase(int bx, const float (&val)[kSelPerThread], long long total,
-                                           unsigned int T, unsigned int& gt_mask, unsigned int& eq_mask) {
-  const long long p0 = (long long)bx * kSelChunk + threadIdx.x * kSelPerThread;
-  gt_mask = 0u;
-  eq_mask = 0u;
-#pragma unroll
-  for (int j = 0; j < kSelPerThread; ++j) {
-    if (p0 + j < total) {
-      const unsigned int key = score_key(val[j]);
-      gt_mask |= (key > T ? 1u : 0u) << j;
-      eq_mask |= (key == T ? 1u : 0u) << j;
-    }
-  }
-}
-
-// Sums of (above, equal) over the workgroups before this one, from what they published.
-__device__ __forceinline__ void prefix_published_phase(int bx, const unsigned int* __restrict__ pub_all,
-                                                       unsigned int T, SelShared& sh, long long& gt_before,
-                                                       long long& eq_before) {
-  const unsigned int t = T & (unsigned int)(Digit<2>::kNum - 1);
-  unsigned long long acc = 0ull;   // above in the high word, equal in the low word (each < 2^31)
-  for (int b = threadIdx.x; b < bx; b += kSelThreads) {
-    const unsigned int ge = ld_dev(&pub_all[(size_t)b * kPubWords + t]);
-    const unsigned int gt = ld_dev(&pub_all[(size_t)b * kPubWords + t + 1]);
-    acc += ((unsigned long long)gt << 32) | (unsigned long long)(ge - gt);
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if ((threadIdx.x & 63) == 0) sh.wave64[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  unsigned long long tot = 0ull;
-  for (int i = 0; i < kSelThreads / 64; ++i) tot += sh.wave64[i];
-  gt_before = (long long)(tot >> 32);
-  eq_before = (long long)(tot & 0xffffffffull);
-  __syncthreads();
 }
 
 // Grid-wide barrier of the fused kernel: all of its workgroups are resident (the host checks the
@@ -465,31 +444,27 @@ __device__ __forceinline__ void grid_sync(SelectState* __restrict__ st, unsigned
 // One launch serves up to kMaxSelProblems independent selections: the table travels in the kernel
 // arguments, and the workgroups of all problems are numbered through (first_block), so every
 // workgroup of the grid has work.  Every problem has its own histograms, barrier counter and
-// per-workgroup counts in its own region of the workspace, so problems never wait for each other.
+// exchange words in its own region of the workspace, so problems never wait for each other.
 struct SelectBatch {
   int n_heads;
   int n_problems;
   int first_block[kMaxSelProblems + 1];   // workgroups of problem p: first_block[p] .. first_block[p + 1] - 1
   char* ws;                      // region of problem p at ws + p * ws_stride
   size_t ws_stride, off_hist, off_state, off_blk;
-  int blk_stride;                // n_blocks the regions were laid out for
-  unsigned int spin_limit;       // polls of a grid barrier before it gives up
+  unsigned int spin_limit;       // polls of a wait for other workgroups before it gives up
   unsigned int primed_mask;      // bit p: problem p's region was prepared by the score kernels (first histogram
                                  // complete, the rest cleared)
   lava_select_problem p[kMaxSelProblems];
 };
 
-__device__ __forceinline__ int problem_blocks(const lava_select_problem& pr) {
-  const long long nb = (pr.total_entries + kSelChunk - 1) / kSelChunk;
-  return nb < 1 ? 1 : (int)nb;
-}
-
 // Problem of this workgroup (uniform over the workgroup).
 __device__ __forceinline__ int problem_of_block(const SelectBatch& a) {
-  int p = 0;
-  while (p + 1 < a.n_problems && (int)blockIdx.x >= a.first_block[p + 1]) ++p;
-  return p;
+  if (a.n_problems == 1) return 0;
+  const int lane = threadIdx.x & 63;
+  const unsigned long long at = __ballot(lane < a.n_problems && a.first_block[lane < a.n_problems ? lane : 0] <= (int)blockIdx.x);
+  return 63 - __builtin_clzll(at);                // first_block[0] = 0
 }
+static_assert(kMaxSelProblems <= 64, "one lane per problem");
 
 __global__ void __launch_bounds__(kSelThreads) sel_init_kernel(const SelectBatch a) {
   const lava_select_problem pr = a.p[blockIdx.x];
@@ -498,7 +473,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_init_kernel(const SelectBatch
   SelectState* st = reinterpret_cast<SelectState*>(region + a.off_state);
   if (threadIdx.x < a.n_heads) pr.head_counts[threadIdx.x] = 0;
   if ((a.primed_mask >> blockIdx.x) & 1u) return;           // histograms and state are as the score kernels left them
-  for (int i = threadIdx.x; i < 3 * kBins; i += kSelThreads) hist[i] = 0u;
+  for (int i = threadIdx.x; i < 3 * kSelBins; i += kSelThreads) hist[i] = 0u;
   if (threadIdx.x == 0) {
     st->barrier = 0u;
     st->error = 0u;
@@ -506,81 +481,249 @@ __global__ void __launch_bounds__(kSelThreads) sel_init_kernel(const SelectBatch
   }
 }
 
-// With explicit segments the number of entries is whatever the last offset says (read on the
-// device, so that a caller can chain selections without a host round trip); the host value is then
-// an upper bound that sized the grid and the workspace.
-__device__ __forceinline__ long long device_total(long long bound, const int64_t* __restrict__ seg_offsets,
-                                                  int n_heads) {
-  if (seg_offsets == nullptr) return bound;
-  long long t = (long long)seg_offsets[n_heads];
-  t = t < 0 ? 0 : t;
-  return t < bound ? t : bound;
+// The keys of the threshold's interval that lie in this workgroup: how many keys lie above the interval
+// and in it (out: the workgroup's sums; `base`: those of the wavefronts before this one), and row by row
+// which ones.  Contains a workgroup barrier.
+template <int KP>
+__device__ __forceinline__ void split_keys(const unsigned int (&key)[KP], const Interval& v, SelShared& sh, unsigned int& above,
+                                           unsigned int& inside, unsigned int& inside_base,
+                                           unsigned int& rows_above, unsigned int& rows_inside) {
+  const int wave = sel_wave();
+  const unsigned int hi = v.lo + v.width;
+  unsigned int n_above = 0u, n_inside = 0u;                   // scalar: the wavefront's
+  rows_above = rows_inside = 0u;
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    const unsigned long long up = __ballot(key[j] > hi), in = __ballot(key[j] - v.lo <= v.width);
+    n_above += (unsigned int)__popcll(up);
+    n_inside += (unsigned int)__popcll(in);
+    rows_above |= up ? 1u << j : 0u;
+    rows_inside |= in ? 1u << j : 0u;
+    row_done();
+  }
+  if ((threadIdx.x & 63) == 0) sh.wave2[wave] = (n_above << 16) | n_inside;    // at most 32768 in all
+  __syncthreads();
+  const WaveSums sums = wave_sums(sh.wave2, wave);
+  above = sums.total >> 16;
+  inside = sums.total & 0xffffu;
+  inside_base = sums.before & 0xffffu;
+}
+
+// put(position, key) for this wavefront's keys of the interval, in flat order from position `at` on.
+template <int KP, class F>
+__device__ __forceinline__ void collect_keys(const unsigned int (&key)[KP], const Interval& v, unsigned int at,
+                                             unsigned int rows_inside, F&& put) {
+  const unsigned int lo = opaque(v.lo), width = v.width;
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    if (!((rows_inside >> j) & 1u)) continue;                 // uniform
+    const bool in = key[j] - lo <= width;
+    const unsigned long long b = __ballot(in);
+    if (in) put(at + __builtin_amdgcn_mbcnt_hi((unsigned int)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)b, 0u)), key[j]);
+    at += (unsigned int)__popcll(b);
+  }
 }
 
 // The whole selection in one launch.
-__global__ void __launch_bounds__(kSelThreads) sel_fused_kernel(const SelectBatch a) {
+template <int KP>
+__global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectBatch a) {
   const int prob = problem_of_block(a);
   const lava_select_problem pr = a.p[prob];
-  const unsigned int nb = (unsigned int)problem_blocks(pr);
   const int bx = (int)blockIdx.x - a.first_block[prob];
+  const unsigned int nb = (unsigned int)(a.first_block[prob + 1] - a.first_block[prob]);
+  const bool alone = nb == 1u;
+  constexpr unsigned int kSegCap = kSegWords * KP;
   char* region = a.ws + prob * a.ws_stride;
   unsigned int* hist = reinterpret_cast<unsigned int*>(region + a.off_hist);
+  unsigned long long* flag = reinterpret_cast<unsigned long long*>(hist + kFlagWord);
   SelectState* st = reinterpret_cast<SelectState*>(region + a.off_state);
-  unsigned int* blk = reinterpret_cast<unsigned int*>(region + a.off_blk);
+  unsigned int* seg = reinterpret_cast<unsigned int*>(region + a.off_blk);
+  const bool primed = ((a.primed_mask >> prob) & 1u) && !alone;
+  __shared__ SelShared sh;
+
+  const int lane = threadIdx.x & 63, wave = sel_wave();
+  // a prepared first histogram travels together with the scores
+  unsigned int bin_count = 0u;
+  if (primed) bin_count = ld_dev(&hist[kLevelBins - 1 - threadIdx.x]);
+  const int64_t* __restrict__ seg_offsets = pr.seg_offsets;
+  const int n_heads = a.n_heads;
   const long long in_off = pr.in_offset_dev ? (long long)*pr.in_offset_dev : 0;
   const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
   const float* __restrict__ scores = pr.scores + in_off;
-  const int64_t* __restrict__ seg_offsets = pr.seg_offsets;
-  const int n_heads = a.n_heads;
-  const long long budget = pr.budget;
+  const int total = (int)device_total(pr.total_entries, seg_offsets, n_heads);
+  const int kept_total = (int)effective_budget(pr.budget, pr.budget_dev, total);
+  const int wave_base = __builtin_amdgcn_readfirstlane((bx * kSelWaves + wave) * (64 * KP));
+  unsigned int key[KP];
+  load_keys<KP>(scores, wave_base, total, key);
+  if (threadIdx.x <= n_heads)                        // published by the barriers below
+    sh.off[threadIdx.x] = seg_offsets ? (int)seg_offsets[threadIdx.x]
+                                      : ((int)threadIdx.x == n_heads ? total : total / n_heads * (int)threadIdx.x);
+  if (alone && threadIdx.x == 0) st->error = 0u;     // nothing cleared the region, and nothing here can fail
+  // Survivor counts of a prepared problem are cleared here, before this workgroup's exchange word is
+  // published: nobody adds to them before having seen all of those (device-scope, as the additions are).
+  if (primed && bx == 0 && threadIdx.x < (unsigned)n_heads)
+    st_dev(reinterpret_cast<unsigned int*>(&pr.head_counts[threadIdx.x]), 0u);
 
-  __shared__ SelShared sh;
-  const long long total = device_total(pr.total_entries, seg_offsets, n_heads);
-  float val[kSelPerThread];
-  load_chunk(bx, scores, total, sh, val);
-  Pick pk;
-  pk.prefix = 0u;
-  pk.need = effective_budget(budget, pr.budget_dev, total);
-  const long long kept_total = pk.need;
-
-  // A primed problem arrives with its first histogram complete (the score kernels built it from the
-  // scores they wrote) and everything else cleared: no init launch, no first pass, one barrier fewer.
-  // Its survivor counts are cleared here, by a workgroup that passes two barriers before anybody adds to them.
-  const bool primed = (a.primed_mask >> prob) & 1u;
-  unsigned int round = 0u;
-  if (primed) {
-    if (bx == 0 && threadIdx.x < (unsigned)n_heads)        // device-scope store: the counts are added to with device-scope atomics
-      st_dev(reinterpret_cast<unsigned int*>(&pr.head_counts[threadIdx.x]), 0u);
-  } else {
-    hist_phase<0>(bx, val, total, pk.prefix, sh, hist);
-    grid_sync(st, ++round, nb, a.spin_limit);
+  Threshold t = {0xffffffffu, 0u};                   // nothing survives
+  unsigned int rows = 0u;                            // rows of this wavefront that may hold survivors
+  unsigned int gt_before = 0u, eq_before = 0u;
+  if (kept_total > 0) {                              // uniform over the problem's workgroups, like everything below
+    // The interval that holds the threshold, at first every key there is; `prepared`: its histogram is there.
+    Interval v = {1u, 0xfffffffeu, 32u, (unsigned int)kept_total, (unsigned int)total};
+    bool counted = primed, first = true;
+    bool crowded = false;                            // one workgroup holds more of the interval's keys than its segment takes
+    unsigned int epoch = 0u, round = 0u, level = 0u;
+    for (;;) {
+      // ---- too many keys to collect (or nothing known yet): count them by their next bits
+      if (first || (!decided(v) && (v.count > kListCap || crowded))) {
+        if (!counted) {
+          __syncthreads();
+          sh.hist[threadIdx.x] = 0u;
+          __syncthreads();
+          if (first) count_first<KP>(key, sh.hist);
+          else count_level<KP>(key, v, sh.hist);
+          lds_done();
+          __syncthreads();
+          bin_count = sh.hist[kLevelBins - 1 - threadIdx.x];
+          if (first && threadIdx.x == kLevelBins - 1) bin_count -= missing<KP>(bx, total);
+          if (!alone) {
+            unsigned int* gh = &hist[level * kLevelBins + (kLevelBins - 1) - threadIdx.x];
+            if (bin_count) __hip_atomic_fetch_add(gh, bin_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            grid_sync(st, ++round, nb, a.spin_limit);
+            bin_count = ld_dev(gh);
+          }
+        }
+        unsigned int pk[3];
+        pick_bin(bin_count, v.need, sh, pk);
+        if (first) v = first_interval(pk);
+        else narrow(v, pk);
+        first = counted = crowded = false;
+        ++level;
+        continue;
+      }
+      // ---- collect them
+      unsigned int above, inside, inside_base;
+      unsigned int rows_above, rows_inside;
+      split_keys<KP>(key, v, sh, above, inside, inside_base, rows_above, rows_inside);
+      rows = rows_above | rows_inside;
+      const bool want_keys = !decided(v);
+      unsigned int n_list = inside, list_before = 0u;
+      if (alone) {
+        if (want_keys) collect_keys<KP>(key, v, inside_base, rows_inside, [&](unsigned int at, unsigned int k) { sh.list[at] = k; });   // inside == v.count <= kListCap
+      } else {
+        // this workgroup's keys to its segment, then its counts; the counts are the signal that the keys are there
+        if (want_keys && inside <= kSegCap)
+          collect_keys<KP>(key, v, inside_base, rows_inside,
+                           [&](unsigned int at, unsigned int k) { st_dev(&seg[(unsigned int)bx * kSegCap + at], k); });
+        drain_vmem();
+        __syncthreads();
+        ++epoch;
+        if (wave == 0) {
+          if (lane == 0)
+            st_dev(&flag[bx], ((unsigned long long)epoch << 48) | ((unsigned long long)above << 24) | inside);
+          unsigned int gt = 0u, before = 0u, pos = 0u, over = 0u, spins = 0u;
+          bool gave_up = false;
+          for (unsigned int b0 = 0; b0 < nb; b0 += 64u) {
+            const unsigned int b = b0 + (unsigned int)lane;
+            unsigned long long x = 0ull;
+            for (;;) {
+              if (b < nb) x = ld_dev(&flag[b]);
+              if (__all(b >= nb || (unsigned int)(x >> 48) >= epoch)) break;
+              if (gave_up || ++spins > a.spin_limit) { gave_up = true; break; }
+              __builtin_amdgcn_s_sleep(1);
+            }
+            if (b >= nb || (unsigned int)(x >> 48) < epoch) x = 0ull;
+            const unsigned int ab = (unsigned int)(x >> 24) & 0xffffffu, in = (unsigned int)x & 0xffffffu;
+            const unsigned int incl = wave_scan(in);
+            if (b < nb) sh.seg_pos[b] = pos + incl - in;
+            pos += (unsigned int)__builtin_amdgcn_readlane((int)incl, 63);
+            if (b < (unsigned int)bx) { gt += ab; before += in; }
+            over |= in > kSegCap ? 1u : 0u;
+          }
+          gt = wave_sum(gt);
+          before = wave_sum(before);
+          over = __any(over != 0u) ? 1u : 0u;
+          if (lane == 0) {
+            if (gave_up) st_dev(&st->error, 1u);
+            sh.seg_pos[nb] = pos;
+            sh.before[0] = gt;
+            sh.before[1] = before;
+            sh.before[2] = over;
+            sh.before[3] = pos;
+          }
+        }
+        __syncthreads();
+        gt_before = __builtin_amdgcn_readfirstlane(sh.before[0]);
+        list_before = __builtin_amdgcn_readfirstlane(sh.before[1]);
+        n_list = __builtin_amdgcn_readfirstlane(sh.before[3]);
+        crowded = want_keys && __builtin_amdgcn_readfirstlane(sh.before[2]) != 0u;
+        if (want_keys && !crowded) {
+          if (n_list > kListCap) n_list = kListCap;                       // (only after a wait gave up)
+          for (unsigned int i = threadIdx.x; i < n_list; i += kSelThreads) {
+            unsigned int lo = 0u, hi = nb;                                // the workgroup whose segment holds entry i
+            while (hi - lo > 1u) {
+              const unsigned int mid = (lo + hi) >> 1;
+              if (sh.seg_pos[mid] <= i) lo = mid; else hi = mid;
+            }
+            sh.list[i] = ld_dev(&seg[lo * kSegCap + (i - sh.seg_pos[lo])]);
+          }
+        }
+      }
+      if (!want_keys) {
+        t = threshold_of(v);
+        if (t.ties) eq_before = list_before;         // all equal to T
+        else gt_before += list_before;               // all survive
+        break;
+      }
+      if (crowded) continue;
+      // ---- the threshold among the collected keys
+      sh.hist[threadIdx.x] = 0u;
+      while (!decided(v)) {
+        __syncthreads();                             // the histogram is clear; the list is complete
+        for (unsigned int i = threadIdx.x; i < n_list; i += kSelThreads) {
+          const unsigned int rel = sh.list[i] - v.lo;
+          if (rel <= v.width) lds_add(lds_offset(sh.hist) + 4u * (rel >> level_shift(v)), 1u);
+        }
+        lds_done();
+        __syncthreads();
+        const unsigned int mine = sh.hist[kLevelBins - 1 - threadIdx.x];
+        sh.hist[kLevelBins - 1 - threadIdx.x] = 0u;
+        unsigned int pk[3];
+        pick_bin(mine, v.need, sh, pk);
+        narrow(v, pk);
+      }
+      t = threshold_of(v);
+      if (!alone) {                                  // those of the workgroups before this one
+        unsigned int gt = 0u, eq = 0u;
+        for (unsigned int i = threadIdx.x; i < list_before && i < n_list; i += kSelThreads) {
+          const unsigned int k = sh.list[i];
+          gt += k > t.T ? 1u : 0u;
+          eq += (k == t.T && t.ties) ? 1u : 0u;
+        }
+        const unsigned int both = wave_sum((gt << 16) | eq);               // list_before <= 16384
+        if (lane == 0) sh.wave[wave] = both;
+        __syncthreads();
+        const unsigned int sum = wave_sums(sh.wave, 0).total;
+        gt_before += sum >> 16;
+        eq_before = sum & 0xffffu;
+      }
+      break;
+    }
   }
-  pk = pick_phase<0>(hist, pk, sh);
-  hist_phase<1>(bx, val, total, pk.prefix, sh, hist + kBins);
-  grid_sync(st, ++round, nb, a.spin_limit);
-  pk = pick_phase<1>(hist + kBins, pk, sh);
-  hist_publish_phase(bx, val, total, pk.prefix, sh, hist + 2 * kBins, blk + (size_t)bx * kPubWords);
-  grid_sync(st, ++round, nb, a.spin_limit);
-  pk = pick_phase<2>(hist + 2 * kBins, pk, sh);
+  __syncthreads();                                   // sh.off; sh.wave / sh.wave2 are free
+  write_survivors<KP>(key, rows, scores, wave_base, total, n_heads, t, gt_before, eq_before, kept_total, pr.budget, alone,
+                      bx == 0, sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
+                      pr.kept_scores ? pr.kept_scores + out_off : nullptr);
+  if (alone) return;
 
-  // the counts of the workgroups before this one were published with the last histogram: no
-  // further pass over the keys and no fourth barrier
-  unsigned int gt_mask, eq_mask;
-  mask_phase(bx, val, total, pk.prefix, gt_mask, eq_mask);
-  long long gt_before, eq_before;
-  prefix_published_phase(bx, blk, pk.prefix, sh, gt_before, eq_before);
-  write_phase(bx, val, total, n_heads, seg_offsets, gt_mask, eq_mask, pk.need, budget, gt_before, eq_before,
-              kept_total, sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
-              pr.kept_scores ? pr.kept_scores + out_off : nullptr);
-
-  // A wait that gave up leaves results computed from incomplete histograms.  The workgroup that
+  // A wait that gave up leaves results computed from incomplete counts.  The workgroup that
   // finishes last (every other one has completed its writes before taking its ticket) then replaces
   // them by a mark no consumer can mistake for a selection: no survivors anywhere, counts -1.
   drain_vmem();
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned int t = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sh.wave[0] = (t + 1u == nb && ld_dev(&st->error) != 0u) ? 1u : 0u;
+    const unsigned int tk = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh.wave[0] = (tk + 1u == nb && ld_dev(&st->error) != 0u) ? 1u : 0u;
   }
   __syncthreads();
   if (sh.wave[0] != 0u) {
@@ -590,51 +733,92 @@ __global__ void __launch_bounds__(kSelThreads) sel_fused_kernel(const SelectBatc
   }
 }
 
-// The same phases as separate launches (kernel boundaries take the place of the grid barriers),
-// for a problem too large to keep its whole grid resident.  STEP 0..2: histogram pass STEP; 3: counts; 4: write.
+// The same phases as separate launches (kernel boundaries take the place of the waits), for a problem
+// too large to keep its whole grid resident.  STEP 0: first histogram; 1..4: histograms of the
+// interval's next bits (nothing to do once it is decided); 5: counts; 6: write.
+constexpr int kStepKeys = 32;
 template <int STEP>
 __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch a) {
-  const int prob = problem_of_block(a);
-  const lava_select_problem pr = a.p[prob];
-  const int bx = (int)blockIdx.x - a.first_block[prob];
-  char* region = a.ws + prob * a.ws_stride;
-  unsigned int* hist = reinterpret_cast<unsigned int*>(region + a.off_hist);
-  unsigned int* blk = reinterpret_cast<unsigned int*>(region + a.off_blk);
+  const lava_select_problem pr = a.p[0];
+  const int bx = (int)blockIdx.x, nb = (int)gridDim.x;
+  unsigned int* hist = reinterpret_cast<unsigned int*>(a.ws + a.off_hist);
+  unsigned int* blk = reinterpret_cast<unsigned int*>(a.ws + a.off_blk);
   const int64_t* __restrict__ seg_offsets = pr.seg_offsets;
   const int n_heads = a.n_heads;
-  const long long budget = pr.budget;
   __shared__ SelShared sh;
-  {
-    const long long total = device_total(pr.total_entries, seg_offsets, n_heads);
-    float val[kSelPerThread];
-    const long long in_off = pr.in_offset_dev ? (long long)*pr.in_offset_dev : 0;
-    const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
-    load_chunk(bx, pr.scores + in_off, total, sh, val);
-    Pick pk;
-    pk.prefix = 0u;
-    pk.need = effective_budget(budget, pr.budget_dev, total);
-    const long long kept_total = pk.need;
-    if constexpr (STEP >= 1) pk = pick_phase<0>(hist, pk, sh);
-    if constexpr (STEP >= 2) pk = pick_phase<1>(hist + kBins, pk, sh);
-    if constexpr (STEP >= 3) pk = pick_phase<2>(hist + 2 * kBins, pk, sh);
-    if constexpr (STEP <= 2) {
-      hist_phase<STEP>(bx, val, total, pk.prefix, sh, hist + STEP * kBins);
+  const int lane = threadIdx.x & 63, wave = sel_wave();
+  const int total = (int)device_total(pr.total_entries, seg_offsets, n_heads);
+  const int kept_total = (int)effective_budget(pr.budget, pr.budget_dev, total);
+  const long long in_off = pr.in_offset_dev ? (long long)*pr.in_offset_dev : 0;
+  const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
+  const float* __restrict__ scores = pr.scores + in_off;
+  if (STEP < 6 && kept_total == 0) return;
+  const int wave_base = __builtin_amdgcn_readfirstlane((bx * kSelWaves + wave) * (64 * kStepKeys));
+  Interval v = {0u, 0u, 0u, 0u, 0u};
+  unsigned int pk[3];
+  if (STEP >= 1 && kept_total > 0) {
+    pick_bin(hist[kLevelBins - 1 - threadIdx.x], (unsigned int)kept_total, sh, pk);
+    v = first_interval(pk);
+    for (int l = 1; l < (STEP < 5 ? STEP : kMaxLevels + 1) && !decided(v); ++l) {
+      __syncthreads();
+      pick_bin(hist[l * kLevelBins + kLevelBins - 1 - threadIdx.x], v.need, sh, pk);
+      narrow(v, pk);
+    }
+    if (STEP <= 4 && decided(v)) return;
+    __syncthreads();
+  }
+  unsigned int key[kStepKeys];
+  load_keys<kStepKeys>(scores, wave_base, total, key);
+  if constexpr (STEP <= 4) {
+    sh.hist[threadIdx.x] = 0u;
+    __syncthreads();
+    if constexpr (STEP == 0) {
+      count_first<kStepKeys>(key, sh.hist);
     } else {
-      unsigned int gt_mask, eq_mask;
-      // counts are recomputed in the write step (cheap) so that both steps share count_phase
-      count_phase(bx, val, total, pk.prefix, sh, blk, a.blk_stride, gt_mask, eq_mask);
-      if constexpr (STEP == 4) {
-        long long gt_before, eq_before;
-        prefix_phase(bx, blk, a.blk_stride, sh, gt_before, eq_before);
-        write_phase(bx, val, total, n_heads, seg_offsets, gt_mask, eq_mask, pk.need, budget, gt_before, eq_before,
-                    kept_total, sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
-                    pr.kept_scores ? pr.kept_scores + out_off : nullptr);
+      count_level<kStepKeys>(key, v, sh.hist);
+    }
+    lds_done();
+    __syncthreads();
+    unsigned int c = sh.hist[threadIdx.x];
+    if (STEP == 0 && threadIdx.x == 0) c -= missing<kStepKeys>(bx, total);
+    if (c) __hip_atomic_fetch_add(&hist[STEP * kLevelBins + threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    const Threshold t = kept_total > 0 ? threshold_of(v) : Threshold{0xffffffffu, 0u};
+    if constexpr (STEP == 5) {
+      unsigned int gt = 0u, eq = 0u;
+#pragma unroll
+      for (int j = 0; j < kStepKeys; ++j) {
+        gt += (unsigned int)__popcll(__ballot(key[j] > t.T));
+        eq += t.ties ? (unsigned int)__popcll(__ballot(key[j] == t.T)) : 0u;
       }
+      if (lane == 0) { sh.wave[wave] = gt; sh.wave2[wave] = eq; }
+      __syncthreads();
+      gt = wave_sums(sh.wave, 0).total;
+      eq = wave_sums(sh.wave2, 0).total;
+      if (threadIdx.x == 0) { blk[bx] = gt; blk[nb + bx] = eq; }
+    } else {
+      unsigned int gt = 0u, eq = 0u;
+      if (kept_total > 0)
+        for (int b = (int)threadIdx.x; b < bx; b += kSelThreads) { gt += blk[b]; eq += blk[nb + b]; }
+      gt = wave_sum(gt);
+      eq = wave_sum(eq);
+      if (lane == 0) { sh.wave[wave] = gt; sh.wave2[wave] = eq; }
+      if (threadIdx.x <= n_heads)
+        sh.off[threadIdx.x] = seg_offsets ? (int)seg_offsets[threadIdx.x]
+                                          : ((int)threadIdx.x == n_heads ? total : total / n_heads * (int)threadIdx.x);
+      __syncthreads();
+      gt = wave_sums(sh.wave, 0).total;
+      eq = wave_sums(sh.wave2, 0).total;
+      __syncthreads();
+      write_survivors<kStepKeys>(key, 0xffffffffu, scores, wave_base, total, n_heads, t, gt, eq, kept_total, pr.budget, false, bx == 0,
+                                 sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
+                                 pr.kept_scores ? pr.kept_scores + out_off : nullptr);
     }
   }
 }
 
 // Workgroups of the fused kernel that can be resident at once on the current device.
+constexpr int kMostKeys = 12;
 static int fused_capacity() {
   static int cached[64];
   static bool known[64];
@@ -642,7 +826,7 @@ static int fused_capacity() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
   if (!known[dev]) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sel_fused_kernel, kSelThreads, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sel_fused_kernel<kMostKeys>, kSelThreads, 0) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return 0;
     cached[dev] = per_cu * cus;
@@ -651,9 +835,43 @@ static int fused_capacity() {
   return cached[dev];
 }
 
+static int64_t workgroups_for(int64_t total, int keys) {
+  const int64_t chunk = (int64_t)kSelThreads * keys, nb = (total + chunk - 1) / chunk;
+  return nb < 1 ? 1 : nb;
+}
+
+// Keys per lane for a launch that starts with problems[0 .. n - 1], of whose workgroups `cap` may be resident:
+// few, because every row of keys costs 0.3 us in all, until the number of workgroups that exchange their
+// counts costs more.  In-kernel times, not prepared, in us (workgroups): 33 K entries: 2 keys 11.0 (17),
+// 4 keys 11.9 (9), 8 keys 13.3 (5); 48 K: 11.9 (24), 12.4 (12); 262 K: 17.7 (128), 16.0 (64), 15.8 (32),
+// 16 keys 18.8 (16); 1 M: 4 keys 24.5 (256), 8 keys 21.1 (128), 12 keys 21 (86), 16 keys 21.7 (64).
+static int fused_keys(const lava_select_problem* problems, int n, int cap) {
+  for (int keys : {2, 4, 8}) {
+    int64_t sum = 0, widest = 0;
+    for (int i = 0; i < n; ++i) {
+      const int64_t nb = workgroups_for(problems[i].total_entries, keys);
+      sum += nb;
+      if (nb > widest) widest = nb;
+    }
+    if (sum <= cap && widest <= (keys == 2 ? 20 : 64)) return keys;
+  }
+  return kMostKeys;
+}
+
+// Calls f(std::integral_constant<int, KP>) for a number of keys per lane fused_keys returned.
+template <class F>
+static void with_keys(int keys, F&& f) {
+  switch (keys) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    default: f(std::integral_constant<int, kMostKeys>{}); break;
+  }
+}
+
 // Selections of a batch: consecutive problems are packed into launches of the fused kernel as long
-// as their workgroups fit into half of the device together (they all have to be resident: each
-// problem meets at its own grid barriers; should another stream hold compute units for so long that
+// as their workgroups fit into half of the device together (they all have to be resident: the workgroups
+// of a problem wait for each other; should another stream hold compute units for so long that
 // a bounded wait gives up, the kernel marks the outputs and the status call reports it).  A single
 // problem wider than that runs as step launches.
 int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_problem* problems, int64_t max_total,
@@ -665,47 +883,66 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
   a.off_hist = w.off_hist;
   a.off_state = w.off_state;
   a.off_blk = w.off_blk;
-  a.blk_stride = w.n_blocks;
   const dim3 block(kSelThreads);
-  // Half of what the device can keep resident: the grid barriers need every workgroup of a launch
-  // on the device at once, and the margin leaves room for whatever else is running there.
-  const int cap = (fused_capacity() < kFusedMaxBlocks ? fused_capacity() : kFusedMaxBlocks) / 2;
   a.spin_limit = tuning().barrier_spin_limit > 0 ? (unsigned int)tuning().barrier_spin_limit : kSpinLimit;
-  int first = 0;
+  // Half of what the device can keep resident: the waits need every workgroup of a launch on the device
+  // at once, and the margin leaves room for whatever else is running there.
+  const int cap = fused_capacity() / 2 < kFusedMaxBlocks ? fused_capacity() / 2 : kFusedMaxBlocks;
+  int first = 0, group_end = 0, keys = kMostKeys;
   while (first < n_problems) {
-    int count = 0, blocks = 0;
-    while (first + count < n_problems && count < kMaxSelProblems) {
-      const int64_t t = problems[first + count].total_entries;
-      const int nb = (int)((t + kSelChunk - 1) / kSelChunk) < 1 ? 1 : (int)((t + kSelChunk - 1) / kSelChunk);
+    if (first == group_end) {
+      // the next group of at most kMaxSelProblems problems: one choice of keys per lane, one clearing launch
+      const int n = n_problems - first < kMaxSelProblems ? n_problems - first : kMaxSelProblems;
+      group_end = first + n;
+      keys = fused_keys(problems + first, n, cap);
+      // Regions and survivor counts are cleared unless no kernel of the group needs that: the one-launch
+      // selection of a problem that fits one workgroup does not, and that of a prepared one clears its counts itself.
+      bool needed = false;
+      a.primed_mask = 0u;
+      for (int i = 0; i < n; ++i) {
+        const lava_select_problem& pr = problems[first + i];
+        a.p[i] = pr;
+        if (pr.primed) a.primed_mask |= 1u << i;
+        const int64_t nb = workgroups_for(pr.total_entries, keys);
+        if (nb > cap || (nb > 1 && !pr.primed)) needed = true;
+      }
+      if (needed && !cleared) {
+        a.ws = static_cast<char*>(ws) + (size_t)first * w.bytes;
+        ProfScope ps(KID_SEL_INIT, s);
+        hipLaunchKernelGGL(sel_init_kernel, dim3(n), block, 0, s, a);
+      }
+    }
+    int count = 0;
+    int64_t blocks = 0;
+    a.primed_mask = 0u;
+    while (first + count < group_end) {
+      const lava_select_problem& pr = problems[first + count];
+      const int64_t nb = workgroups_for(pr.total_entries, keys);
       if (count > 0 && blocks + nb > cap) break;
-      a.first_block[count] = blocks;
+      a.first_block[count] = (int)blocks;
       blocks += nb;
-      a.p[count] = problems[first + count];
+      a.p[count] = pr;
+      if (pr.primed) a.primed_mask |= 1u << count;
       ++count;
     }
     a.n_problems = count;
-    a.first_block[count] = blocks;
+    a.first_block[count] = (int)blocks;
     a.ws = static_cast<char*>(ws) + (size_t)first * w.bytes;
-    a.primed_mask = 0u;
-    for (int i = 0; i < count; ++i)
-      if (a.p[i].primed) a.primed_mask |= 1u << i;
-    const bool all_primed = a.primed_mask == (count == 32 ? 0xffffffffu : (1u << count) - 1u);
     const bool fused = blocks <= cap;
-    if (!(fused && (all_primed || cleared))) {             // the one-launch selection clears a primed problem's counts itself
-      ProfScope ps(KID_SEL_INIT, s);
-      hipLaunchKernelGGL(sel_init_kernel, dim3(count), block, 0, s, a);
-    }
     if (fused) {
       ProfScope ps(KID_SEL_FUSED, s);
-      hipLaunchKernelGGL(sel_fused_kernel, dim3(blocks), block, 0, s, a);
+      const dim3 grid((unsigned)blocks);
+      with_keys(keys, [&](auto kp) { hipLaunchKernelGGL(sel_fused_kernel<decltype(kp)::value>, grid, block, 0, s, a); });
     } else {                                               // a single problem wider than the device allows
       ProfScope ps(KID_SEL_STEPS, s);
-      const dim3 grid(blocks);
-      if (!all_primed) hipLaunchKernelGGL(sel_step_kernel<0>, grid, block, 0, s, a);
+      const dim3 grid((unsigned)workgroups_for(a.p[0].total_entries, kStepKeys));
+      if (!a.p[0].primed) hipLaunchKernelGGL(sel_step_kernel<0>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<1>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<2>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<3>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<4>, grid, block, 0, s, a);
+      hipLaunchKernelGGL(sel_step_kernel<5>, grid, block, 0, s, a);
+      hipLaunchKernelGGL(sel_step_kernel<6>, grid, block, 0, s, a);
     }
     const int32_t st = launch_status();
     if (st != LAVA_OK) return st;

@@ -493,12 +493,12 @@ struct PoolArgs {
 };
 
 // Histogram of the selection's first digit over the scores a workgroup has just written, for a selection
-// workspace prepared alongside (lava_window_scores_primed): per-workgroup counts in `bins` (kSelBins words
+// workspace prepared alongside (lava_window_scores_primed): per-workgroup counts in `bins` (kSelDigit0Bins words
 // of LDS, zeroed and published by a barrier before the first call), then one device-scope add per
 // non-empty bin.  Runs of equal digits (pooling makes plateaus) are counted once per run by the caller.
 __device__ __forceinline__ void digit0_count(unsigned int* bins, float score, unsigned int& run_digit,
                                              unsigned int& run_len) {
-  const unsigned int digit = score_key(score) >> kSelDigit0Shift;
+  const unsigned int digit = sel_digit0(score_key(score));
   if (digit != run_digit) {
     if (run_len != 0u) atomicAdd(&bins[run_digit], run_len);
     run_digit = digit;
@@ -511,7 +511,7 @@ __device__ __forceinline__ void digit0_flush(unsigned int* bins, unsigned int ru
                                              unsigned int* __restrict__ global_hist) {
   if (run_len != 0u) atomicAdd(&bins[run_digit], run_len);
   __syncthreads();
-  for (int i = threadIdx.x; i < kSelBins; i += THREADS) {
+  for (int i = threadIdx.x; i < kSelDigit0Bins; i += THREADS) {
     const unsigned int c = bins[i];
     if (c) __hip_atomic_fetch_add(&global_hist[i], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -696,12 +696,12 @@ __device__ __forceinline__ void scores_finish(const PoolArgs& pa, float vb, int 
                                               unsigned int* s_last, unsigned int n_blocks, unsigned int block_id,
                                               int n_heads, bool writes_vbar, int wave, unsigned int* bins) {
   constexpr int kWaves = THREADS / 64;
-  // `bins`: kSelBins words of LDS that only wavefront 0 has used since the workgroup's last barrier (the
+  // `bins`: kSelDigit0Bins words of LDS that only wavefront 0 has used since the workgroup's last barrier (the
   // start of its own tile ring, which it is done with)
   const bool count_digits = pa.sel_hist0 != nullptr;
   const PlanInputs plan_in = plan_prefetch(pa.plan, pa.plan_seq);
   if (count_digits && wave == 0)
-    for (int i = threadIdx.x; i < kSelBins; i += 64) bins[i] = 0u;
+    for (int i = threadIdx.x; i < kSelDigit0Bins; i += 64) bins[i] = 0u;
   unsigned int run_digit = 0u, run_len = 0u;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) vb = fmaxf(vb, __shfl_xor(vb, off));
@@ -786,8 +786,8 @@ __device__ __forceinline__ void scores_finish(const PoolArgs& pa, float vb, int 
   if (last && pa.plan.e != nullptr) {                        // uniform
     __syncthreads();                                         // s_t[0]; every wavefront is done with `bins`
     // scratch: what is left of wavefront 0's own tile ring behind the bins
-    static_assert(kSelBins * 4 + sizeof(BudgetScratchT<kMaxPlannedLayers>) <= 16 * 1024, "wavefront 0's ring");
-    plan_budgets(pa.plan, plan_in, pa.plan_seq, (float)s_t[0], bins + kSelBins);
+    static_assert(kSelDigit0Bins * 4 + sizeof(BudgetScratchT<kMaxPlannedLayers>) <= 16 * 1024, "wavefront 0's ring");
+    plan_budgets(pa.plan, plan_in, pa.plan_seq, (float)s_t[0], bins + kSelDigit0Bins);
   }
 }
 
@@ -1260,10 +1260,10 @@ poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_ha
                 const BudgetPlanArgs plan, int plan_seq) {
   __shared__ float s_in[kPoolChunk + 2 * kPoolMaxHalf];
   __shared__ BudgetScratchT<kMaxPlannedLayers> s_plan;
-  __shared__ unsigned int s_bins[kSelBins];
+  __shared__ unsigned int s_bins[kSelDigit0Bins];
   const PlanInputs plan_in = plan_prefetch(plan, plan_seq);
   if (sel_hist0 != nullptr)
-    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) s_bins[i] = 0u;      // published by the barrier below
+    for (int i = threadIdx.x; i < kSelDigit0Bins; i += kPoolThreads) s_bins[i] = 0u;      // published by the barrier below
   unsigned int run_digit = 0u, run_len = 0u;
   __shared__ float s_vmax[kPoolThreads / 64];
   __shared__ double s_s[kPoolThreads / 64], s_t[kPoolThreads / 64];
