@@ -1365,14 +1365,16 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   int64_t max_bx = share(target_wgs) / ((int64_t)d.n_kv_heads * p.n_chunks);
   if (max_bx < 1) max_bx = 1;
   int64_t tpb = (n_tiles + max_bx - 1) / max_bx;
-  if (tpb < 16) tpb = 16;
+  // Short sequences: spans so short that their tiles and the pooling halo's two are one round of the eight
+  // wavefronts (4115 tokens, 8 heads: 16 tiles a workgroup 48.0 us a layer, 8: 44.6, 6: 44.3, 4: 45.4);
+  // 32-bit inputs, whose products take 16 times as long, half of that (1024 tokens, 2 heads: 16 tiles 69.5 us,
+  // 8: 52.0, 6: 48.0, 4: 44.2).
+  const int64_t shortest = d.dtype == LAVA_F32 ? 4 : 6;
+  if (tpb < shortest) tpb = shortest;
   // all heads of a group in one workgroup -> the scores kernel can finish the scores itself, which
   // needs the workgroup's span of raw scores in LDS: a bounded number of tiles per workgroup
   p.fused_pool = p.n_chunks == 1;
   const int64_t fused_cap = p.narrow ? kFusedTilesNarrow : kFusedTilesWide;
-  if (p.fused_pool && tpb > fused_cap) tpb = fused_cap;
-  p.tiles_per_block = (int)tpb;
-  p.blocks_x = (int)((n_tiles + tpb - 1) / tpb);
   // bounds that hold for either shape, alone or in a batch, and never shrink when n grows: a
   // workspace sized for the longest sequence of a batch must also hold the (differently split)
   // partials of every shorter one
@@ -1381,6 +1383,24 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   if (bx_alone < 1) bx_alone = 1;
   const int64_t capped = (n_tiles + kFusedTilesNarrow - 1) / kFusedTilesNarrow;
   p.blocks_x_bound = (int)(bx_alone > capped ? bx_alone : capped);
+  if (p.fused_pool && tpb > fused_cap) {
+    tpb = fused_cap;
+    if (shared) {
+      // Several rounds of workgroups: the batch as a whole is cut into as many workgroups as fill whole
+      // rounds, instead of longest spans whose last round leaves half the device idle (32 sequences of 32768
+      // tokens: 2816 workgroups of up to 96 tiles, 5.5 rounds of 512, 1310 us for the whole stack; 3072 of 86,
+      // 6 rounds, 1290 us).
+      const int64_t all = (batch_tokens + kTileKeys - 1) / kTileKeys * d.n_kv_heads;
+      const int64_t rounds = (all + fused_cap * target_wgs - 1) / (fused_cap * target_wgs);
+      const int64_t fewest = (n_tiles + fused_cap - 1) / fused_cap;
+      int64_t bx = n_tiles * rounds * target_wgs / all;
+      if (bx > p.blocks_x_bound) bx = p.blocks_x_bound;      // what the workspace holds; at least `fewest`
+      if (bx < fewest) bx = fewest;
+      tpb = (n_tiles + bx - 1) / bx;
+    }
+  }
+  p.tiles_per_block = (int)tpb;
+  p.blocks_x = (int)((n_tiles + tpb - 1) / tpb);
   // value norms: one workgroup per CU for a sequence alone, at least 8 tiles (one per wavefront)
   // each.  Sequences of a batch keep that cut (no share): the kernel's set-up is short, and many
   // small workgroups even out the unequal lengths better than few long ones.

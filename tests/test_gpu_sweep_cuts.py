@@ -1,0 +1,67 @@
+"""How a launch is cut into workgroups: short sequences (spans of a few tiles), and batches whose workgroups fill whole
+rounds.  Scores against the oracle, and canaries behind the workspace the library asked for."""
+import numpy as np
+import pytest
+
+from oracle import lava_oracle as O
+from paper_2509_09754_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lava():
+    from paper_2509_09754_amd import lava as L
+    return L
+
+
+def run(lava, desc, shapes, inps):
+    """The scores of a batch, with a guarded workspace."""
+    q, k, v = (torch.cat([lava.to_device(getattr(i, n), s.dtype).reshape(-1) for s, i in zip(shapes, inps)])
+               for n in ("q_win", "k", "v"))
+    lens = [s.n for s in shapes]
+    need = lava.lava_window_scores_workspace_bytes(desc, len(lens), sum(lens))
+    buf = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    out = lava.lava_window_scores(desc, lens, q, k, v, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    return [x.cpu().numpy() for x in out]
+
+
+def check(shapes, inps, out):
+    """Scores: fp32 sums of exact products, 1e-5 of the value; the statistic: 1e-4 (its logarithms are fp32)."""
+    scores, vbar, stat = out
+    at = 0
+    for b, (s, i) in enumerate(zip(shapes, inps)):
+        want = O.lava_scores(*i.f64(), s.window, s.pool_kernel)[0]
+        got = scores[at: at + s.n_kv_heads * s.n].reshape(s.n_kv_heads, s.n).astype(np.float64)
+        at += s.n_kv_heads * s.n
+        mask = want > 1e-30 * want.max()
+        assert np.max(np.abs(got[:, : s.n_prefix][mask] - want[mask]) / want[mask]) < 1e-5
+        assert np.all(np.isposinf(got[:, s.n_prefix:]))
+        e = O.layer_entropy(want)
+        assert abs(stat[b] - e) <= 1e-4 * abs(e) + 2e-5 / want.size
+
+
+# one tile, one span, several spans with a ragged last one; one round of wavefronts per span and two
+@pytest.mark.parametrize("cfg,n", [(1, 9), (1, 128), (1, 129), (1, 1000), (1, 2049), (2, 33), (2, 191), (2, 193), (2, 1537),
+                                   (2, 6143 + 32)])
+def test_short_sequences(lava, cfg, n):
+    print(f"short sequence cfg{cfg} n={n}", flush=True)
+    s = synth.config(cfg, n=n, budget=0, heavy_count=8 if n > 64 else 1)
+    i = synth.gen_layer(s, n)
+    desc = lava.LayerDesc.make(s.n_q_heads, s.n_kv_heads, s.head_dim, s.window, s.dtype)
+    check([s], [i], run(lava, desc, [s], [i]))
+
+
+def test_batch_of_whole_rounds(lava):
+    """Sequences of very different length in one launch of several rounds (2 KV heads: few workgroups per token)."""
+    print("batch cut into whole rounds", flush=True)
+    base = synth.LayerShape(8, 2, 64, 0, 8, "bf16", 0, heavy_frac=0.01)
+    import dataclasses
+    lens = [40000, 33, 3000, 131071, 9, 50001, 77777, 131072, 64, 100000] + [90000 + 17 * j for j in range(10)]
+    shapes = [dataclasses.replace(base, n=n, heavy_count=4 if n > 64 else 1) for n in lens]
+    inps = [synth.gen_layer(s, 3 + j) for j, s in enumerate(shapes)]
+    desc = lava.LayerDesc.make(8, 2, 64, 8, "bf16")
+    check(shapes, inps, run(lava, desc, shapes, inps))
