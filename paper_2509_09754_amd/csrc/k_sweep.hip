@@ -308,6 +308,19 @@ __device__ __forceinline__ void clear_selection_region(const SweepArgs& a, int z
   if (threadIdx.x < kSelStateWords) state[threadIdx.x] = 0u;
 }
 
+// A group split into chunks: the raw scores of head g's span of tiles start from +0 (the chunks' workgroups join
+// theirs with an integer maximum).  Done by the first kernel of the call; as a launch of its own it took 4.7 us.
+// Called after the tile loop: the ring counts loads, which stores in between would upset.
+__device__ __forceinline__ void clear_raw_scores(const SweepArgs& a, const SweepSeq& sq, int g, long long t_begin, long long t_end,
+                                                 int threads) {
+  if (a.n_chunks == 1) return;
+  const long long n_prefix = sq.n - a.w;
+  float* raw = reinterpret_cast<float*>(a.ws + sq.ws_off + a.off_sraw) + (long long)g * n_prefix;
+  long long end = t_end * kTileKeys;
+  if (end > n_prefix) end = n_prefix;
+  for (long long i = t_begin * kTileKeys + threadIdx.x; i < end; i += threads) raw[i] = 0.0f;
+}
+
 // The value-norm sweep of one wavefront: tiles first, first + WAVES, ... (cnt of them) of the head at
 // vg, whose first STAGES - 1 tiles have already been requested into `ring`.  Returns this lane's maximum
 // over its rows (row lane % 32 of every tile) of sum_c |V[row, c]|; with token_norm the rows' own norms
@@ -455,6 +468,7 @@ stats_kernel(const SweepArgs a) {
       float* __restrict__ vnorm_part = reinterpret_cast<float*>(a.ws + sq.ws_off + a.off_vnorm_part);
       vnorm_part[(long long)g * sq.vnorm_blocks + blockIdx.x] = m;
     }
+    if (with_v) clear_raw_scores(a, sq, g, t_begin, t_end, Shape<DT, D, W>::kThreads);
   } else {
     float2 mine;
     if (stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, s_red, mine))
@@ -1230,6 +1244,7 @@ vnorm_kernel(const SweepArgs a) {
     if (p < cnt) dma.issue(vg, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
   const float best = vnorm_tiles<DT, D, kWaves, kStages, false>(dma, frags, vg, nullptr, n, first, cnt, ring, lane,
                                                                  a.token_norm != 0, row_norm + (long long)g * n);
+  clear_raw_scores(a, sq, g, t_begin, t_end, VShape<DT, D>::kThreads);
   float wave_best = best;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) wave_best = fmaxf(wave_best, __shfl_xor(wave_best, off));
@@ -1249,7 +1264,7 @@ vnorm_kernel(const SweepArgs a) {
 // reduction order; the last workgroup to finish forms e = (ln S - T / S) / (H_kv * n')  (Eq. 4-5).
 // ------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 256;
-constexpr int kPoolPerThread = 8;
+constexpr int kPoolPerThread = 4;   // 21013 tokens, 4 heads: 8 entries per thread 10.7 us, 4: 8.5 (latency of one workgroup, not bytes)
 constexpr int kPoolChunk = kPoolThreads * kPoolPerThread;
 
 __global__ void __launch_bounds__(kPoolThreads)
@@ -1314,12 +1329,6 @@ poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_ha
     __syncthreads();
     plan_budgets(plan, plan_in, plan_seq, (float)s_t[0], &s_plan);
   }
-}
-
-__global__ void __launch_bounds__(256) fill_zero_kernel(float* __restrict__ p, long long count) {
-  const long long i0 = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-  for (int j = 0; j < 4; ++j)
-    if (i0 + j < count) p[i0 + j] = 0.0f;
 }
 
 // ------------------------------------------------------------------------------------------ host
@@ -1463,6 +1472,9 @@ __global__ void __launch_bounds__(256) unit_vnorm_kernel(const SweepArgs a) {
   if (i < a.H_kv * sq.vnorm_blocks) vnorm_part[i] = 1.0f;
   for (int j = i; j < kCtlUnitA + a.H_kv * sq.blocks_x; j += (int)gridDim.x * 256) counters[j] = 0u;
   if (blockIdx.x == 0) clear_selection_region(a, (int)blockIdx.z, 256);
+  const long long n_tiles = (sq.n + kTileKeys - 1) / kTileKeys, per = (n_tiles + gridDim.x - 1) / gridDim.x;
+  const long long t0 = blockIdx.x * per, t1 = t0 + per < n_tiles ? t0 + per : n_tiles;
+  for (int g = 0; g < a.H_kv; ++g) clear_raw_scores(a, sq, g, t0, t1, 256);
 }
 
 int32_t launch_unit_vnorm(const lava_layer_desc& d, const SweepArgs& a, int max_vnorm_blocks, hipStream_t s) {
@@ -1543,13 +1555,6 @@ int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, int max_bloc
                       hipStream_t s) {
   const dim3 grid(max_blocks_x, d.n_kv_heads * p.n_chunks, a.n_seq);
   ProfScope ps(KID_SCORES, s);
-  if (p.n_chunks > 1) {
-    // partial group maxima are combined with integer atomicMax; start from +0 (a fill kernel,
-    // not a memset node, so the call sequence can be captured in a HIP graph).  One sequence per launch here.
-    const long long count = (long long)d.n_kv_heads * (a.s[0].n - d.window);
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, s,
-                       reinterpret_cast<float*>(a.ws + a.s[0].ws_off + a.off_sraw), count);
-  }
 #define LAVA_SCORES_W(DTV, DV, GTV, WV)                                                                     \
   do {                                                                                                      \
     if (p.fused_pool)                                                                                       \

@@ -96,8 +96,12 @@ __device__ __forceinline__ bool arrive_last(unsigned int* ctr, unsigned int n, u
   drain_vmem();
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned int t = arrive_two_level(ctr, n, id, 1u);
-    *s_flag = (t != 0xffffffffu && t + 1u == arrive_groups(n)) ? 1u : 0u;
+    if (n <= 64u) {                       // few enough for one address: one trip to memory instead of two
+      *s_flag = __hip_atomic_fetch_add(&ctr[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == n ? 1u : 0u;
+    } else {
+      const unsigned int t = arrive_two_level(ctr, n, id, 1u);
+      *s_flag = (t != 0xffffffffu && t + 1u == arrive_groups(n)) ? 1u : 0u;
+    }
   }
   __syncthreads();
   return *s_flag != 0u;
