@@ -161,14 +161,35 @@ def _check(status: int, where: str) -> None:
         raise LavaError(status, where)
 
 
+# What a call costs on the host decides how fast short layers run: the three calls of a layer took 34 us of
+# which the library's own launches are 13.  Addresses go to ctypes as plain integers (no c_void_p objects),
+# lengths as a C array (no numpy), and the current stream comes as its raw handle: a Stream object takes
+# 3 us per call.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream, _cuda_getDevice as _device_index
+except ImportError:          # a torch without these: the public, slower way
+    _raw_stream = _device_index = None
+
+
+def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device_index())
+
+
+def _lengths(seq_lens):
+    """(C array of int64, number of sequences, their sum)."""
+    if type(seq_lens) in (list, tuple) and all(type(n) is int and 0 <= n < 1 << 40 for n in seq_lens):
+        return (ctypes.c_int64 * len(seq_lens))(*seq_lens), len(seq_lens), sum(seq_lens)
+    lens = np.asarray(seq_lens, dtype=np.int64)
+    n = int(lens.shape[0])
+    return (ctypes.c_int64 * n)(*lens.ravel()[:n].tolist()), n, int(lens.sum())
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None) -> torch.Tensor:
@@ -218,10 +239,9 @@ def lava_window_scores(desc: LayerDesc, seq_lens: Sequence[int], q_win: torch.Te
     """Scores [sum_b H_kv * N_b] (per sequence [H_kv][N_b]), vbar [batch, H_kv], layer_stat [batch].
     With select_workspace the call is lava_window_scores_primed; with budget_plan (see make_budget_plan)
     it is lava_window_scores_planned, which also accepts select_workspace."""
-    lens = np.ascontiguousarray(np.asarray(seq_lens, dtype=np.int64))
-    batch, total = int(lens.shape[0]), int(lens.sum())
-    dev = k.device
-    _dev(q_win, "q_win", desc.torch_dtype), _dev(k, "k", desc.torch_dtype), _dev(v, "v", desc.torch_dtype)
+    lens, batch, total = _lengths(seq_lens)
+    dtype = desc.torch_dtype
+    _dev(q_win, "q_win", dtype), _dev(k, "k", dtype), _dev(v, "v", dtype)
     row = desc.n_kv_heads * desc.head_dim
     if k.numel() != total * row or v.numel() != total * row:
         raise ValueError("k / v hold a different number of tokens than seq_lens")
@@ -232,16 +252,16 @@ def lava_window_scores(desc: LayerDesc, seq_lens: Sequence[int], q_win: torch.Te
         if lse.numel() != batch * desc.n_q_heads * desc.window:
             raise ValueError("lse must be [batch, H, w]")
     if scores is None:
-        scores = torch.empty(total * desc.n_kv_heads, dtype=torch.float32, device=dev)
+        scores = torch.empty(total * desc.n_kv_heads, dtype=torch.float32, device=k.device)
     if vbar is None:
-        vbar = torch.empty(batch, desc.n_kv_heads, dtype=torch.float32, device=dev)
+        vbar = torch.empty(batch, desc.n_kv_heads, dtype=torch.float32, device=k.device)
     if layer_stat is None:
-        layer_stat = torch.empty(batch, dtype=torch.float32, device=dev)
+        layer_stat = torch.empty(batch, dtype=torch.float32, device=k.device)
     if workspace is None:
         nbytes = lava_window_scores_workspace_bytes(desc, batch, total)
-        workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=k.device)
     if budget_plan is not None:
-        st = lib.lava_window_scores_planned(ctypes.byref(desc), batch, lens.ctypes.data_as(ctypes.c_void_p), _ptr(q_win),
+        st = lib.lava_window_scores_planned(ctypes.byref(desc), batch, lens, _ptr(q_win),
                                             _ptr(k), _ptr(v), _ptr(lse), _ptr(scores), _ptr(vbar), _ptr(layer_stat),
                                             _ptr(workspace), workspace.numel(), _ptr(select_workspace),
                                             select_workspace.numel() if select_workspace is not None else 0,
@@ -249,13 +269,13 @@ def lava_window_scores(desc: LayerDesc, seq_lens: Sequence[int], q_win: torch.Te
         _check(st, "lava_window_scores_planned")
         return scores, vbar, layer_stat
     if select_workspace is not None:
-        st = lib.lava_window_scores_primed(ctypes.byref(desc), batch, lens.ctypes.data_as(ctypes.c_void_p), _ptr(q_win),
+        st = lib.lava_window_scores_primed(ctypes.byref(desc), batch, lens, _ptr(q_win),
                                            _ptr(k), _ptr(v), _ptr(lse), _ptr(scores), _ptr(vbar), _ptr(layer_stat),
                                            _ptr(workspace), workspace.numel(), _ptr(select_workspace),
                                            select_workspace.numel(), _stream(stream))
         _check(st, "lava_window_scores_primed")
         return scores, vbar, layer_stat
-    st = lib.lava_window_scores(ctypes.byref(desc), batch, lens.ctypes.data_as(ctypes.c_void_p), _ptr(q_win),
+    st = lib.lava_window_scores(ctypes.byref(desc), batch, lens, _ptr(q_win),
                                 _ptr(k), _ptr(v), _ptr(lse), _ptr(scores), _ptr(vbar), _ptr(layer_stat),
                                 _ptr(workspace), workspace.numel(), _stream(stream))
     _check(st, "lava_window_scores")
@@ -315,21 +335,20 @@ def lava_select_topk(n_heads: int, scores: torch.Tensor, budget: int, seg_offset
     """primed: `workspace` was prepared by lava_window_scores(select_workspace=workspace) for these scores."""
     _dev(scores, "scores", torch.float32)
     total = scores.numel() if total_entries is None else int(total_entries)
-    dev = scores.device
     if seg_offsets is not None:
         _dev(seg_offsets, "seg_offsets", torch.int64)
     if budget_dev is not None:
         _dev(budget_dev, "budget_dev", torch.int64)
     if head_counts is None:
-        head_counts = torch.empty(n_heads, dtype=torch.int32, device=dev)
+        head_counts = torch.empty(n_heads, dtype=torch.int32, device=scores.device)
     if head_offsets is None:
-        head_offsets = torch.empty(n_heads + 1, dtype=torch.int64, device=dev)
+        head_offsets = torch.empty(n_heads + 1, dtype=torch.int64, device=scores.device)
     if kept_idx is None:
-        kept_idx = torch.empty(max(int(budget), 1), dtype=torch.int32, device=dev)
+        kept_idx = torch.empty(max(int(budget), 1), dtype=torch.int32, device=scores.device)
     if kept_scores is None and want_scores:
-        kept_scores = torch.empty(max(int(budget), 1), dtype=torch.float32, device=dev)
+        kept_scores = torch.empty(max(int(budget), 1), dtype=torch.float32, device=scores.device)
     if workspace is None:
-        workspace = torch.empty(max(lava_select_workspace_bytes(total), 256), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(lava_select_workspace_bytes(total), 256), dtype=torch.uint8, device=scores.device)
     if primed:
         if seg_offsets is not None:
             raise ValueError("a prepared workspace serves equal segments only")
