@@ -321,6 +321,12 @@ __device__ __forceinline__ void clear_raw_scores(const SweepArgs& a, const Sweep
   for (long long i = t_begin * kTileKeys + threadIdx.x; i < end; i += threads) raw[i] = 0.0f;
 }
 
+// Workgroup barrier that leaves the tile loads in flight (what it orders is the reads and loads of the asm and
+// DMA protocol above, each of which has waited for its own).
+__device__ __forceinline__ void wave_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // The value-norm sweep of one wavefront: tiles first, first + WAVES, ... (cnt of them) of the head at
 // vg, whose first STAGES - 1 tiles have already been requested into `ring`.  Returns this lane's maximum
 // over its rows (row lane % 32 of every tile) of sum_c |V[row, c]|; with token_norm the rows' own norms
@@ -425,6 +431,12 @@ stats_kernel(const SweepArgs a) {
       clear_selection_region(a, (int)blockIdx.z, Shape<DT, D, W>::kThreads);
     }
   }
+  // VN: the query rows, once per workgroup, into the last stage of the first GT wavefronts' rings, ahead of the
+  // first tiles
+  static_assert(!VN || kWaves >= GT, "one staging buffer per head");
+  if constexpr (VN) {
+    if (wave < GT) request_q<DT, D>(dma, q_win, h0, nh, wave, w, a.bph, lane, ring + (kStages - 1) * T::kTileChunks);
+  }
   // with the value rows first, the ring holds both streams in turn: the wavefront's cnt value tiles, then
   // its cnt key tiles (a wavefront with few tiles already requests keys here)
 #pragma unroll
@@ -432,14 +444,29 @@ stats_kernel(const SweepArgs a) {
     if (p < cnt) dma.issue(first_stream, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
     else if (with_v && p < 2 * cnt) dma.issue(kg, first + (long long)(p - cnt) * kWaves, n, lane, ring + p * T::kTileChunks);
   }
-  // Every wavefront fetches its own copy of the query rows, after its first tiles so that the two
-  // latencies overlap.  (Staging them once per workgroup through LDS, as the scores kernel does, was
-  // measured slower here: the wavefronts then leave the barrier in step and the sweep loses more
-  // than the set-up gains.)  Both are in before the loop: otherwise the compiler, which cannot count
+  // VN: the value rows, which need no query rows, come first, so the wavefronts have drifted apart again by the
+  // time the keys begin.  Every wavefront fetching its own copy of the query rows (eight times the traffic on lines
+  // all workgroups want at once, and a wait for the first tiles as well) began the sweep 7.3 us after the
+  // workgroup, staging them 3.5 us: 4115 tokens 14.6 -> 9.4 us for the launch, 32768 31.6 -> 29.4, 131072
+  // 106 -> 102.
+  // Otherwise every wavefront fetches its own copy, after its first tiles so that the two latencies
+  // overlap.  (Staging was measured slower there: the wavefronts leave the barrier in step and the sweep loses
+  // more than the set-up gains.)  Both are in before the loop: otherwise the compiler, which cannot count
   // the ring's loads across iterations, waits for everything in flight before each tile's products.
   u32x4 qf[GT][T::kSteps];
-  load_q<DT, D, GT>(q_win, h0, nh, w, a.bph, lane, qf);
-  wait_vmcnt<0>();
+  if constexpr (VN) {
+    int young = 0;
+#pragma unroll
+    for (int p = 0; p < kStages - 1; ++p) young += (p < cnt || (with_v && p < 2 * cnt)) ? 1 : 0;
+    if (wave < GT) wait_tile<DT, D>(young);
+    wave_barrier();
+#pragma unroll
+    for (int t = 0; t < GT; ++t) frags.read(lds_addr(&s_tile[t][kStages - 1][0]), qf[t]);
+    wave_barrier();
+  } else {
+    load_q<DT, D, GT>(q_win, h0, nh, w, a.bph, lane, qf);
+    wait_vmcnt<0>();
+  }
   float v_best = 0.0f;
   int slot0 = 0;
   if constexpr (VN) {

@@ -345,6 +345,17 @@ __device__ __forceinline__ void stage_q(const u32x4* __restrict__ qg, int hb0, i
   }
 }
 
+// Row block hb of the chunk hb0 .. hb0 + nh - 1 as a tile in LDS, requested with direct-to-LDS loads by one
+// wavefront: no registers, and the block is read once per workgroup.  Rows beyond the window repeat its last
+// one, blocks beyond the chunk its last block: their results are masked or never used.
+template <int DT, int D>
+__device__ __forceinline__ void request_q(const TileDma<DT, D>& dma, const u32x4* __restrict__ qg, int hb0, int nh, int t, int w,
+                                          int bph, int lane, u32x4* buf) {
+  const int hb = hb0 + (t < nh ? t : nh - 1), head = hb / bph, row0 = (hb % bph) * 32;
+  const char* rows = reinterpret_cast<const char*>(qg) + ((long long)head * w + row0) * Tile<DT, D>::kRowBytes;
+  dma.issue_clamped(rows, 0, w - row0 < 32 ? w - row0 : 32, lane, buf);
+}
+
 // One head's 32 x 32 block of raw dot products: keys x rows (KEYS_AS_ROWS) or rows x keys.
 template <int DT, int D, bool KEYS_AS_ROWS>
 __device__ __forceinline__ f32x16 dot_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps],
