@@ -558,65 +558,72 @@ __device__ __forceinline__ void digit0_flush(unsigned int* bins, unsigned int ru
   }
 }
 
-// Exponent bias of every (head, row) of a scores workgroup, step 1: thread (row, slice) merges its slice
-// of the head's statistics partials in workgroup order into s_merge[slice][row] (always the same fixed
-// order, independent loads: deterministic, no tickets).  DEVICE_SCOPE: the partials were written by
-// other workgroups of the SAME launch (device-scope stores), so they are read with device-scope loads.
-// `part` points at partial 0 of the head's (chunk's) rows.  The caller synchronises afterwards.
-template <int GT, int THREADS, bool DEVICE_SCOPE>
-__device__ __forceinline__ void merge_partials(const float2* __restrict__ part, int stat_blocks, bool have_lse,
-                                               float c2, float2* s_merge) {
-  constexpr int kRows = GT * 32;
-  constexpr int kSlices = THREADS / kRows;
-  const int row = threadIdx.x % kRows, slice = threadIdx.x / kRows;
+// Exponent bias of every (head, row) of a scores workgroup, step 1: the head's statistics partials are cut into
+// kMergeSlices runs of workgroups; "merger" (slice, row) merges its run in workgroup order into
+// s_merge[slice][row] (always the same fixed order, independent loads: deterministic, no tickets).  In a workgroup
+// with wavefronts to spare the mergers are those that do not fetch query rows.  DEVICE_SCOPE: the partials were
+// written by other workgroups of the SAME launch (device-scope stores), so they are read with device-scope
+// loads.  `part` points at partial 0 of the head's (chunk's) rows.  LDS is accessed by instruction here, so that
+// tiles requested before stay in flight; the caller synchronises afterwards.
+template <int GT, int WAVES>
+struct Merge {
+  static constexpr int kRows = GT * 32;
+  static constexpr bool kSplit = WAVES >= 2 * GT;             // wavefronts GT .. merge, the others fetch query rows
+  static constexpr int kThreads = (kSplit ? WAVES - GT : WAVES) * 64;
+  static constexpr int kSlices = kThreads / kRows;
+  static_assert(kSlices >= 1, "a merger per row");
+};
+template <int GT, int WAVES, bool DEVICE_SCOPE>
+__device__ __forceinline__ void merge_partials(int merger, const float2* __restrict__ part, int stat_blocks, float c2,
+                                               const float2* s_merge) {
+  using M = Merge<GT, WAVES>;
+  constexpr int kRows = M::kRows;
+  if (merger < 0 || merger >= M::kSlices * kRows) return;
+  const int row = merger % kRows, slice = merger / kRows;
   float m = -INFINITY, z = 0.0f;
-  if (!have_lse) {
-    const int per = (stat_blocks + kSlices - 1) / kSlices;
-    const int b_begin = slice * per, b_end = (b_begin + per < stat_blocks) ? b_begin + per : stat_blocks;
-    const float2* p = part + row;
-    for (int b0 = b_begin; b0 < b_end; b0 += 16) {
-      float2 x[16];
+  const int per = (stat_blocks + M::kSlices - 1) / M::kSlices;
+  const int b_begin = slice * per, b_end = (b_begin + per < stat_blocks) ? b_begin + per : stat_blocks;
+  const float2* p = part + row;
+  for (int b0 = b_begin; b0 < b_end; b0 += 16) {
+    float2 x[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        if (b0 + u < b_end)
-          x[u] = DEVICE_SCOPE ? ld_dev_f2(&p[(long long)(b0 + u) * kRows]) : p[(long long)(b0 + u) * kRows];
-        else
-          x[u] = make_float2(-INFINITY, 0.0f);
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) merge_stat(m, z, x[u].x, x[u].y, c2);
+    for (int u = 0; u < 16; ++u) {
+      if (b0 + u < b_end)
+        x[u] = DEVICE_SCOPE ? ld_dev_f2(&p[(long long)(b0 + u) * kRows]) : p[(long long)(b0 + u) * kRows];
+      else
+        x[u] = make_float2(-INFINITY, 0.0f);
     }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) merge_stat(m, z, x[u].x, x[u].y, c2);
   }
-  s_merge[slice * kRows + row] = make_float2(m, z);
+  lds_write64(lds_addr(s_merge) + (unsigned int)(slice * kRows + row) * 8u, make_float2(m, z));
 }
 
 // Step 2: the slices are merged in slice order; bias = log2(row normaliser * w) in the exp2 domain,
-// +inf for padding rows (their exponentials vanish).
-template <int GT, int THREADS>
-__device__ __forceinline__ void write_bias(const float2* s_merge, const float* __restrict__ lse, int h0, int nh, int w,
-                                           int bph, float c2, float* s_bias) {
-  constexpr int kRows = GT * 32;
-  constexpr int kSlices = THREADS / kRows;
-  if (threadIdx.x < kRows) {
-    const int t = threadIdx.x >> 5;
-    const int head = (h0 + t) / bph, rr = ((h0 + t) % bph) * 32 + (int)(threadIdx.x & 31);   // head and window row of this block row
-    float bias = INFINITY;
-    if (t < nh && rr < w) {
-      if (lse != nullptr) {
-        bias = lse[(long long)head * w + rr] * kLog2e;
-      } else {
-        float m = -INFINITY, z = 0.0f;
+// +inf for padding rows (their exponentials vanish).  Thread t < kRows does row t.
+template <int GT, int WAVES>
+__device__ __forceinline__ void write_bias(const float2* s_merge, int nh, int h0, int w, int bph, float c2, const float* s_bias) {
+  using M = Merge<GT, WAVES>;
+  if (threadIdx.x >= M::kRows) return;
+  const int t = threadIdx.x >> 5, rr = ((h0 + t) % bph) * 32 + (int)(threadIdx.x & 31);   // block and window row
+  float m = -INFINITY, z = 0.0f;
 #pragma unroll
-        for (int sl = 0; sl < kSlices; ++sl) {
-          const float2 x = s_merge[sl * kRows + threadIdx.x];
-          merge_stat(m, z, x.x, x.y, c2);
-        }
-        bias = m * c2 + log2f(z);
-      }
-      bias += log2f((float)w);
-    }
-    s_bias[threadIdx.x] = bias;
+  for (int sl = 0; sl < M::kSlices; ++sl) {
+    const float2 x = lds_read64(lds_addr(s_merge) + (unsigned int)(sl * M::kRows + (int)threadIdx.x) * 8u);
+    merge_stat(m, z, x.x, x.y, c2);
   }
+  const float bias = t < nh && rr < w ? m * c2 + log2f(z) + log2f((float)w) : INFINITY;
+  lds_write32(lds_addr(s_bias) + threadIdx.x * 4u, bias);
+}
+// ... or the bias of the caller's log-sum-exp, by merger t < kRows
+template <int GT>
+__device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict__ lse, int nh, int h0, int w, int bph,
+                                            const float* s_bias) {
+  if (merger < 0 || merger >= GT * 32) return;
+  const int t = merger >> 5, head = (h0 + t) / bph, rr = ((h0 + t) % bph) * 32 + (merger & 31);
+  float bias = INFINITY;
+  if (t < nh && rr < w) bias = lse[(long long)head * w + rr] * kLog2e + log2f((float)w);
+  lds_write32(lds_addr(s_bias) + (unsigned int)merger * 4u, bias);
 }
 
 // The score sweep of one wavefront over the jobs of its workgroup: the workgroup's own tiles
@@ -883,10 +890,11 @@ scores_kernel(const SweepArgs a) {
   }
 
   constexpr int kThreads = Shape<DT, D, W>::kThreads;
-  constexpr int kRows = GT * 32;
-  __shared__ float2 s_merge[kThreads];
+  using M = Merge<GT, kWaves>;
+  __shared__ float2 s_merge[M::kSlices * M::kRows];
 
-  // start the ring first: these loads only need the key pointer
+  __shared__ unsigned int s_next_job;
+  if (threadIdx.x == 0) s_next_job = kWaves * (kStages - 1);   // published by the barriers below
   TileDma<DT, D> dma;
   dma.init(lane);
   FragReader<DT, D> frags;
@@ -908,8 +916,6 @@ scores_kernel(const SweepArgs a) {
     if (j < n_own) return t_begin + j;
     return (j == n_own && halo_left) ? t_begin - 1 : t_end;
   };
-  __shared__ unsigned int s_next_job;
-  if (threadIdx.x == 0) s_next_job = kWaves * (kStages - 1);   // published by the barriers below
   int fifo[kStages];                                            // jobs requested and not yet computed; -1: none
 #pragma unroll
   for (int p = 0; p < kStages; ++p) {
@@ -917,24 +923,34 @@ scores_kernel(const SweepArgs a) {
     fifo[p] = (p < kStages - 1 && j < n_jobs) ? j : -1;
   }
   u32x4* ring = s_tile[wave][0];
+  // Set-up: the first wavefronts request the query rows into the last stage of their rings (idle until the loop
+  // starts) while the others merge the normalisers of every (head, row), from the statistics partials or the
+  // caller's log-sum-exp; then everybody requests first tiles.  Loads return in order and the compiler cannot
+  // count the conditional ones, so what is waited for goes out ahead of the tiles: with the tiles first and
+  // the query rows copied through registers the loop began 7.2 us after the workgroup, of which 4.5 were the
+  // first tiles' way (131072 tokens), and the device idled until the second ones arrived.
+  static_assert(kWaves >= GT, "one staging buffer per head");
+  const int merger = M::kSplit ? (int)threadIdx.x - GT * 64 : (int)threadIdx.x;
+  if (lse != nullptr)
+    bias_of_lse<GT>(merger, lse, nh, h0, w, a.bph, s_bias);
+  else
+    merge_partials<GT, kWaves, false>(merger, stat_part + (long long)blockIdx.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
+  asm volatile("" ::: "memory");
+  if (wave < GT) request_q<DT, D>(dma, q_win, h0, nh, wave, w, a.bph, lane, ring + (kStages - 1) * T::kTileChunks);
+  int young = 0;
 #pragma unroll
   for (int p = 0; p < kStages - 1; ++p)
-    if (fifo[p] >= 0) dma.issue(kg, job_tile(fifo[p]), n, lane, ring + p * T::kTileChunks);
-
-  // the query rows go through the last stage of the first GT wavefronts' rings (idle until the loop
-  // starts); their loads are in flight together with the normaliser partials below
-  static_assert(kWaves >= GT, "one staging buffer per head");
-  stage_q<DT, D, GT, kThreads>(q_win, h0, nh, w, a.bph, [&](int t) { return &s_tile[t][kStages - 1][0]; });
-
-  // exponent bias of every (head, row), from the statistics partials or the caller's log-sum-exp
-  merge_partials<GT, kThreads, false>(stat_part + (long long)blockIdx.y * stat_blocks * kRows, stat_blocks,
-                                      lse != nullptr, c2, s_merge);
-  __syncthreads();
-  write_bias<GT, kThreads>(s_merge, lse, h0, nh, w, a.bph, c2, s_bias);
+    if (fifo[p] >= 0) {
+      dma.issue(kg, job_tile(fifo[p]), n, lane, ring + p * T::kTileChunks);
+      ++young;
+    }
+  if (wave < GT) wait_tile<DT, D>(young);
+  wave_barrier();
+  if (lse == nullptr) write_bias<GT, kWaves>(s_merge, nh, h0, w, a.bph, c2, s_bias);
   u32x4 qf[GT][T::kSteps];
 #pragma unroll
   for (int t = 0; t < GT; ++t) frags.read(lds_addr(&s_tile[t][kStages - 1][0]), qf[t]);
-  __syncthreads();
+  wave_barrier();
 
   scores_tiles<DT, D, GT, kWaves, kStages, FUSED>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
                                                   halo_right, n_jobs, fifo, ring, &s_next_job, s_bias, s_span,
@@ -978,7 +994,7 @@ struct SweepSmem {
   union {
     float2 red[S::kWaves][kMaxChunkHeads * 32];            // statistics units: per-wavefront results
     struct {
-      float2 merge[S::kThreads];                           // score units: slices of the partial merge
+      float2 merge[Merge<GT, S::kWaves>::kSlices * GT * 32];   // score units: slices of the partial merge
       __attribute__((aligned(16))) float span[(S::kFusedTiles + 2) * kTileKeys];   // raw scores of the span + halo
     } sc;
   };
@@ -1199,10 +1215,12 @@ sweep_kernel(const SweepArgs a) {
     float vb = 0.0f;   // this thread's share of the head's value-norm partials (an earlier launch wrote them)
     for (int i = threadIdx.x; i < pa.vnorm_blocks; i += kThreads)
       vb = fmaxf(vb, pa.vnorm_part[(long long)g * pa.vnorm_blocks + i]);
-    merge_partials<GT, kThreads, true>(stat_part + (long long)g * sq.blocks_x * kRows, sq.blocks_x, false, c2,
-                                       sm.sc.merge);
+    merge_partials<GT, kWaves, true>((int)threadIdx.x, stat_part + (long long)g * sq.blocks_x * kRows, sq.blocks_x, c2,
+                                     sm.sc.merge);
+    lds_reads_done();
     __syncthreads();
-    write_bias<GT, kThreads>(sm.sc.merge, nullptr, g * G, G < GT ? G : GT, w, a.bph, c2, sm.bias);
+    write_bias<GT, kWaves>(sm.sc.merge, G < GT ? G : GT, g * G, w, a.bph, c2, sm.bias);
+    lds_reads_done();
     __syncthreads();
     scores_tiles<DT, D, GT, kWaves, kStages, true>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
                                                    halo_right, n_jobs, fifo, ring, &sm.next_job, sm.bias, sm.sc.span,

@@ -257,6 +257,15 @@ __device__ __forceinline__ unsigned int lds_fetch_inc(unsigned int a) {
   return v;
 }
 
+__device__ __forceinline__ void lds_write64(unsigned int a, float2 x) {
+  asm volatile("ds_write_b64 %0, %1" : : "v"(a), "v"(x) : "memory");
+}
+__device__ __forceinline__ float2 lds_read64(unsigned int a) {
+  float2 x;
+  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x) : "v"(a) : "memory");
+  return x;
+}
+
 __device__ __forceinline__ void lds_write32(unsigned int a, float x) {
   asm volatile("ds_write_b32 %0, %1" : : "v"(a), "v"(x) : "memory");
 }
@@ -319,29 +328,6 @@ __device__ __forceinline__ void load_q(const u32x4* __restrict__ qg, int hb0, in
       if (t < nh && row < w) x = qg[((long long)head * w + row) * T::kCpr + 2 * j + half];
       qf[t][j] = x;
     }
-  }
-}
-
-// Query rows of the chunk's row blocks, copied once per workgroup into tile-shaped LDS buffers (one per
-// block: row r of block t at row r, 16-byte chunks swizzled like a key tile, zero beyond the window
-// or the chunk), from where every wavefront reads them as fragments with FragReader.  Letting each
-// wavefront fetch its own copy from global memory costs kWaves times the traffic on a handful of
-// cache lines that every workgroup of the grid wants at the same moment.
-// bufs(t) returns the buffer of head t.  The caller synchronises the workgroup afterwards.
-template <int DT, int D, int GT, int THREADS, class BUFS>
-__device__ __forceinline__ void stage_q(const u32x4* __restrict__ qg, int hb0, int nh, int w, int bph, BUFS&& bufs) {
-  using T = Tile<DT, D>;
-  constexpr int kPerHead = kTileKeys * T::kCpr;
-  constexpr int kTotal = GT * kPerHead;
-#pragma unroll
-  for (int i = 0; i < (kTotal + THREADS - 1) / THREADS; ++i) {
-    const int c = i * THREADS + (int)threadIdx.x;
-    if (kTotal % THREADS != 0 && c >= kTotal) break;
-    const int t = c / kPerHead, rr = (c / T::kCpr) % kTileKeys, ch = c % T::kCpr;
-    u32x4 x = u32x4{0u, 0u, 0u, 0u};
-    const int head = (hb0 + t) / bph, row = ((hb0 + t) % bph) * 32 + rr;
-    if (t < nh && row < w) x = qg[((long long)head * w + row) * T::kCpr + ch];
-    bufs(t)[rr * T::kCpr + (ch ^ (rr & 7))] = x;
   }
 }
 
