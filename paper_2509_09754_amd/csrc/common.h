@@ -106,10 +106,10 @@ int pool_blocks(const lava_layer_desc& d, int64_t n);
 
 int32_t launch_vnorm(const lava_layer_desc& d, int64_t n, const void* v, float* vnorm_part,
                      uint32_t* counters, const SweepPlan& p, hipStream_t s);
-// Arguments of a sweep launch.  One launch covers up to kMaxSeqPerLaunch sequences of a batch
-// (blockIdx.z picks the sequence): the whole table travels in the kernel arguments, so nothing is
-// copied to the device and the call stays capturable.  Workgroups beyond a sequence's own count
-// (the grid is sized for the longest sequence) return at once.
+// Arguments of a sweep launch.  One launch covers up to kMaxSeqPerLaunch sequences of a batch: the whole
+// table travels in the kernel arguments, so nothing is copied to the device and the call stays capturable.
+// Statistics and scores launches number the workgroups of all sequences through; the value-norm launch picks the
+// sequence by blockIdx.z, and workgroups beyond a sequence's own count return at once.
 constexpr int kMaxSeqPerLaunch = 32;
 
 struct SweepSeq {
@@ -120,7 +120,7 @@ struct SweepSeq {
   int tiles_per_block;
   int vnorm_blocks;          // value-norm partials per KV head the scores kernel finds
   int vnorm_tiles_per_block;
-  int unit_base;             // persistent launch: work units of the sequences before this one (H_kv * blocks_x each)
+  int unit_base;             // workgroups (work units) of the sequences before this one: H_kv * n_chunks * blocks_x each
 };
 
 // Budgets formed right after the layer statistic, by the workgroup that formed it (e == nullptr: none).
@@ -155,25 +155,24 @@ struct SweepArgs {
   char* sel_ws;
   size_t sel_stride, sel_off_hist, sel_off_state;
   BudgetPlanArgs plan;
-  int n_units;               // persistent launch: H_kv * sum of blocks_x over the table
+  int n_units;               // H_kv * n_chunks * sum of blocks_x over the table
   unsigned int spin_limit;   // persistent launch: polls of a wait for other workgroups before it gives up
   unsigned int help_after;   // persistent launch: polls after which a waiting workgroup looks for unclaimed units (>= 1)
   int orphan_mod;            // persistent launch, testing aid: owners leave every orphan_mod-th statistics unit unclaimed (0: none)
   SweepSeq s[kMaxSeqPerLaunch];
 };
 
-// grid.x of the launches below: the largest blocks_x / vnorm_blocks in the table
+// max_vnorm_blocks: the largest vnorm_blocks in the table
 int32_t launch_vnorm(const lava_layer_desc& d, const SweepArgs& a, int max_vnorm_blocks, hipStream_t s);
 // value factor 1 for every head (scores without the value norm): fills the partials, clears the tickets
 int32_t launch_unit_vnorm(const lava_layer_desc& d, const SweepArgs& a, int max_vnorm_blocks, hipStream_t s);
 // with_vnorm: the launch also sweeps the value rows (SweepSeq::vnorm_blocks == blocks_x, no launch_vnorm)
-int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, int max_blocks_x, const SweepPlan& p,
+int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p,
                      bool with_vnorm, hipStream_t s);
 // statistics and scores in one persistent launch (all heads of a group in one workgroup, no caller LSE)
 int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s);
 // not fused (a group split into chunks): one sequence per launch, raw scores to the region's s_raw
-int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, int max_blocks_x, const SweepPlan& p,
-                      hipStream_t s);
+int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s);
 float sweep_exp2_scale(const lava_layer_desc& d);
 int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const float* s_raw,
                         const float* vnorm_part, int vnorm_blocks, float* scores, float* vbar,

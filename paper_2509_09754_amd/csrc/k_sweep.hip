@@ -327,6 +327,28 @@ __device__ __forceinline__ void wave_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// A statistics / scores launch numbers the workgroups of all its sequences through (SweepSeq::unit_base): sequence
+// z of the launch, KV head and chunk y, span x.  A grid as wide as the longest sequence left the dispatcher to
+// start and retire the missing workgroups of the others: 16 sequences of 4096 to 65536 tokens, 3200 workgroups
+// of which 1992 had work, 4.3 us between two of them on a slot where a full grid has 1.
+struct Unit {
+  int z, y, x;
+};
+__device__ __forceinline__ Unit unit_of_block(const SweepArgs& a) {
+  Unit u;
+  u.z = 0;
+  if (a.n_seq > 1) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long at = __ballot(lane < a.n_seq && a.s[lane < a.n_seq ? lane : 0].unit_base <= (int)blockIdx.x);
+    u.z = 63 - __builtin_clzll(at);                            // unit_base[0] = 0
+  }
+  const unsigned int rel = blockIdx.x - (unsigned int)a.s[u.z].unit_base, bx = (unsigned int)a.s[u.z].blocks_x;
+  u.y = __builtin_amdgcn_readfirstlane((int)(rel / bx));
+  u.x = (int)rel - u.y * (int)bx;
+  return u;
+}
+static_assert(kMaxSeqPerLaunch <= 64, "one lane per sequence");
+
 // The value-norm sweep of one wavefront: tiles first, first + WAVES, ... (cnt of them) of the head at
 // vg, whose first STAGES - 1 tiles have already been requested into `ring`.  Returns this lane's maximum
 // over its rows (row lane % 32 of every tile) of sum_c |V[row, c]|; with token_norm the rows' own norms
@@ -383,13 +405,13 @@ template <int DT, int D, int GT, int W, bool VN>
 __global__ void __launch_bounds__((Shape<DT, D, W>::kThreads), (Shape<DT, D, W>::kMinWaves))
 stats_kernel(const SweepArgs a) {
   using T = Tile<DT, D>;
-  const SweepSeq sq = a.s[blockIdx.z];
-  if (blockIdx.x >= (unsigned int)sq.blocks_x) return;
+  const Unit u = unit_of_block(a);
+  const SweepSeq sq = a.s[u.z];
   const long long n = sq.n;
   const int w = a.w, G = a.G, n_chunks = a.n_chunks, tiles_per_block = sq.tiles_per_block;
   const float c2 = a.c2;
   const u32x4* __restrict__ q_win =
-      static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + blockIdx.z) * a.H * w * T::kCpr;
+      static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + u.z) * a.H * w * T::kCpr;
   const u32x4* __restrict__ k = static_cast<const u32x4*>(a.k) + (long long)a.H_kv * sq.tok * T::kCpr;
   float2* __restrict__ stat_part = reinterpret_cast<float2*>(a.ws + sq.ws_off + a.off_stat_part);
   constexpr int kWaves = Shape<DT, D, W>::kWaves;
@@ -398,7 +420,7 @@ stats_kernel(const SweepArgs a) {
   __shared__ float2 s_red[kWaves][kMaxChunkHeads * 32];   // [wave][head*32+row]
 
   const int lane = threadIdx.x & 63, wave = wave_index();
-  const int g = blockIdx.y / n_chunks, chunk = blockIdx.y % n_chunks;
+  const int g = u.y / n_chunks, chunk = u.y % n_chunks;
   const int h0 = g * G + chunk * GT;
   const int nh = (G - chunk * GT) < GT ? (G - chunk * GT) : GT;
   const char* kg = reinterpret_cast<const char*>(k) + (long long)g * n * T::kRowBytes;
@@ -409,7 +431,7 @@ stats_kernel(const SweepArgs a) {
   frags.init(lane);
 
   const long long n_tiles = (n + kTileKeys - 1) / kTileKeys;
-  const long long t_begin = (long long)blockIdx.x * tiles_per_block;
+  const long long t_begin = (long long)u.x * tiles_per_block;
   long long t_end = t_begin + tiles_per_block;
   if (t_end > n_tiles) t_end = n_tiles;
 
@@ -424,11 +446,11 @@ stats_kernel(const SweepArgs a) {
       const u32x4* __restrict__ v = static_cast<const u32x4*>(a.v) + (long long)a.H_kv * sq.tok * T::kCpr;
       first_stream = reinterpret_cast<const char*>(v) + (long long)g * n * T::kRowBytes;
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
+    if (u.x == 0 && u.y == 0) {
       uint32_t* __restrict__ counters = reinterpret_cast<uint32_t*>(a.ws + sq.ws_off + a.off_counter);
       const int n_counter_words = kCtlUnitA + a.H_kv * sq.blocks_x;
       for (int i = threadIdx.x; i < n_counter_words; i += Shape<DT, D, W>::kThreads) counters[i] = 0u;
-      clear_selection_region(a, (int)blockIdx.z, Shape<DT, D, W>::kThreads);
+      clear_selection_region(a, (int)u.z, Shape<DT, D, W>::kThreads);
     }
   }
   // VN: the query rows, once per workgroup, into the last stage of the first GT wavefronts' rings, ahead of the
@@ -487,19 +509,19 @@ stats_kernel(const SweepArgs a) {
     if (lane == 0) s_vmax[wave] = v_best;                      // read after the barrier of the merge below
     float2 mine;
     const bool owner = stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, s_red, mine);
-    if (owner) stat_part[((long long)blockIdx.y * sq.blocks_x + blockIdx.x) * (GT * 32) + threadIdx.x] = mine;
+    if (owner) stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (GT * 32) + threadIdx.x] = mine;
     if (with_v && threadIdx.x == 0) {
       float m = s_vmax[0];
 #pragma unroll
       for (int i = 1; i < kWaves; ++i) m = fmaxf(m, s_vmax[i]);
       float* __restrict__ vnorm_part = reinterpret_cast<float*>(a.ws + sq.ws_off + a.off_vnorm_part);
-      vnorm_part[(long long)g * sq.vnorm_blocks + blockIdx.x] = m;
+      vnorm_part[(long long)g * sq.vnorm_blocks + u.x] = m;
     }
     if (with_v) clear_raw_scores(a, sq, g, t_begin, t_end, Shape<DT, D, W>::kThreads);
   } else {
     float2 mine;
     if (stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, s_red, mine))
-      stat_part[((long long)blockIdx.y * sq.blocks_x + blockIdx.x) * (GT * 32) + threadIdx.x] = mine;
+      stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (GT * 32) + threadIdx.x] = mine;
   }
 }
 
@@ -843,9 +865,9 @@ template <int DT, int D, int GT, bool FUSED, int W>
 __global__ void __launch_bounds__((Shape<DT, D, W>::kThreads), (Shape<DT, D, W>::kMinWaves))
 scores_kernel(const SweepArgs a) {
   using T = Tile<DT, D>;
-  const SweepSeq sq = a.s[blockIdx.z];
-  if (blockIdx.x >= (unsigned int)sq.blocks_x) return;
-  const int seq = a.first_seq + (int)blockIdx.z;
+  const Unit u = unit_of_block(a);
+  const SweepSeq sq = a.s[u.z];
+  const int seq = a.first_seq + (int)u.z;
   const long long n = sq.n;
   const int w = a.w, G = a.G, n_chunks = a.n_chunks, tiles_per_block = sq.tiles_per_block;
   const int stat_blocks = sq.blocks_x;
@@ -877,7 +899,7 @@ scores_kernel(const SweepArgs a) {
   __shared__ __attribute__((aligned(16))) float s_span[FUSED ? (Shape<DT, D, W>::kFusedTiles + 2) * kTileKeys : 4];   // raw scores of the span + halo tiles
 
   const int lane = threadIdx.x & 63, wave = wave_index();
-  const int g = blockIdx.y / n_chunks, chunk = blockIdx.y % n_chunks;
+  const int g = u.y / n_chunks, chunk = u.y % n_chunks;
   const int h0 = g * G + chunk * GT;
   const int nh = (G - chunk * GT) < GT ? (G - chunk * GT) : GT;
   const char* kg = reinterpret_cast<const char*>(k) + (long long)g * n * T::kRowBytes;
@@ -900,7 +922,7 @@ scores_kernel(const SweepArgs a) {
   FragReader<DT, D> frags;
   frags.init(lane);
   const long long n_tiles = (n_prefix + kTileKeys - 1) / kTileKeys;
-  const long long t_begin = (long long)blockIdx.x * tiles_per_block;
+  const long long t_begin = (long long)u.x * tiles_per_block;
   long long t_end = t_begin + tiles_per_block;
   if (t_end > n_tiles) t_end = n_tiles;
   // Jobs of the workgroup: its own tiles, then (FUSED) the pooling halo, i.e. the tile before and the
@@ -934,7 +956,7 @@ scores_kernel(const SweepArgs a) {
   if (lse != nullptr)
     bias_of_lse<GT>(merger, lse, nh, h0, w, a.bph, s_bias);
   else
-    merge_partials<GT, kWaves, false>(merger, stat_part + (long long)blockIdx.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
+    merge_partials<GT, kWaves, false>(merger, stat_part + (long long)u.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
   asm volatile("" ::: "memory");
   if (wave < GT) request_q<DT, D>(dma, q_win, h0, nh, wave, w, a.bph, lane, ring + (kStages - 1) * T::kTileChunks);
   int young = 0;
@@ -960,8 +982,8 @@ scores_kernel(const SweepArgs a) {
     __shared__ double s_s[kWaves], s_t[kWaves];
     __shared__ unsigned int s_last;
     scores_finish<kThreads>(pa, vb, g, n, n_prefix, w, t_begin, t_end, n_tiles, s_span, s_vb, s_s, s_t, &s_last,
-                            sq.blocks_x * gridDim.y, blockIdx.y * sq.blocks_x + blockIdx.x, (int)gridDim.y,
-                            blockIdx.x == 0, wave, reinterpret_cast<unsigned int*>(&s_tile[0][0][0]));
+                            (unsigned int)(sq.blocks_x * a.H_kv), (unsigned int)(u.y * sq.blocks_x + u.x), a.H_kv,
+                            u.x == 0, wave, reinterpret_cast<unsigned int*>(&s_tile[0][0][0]));
   }
 }
 
@@ -1555,9 +1577,9 @@ float sweep_exp2_scale(const lava_layer_desc& d) {
     }                                                                               \
   } while (0)
 
-int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, int max_blocks_x, const SweepPlan& p,
+int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p,
                      bool with_vnorm, hipStream_t s) {
-  const dim3 grid(max_blocks_x, d.n_kv_heads * p.n_chunks, a.n_seq);
+  const dim3 grid(a.n_units);
   ProfScope ps(with_vnorm ? KID_PREPASS : KID_STATS, s);
 #define LAVA_STATS_W(DTV, DV, GTV, WV)                                                                             \
   do {                                                                                                             \
@@ -1596,9 +1618,8 @@ int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
   return launch_status();
 }
 
-int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, int max_blocks_x, const SweepPlan& p,
-                      hipStream_t s) {
-  const dim3 grid(max_blocks_x, d.n_kv_heads * p.n_chunks, a.n_seq);
+int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s) {
+  const dim3 grid(a.n_units);
   ProfScope ps(KID_SCORES, s);
 #define LAVA_SCORES_W(DTV, DV, GTV, WV)                                                                     \
   do {                                                                                                      \

@@ -224,7 +224,8 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
   for (int b0 = 0; b0 < batch; b0 += per_launch) {
     a.first_seq = b0;
     a.n_seq = batch - b0 < per_launch ? batch - b0 : per_launch;
-    int max_bx = 0, max_vb = 0;
+    int max_vb = 0;
+    a.n_units = 0;
     SweepPlan plan = plan_max;
     int64_t launch_tokens = 0;
     for (int i = 0; i < a.n_seq; ++i) launch_tokens += seq_lens[b0 + i];
@@ -253,7 +254,8 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
       sq.tiles_per_block = plan.tiles_per_block;
       sq.vnorm_blocks = plan.vnorm_blocks;
       sq.vnorm_tiles_per_block = plan.vnorm_tiles_per_block;
-      if (plan.blocks_x > max_bx) max_bx = plan.blocks_x;
+      sq.unit_base = a.n_units;
+      a.n_units += d.n_kv_heads * plan_max.n_chunks * plan.blocks_x;
       if (plan.vnorm_blocks > max_vb) max_vb = plan.vnorm_blocks;
       tok += n;
     }
@@ -277,12 +279,6 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
       if (st != LAVA_OK) return st;
     }
     if (persistent) {
-      int units = 0;
-      for (int i = 0; i < a.n_seq; ++i) {
-        a.s[i].unit_base = units;
-        units += d.n_kv_heads * a.s[i].blocks_x;
-      }
-      a.n_units = units;
       a.spin_limit = tuning().barrier_spin_limit > 0 ? (unsigned int)tuning().barrier_spin_limit : 1u << 18;
       a.help_after = a.spin_limit / 4 < 64u ? (a.spin_limit / 4 > 0u ? a.spin_limit / 4 : 1u) : 64u;
       a.orphan_mod = tuning().sweep_orphan_units;
@@ -291,10 +287,10 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
       continue;
     }
     if (lse == nullptr) {
-      st = launch_stats(d, a, max_bx, plan_launch, prepass, s);
+      st = launch_stats(d, a, plan_launch, prepass, s);
       if (st != LAVA_OK) return st;
     }
-    st = launch_scores(d, a, max_bx, plan_launch, s);
+    st = launch_scores(d, a, plan_launch, s);
     if (st != LAVA_OK) return st;
     if (!together) {                                         // one sequence: `plan` is its plan
       const SweepSeq& sq = a.s[0];
