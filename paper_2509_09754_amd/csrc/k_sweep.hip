@@ -59,8 +59,30 @@ struct Shape {
   static_assert(kStages >= 2 && kStages <= kMaxRingStages, "ring depth");
 };
 
+// Sum over the wavefront's lanes in a fixed order, in every lane: data-parallel-primitive moves (shifts inside rows
+// of 16 lanes, then the last lane of one row to the next ones) instead of 24 trips through the LDS unit.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_f64(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)b, CTRL, ROWS, 0xf, false);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return x + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));   // +0 where no lane shifts in
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  x = dpp_add_f64<0x111, 0xf>(x);
+  x = dpp_add_f64<0x112, 0xf>(x);
+  x = dpp_add_f64<0x114, 0xf>(x);
+  x = dpp_add_f64<0x118, 0xf>(x);
+  x = dpp_add_f64<0x142, 0xa>(x);
+  x = dpp_add_f64<0x143, 0xc>(x);
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)b, 63);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)(b >> 32), 63);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Layer statistic from per-lane partial sums S = sum s, T = sum s ln s (fp64): fixed-order reduction
-// over lanes (xor tree), wavefronts and, by the last workgroup to arrive, workgroups; then
+// over lanes, wavefronts and, by the last workgroup to arrive, workgroups; then
 // e = (ln S - T / S) / n_entries  (Eq. 4-5 in closed form).  Contains workgroup barriers.  Returns true in
 // every thread of that last workgroup, whose thread 0 has then also left the statistic (as stored,
 // rounded to fp32) in s_t[0] for whatever the workgroup does next with it (not yet published by a barrier).
@@ -71,10 +93,8 @@ __device__ __forceinline__ bool entropy_finish(double acc_s, double acc_t, doubl
                                                float* __restrict__ layer_stat, double* s_s, double* s_t,
                                                unsigned int* s_last, const uint32_t* error_word = nullptr) {
   constexpr int kW = THREADS / 64;
-  for (int off = 32; off > 0; off >>= 1) {
-    acc_s += __shfl_xor(acc_s, off);
-    acc_t += __shfl_xor(acc_t, off);
-  }
+  acc_s = wave_sum_f64(acc_s);
+  acc_t = wave_sum_f64(acc_t);
   if ((threadIdx.x & 63) == 0) { s_s[threadIdx.x >> 6] = acc_s; s_t[threadIdx.x >> 6] = acc_t; }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -91,10 +111,8 @@ __device__ __forceinline__ bool entropy_finish(double acc_s, double acc_t, doubl
     S += ld_dev_f64(&ent_part[i].x);
     Tt += ld_dev_f64(&ent_part[i].y);
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    S += __shfl_xor(S, off);
-    Tt += __shfl_xor(Tt, off);
-  }
+  S = wave_sum_f64(S);
+  Tt = wave_sum_f64(Tt);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) { s_s[threadIdx.x >> 6] = S; s_t[threadIdx.x >> 6] = Tt; }
   __syncthreads();
@@ -787,63 +805,76 @@ __device__ __forceinline__ void scores_finish(const PoolArgs& pa, float vb, int 
   long long p_end = t_end * kTileKeys;
   if (p_end > n_prefix) p_end = n_prefix;
   const long long span0 = (t_begin - 1) * kTileKeys;      // position held by s_span[0]
-  // Eight consecutive positions per thread: 24 raw scores (positions base-8 .. base+15, six
-  // 128-bit reads) cover every tap of a pooling window of up to 15; positions outside the prefix
-  // do not take part in the maximum (the window is clipped, not padded).
+  // kPer consecutive positions per thread: kPer + 16 raw scores (positions base-8 .. base+kPer+7) cover every tap
+  // of a pooling window of up to 15; positions outside the prefix do not take part in the maximum (the
+  // window is clipped, not padded).  Eight where the span has work for all threads (six 128-bit reads), two
+  // where it is short: a thread's logarithms are a serial chain.
   double acc_s = 0.0, acc_t = 0.0;
-  constexpr int kPer = 8;
-  static_assert(kPoolMaxHalf <= kPer - 1, "taps must stay inside the 24 values read");
+  static_assert(kPoolMaxHalf <= 8, "taps must stay inside the values read");
   const float* out_head = pa.scores + (long long)g * n;
-  for (long long base = p_begin + (long long)threadIdx.x * kPer; base < p_end; base += (long long)THREADS * kPer) {
-    float raw[3 * kPer];
-    const float4* src = reinterpret_cast<const float4*>(&s_span[(int)(base - kPer - span0)]);
+  auto pool = [&](auto per) {
+    constexpr int kPer = decltype(per)::value;
+    constexpr int kVec = kPer < 4 ? kPer : 4;
+    typedef float vec __attribute__((ext_vector_type(kVec)));
+    for (long long base = p_begin + (long long)threadIdx.x * kPer; base < p_end; base += (long long)THREADS * kPer) {
+      float raw[kPer + 16];
+      const vec* src = reinterpret_cast<const vec*>(&s_span[(int)(base - 8 - span0)]);
 #pragma unroll
-    for (int i = 0; i < 3 * kPer / 4; ++i) {
-      const float4 x = src[i];
-      raw[4 * i + 0] = x.x; raw[4 * i + 1] = x.y; raw[4 * i + 2] = x.z; raw[4 * i + 3] = x.w;
-    }
+      for (int i = 0; i < (kPer + 16) / kVec; ++i) {
+        const vec x = src[i];
 #pragma unroll
-    for (int i = 0; i < 3 * kPer; ++i) {
-      const long long pos = base - kPer + i;
-      if (pos < 0 || pos >= n_prefix) raw[i] = -INFINITY;
-    }
-    float sc[kPer];
+        for (int e = 0; e < kVec; ++e) raw[kVec * i + e] = x[e];
+      }
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) sc[j] = raw[kPer + j];
+      for (int i = 0; i < kPer + 16; ++i) {
+        const long long pos = base - 8 + i;
+        if (pos < 0 || pos >= n_prefix) raw[i] = -INFINITY;
+      }
+      float sc[kPer];
 #pragma unroll
-    for (int dd = 1; dd <= kPoolMaxHalf; ++dd) {
-      if (dd <= pa.pool_half) {                              // uniform
+      for (int j = 0; j < kPer; ++j) sc[j] = raw[8 + j];
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) sc[j] = fmaxf(sc[j], fmaxf(raw[kPer + j - dd], raw[kPer + j + dd]));
+      for (int dd = 1; dd <= kPoolMaxHalf; ++dd) {
+        if (dd <= pa.pool_half) {                              // uniform
+#pragma unroll
+          for (int j = 0; j < kPer; ++j) sc[j] = fmaxf(sc[j], fmaxf(raw[8 + j - dd], raw[8 + j + dd]));
+        }
+      }
+      float fac[kPer];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) fac[j] = vb;
+      if (pa.token_norm) {                                     // uniform
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+          if (base + j < p_end) fac[j] = out_head[base + j];
+      }
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        sc[j] *= fac[j];
+        if (base + j < p_end) {
+          acc_s += (double)sc[j];
+          if (sc[j] > 0.0f) acc_t += (double)sc[j] * (double)logf(sc[j]);
+          if (count_digits) digit0_count(bins, sc[j], run_digit, run_len);
+        }
+      }
+      if (base + kPer <= p_end && (reinterpret_cast<uintptr_t>(out_head + base) & (4 * kVec - 1)) == 0) {
+        vec* dst = reinterpret_cast<vec*>(const_cast<float*>(out_head) + base);
+#pragma unroll
+        for (int i = 0; i < kPer / kVec; ++i) {
+          vec x;
+#pragma unroll
+          for (int e = 0; e < kVec; ++e) x[e] = sc[kVec * i + e];
+          dst[i] = x;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+          if (base + j < p_end) pa.scores[(long long)g * n + base + j] = sc[j];
       }
     }
-    float fac[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) fac[j] = vb;
-    if (pa.token_norm) {                                     // uniform
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        if (base + j < p_end) fac[j] = out_head[base + j];
-    }
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      sc[j] *= fac[j];
-      if (base + j < p_end) {
-        acc_s += (double)sc[j];
-        if (sc[j] > 0.0f) acc_t += (double)sc[j] * (double)logf(sc[j]);
-        if (count_digits) digit0_count(bins, sc[j], run_digit, run_len);
-      }
-    }
-    if (base + kPer <= p_end && (reinterpret_cast<uintptr_t>(out_head + base) & 15) == 0) {
-      float4* dst = reinterpret_cast<float4*>(const_cast<float*>(out_head) + base);
-      dst[0] = make_float4(sc[0], sc[1], sc[2], sc[3]);
-      dst[1] = make_float4(sc[4], sc[5], sc[6], sc[7]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        if (base + j < p_end) pa.scores[(long long)g * n + base + j] = sc[j];
-    }
-  }
+  };
+  if (p_end - p_begin <= 2 * THREADS) pool(std::integral_constant<int, 2>{});   // uniform
+  else pool(std::integral_constant<int, 8>{});
   // the workgroup that owns the head's last prefix tile also writes the window entries
   if (t_begin < t_end && t_end == n_tiles && threadIdx.x < (unsigned)w) {
     pa.scores[(long long)g * n + n_prefix + threadIdx.x] = INFINITY;

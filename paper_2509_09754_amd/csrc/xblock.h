@@ -96,7 +96,7 @@ __device__ __forceinline__ bool arrive_last(unsigned int* ctr, unsigned int n, u
   drain_vmem();
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (n <= 64u) {                       // few enough for one address: one trip to memory instead of two
+    if (n <= 256u) {                       // few enough for one address: one trip to memory instead of two (176 workgroups: 0.5 us)
       *s_flag = __hip_atomic_fetch_add(&ctr[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == n ? 1u : 0u;
     } else {
       const unsigned int t = arrive_two_level(ctr, n, id, 1u);
