@@ -45,7 +45,7 @@ def check(shapes, inps, out):
 
 
 # one tile, one span, several spans with a ragged last one; one round of wavefronts per span and two
-@pytest.mark.parametrize("cfg,n", [(1, 9), (1, 128), (1, 129), (1, 1000), (1, 2049), (2, 33), (2, 191), (2, 193), (2, 1537),
+@pytest.mark.parametrize("cfg,n", [(1, 9), (1, 128), (1, 129), (1, 1000), (1, 2049), (1, 4097), (2, 33), (2, 191), (2, 193), (2, 1537),
                                    (2, 6143 + 32)])
 def test_short_sequences(lava, cfg, n):
     print(f"short sequence cfg{cfg} n={n}", flush=True)
