@@ -88,16 +88,21 @@ struct DecodeArgs {
 
 __device__ __forceinline__ long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
 
-__device__ __forceinline__ long long uniform64(long long x) {
-  const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)((unsigned long long)x & 0xffffffffull));
-  const unsigned int hi = __builtin_amdgcn_readfirstlane((unsigned int)((unsigned long long)x >> 32));
-  return (long long)(((unsigned long long)hi << 32) | lo);
+// Values of a lane both kernels agree on, as scalars (no trip through the LDS unit).
+__device__ __forceinline__ unsigned int lane_value(unsigned int x, int lane) {
+  return (unsigned int)__builtin_amdgcn_readlane((int)x, lane);
+}
+__device__ __forceinline__ long long lane_value64(long long x, int lane) {
+  const unsigned long long u = (unsigned long long)x;
+  return (long long)(((unsigned long long)lane_value((unsigned int)(u >> 32), lane) << 32) | lane_value((unsigned int)u, lane));
 }
 
 // The units of one sequence, found by every wavefront on its own with one coalesced load of the
 // head offsets: lane g holds head g.  Units are numbered head by head, each head's packed chunks
 // first, then its tail chunks.  Offsets a kernel may follow start at >= 0, never decrease and end
 // within the stated capacity; anything else makes `usable` false and nothing is read.
+// A decode step over one layer is two launches of dependent trips to memory; the map is on both chains, so its sums
+// and look-ups are lane moves and scalar reads, not shuffles (batch 1, 8192 rows: 14.4 -> 13.5 us for the step).
 struct UnitMap {
   bool usable;
   unsigned int total;        // units of the sequence
@@ -107,31 +112,34 @@ struct UnitMap {
   long long off, len;        // lane g: first packed row and number of packed rows of head g
 };
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int dpp_add(unsigned int x) {
+  return x + (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+
 __device__ __forceinline__ UnitMap map_units(const long long* __restrict__ offs, int n_heads, long long capacity,
                                              int rows_per_unit, long long tail_len, int lane) {
   UnitMap m;
-  // lane g holds offs[g]; the end of the last head comes from a load of its own, because with 64
-  // heads no lane is left to hold offs[64]
   const bool head = lane < n_heads;
   const long long o = head ? offs[lane] : 0;
-  const long long o_end = offs[n_heads];
-  const long long o_down = __shfl_down(o, 1);
-  const long long o_next = lane == n_heads - 1 ? o_end : o_down;
-  const bool bad = (head && o_next < o) || (lane == 0 && o < 0) || o_end > capacity;
+  const long long o_next = head ? offs[lane + 1] : 0;
+  const bool bad = (head && (o_next < o || o_next > capacity)) || (lane == 0 && o < 0);
   m.usable = __ballot(bad) == 0ull;
   m.off = o;
   m.len = head && m.usable ? o_next - o : 0;
   const unsigned int tail_units = tail_len > 0 ? (unsigned int)ceil_div(tail_len, rows_per_unit) : 0u;
-  m.packed = (unsigned int)ceil_div(m.len, rows_per_unit);
+  // a usable length fits 31 bits (capacity < 2^31)
+  m.packed = ((unsigned int)m.len + (unsigned int)rows_per_unit - 1u) / (unsigned int)rows_per_unit;
   m.cnt = head && m.usable ? m.packed + tail_units : 0u;
-  unsigned int incl = m.cnt;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned int up = __shfl_up(incl, d);
-    if (lane >= d) incl += up;
-  }
+  unsigned int incl = m.cnt;                                 // inclusive sum over the lanes
+  incl = dpp_add<0x111, 0xf>(incl);
+  incl = dpp_add<0x112, 0xf>(incl);
+  incl = dpp_add<0x114, 0xf>(incl);
+  incl = dpp_add<0x118, 0xf>(incl);
+  incl = dpp_add<0x142, 0xa>(incl);
+  incl = dpp_add<0x143, 0xc>(incl);
   m.incl = incl;
-  m.total = __shfl(incl, 63);
+  m.total = lane_value(incl, 63);
   return m;
 }
 
@@ -152,10 +160,9 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
                                a.rows_per_unit, a.tail_len, lane);
   if (!um.usable || blockIdx.x >= um.total) return;         // bad offsets (the merge reports them) or no such unit
   const int g = __builtin_ctzll(__ballot(um.incl > blockIdx.x));
-  const long long u = (long long)blockIdx.x - (__builtin_amdgcn_readfirstlane(__shfl(um.incl, g)) -
-                                                __builtin_amdgcn_readfirstlane(__shfl(um.cnt, g)));
-  const long long packed_units = __builtin_amdgcn_readfirstlane(__shfl(um.packed, g));
-  const long long off_g = uniform64(__shfl(um.off, g)), len_g = uniform64(__shfl(um.len, g));
+  const long long u = (long long)blockIdx.x - ((long long)lane_value(um.incl, g) - (long long)lane_value(um.cnt, g));
+  const long long packed_units = lane_value(um.packed, g);
+  const long long off_g = lane_value64(um.off, g), len_g = lane_value64(um.len, g);
 
   const char* kb;
   const char* vb;
@@ -378,8 +385,8 @@ __global__ void __launch_bounds__(256) decode_merge_kernel(DecodeArgs a, float* 
   const int b = blockIdx.y, g = blockIdx.x;
   const UnitMap um = map_units(a.head_offsets + (long long)b * (a.H_kv + 1), a.H_kv, a.rows_capacity,
                                a.rows_per_unit, a.tail_len, (int)(threadIdx.x & 63));
-  const int mine = (int)__builtin_amdgcn_readfirstlane(__shfl(um.cnt, g));
-  const long long first = (long long)__builtin_amdgcn_readfirstlane(__shfl(um.incl, g)) - mine;
+  const int mine = (int)lane_value(um.cnt, g);
+  const long long first = (long long)lane_value(um.incl, g) - mine;
   const bool overflow = !um.usable || um.total > (unsigned int)a.units_bound;
   const float2* ml = a.part_ml + ((long long)b * a.units_bound + first) * GP;
   const float* pa = a.part_acc + ((long long)b * a.units_bound + first) * GP * D;
