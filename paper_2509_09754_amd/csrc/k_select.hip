@@ -118,6 +118,13 @@ __device__ __forceinline__ long long device_total(long long bound, const int64_t
   return t < bound ? t : bound;
 }
 
+// First entry of head h (h == n_heads: the end), in the range of an int whatever the caller's table holds.
+__device__ __forceinline__ int segment_start(const int64_t* __restrict__ seg_offsets, int h, int n_heads, int total) {
+  if (seg_offsets == nullptr) return h == n_heads ? total : total / n_heads * h;
+  const long long p = (long long)seg_offsets[h];
+  return p < 0 ? 0 : (p > 0x7fffffffll ? 0x7fffffff : (int)p);
+}
+
 // A workgroup's keys: wavefront w holds the 64 * KP consecutive entries from wave_base on as KP rows of
 // 64 (row j, lane l: entry wave_base + 64 j + l), so that loads are coalesced whatever the alignment of
 // the scores and the flat order inside a wavefront is row by row, lane by lane: positions are bit counts
@@ -556,8 +563,7 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   unsigned int key[KP];
   load_keys<KP>(scores, wave_base, total, key);
   if (threadIdx.x <= n_heads)                        // published by the barriers below
-    sh.off[threadIdx.x] = seg_offsets ? (int)seg_offsets[threadIdx.x]
-                                      : ((int)threadIdx.x == n_heads ? total : total / n_heads * (int)threadIdx.x);
+    sh.off[threadIdx.x] = segment_start(seg_offsets, (int)threadIdx.x, n_heads, total);
   if (alone && threadIdx.x == 0) st->error = 0u;     // nothing cleared the region, and nothing here can fail
   // Survivor counts of a prepared problem are cleared here, before this workgroup's exchange word is
   // published: nobody adds to them before having seen all of those (device-scope, as the additions are).
@@ -804,8 +810,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
       eq = wave_sum(eq);
       if (lane == 0) { sh.wave[wave] = gt; sh.wave2[wave] = eq; }
       if (threadIdx.x <= n_heads)
-        sh.off[threadIdx.x] = seg_offsets ? (int)seg_offsets[threadIdx.x]
-                                          : ((int)threadIdx.x == n_heads ? total : total / n_heads * (int)threadIdx.x);
+        sh.off[threadIdx.x] = segment_start(seg_offsets, (int)threadIdx.x, n_heads, total);
       __syncthreads();
       gt = wave_sums(sh.wave, 0).total;
       eq = wave_sums(sh.wave2, 0).total;

@@ -1362,16 +1362,19 @@ vnorm_kernel(const SweepArgs a) {
 // reduction order; the last workgroup to finish forms e = (ln S - T / S) / (H_kv * n')  (Eq. 4-5).
 // ------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 256;
-constexpr int kPoolPerThread = 4;   // 21013 tokens, 4 heads: 8 entries per thread 10.7 us, 4: 8.5 (latency of one workgroup, not bytes)
+// Entries per thread: 4 (21013 tokens, 4 heads: 8.5 us; 8: 10.7, the latency of one long workgroup, not bytes), or 8
+// where the workspace has no room for the partials of that many workgroups.
+constexpr int kPoolPerThread = 8;
 constexpr int kPoolChunk = kPoolThreads * kPoolPerThread;
 
+template <int PER>
 __global__ void __launch_bounds__(kPoolThreads)
 poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_half, int token_norm,
                 const float* __restrict__ vnorm_part, int vnorm_blocks, float* __restrict__ scores,
                 float* __restrict__ vbar, float* __restrict__ layer_stat,
                 double2* __restrict__ ent_part, uint32_t* __restrict__ counters, unsigned int* __restrict__ sel_hist0,
                 const BudgetPlanArgs plan, int plan_seq) {
-  __shared__ float s_in[kPoolChunk + 2 * kPoolMaxHalf];
+  __shared__ float s_in[kPoolThreads * PER + 2 * kPoolMaxHalf];
   __shared__ BudgetScratchT<kMaxPlannedLayers> s_plan;
   __shared__ unsigned int s_bins[kSelDigit0Bins];
   const PlanInputs plan_in = plan_prefetch(plan, plan_seq);
@@ -1383,7 +1386,7 @@ poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_ha
   __shared__ unsigned int s_last;
   const int g = blockIdx.y;
   const long long n_prefix = n - w;
-  const long long i0 = (long long)blockIdx.x * kPoolChunk;
+  const long long i0 = (long long)blockIdx.x * kPoolThreads * PER;
 
   // Vbar of this head from the value-norm partials
   float vb = 0.0f;
@@ -1392,7 +1395,7 @@ poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_ha
   for (int off = 32; off > 0; off >>= 1) vb = fmaxf(vb, __shfl_xor(vb, off));
   if ((threadIdx.x & 63) == 0) s_vmax[threadIdx.x >> 6] = vb;
 
-  for (int i = threadIdx.x; i < kPoolChunk + 2 * pool_half; i += kPoolThreads) {
+  for (int i = threadIdx.x; i < kPoolThreads * PER + 2 * pool_half; i += kPoolThreads) {
     const long long p = i0 + i - pool_half;
     s_in[i] = (p >= 0 && p < n_prefix) ? s_raw[(long long)g * n_prefix + p] : -INFINITY;
   }
@@ -1403,7 +1406,7 @@ poolstat_kernel(const float* __restrict__ s_raw, long long n, int w, int pool_ha
 
   double acc_s = 0.0, acc_t = 0.0;
 #pragma unroll
-  for (int j = 0; j < kPoolPerThread; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int i = j * kPoolThreads + threadIdx.x;
     const long long p = i0 + i;
     if (p < n_prefix) {
@@ -1530,6 +1533,12 @@ int pool_blocks(const lava_layer_desc& d, int64_t n) {
   return (int)((n + kPoolChunk - 1) / kPoolChunk);
 }
 
+// workgroups per KV head whose statistic partials a sequence's workspace region holds
+static size_t ent_blocks(const lava_layer_desc& d, int64_t n, const SweepPlan& p) {
+  const size_t pool = (size_t)pool_blocks(d, n), sweep = (size_t)p.blocks_x_bound * p.n_chunks;
+  return pool > sweep ? pool : sweep;
+}
+
 ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n) {
   const SweepPlan p = make_sweep_plan(d, n);
   ScoreWorkspace w;
@@ -1541,9 +1550,7 @@ ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n) {
   w.off_sraw = off;          // only a group split into chunks goes through raw scores in memory
   if (!p.fused_pool) off += align_up(sizeof(float) * (size_t)d.n_kv_heads * (size_t)(n - d.window));
   w.off_ent_part = off;
-  const size_t ent_blocks = (size_t)pool_blocks(d, n) > (size_t)p.blocks_x_bound * p.n_chunks
-                                ? (size_t)pool_blocks(d, n) : (size_t)p.blocks_x_bound * p.n_chunks;
-  off += align_up(sizeof(double2) * (size_t)d.n_kv_heads * ent_blocks);
+  off += align_up(sizeof(double2) * (size_t)d.n_kv_heads * ent_blocks(d, n, p));
   w.off_counter = off;
   off += align_up(sizeof(uint32_t) * ((size_t)kCtlUnitA + (size_t)d.n_kv_heads * p.blocks_x_bound));
   w.bytes = off;
@@ -1678,11 +1685,17 @@ int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const float* s_raw,
                         const float* vnorm_part, int vnorm_blocks, float* scores, float* vbar,
                         float* layer_stat, double2* ent_part, uint32_t* counters, unsigned int* sel_hist0,
                         const BudgetPlanArgs& plan, int plan_seq, hipStream_t s) {
-  const dim3 grid(pool_blocks(d, n), d.n_kv_heads), block(kPoolThreads);
+  const int64_t fine = (n + kPoolThreads * 4 - 1) / (kPoolThreads * 4);
+  const bool four = (size_t)fine <= ent_blocks(d, n, make_sweep_plan(d, n));
+  const dim3 grid(four ? (unsigned)fine : (unsigned)pool_blocks(d, n), d.n_kv_heads), block(kPoolThreads);
   ProfScope ps(KID_POOLSTAT, s);
-  hipLaunchKernelGGL(poolstat_kernel, grid, block, 0, s, s_raw, (long long)n, d.window,
-                     d.pool_kernel / 2, d.score_kind == LAVA_SCORE_TOKEN_NORM ? 1 : 0, vnorm_part, vnorm_blocks, scores, vbar, layer_stat, ent_part,
-                     counters, sel_hist0, plan, plan_seq);
+#define LAVA_POOLSTAT(PER)                                                                                        \
+  hipLaunchKernelGGL(poolstat_kernel<PER>, grid, block, 0, s, s_raw, (long long)n, d.window, d.pool_kernel / 2,   \
+                     d.score_kind == LAVA_SCORE_TOKEN_NORM ? 1 : 0, vnorm_part, vnorm_blocks, scores, vbar,       \
+                     layer_stat, ent_part, counters, sel_hist0, plan, plan_seq)
+  if (four) LAVA_POOLSTAT(4);
+  else LAVA_POOLSTAT(8);
+#undef LAVA_POOLSTAT
   return launch_status();
 }
 

@@ -65,3 +65,25 @@ def test_batch_of_whole_rounds(lava):
     inps = [synth.gen_layer(s, 3 + j) for j, s in enumerate(shapes)]
     desc = lava.LayerDesc.make(8, 2, 64, 8, "bf16")
     check(shapes, inps, run(lava, desc, shapes, inps))
+
+
+@pytest.mark.parametrize("n", [40, 1024 + 8, 8000, 8500])
+@pytest.mark.parametrize("kind", ["lava", "lse", "attention"])
+def test_split_group(lava, n, kind):
+    """A group swept in two parts: the raw scores the parts join start from zero whichever kernel is the call's first
+    (statistics, value norms, the fill of the attention score), also in a workspace full of large floats, and the
+    pooling launch takes 4 or 8 entries per thread (8 where 64 heads leave the workspace few partials)."""
+    print(f"split group {kind} n={n}", flush=True)
+    s = synth.LayerShape(320, 64, 64, n, 8, "bf16", 0, heavy_count=64)
+    i = synth.gen_layer(s, n)
+    desc = lava.LayerDesc.make(320, 64, 64, 8, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION if kind == "attention" else lava.LAVA_SCORE_LAVA)
+    q, k, v = (lava.to_device(a, "bf16") for a in (i.q_win, i.k, i.v))
+    lse = torch.from_numpy(O.window_lse(*i.f64()[:2]).astype(np.float32)).cuda() if kind == "lse" else None
+    need = lava.lava_window_scores_workspace_bytes(desc, 1, n)
+    ws = torch.full((need,), 0x7E, dtype=torch.uint8, device="cuda")
+    scores, _, _ = lava.lava_window_scores(desc, [n], q, k, v, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    want = O.lava_scores(*i.f64(), 8, 7, use_value_norm=kind != "attention")[0]
+    got = scores.cpu().numpy().reshape(64, n)[:, : n - 8].astype(np.float64)
+    mask = want > 1e-30 * want.max()
+    assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
