@@ -23,6 +23,9 @@
 // (several problems, not prepared) 28 -> 18.  Inside the kernel at 262 K, not prepared: scores in and
 // counted 5.8 us (1.5 of it the loads, 2.5 the wait), pick 0.7, split 0.7, exchange 3.3, threshold 1.3,
 // write 2; a row of keys per lane costs 0.3 us of vector work in all, which is why a lane holds few.
+// Not everywhere ahead of the three digits (calls in a loop, not prepared, digits -> now): 1 M entries, budget n/4, 32 -> 35
+// with plateaus, 35 -> 42 within 10 % of each other; 1 M scores near 2^-60, below the first histogram, 33 -> 41;
+// 4 M as step launches 54 -> 56 to 65 -> 93.
 #include <type_traits>
 
 #include "common.h"
