@@ -25,7 +25,7 @@
 // write 2; a row of keys per lane costs 0.3 us of vector work in all, which is why a lane holds few.
 // Not everywhere ahead of the three digits (calls in a loop, not prepared, digits -> now): 1 M entries, budget n/4, 32 -> 35
 // with plateaus, 35 -> 42 within 10 % of each other; 1 M scores near 2^-60, below the first histogram, 33 -> 41;
-// 4 M as step launches 54 -> 56 to 65 -> 93.
+// 4 M as step launches 54 -> 54 to 66 -> 91 (16 M: 161 -> 111 to 187 -> 185).
 #include <type_traits>
 
 #include "common.h"
@@ -743,9 +743,47 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
 }
 
 // The same phases as separate launches (kernel boundaries take the place of the waits), for a problem
-// too large to keep its whole grid resident.  STEP 0: first histogram; 1..4: histograms of the
-// interval's next bits (nothing to do once it is decided); 5: counts; 6: write.
+// too large to keep its whole grid resident.  STEP 0: first histogram; 1..3: histograms of the interval's next
+// 11 bits (nothing to do once it is decided); 4: counts; 5: write.  Digits of 11 bits because every launch counts:
+// a bin of the first histogram (19 bits) is one key wide after two of them, an end bin (32 bits) after three, where
+// digits of 10 bits took a launch more (4 M plateaus 56.2 -> 53.8 us, 4 M near 2^-60 78.1 -> 68.5, 16 M 170 -> 137).
 constexpr int kStepKeys = 32;
+constexpr int kStepBits = 11;
+constexpr int kStepBins = 1 << kStepBits;
+constexpr int kStepHist = kLevelBins;                 // word of the first of them: behind the first histogram
+static_assert(kStepHist + 2 * kStepBins + (1 << (32 - 2 * kStepBits)) <= 3 * kSelBins, "histogram area");
+static_assert(kStepBins == 2 * kSelThreads && kStepBins + 1 <= (int)kListCap, "two bins per thread, counted in the list's place");
+
+__device__ __forceinline__ unsigned int step_shift(const Interval& v) {
+  return v.bits > (unsigned int)kStepBits ? v.bits - kStepBits : 0u;
+}
+// Bins an interval's next histogram has.
+__device__ __forceinline__ int step_bins(const Interval& v) { return 1 << (v.bits - step_shift(v)); }
+
+// The interval narrowed by histogram `h` (complete: an earlier launch's); thread t owns the bins
+// kStepBins - 1 - 2 t and the one below.  Contains workgroup barriers.
+__device__ __forceinline__ void step_narrow(Interval& v, const unsigned int* __restrict__ h, SelShared& sh) {
+  const int n = step_bins(v), upper = kStepBins - 1 - 2 * (int)threadIdx.x;
+  const unsigned int c1 = upper < n ? h[upper] : 0u, c0 = upper - 1 < n ? h[upper - 1] : 0u;
+  unsigned int pair[3];
+  pick_bin(c1 + c0, v.need, sh, pair);                // (pair's index, survivors needed from it, its count)
+  // the pair's owner knows the two counts
+  if (threadIdx.x == (unsigned int)(kLevelBins - 1) - pair[0]) {
+    const bool in_upper = pair[1] <= c1;
+    sh.before[0] = in_upper ? (unsigned int)upper : (unsigned int)(upper - 1);
+    sh.before[1] = in_upper ? pair[1] : pair[1] - c1;
+    sh.before[2] = in_upper ? c1 : c0;
+  }
+  __syncthreads();
+  const unsigned int s = step_shift(v), skip = sh.before[0] << s, most = (1u << s) - 1u;
+  v.lo += skip;
+  v.width = v.width - skip < most ? v.width - skip : most;
+  v.bits = s;
+  v.need = sh.before[1];
+  v.count = sh.before[2];
+  __syncthreads();
+}
+
 template <int STEP>
 __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch a) {
   const lava_select_problem pr = a.p[0];
@@ -761,39 +799,47 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
   const long long in_off = pr.in_offset_dev ? (long long)*pr.in_offset_dev : 0;
   const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
   const float* __restrict__ scores = pr.scores + in_off;
-  if (STEP < 6 && kept_total == 0) return;
+  if (STEP < 5 && kept_total == 0) return;
   const int wave_base = __builtin_amdgcn_readfirstlane((bx * kSelWaves + wave) * (64 * kStepKeys));
   Interval v = {0u, 0u, 0u, 0u, 0u};
-  unsigned int pk[3];
   if (STEP >= 1 && kept_total > 0) {
+    unsigned int pk[3];
     pick_bin(hist[kLevelBins - 1 - threadIdx.x], (unsigned int)kept_total, sh, pk);
     v = first_interval(pk);
-    for (int l = 1; l < (STEP < 5 ? STEP : kMaxLevels + 1) && !decided(v); ++l) {
-      __syncthreads();
-      pick_bin(hist[l * kLevelBins + kLevelBins - 1 - threadIdx.x], v.need, sh, pk);
-      narrow(v, pk);
-    }
-    if (STEP <= 4 && decided(v)) return;
     __syncthreads();
+    for (int l = 0; l < (STEP < 4 ? STEP - 1 : 3) && !decided(v); ++l) step_narrow(v, hist + kStepHist + l * kStepBins, sh);
+    if (STEP <= 3 && decided(v)) return;
   }
   unsigned int key[kStepKeys];
   load_keys<kStepKeys>(scores, wave_base, total, key);
-  if constexpr (STEP <= 4) {
+  if constexpr (STEP == 0) {
     sh.hist[threadIdx.x] = 0u;
     __syncthreads();
-    if constexpr (STEP == 0) {
-      count_first<kStepKeys>(key, sh.hist);
-    } else {
-      count_level<kStepKeys>(key, v, sh.hist);
-    }
+    count_first<kStepKeys>(key, sh.hist);
     lds_done();
     __syncthreads();
     unsigned int c = sh.hist[threadIdx.x];
-    if (STEP == 0 && threadIdx.x == 0) c -= missing<kStepKeys>(bx, total);
-    if (c) __hip_atomic_fetch_add(&hist[STEP * kLevelBins + threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) c -= missing<kStepKeys>(bx, total);
+    if (c) __hip_atomic_fetch_add(&hist[threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if constexpr (STEP <= 3) {
+    unsigned int* bins = sh.list;
+    bins[threadIdx.x] = bins[threadIdx.x + kSelThreads] = 0u;
+    __syncthreads();
+    const unsigned int shift = step_shift(v), base = lds_offset(bins);
+#pragma unroll
+    for (int j = 0; j < kStepKeys; ++j) {
+      const unsigned int rel = key[j] - v.lo;
+      count_row(base + 4u * (rel <= v.width ? rel >> shift : (unsigned int)kStepBins));   // kStepBins: a bin nobody reads
+    }
+    lds_done();
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < step_bins(v); i += kSelThreads) {
+      const unsigned int c = bins[i];
+      if (c) __hip_atomic_fetch_add(&hist[kStepHist + (STEP - 1) * kStepBins + i], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   } else {
     const Threshold t = kept_total > 0 ? threshold_of(v) : Threshold{0xffffffffu, 0u};
-    if constexpr (STEP == 5) {
+    if constexpr (STEP == 4) {
       unsigned int gt = 0u, eq = 0u;
 #pragma unroll
       for (int j = 0; j < kStepKeys; ++j) {
@@ -950,7 +996,6 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
       hipLaunchKernelGGL(sel_step_kernel<3>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<4>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<5>, grid, block, 0, s, a);
-      hipLaunchKernelGGL(sel_step_kernel<6>, grid, block, 0, s, a);
     }
     const int32_t st = launch_status();
     if (st != LAVA_OK) return st;

@@ -124,3 +124,14 @@ def test_prepared_equals_plain(lava, n):
     b = lava.evict_layer(desc, n, q, k, v, sh.budget, primed=False)
     for key in ("scores", "head_counts", "head_offsets", "kept_idx", "kept_scores", "k_hat"):
         assert torch.equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("kind", ["narrow", "tiny", "huge", "signed", "equal"])
+def test_select_step_launches(lava, kind):
+    """Two digits behind a bin of the first histogram, three behind its end bins, none where all keys are equal."""
+    n, nh = 3_400_000, 4
+    print(f"select step launches {kind}", flush=True)
+    s = flat(kind, n, 11)
+    sc = torch.from_numpy(s).cuda()
+    for budget in (n // 50, n // 2):
+        check(lava.lava_select_topk(nh, sc, budget), s, nh, budget)
