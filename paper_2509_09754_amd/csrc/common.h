@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "../../include/lava.h"
+#include "select_layout.h"
 
 namespace lava {
 
@@ -55,7 +56,6 @@ __device__ __forceinline__ unsigned int score_key(float f) {
   const unsigned int b = __float_as_uint(f + 0.0f);          // -0 + 0 = +0; every other value stays as it is
   return b ^ ((unsigned int)((int)b >> 31) | 0x80000000u);
 }
-constexpr int kSelBins = 2048;              // a selection region's histogram area is 3 * kSelBins words
 // The selection's first digit: 1024 bins, each a sixteenth of an octave of the score, for scores from 2^-44
 // to 2^20; the end bins take whatever lies beyond.  Sixteenths because the threshold's bin then usually holds
 // few enough keys to be collected at once (the top bits of the key, a quarter of an octave, held thousands).
@@ -66,9 +66,6 @@ __device__ __forceinline__ unsigned int sel_digit0(unsigned int key) {
   const unsigned int d = (key - kSelKeyBase) >> kSelDigit0Shift;
   return key < kSelKeyBase ? 0u : (d < (unsigned int)kSelDigit0Bins ? d : (unsigned int)kSelDigit0Bins - 1u);
 }
-
-constexpr size_t kAlign = 256;
-constexpr size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
 
 // ---------------------------------------------------------------- sweep (K, V) kernels
 constexpr int kTileKeys = 32;        // keys per MFMA tile
@@ -178,17 +175,8 @@ int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const float* s_raw,
                         const float* vnorm_part, int vnorm_blocks, float* scores, float* vbar,
                         float* layer_stat, double2* ent_part, uint32_t* counters, unsigned int* sel_hist0,
                         const BudgetPlanArgs& plan, int plan_seq, hipStream_t s);
-// words of a selection's state block (cleared together with its histograms)
-constexpr int kSelStateWords = 8;
 
 // ---------------------------------------------------------------- selection / compaction
-struct SelectWorkspace {
-  size_t off_hist;      // uint32 [3][2048]
-  size_t off_state;     // SelectState
-  size_t off_blk;       // uint32 [2][n_blocks]: keys above / equal to the threshold per workgroup
-  int n_blocks;
-  size_t bytes;
-};
 SelectWorkspace make_select_workspace(int64_t total);
 
 int32_t launch_select(int n_heads, const float* scores, const int64_t* seg_offsets, int64_t total,

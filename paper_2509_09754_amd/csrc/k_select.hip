@@ -33,8 +33,6 @@
 
 namespace lava {
 
-constexpr int kSelThreads = 1024;   // few, large workgroups: a wait for the others and a histogram merge cost per workgroup
-constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kMaxHeads = 64;
 constexpr int kLevelBits = 10;
 constexpr int kLevelBins = 1 << kLevelBits;
@@ -42,7 +40,6 @@ static_assert(kLevelBins == kSelThreads && kSelDigit0Bins == kLevelBins, "one bi
 constexpr int kMaxLevels = 4;                           // ceil(32 / 10) histograms behind the first
 constexpr unsigned int kSpinLimit = 1u << 18;           // polls of a wait for other workgroups before giving up (default)
 constexpr unsigned int kListCap = 16384;                // keys of the threshold's interval a workgroup collects in LDS
-constexpr int kSegWords = 64;                           // of which a workgroup may contribute this many per key a lane holds
 constexpr int kFusedMaxBlocks = 512;                    // workgroups of a problem in the one-launch selection
 
 // The region's histogram area (3 * kSelBins words, zeroed beforehand): the first histogram, up to
@@ -57,26 +54,6 @@ struct SelectState {
   unsigned int reserved[5];
 };
 static_assert(sizeof(SelectState) == kSelStateWords * sizeof(unsigned int), "cleared word by word by the score kernels");
-
-// Layout of a selection's workspace for `total` entries (also evaluated at compile time, for the
-// built-in scratch array of lava_select_topk_static).
-static constexpr SelectWorkspace select_layout(int64_t total) {
-  constexpr int64_t kChunk = kSelThreads * 16;
-  SelectWorkspace w{};
-  w.n_blocks = (int)((total + kChunk - 1) / kChunk);
-  if (w.n_blocks < 1) w.n_blocks = 1;
-  size_t off = 0;
-  w.off_hist = off;  off += align_up(sizeof(unsigned int) * 3 * kSelBins);
-  w.off_state = off; off += align_up(sizeof(SelectState));
-  // two counts per workgroup for the step launches; the fused kernel's segments: kSegWords for every 1024 entries
-  constexpr int kRegionBlocks = 1024;
-  size_t words = 2 * (size_t)w.n_blocks;
-  const size_t fused = (size_t)(w.n_blocks < kRegionBlocks ? w.n_blocks : kRegionBlocks) * (16 * kSegWords + 1);
-  if (fused > words) words = fused;
-  w.off_blk = off;   off += align_up(sizeof(unsigned int) * words);
-  w.bytes = off;
-  return w;
-}
 
 SelectWorkspace make_select_workspace(int64_t total) { return select_layout(total); }
 
@@ -462,6 +439,7 @@ struct SelectBatch {
   char* ws;                      // region of problem p at ws + p * ws_stride
   size_t ws_stride, off_hist, off_state, off_blk;
   unsigned int spin_limit;       // polls of a wait for other workgroups before it gives up
+  unsigned int seg_words;        // one-launch selection: words of a workgroup's segment
   unsigned int primed_mask;      // bit p: problem p's region was prepared by the score kernels (first histogram
                                  // complete, the rest cleared)
   lava_select_problem p[kMaxSelProblems];
@@ -542,7 +520,7 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   const int bx = (int)blockIdx.x - a.first_block[prob];
   const unsigned int nb = (unsigned int)(a.first_block[prob + 1] - a.first_block[prob]);
   const bool alone = nb == 1u;
-  constexpr unsigned int kSegCap = kSegWords * KP;
+  const unsigned int seg_words = a.seg_words;
   char* region = a.ws + prob * a.ws_stride;
   unsigned int* hist = reinterpret_cast<unsigned int*>(region + a.off_hist);
   unsigned long long* flag = reinterpret_cast<unsigned long long*>(hist + kFlagWord);
@@ -621,9 +599,9 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
         if (want_keys) collect_keys<KP>(key, v, inside_base, rows_inside, [&](unsigned int at, unsigned int k) { sh.list[at] = k; });   // inside == v.count <= kListCap
       } else {
         // this workgroup's keys to its segment, then its counts; the counts are the signal that the keys are there
-        if (want_keys && inside <= kSegCap)
+        if (want_keys && inside <= seg_words)
           collect_keys<KP>(key, v, inside_base, rows_inside,
-                           [&](unsigned int at, unsigned int k) { st_dev(&seg[(unsigned int)bx * kSegCap + at], k); });
+                           [&](unsigned int at, unsigned int k) { st_dev(&seg[(unsigned int)bx * seg_words + at], k); });
         drain_vmem();
         __syncthreads();
         ++epoch;
@@ -647,7 +625,7 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
             if (b < nb) sh.seg_pos[b] = pos + incl - in;
             pos += (unsigned int)__builtin_amdgcn_readlane((int)incl, 63);
             if (b < (unsigned int)bx) { gt += ab; before += in; }
-            over |= in > kSegCap ? 1u : 0u;
+            over |= in > seg_words ? 1u : 0u;
           }
           gt = wave_sum(gt);
           before = wave_sum(before);
@@ -674,7 +652,7 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
               const unsigned int mid = (lo + hi) >> 1;
               if (sh.seg_pos[mid] <= i) lo = mid; else hi = mid;
             }
-            sh.list[i] = ld_dev(&seg[lo * kSegCap + (i - sh.seg_pos[lo])]);
+            sh.list[i] = ld_dev(&seg[lo * seg_words + (i - sh.seg_pos[lo])]);
           }
         }
       }
@@ -872,7 +850,6 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
 }
 
 // Workgroups of the fused kernel that can be resident at once on the current device.
-constexpr int kMostKeys = 12;
 static int fused_capacity() {
   static int cached[64];
   static bool known[64];
@@ -887,11 +864,6 @@ static int fused_capacity() {
     known[dev] = true;
   }
   return cached[dev];
-}
-
-static int64_t workgroups_for(int64_t total, int keys) {
-  const int64_t chunk = (int64_t)kSelThreads * keys, nb = (total + chunk - 1) / chunk;
-  return nb < 1 ? 1 : nb;
 }
 
 // Keys per lane for a launch that starts with problems[0 .. n - 1], of whose workgroups `cap` may be resident:
@@ -967,7 +939,7 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
       }
     }
     int count = 0;
-    int64_t blocks = 0;
+    int64_t blocks = 0, widest = 1;
     a.primed_mask = 0u;
     while (first + count < group_end) {
       const lava_select_problem& pr = problems[first + count];
@@ -975,12 +947,14 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
       if (count > 0 && blocks + nb > cap) break;
       a.first_block[count] = (int)blocks;
       blocks += nb;
+      if (nb > widest) widest = nb;
       a.p[count] = pr;
       if (pr.primed) a.primed_mask |= 1u << count;
       ++count;
     }
     a.n_problems = count;
     a.first_block[count] = (int)blocks;
+    a.seg_words = segment_words(keys, widest, w.blk_words);
     a.ws = static_cast<char*>(ws) + (size_t)first * w.bytes;
     const bool fused = blocks <= cap;
     if (fused) {

@@ -1,0 +1,84 @@
+"""Selections whose workgroups of 12 keys per lane do not divide their workspace region, with the threshold's interval
+crowded into the last, partly filled workgroup: survivors against the oracle (integer-exact), canaries behind the
+workspace, and the neighbours of a problem in a table."""
+import numpy as np
+import pytest
+
+from oracle import lava_oracle as O
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+CHUNK = 12 * 1024
+NH = 8
+CANARY = 0x5A
+
+
+@pytest.fixture(scope="module")
+def lava():
+    from paper_2509_09754_amd import lava as L
+    return L
+
+
+def crowded_end(n, inside, seed):
+    """(scores, budget): `inside` distinct scores of one interval of the first histogram lie in the last workgroup, no
+    others in that interval; some scores lie above it, the budget cuts in the middle of it."""
+    r = np.random.Generator(np.random.PCG64(seed))
+    s = (1e-3 * np.exp(0.3 * r.standard_normal(n))).astype(np.float32)
+    first = (n - 1) // CHUNK * CHUNK
+    assert first >= CHUNK and n - first >= inside
+    above = r.choice(first, 500, replace=False)
+    s[above] = (2.0 + r.random(500)).astype(np.float32)
+    at = first + r.choice(n - first, inside, replace=False)
+    s[at] = (1.0 + r.permutation(inside) * (0.04 / inside)).astype(np.float32)
+    return s, 500 + inside // 2
+
+
+def check(out, s, budget):
+    counts, offs, idx, kept = (x.cpu().numpy() for x in out)
+    starts = (np.arange(NH + 1) * (s.size // NH)).astype(np.int64)
+    rc, ro, ri, _ = O.select_topk(s.astype(np.float64), starts, budget)
+    assert np.array_equal(counts, rc) and np.array_equal(offs, ro) and np.array_equal(idx, ri)
+    flat = np.concatenate([starts[g] + ri[ro[g]: ro[g + 1]] for g in range(NH)]).astype(np.int64)
+    assert np.array_equal(kept.view(np.uint32), s[flat].view(np.uint32))
+
+
+def outputs(budget):
+    return (torch.empty(NH, dtype=torch.int32, device="cuda"), torch.empty(NH + 1, dtype=torch.int64, device="cuda"),
+            torch.empty(budget, dtype=torch.int32, device="cuda"), torch.empty(budget, device="cuda"))
+
+
+# the last workgroup's keys: fewer than its segment takes, its last word, one more (1048576 entries: 762 words), and more
+@pytest.mark.parametrize("inside", [300, 577, 762, 763, 768, 769, 1500])
+@pytest.mark.parametrize("n", [557056, 573440, 1048576])
+def test_last_workgroup_of_a_problem(lava, n, inside):
+    print(f"select bounds n={n} inside={inside}", flush=True)
+    s, budget = crowded_end(n, inside, n + inside)
+    need = lava.lava_select_workspace_bytes(n)
+    buf = torch.full((need + 8192,), CANARY, dtype=torch.uint8, device="cuda")
+    out = outputs(budget)
+    lava.lava_select_topk(NH, torch.from_numpy(s).cuda(), budget, head_counts=out[0], head_offsets=out[1], kept_idx=out[2],
+                          kept_scores=out[3], workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == CANARY).all())
+    check(out, s, budget)
+
+
+@pytest.mark.parametrize("n", [81920, 262144])
+def test_last_workgroup_of_every_problem_of_a_table(lava, n):
+    """32 problems of one size: as many workgroups as make 12 keys per lane, regions back to back."""
+    print(f"select bounds table n={n}", flush=True)
+    data, probs = [], []
+    for p in range(32):
+        s, budget = crowded_end(n, 400 + 12 * p, n + p)
+        sc, out = torch.from_numpy(s).cuda(), outputs(budget)
+        data.append((s, sc, budget, out))
+        probs.append(lava.select_problem(sc, budget, *out))
+    need = lava.lava_select_batch_workspace_bytes(len(probs), n)
+    buf = torch.full((need + 8192,), CANARY, dtype=torch.uint8, device="cuda")
+    lava.lava_select_topk_batch(NH, probs, n, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == CANARY).all())
+    assert lava.lava_select_batch_status(buf[:need], len(probs), n) == lava.LAVA_OK
+    for s, _, budget, out in data:
+        check(out, s, budget)
