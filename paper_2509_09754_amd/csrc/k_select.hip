@@ -114,7 +114,7 @@ template <int KP>
 __device__ __forceinline__ void load_keys(const float* __restrict__ scores, int wave_base, int total,
                                           unsigned int (&key)[KP]) {
   const int lane = (int)(threadIdx.x & 63);
-  if (wave_base + 64 * KP <= total) {               // uniform; all loads in flight before the first use
+  if (span_complete(wave_base, 64 * KP, total)) {   // uniform; all loads in flight before the first use
     const float* __restrict__ src = scores + wave_base + lane;
 #pragma unroll
     for (int j = 0; j < KP; ++j) key[j] = __float_as_uint(src[64 * j]);
@@ -303,7 +303,6 @@ __device__ __forceinline__ void write_survivors(const unsigned int (&key)[KP], u
                                                 int32_t* __restrict__ head_counts, int64_t* __restrict__ head_offsets,
                                                 int32_t* __restrict__ kept_idx, float* __restrict__ kept_scores) {
   const int lane = threadIdx.x & 63, wave = sel_wave();
-  const int wave_end = wave_base + 64 * KP;
   // lane j: which keys of row j lie above T / are equal to it
   unsigned long long row_gt = 0ull, row_eq = 0ull;
 #pragma unroll
@@ -342,8 +341,9 @@ __device__ __forceinline__ void write_survivors(const unsigned int (&key)[KP], u
   const unsigned long long started = __ballot(lane < n_heads && start <= wave_base);
   int g = started ? 63 - __builtin_clzll(started) : 0;        // head of the wavefront's first entry
   const int g_first = g;
-  unsigned long long starts = __ballot(lane > 0 && lane < n_heads && start >= wave_base && start < wave_end && start < total);
-  const bool several = __ballot(lane > 0 && lane < n_heads && start > wave_base && start < wave_end) != 0ull;
+  const bool here = lane > 0 && lane < n_heads && in_span(start, wave_base, 64 * KP);
+  unsigned long long starts = __ballot(here && start < total);
+  const bool several = __ballot(here && start > wave_base) != 0ull;
   unsigned int s_prev = s_begin;
   while (starts) {
     const int h = __builtin_ctzll(starts);

@@ -61,4 +61,9 @@ constexpr unsigned int segment_words(int keys, int64_t workgroups, size_t blk_wo
   return (unsigned int)(share < most ? share : most);
 }
 
+// Entries of a wavefront are base .. base + span - 1, and totals go up to 2^31 - 1: base + span may be 2^31, so it
+// is never formed.
+constexpr bool span_complete(int base, int span, int total) { return base <= total - span; }   // every entry exists
+constexpr bool in_span(int p, int base, int span) { return p >= base && p - base < span; }      // p, base >= 0
+
 }  // namespace lava

@@ -82,3 +82,30 @@ def test_last_workgroup_of_every_problem_of_a_table(lava, n):
     assert lava.lava_select_batch_status(buf[:need], len(probs), n) == lava.LAVA_OK
     for s, _, budget, out in data:
         check(out, s, budget)
+
+
+@pytest.mark.parametrize("short", [0, 1, 63, 2046, 2048])
+def test_totals_up_to_31_bits(lava, short):
+    """2^31 - 1 entries and a little fewer: the last wavefront's entries end at the last index there is, heads start in it,
+    and its scores are ranked.  All scores are 0 but a few, so the survivors are known."""
+    n = (1 << 31) - 1 - short
+    if torch.cuda.mem_get_info()[0] < 4 * n + (1 << 30):
+        pytest.skip("not enough free memory for 2^31 scores")
+    print(f"select bounds n={n}", flush=True)
+    buf = torch.zeros(n + 4096, device="cuda")
+    buf[n:] = 9.0                                                    # nobody may rank these
+    at = sorted({0, 5, n // 2, n - 2048, n - 1900, n - 1000, n - 700, n - 2, n - 1})
+    buf[torch.tensor(at, device="cuda")] = torch.arange(1, len(at) + 1, device="cuda", dtype=torch.float32)
+    starts = [0, n // 2 + 1, n - 1900, n - 1900, n - 1500, n - 700, n - 1, n, n]      # NH heads, two of them empty
+    budget = len(at) + 3                                             # three zeros: the first ones in flat order
+    flat = sorted(at + [1, 2, 3])
+    head = [max(h for h in range(NH) if starts[h] <= p) for p in flat]
+    out = outputs(budget)
+    ws = torch.empty(lava.lava_select_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    lava.lava_select_topk(NH, buf, budget, seg_offsets=torch.tensor(starts, device="cuda"), total_entries=n, head_counts=out[0],
+                          head_offsets=out[1], kept_idx=out[2], kept_scores=out[3], workspace=ws)
+    counts, offs, idx, kept = (x.cpu().numpy() for x in out)
+    want = np.bincount(head, minlength=NH)
+    assert counts.tolist() == want.tolist() and offs.tolist() == np.concatenate([[0], np.cumsum(want)]).tolist()
+    assert idx.tolist() == [p - starts[h] for p, h in zip(flat, head)]
+    assert kept.tolist() == [at.index(p) + 1.0 if p in at else 0.0 for p in flat]

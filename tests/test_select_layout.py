@@ -52,3 +52,33 @@ def test_segments_end_inside_the_region(tmp_path):
     res = run(SEGMENTS, tmp_path)
     assert res.returncode == 0, res.stdout
     assert int(res.stdout) > 5000
+
+
+SPANS = r"""
+#include <climits>
+#include <cstdio>
+#include <initializer_list>
+#include "select_layout.h"
+using namespace lava;
+int main() {
+  long long checked = 0;
+  for (int span : {64 * 2, 64 * 4, 64 * 8, 64 * kMostKeys, 64 * 32})
+    for (long long total : {1ll, span - 1ll, (long long)span, span + 1ll, (1ll << 30) + 5, INT_MAX - 2ll * span, (long long)INT_MAX - span,
+                            INT_MAX - span + 1ll, INT_MAX - 64ll, INT_MAX - 1ll, (long long)INT_MAX})
+      for (long long base : {0ll, (total - 1) / span * span, total / span * span, (total / span > 0 ? total / span - 1 : 0) * span}) {
+        if (base > INT_MAX) continue;
+        if (span_complete((int)base, span, (int)total) != (base + span <= total)) return 1;
+        for (long long p : {0ll, base, base + 1, base + span - 1, base + span, total - 1, total, (long long)INT_MAX})
+          if (p <= INT_MAX && in_span((int)p, (int)base, span) != (p >= base && p < base + span)) return 2;
+        ++checked;
+      }
+  std::printf("%lld\n", checked);
+  return 0;
+}
+"""
+
+
+def test_spans_at_the_end_of_31_bits(tmp_path):
+    """Where a wavefront's entries end is decided without forming an index beyond 2^31 - 1."""
+    res = run(SPANS, tmp_path)
+    assert res.returncode == 0 and int(res.stdout) > 100, (res.returncode, res.stdout)
