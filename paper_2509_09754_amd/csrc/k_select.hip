@@ -108,25 +108,32 @@ __device__ __forceinline__ int segment_start(const int64_t* __restrict__ seg_off
 // A workgroup's keys: wavefront w holds the 64 * KP consecutive entries from wave_base on as KP rows of
 // 64 (row j, lane l: entry wave_base + 64 j + l), so that loads are coalesced whatever the alignment of
 // the scores and the flat order inside a wavefront is row by row, lane by lane: positions are bit counts
-// of ballots, nothing goes through LDS.  Entries beyond the end get key 0, which no score has (a NaN
-// would: a documented precondition).
+// of ballots, nothing goes through LDS.  Entries beyond the end get key 0, which no entry has: the one score
+// whose image it is, the NaN with all bits set, gets 1, so that it is ranked like any other (NaN is no valid score,
+// but a slot counted and not written would be an index from nowhere for the gather behind the selection).
 template <int KP>
 __device__ __forceinline__ void load_keys(const float* __restrict__ scores, int wave_base, int total,
                                           unsigned int (&key)[KP]) {
   const int lane = (int)(threadIdx.x & 63);
+  auto ranked = [](unsigned int bits) -> unsigned int {
+    const unsigned int k = score_key(__uint_as_float(bits));
+    return k > 1u ? k : 1u;
+  };
   if (span_complete(wave_base, 64 * KP, total)) {   // uniform; all loads in flight before the first use
     const float* __restrict__ src = scores + wave_base + lane;
 #pragma unroll
     for (int j = 0; j < KP; ++j) key[j] = __float_as_uint(src[64 * j]);
+#pragma unroll
+    for (int j = 0; j < KP; ++j) key[j] = ranked(key[j]);
   } else {
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
       const int p = wave_base + lane + 64 * j;
-      key[j] = p < total ? __float_as_uint(scores[p]) : 0xffffffffu;   // a NaN whose key is 0
+      key[j] = p < total ? __float_as_uint(scores[p]) : 0u;
     }
-  }
 #pragma unroll
-  for (int j = 0; j < KP; ++j) key[j] = score_key(__uint_as_float(key[j]));
+    for (int j = 0; j < KP; ++j) key[j] = wave_base + lane + 64 * j < total ? ranked(key[j]) : 0u;
+  }
 }
 static_assert(kMaxHeads <= 64, "one lane per head");
 
@@ -388,10 +395,11 @@ __device__ __forceinline__ void write_survivors(const unsigned int (&key)[KP], u
         }
         kept_idx[slot] = p - from;
         if (kept_scores) {
-          // the score behind a key; both zeros share one, so those are read again
+          // the score behind a key; both zeros share one and a NaN's bits are not all kept, so those are read again
+          constexpr unsigned int kLowest = 0x007fffffu, kHighest = 0xff800000u;      // keys of -inf and +inf
           const unsigned int k = key[j];
           float f = __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
-          if (k == 0x80000000u) f = scores[p];
+          if (k == 0x80000000u || k - kLowest > kHighest - kLowest) f = scores[p];
           kept_scores[slot] = f;
         }
       }

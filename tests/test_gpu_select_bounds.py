@@ -109,3 +109,32 @@ def test_totals_up_to_31_bits(lava, short):
     assert counts.tolist() == want.tolist() and offs.tolist() == np.concatenate([[0], np.cumsum(want)]).tolist()
     assert idx.tolist() == [p - starts[h] for p, h in zip(flat, head)]
     assert kept.tolist() == [at.index(p) + 1.0 if p in at else 0.0 for p in flat]
+
+
+def image(bits):
+    """The order-preserving integer image of a float's bits."""
+    return np.where(bits >> 31, ~bits, bits | 0x80000000).astype(np.uint32)
+
+
+# one workgroup, several (2 and 12 keys per lane), the step launches
+@pytest.mark.parametrize("n", [1001, 30001, 600001, 3_400_001])
+def test_every_slot_is_written_whatever_the_bits(lava, n):
+    """NaN is no valid score, but every slot that head_offsets counts holds an index all the same, also where the budget
+    reaches the NaN with all bits set: survivors are ranked by the image of their bits, and kept_scores repeats them."""
+    print(f"select bits n={n}", flush=True)
+    r = np.random.Generator(np.random.PCG64(n))
+    bits = r.standard_normal(n).astype(np.float32).view(np.uint32).copy()
+    odd = r.choice(n, 40, replace=False)
+    bits[odd] = np.array([0xffffffff, 0xffffffff, 0xffc00000, 0x7fc00000, 0x7fffffff, 0x7f800000, 0xff800000, 0x80000000], np.uint32)[np.arange(40) % 8]
+    bits[n - 1] = 0xffffffff
+    image_of = image(np.where(bits == 0x80000000, np.uint32(0), bits))
+    order = np.argsort(-image_of.astype(np.int64), kind="stable")
+    sc = torch.from_numpy(bits.view(np.int32)).cuda().view(torch.float32)
+    for budget in (10, n - 11, n - 3, n):
+        keep = np.sort(order[:budget])
+        out = (torch.empty(1, dtype=torch.int32, device="cuda"), torch.empty(2, dtype=torch.int64, device="cuda"),
+               torch.full((budget,), -7, dtype=torch.int32, device="cuda"), torch.empty(budget, device="cuda"))
+        lava.lava_select_topk(1, sc, budget, head_counts=out[0], head_offsets=out[1], kept_idx=out[2], kept_scores=out[3])
+        assert out[0].tolist() == [budget] and out[1].tolist() == [0, budget]
+        assert np.array_equal(out[2].cpu().numpy(), keep)
+        assert np.array_equal(out[3].view(torch.int32).cpu().numpy().view(np.uint32), bits[keep])
