@@ -67,7 +67,7 @@ def test_batch_of_whole_rounds(lava):
     check(shapes, inps, run(lava, desc, shapes, inps))
 
 
-@pytest.mark.parametrize("n", [40, 1024 + 8, 8000, 8500])
+@pytest.mark.parametrize("n", [40, 1024 + 8, 2049 + 8, 8000, 8500])
 @pytest.mark.parametrize("kind", ["lava", "lse", "attention"])
 def test_split_group(lava, n, kind):
     """A group swept in two parts: the raw scores the parts join start from zero whichever kernel is the call's first
