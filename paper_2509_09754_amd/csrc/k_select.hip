@@ -59,7 +59,7 @@ SelectWorkspace make_select_workspace(int64_t total) { return select_layout(tota
 
 struct SelShared {
   unsigned int list[kListCap];              // keys of the threshold's interval, all workgroups', in workgroup order
-  unsigned int hist[kLevelBins + 1];        // the last word collects what belongs to no bin
+  unsigned int hist[kLevelBins];
   unsigned int seg_pos[kFusedMaxBlocks + 1];// where workgroup b's keys start in `list`
   int off[kMaxHeads + 1];                   // segment starts
   unsigned int cnt[kMaxHeads];              // survivors per head in this workgroup
@@ -182,6 +182,23 @@ __device__ __forceinline__ void count_row(unsigned int at) {
   row_done();
 }
 
+// ... for the lanes inside the interval that is counted.  The others stay out of it altogether: a bin for them
+// that nobody reads takes up to 64 adds to one address, one after the other (1 M entries, budget n/4, scores within
+// 10 % of each other: 9.3 us for this histogram, 1.9 without such a bin; 41.6 -> 34.2 for the call, 4 M 83 -> 63.7).
+__device__ __forceinline__ void count_row(bool in, unsigned int at) {
+  const unsigned long long lanes = __ballot(in);
+  if (lanes != 0ull) {                                        // uniform
+    const int leader = __builtin_ctzll(lanes);
+    const unsigned int at0 = (unsigned int)__builtin_amdgcn_readlane((int)at, leader);
+    if (__ballot(in && at == at0) == lanes) {
+      if ((int)(threadIdx.x & 63) == leader) lds_add(at0, (unsigned int)__popcll(lanes));
+    } else if (in) {
+      lds_add(at, 1u);
+    }
+  }
+  row_done();
+}
+
 // First histogram (bins sel_digit0) over this wavefront's keys, in `hist` (LDS; zeroed and published by a
 // barrier before).  Entries beyond the end have key 0, i.e. count in bin 0: the caller takes them out again.
 template <int KP>
@@ -205,7 +222,7 @@ __device__ __forceinline__ void count_level(const unsigned int (&key)[KP], const
 #pragma unroll
   for (int j = 0; j < KP; ++j) {
     const unsigned int rel = key[j] - v.lo;
-    count_row(base + 4u * (rel <= v.width ? rel >> shift : (unsigned int)kLevelBins));   // kLevelBins: a bin nobody reads
+    count_row(rel <= v.width, base + 4u * (rel >> shift));
   }
 }
 
@@ -738,7 +755,7 @@ constexpr int kStepBits = 11;
 constexpr int kStepBins = 1 << kStepBits;
 constexpr int kStepHist = kLevelBins;                 // word of the first of them: behind the first histogram
 static_assert(kStepHist + 2 * kStepBins + (1 << (32 - 2 * kStepBits)) <= 3 * kSelBins, "histogram area");
-static_assert(kStepBins == 2 * kSelThreads && kStepBins + 1 <= (int)kListCap, "two bins per thread, counted in the list's place");
+static_assert(kStepBins == 2 * kSelThreads && kStepBins <= (int)kListCap, "two bins per thread, counted in the list's place");
 
 __device__ __forceinline__ unsigned int step_shift(const Interval& v) {
   return v.bits > (unsigned int)kStepBits ? v.bits - kStepBits : 0u;
@@ -815,7 +832,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
 #pragma unroll
     for (int j = 0; j < kStepKeys; ++j) {
       const unsigned int rel = key[j] - v.lo;
-      count_row(base + 4u * (rel <= v.width ? rel >> shift : (unsigned int)kStepBins));   // kStepBins: a bin nobody reads
+      count_row(rel <= v.width, base + 4u * (rel >> shift));
     }
     lds_done();
     __syncthreads();
