@@ -37,14 +37,24 @@ constexpr int kMaxHeads = 64;
 constexpr int kLevelBits = 10;
 constexpr int kLevelBins = 1 << kLevelBits;
 static_assert(kLevelBins == kSelThreads && kSelDigit0Bins == kLevelBins, "one bin per thread");
-constexpr int kMaxLevels = 4;                           // ceil(32 / 10) histograms behind the first
 constexpr unsigned int kSpinLimit = 1u << 18;           // polls of a wait for other workgroups before giving up (default)
 constexpr unsigned int kListCap = 16384;                // keys of the threshold's interval a workgroup collects in LDS
 constexpr int kFusedMaxBlocks = 512;                    // workgroups of a problem in the one-launch selection
 
-// The region's histogram area (3 * kSelBins words, zeroed beforehand): the first histogram, up to
-// kMaxLevels further ones, then one 64-bit word per workgroup of the one-launch selection.
-constexpr int kFlagWord = (1 + kMaxLevels) * kLevelBins;
+// The first histogram's end bins hold whatever lies beyond its range.  A selection that counts it itself (one that is not
+// prepared) counts their keys a second time, by their offset from the bin's lowest key in steps of half an octave: the
+// next histogram of either end bin, without another pass and another wait for the other workgroups.  Bins of the low
+// end from word 0 on, of the high end from kEndHigh on; the last word is where entries beyond the end go.
+constexpr int kEndShift = 32 - kLevelBits;
+constexpr int kEndHigh = 768;
+constexpr unsigned int kHighLo = kSelKeyBase + ((unsigned int)(kLevelBins - 1) << kSelDigit0Shift);   // lowest key of the last bin
+static_assert(((kSelKeyBase + (1u << kSelDigit0Shift) - 2u) >> kEndShift) < kEndHigh &&
+              kEndHigh + ((0xffffffffu - kHighLo) >> kEndShift) < kLevelBins - 1, "both ends fit");
+
+// The region's histogram area (3 * kSelBins words, zeroed beforehand): the first histogram, if not prepared the end
+// bins' one, the further ones (at most four: 32 bits, or three: 22), then one 64-bit word per workgroup of the one-launch selection.
+__device__ __forceinline__ constexpr int next_hist_word(bool primed) { return primed ? kLevelBins : 2 * kLevelBins; }
+constexpr int kFlagWord = 5 * kLevelBins;
 static_assert(kFlagWord + 2 * kFusedMaxBlocks <= 3 * kSelBins, "histogram area");
 
 struct SelectState {
@@ -199,19 +209,32 @@ __device__ __forceinline__ void count_row(bool in, unsigned int at) {
   row_done();
 }
 
-// First histogram (bins sel_digit0) over this wavefront's keys, in `hist` (LDS; zeroed and published by a
-// barrier before).  Entries beyond the end have key 0, i.e. count in bin 0: the caller takes them out again.
+// First histogram (bins sel_digit0) over this wavefront's keys, in `hist`, and the end bins' one in `ends` (LDS; zeroed
+// and published by a barrier before).  Entries beyond the end have key 0, i.e. count in bin 0: the caller takes them out again.
+// The keys of an end bin are counted there per row and not per lane, which would be one address for many.
 template <int KP>
-__device__ __forceinline__ void count_first(const unsigned int (&key)[KP], unsigned int* hist) {
-  constexpr unsigned int kFirst = kSelKeyBase >> kSelDigit0Shift;
+__device__ __forceinline__ void count_first(const unsigned int (&key)[KP], unsigned int* hist, unsigned int* ends) {
+  constexpr unsigned int kFirst = kSelKeyBase >> kSelDigit0Shift, kLast = kFirst + kSelDigit0Bins - 1u;
   static_assert((kFirst << kSelDigit0Shift) == kSelKeyBase, "bins are aligned in the key");
-  const unsigned int base = lds_offset(hist) - 4u * kFirst;
+  const unsigned int base = lds_offset(hist) - 4u * kFirst, ends_at = lds_offset(ends);
 #pragma unroll
   for (int j = 0; j < KP; ++j) {
     unsigned int d = key[j] >> kSelDigit0Shift;
     d = d < kFirst ? kFirst : d;
-    d = d > kFirst + kSelDigit0Bins - 1u ? kFirst + kSelDigit0Bins - 1u : d;
-    count_row(base + 4u * d);
+    d = d > kLast ? kLast : d;
+    unsigned int at = base + 4u * d;
+    const bool end = d - (kFirst + 1u) > kLast - kFirst - 2u;
+    const unsigned long long in_ends = __ballot(end);
+    if (in_ends != 0ull) {                                    // uniform
+      const unsigned long long low = __ballot(d == kFirst);
+      if ((threadIdx.x & 63) == 0) {
+        lds_add(base + 4u * kFirst, (unsigned int)__popcll(low));
+        lds_add(base + 4u * kLast, (unsigned int)__popcll(in_ends & ~low));
+      }
+      const unsigned int of_end = d == kFirst ? (key[j] - 1u) >> kEndShift : kEndHigh + ((key[j] - kHighLo) >> kEndShift);
+      if (end) at = ends_at + 4u * of_end;
+    }
+    count_row(at);
   }
 }
 
@@ -299,6 +322,18 @@ __device__ __forceinline__ void narrow(Interval& v, const unsigned int (&pk)[3])
   v.bits = sh;
   v.need = pk[1];
   v.count = pk[2];
+}
+
+// The interval of an end bin (`low`: the first one) narrowed by the histogram of the ends in `ends`; READ: how to read
+// a word of it.  Contains workgroup barriers.
+template <class READ>
+__device__ __forceinline__ void narrow_end(Interval& v, bool low, SelShared& sh, READ&& read) {
+  const int bin = kLevelBins - 1 - (int)threadIdx.x, word = low ? bin : kEndHigh + bin;
+  const unsigned int mine = word < (low ? kEndHigh : kLevelBins - 1) ? read(word) : 0u;
+  __syncthreads();                                   // sh.pick has been read
+  unsigned int pk[3];
+  pick_bin(mine, v.need, sh, pk);
+  narrow(v, pk);
 }
 
 // What a survivor is: key > T, or key == T and among the first `ties` such keys in flat order.
@@ -594,7 +629,6 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   const int64_t* __restrict__ seg_offsets = pr.seg_offsets;
   const int n_heads = a.n_heads;
   const long long in_off = pr.in_offset_dev ? (long long)*pr.in_offset_dev : 0;
-  const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
   const float* __restrict__ scores = pr.scores + in_off;
   const int total = (int)device_total(pr.total_entries, seg_offsets, n_heads);
   const int kept_total = (int)effective_budget(pr.budget, pr.budget_dev, total);
@@ -613,38 +647,53 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   unsigned int rows = 0u;                            // rows of this wavefront that may hold survivors
   unsigned int gt_before = 0u, eq_before = 0u;
   if (kept_total > 0) {                              // uniform over the problem's workgroups, like everything below
-    // The interval that holds the threshold, at first every key there is; `prepared`: its histogram is there.
-    Interval v = {1u, 0xfffffffeu, 32u, (unsigned int)kept_total, (unsigned int)total};
-    bool counted = primed, first = true;
+    // ---- the first histogram, unless the region was prepared, and the interval that holds the threshold
+    unsigned int round = 0u;
+    unsigned int pk[3];
+    if (!primed) {
+      sh.hist[threadIdx.x] = sh.list[threadIdx.x] = 0u;        // sh.list: the end bins' histogram, until keys are collected there
+      __syncthreads();
+      count_first<KP>(key, sh.hist, sh.list);
+      lds_done();
+      __syncthreads();
+      bin_count = sh.hist[kLevelBins - 1 - threadIdx.x];
+      if (threadIdx.x == kLevelBins - 1) bin_count -= missing<KP>(bx, total);
+      if (!alone) {
+        unsigned int* gh = &hist[(kLevelBins - 1) - threadIdx.x];
+        if (bin_count) __hip_atomic_fetch_add(gh, bin_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned int of_end = sh.list[threadIdx.x];
+        if (of_end) __hip_atomic_fetch_add(&hist[kLevelBins + threadIdx.x], of_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        grid_sync(st, ++round, nb, a.spin_limit);
+        bin_count = ld_dev(gh);
+      }
+    }
+    pick_bin(bin_count, (unsigned int)kept_total, sh, pk);
+    Interval v = first_interval(pk);
+    if (!primed && v.bits == 32u && !decided(v))
+      narrow_end(v, pk[0] == 0u, sh, [&](int w) { return alone ? sh.list[w] : ld_dev(&hist[kLevelBins + w]); });
+    int word = next_hist_word(primed);               // of the next histogram in the region
     bool crowded = false;                            // one workgroup holds more of the interval's keys than its segment takes
-    unsigned int epoch = 0u, round = 0u, level = 0u;
+    unsigned int epoch = 0u;
     for (;;) {
-      // ---- too many keys to collect (or nothing known yet): count them by their next bits
-      if (first || (!decided(v) && (v.count > kListCap || crowded))) {
-        if (!counted) {
-          __syncthreads();
-          sh.hist[threadIdx.x] = 0u;
-          __syncthreads();
-          if (first) count_first<KP>(key, sh.hist);
-          else count_level<KP>(key, v, sh.hist);
-          lds_done();
-          __syncthreads();
-          bin_count = sh.hist[kLevelBins - 1 - threadIdx.x];
-          if (first && threadIdx.x == kLevelBins - 1) bin_count -= missing<KP>(bx, total);
-          if (!alone) {
-            unsigned int* gh = &hist[level * kLevelBins + (kLevelBins - 1) - threadIdx.x];
-            if (bin_count) __hip_atomic_fetch_add(gh, bin_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            grid_sync(st, ++round, nb, a.spin_limit);
-            bin_count = ld_dev(gh);
-          }
+      // ---- too many keys to collect: count them by their next bits
+      while (!decided(v) && (v.count > kListCap || crowded)) {
+        __syncthreads();
+        sh.hist[threadIdx.x] = 0u;
+        __syncthreads();
+        count_level<KP>(key, v, sh.hist);
+        lds_done();
+        __syncthreads();
+        bin_count = sh.hist[kLevelBins - 1 - threadIdx.x];
+        if (!alone) {
+          unsigned int* gh = &hist[word + (kLevelBins - 1) - threadIdx.x];
+          if (bin_count) __hip_atomic_fetch_add(gh, bin_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          grid_sync(st, ++round, nb, a.spin_limit);
+          bin_count = ld_dev(gh);
         }
-        unsigned int pk[3];
         pick_bin(bin_count, v.need, sh, pk);
-        if (first) v = first_interval(pk);
-        else narrow(v, pk);
-        first = counted = crowded = false;
-        ++level;
-        continue;
+        narrow(v, pk);
+        word += kLevelBins;
+        crowded = false;
       }
       // ---- collect them
       unsigned int above, inside, inside_base;
@@ -759,9 +808,11 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
     }
   }
   __syncthreads();                                   // sh.off; sh.wave / sh.wave2 are free
-  write_survivors<KP>(key, rows, scores, wave_base, total, n_heads, t, gt_before, eq_before, kept_total, pr.budget, alone,
-                      bx == 0, sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
-                      pr.kept_scores ? pr.kept_scores + out_off : nullptr);
+  const lava_select_problem& out = a.p[opaque(prob)];   // read again here: fewer scalars live until now
+  const long long out_off = out.out_offset_dev ? (long long)*out.out_offset_dev : 0;
+  write_survivors<KP>(key, rows, scores, wave_base, total, n_heads, t, gt_before, eq_before, kept_total, out.budget, alone,
+                      bx == 0, sh, out.head_counts, out.head_offsets, out.kept_idx + out_off,
+                      out.kept_scores ? out.kept_scores + out_off : nullptr);
   if (alone) return;
 
   // A wait that gave up leaves results computed from incomplete counts.  The workgroup that
@@ -775,22 +826,23 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   }
   __syncthreads();
   if (sh.wave[0] != 0u) {
-    if (threadIdx.x < (unsigned)n_heads) pr.head_counts[threadIdx.x] = -1;
-    if (threadIdx.x <= (unsigned)n_heads) pr.head_offsets[threadIdx.x] = 0;
-    if (threadIdx.x == 0 && pr.error_dev != nullptr) *pr.error_dev = 1;
+    if (threadIdx.x < (unsigned)n_heads) out.head_counts[threadIdx.x] = -1;
+    if (threadIdx.x <= (unsigned)n_heads) out.head_offsets[threadIdx.x] = 0;
+    if (threadIdx.x == 0 && out.error_dev != nullptr) *out.error_dev = 1;
   }
 }
 
 // The same phases as separate launches (kernel boundaries take the place of the waits), for a problem
-// too large to keep its whole grid resident.  STEP 0: first histogram; 1..3: histograms of the interval's next
-// 11 bits (nothing to do once it is decided); 4: counts; 5: write.  Digits of 11 bits because every launch counts:
-// a bin of the first histogram (19 bits) is one key wide after two of them, an end bin (32 bits) after three, where
-// digits of 10 bits took a launch more (4 M plateaus 56.2 -> 53.8 us, 4 M near 2^-60 78.1 -> 68.5, 16 M 170 -> 137).
+// too large to keep its whole grid resident.  STEP 0: first histogram and that of its end bins; 1..3: histograms of the
+// interval's next 11 bits (nothing to do once it is decided); 4: counts; 5: write.  Digits of 11 bits because every launch
+// counts: a bin of the first histogram (19 bits) and one of the ends (22) are one key wide after two of them; a prepared
+// region has no histogram of the ends, and their 32 bits take the third.
 constexpr int kStepKeys = 32;
 constexpr int kStepBits = 11;
 constexpr int kStepBins = 1 << kStepBits;
-constexpr int kStepHist = kLevelBins;                 // word of the first of them: behind the first histogram
-static_assert(kStepHist + 2 * kStepBins + (1 << (32 - 2 * kStepBits)) <= 3 * kSelBins, "histogram area");
+static_assert(next_hist_word(true) + 2 * kStepBins + (1 << (32 - 2 * kStepBits)) <= 3 * kSelBins &&
+              next_hist_word(false) + 2 * kStepBins <= 3 * kSelBins && kEndShift <= 2 * kStepBits && kSelDigit0Shift <= 2 * kStepBits,
+              "histogram area; two histograms behind one that was not prepared");
 static_assert(kStepBins == 2 * kSelThreads && kStepBins <= (int)kListCap, "two bins per thread, counted in the list's place");
 
 __device__ __forceinline__ unsigned int step_shift(const Interval& v) {
@@ -828,6 +880,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
   const lava_select_problem pr = a.p[0];
   const int bx = (int)blockIdx.x, nb = (int)gridDim.x;
   unsigned int* hist = reinterpret_cast<unsigned int*>(a.ws + a.off_hist);
+  unsigned int* step_hist = hist + next_hist_word(pr.primed != 0);
   unsigned int* blk = reinterpret_cast<unsigned int*>(a.ws + a.off_blk);
   const int64_t* __restrict__ seg_offsets = pr.seg_offsets;
   const int n_heads = a.n_heads;
@@ -845,21 +898,25 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
     unsigned int pk[3];
     pick_bin(hist[kLevelBins - 1 - threadIdx.x], (unsigned int)kept_total, sh, pk);
     v = first_interval(pk);
+    if (!pr.primed && v.bits == 32u && !decided(v))
+      narrow_end(v, pk[0] == 0u, sh, [&](int w) { return hist[kLevelBins + w]; });
     __syncthreads();
-    for (int l = 0; l < (STEP < 4 ? STEP - 1 : 3) && !decided(v); ++l) step_narrow(v, hist + kStepHist + l * kStepBins, sh);
+    for (int l = 0; l < (STEP < 4 ? STEP - 1 : 3) && !decided(v); ++l) step_narrow(v, step_hist + l * kStepBins, sh);
     if (STEP <= 3 && decided(v)) return;
   }
   unsigned int key[kStepKeys];
   load_keys<kStepKeys>(scores, wave_base, total, key);
   if constexpr (STEP == 0) {
-    sh.hist[threadIdx.x] = 0u;
+    sh.hist[threadIdx.x] = sh.list[threadIdx.x] = 0u;
     __syncthreads();
-    count_first<kStepKeys>(key, sh.hist);
+    count_first<kStepKeys>(key, sh.hist, sh.list);
     lds_done();
     __syncthreads();
     unsigned int c = sh.hist[threadIdx.x];
     if (threadIdx.x == 0) c -= missing<kStepKeys>(bx, total);
     if (c) __hip_atomic_fetch_add(&hist[threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned int of_end = sh.list[threadIdx.x];
+    if (of_end) __hip_atomic_fetch_add(&hist[kLevelBins + threadIdx.x], of_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if constexpr (STEP <= 3) {
     unsigned int* bins = sh.list;
     bins[threadIdx.x] = bins[threadIdx.x + kSelThreads] = 0u;
@@ -874,7 +931,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
     __syncthreads();
     for (int i = (int)threadIdx.x; i < step_bins(v); i += kSelThreads) {
       const unsigned int c = bins[i];
-      if (c) __hip_atomic_fetch_add(&hist[kStepHist + (STEP - 1) * kStepBins + i], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (c) __hip_atomic_fetch_add(&step_hist[(STEP - 1) * kStepBins + i], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   } else {
     const Threshold t = kept_total > 0 ? threshold_of(v) : Threshold{0xffffffffu, 0u};
@@ -1028,7 +1085,7 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
       if (!a.p[0].primed) hipLaunchKernelGGL(sel_step_kernel<0>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<1>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<2>, grid, block, 0, s, a);
-      hipLaunchKernelGGL(sel_step_kernel<3>, grid, block, 0, s, a);
+      if (a.p[0].primed) hipLaunchKernelGGL(sel_step_kernel<3>, grid, block, 0, s, a);   // its end bins are 32 bits wide
       hipLaunchKernelGGL(sel_step_kernel<4>, grid, block, 0, s, a);
       hipLaunchKernelGGL(sel_step_kernel<5>, grid, block, 0, s, a);
     }

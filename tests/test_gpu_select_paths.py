@@ -135,3 +135,27 @@ def test_select_step_launches(lava, kind):
     sc = torch.from_numpy(s).cuda()
     for budget in (n // 50, n // 2):
         check(lava.lava_select_topk(nh, sc, budget), s, nh, budget)
+
+
+# one workgroup, several, the step launches; values scaled so that all scores lie in the first histogram's range, or in
+# either of its end bins, of which a prepared region holds no further histogram
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -70, 2.0 ** 50])
+@pytest.mark.parametrize("n", [200, 20011, 400003])
+def test_prepared_equals_plain_in_every_bin(lava, n, scale):
+    print(f"prepared selection n={n} scale={scale}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(8, 16, 64, device="cuda", generator=g).bfloat16()
+    k, v = (torch.randn(8, n, 64, device="cuda", generator=g).bfloat16() for _ in range(2))
+    v = (v.float() * scale).bfloat16()
+    desc = lava.LayerDesc.make(8, 8, 64, 16, "bf16")
+    ws = torch.full((lava.lava_select_workspace_bytes(8 * n),), 0x5A, dtype=torch.uint8, device="cuda")
+    scores, _, _ = lava.lava_window_scores(desc, [n], q, k, v, select_workspace=ws)
+    for i, budget in enumerate((8 * 20, 8 * n // 3)):
+        if i > 0:
+            lava.lava_window_scores(desc, [n], q, k, v, scores=scores, select_workspace=ws)
+        a = lava.lava_select_topk(8, scores, budget, workspace=ws, primed=True)
+        b = lava.lava_select_topk(8, scores, budget)
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+        top = torch.sort(scores, descending=True, stable=True).indices[:budget].sort().values
+        assert torch.equal(b[2].long(), top % n)
