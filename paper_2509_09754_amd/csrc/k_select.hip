@@ -988,7 +988,8 @@ static int fused_capacity() {
 // few, because every row of keys costs 0.3 us in all, until the number of workgroups that exchange their
 // counts costs more.  In-kernel times, not prepared, in us (workgroups): 33 K entries: 2 keys 11.0 (17),
 // 4 keys 11.9 (9), 8 keys 13.3 (5); 48 K: 11.9 (24), 12.4 (12); 262 K: 17.7 (128), 16.0 (64), 15.8 (32),
-// 16 keys 18.8 (16); 1 M: 4 keys 24.5 (256), 8 keys 21.1 (128), 12 keys 21 (86), 16 keys 21.7 (64).
+// 16 keys 18.8 (16).  Calls, 1 M entries, budget n/100 and n/4: 8 keys 25.8 and 30.3 (128), 12 keys 25.5 and 31.8 (86);
+// 1.5 M: 8 keys 28.5 and 35.6 (184), 12 keys 27.4 and 35.6 (123), 16 keys 28.6 and 39.4 (92).
 static int fused_keys(const lava_select_problem* problems, int n, int cap) {
   for (int keys : {2, 4, 8}) {
     int64_t sum = 0, widest = 0;
@@ -997,7 +998,7 @@ static int fused_keys(const lava_select_problem* problems, int n, int cap) {
       sum += nb;
       if (nb > widest) widest = nb;
     }
-    if (sum <= cap && widest <= (keys == 2 ? 20 : 64)) return keys;
+    if (sum <= cap && widest <= (keys == 2 ? 20 : keys == 4 ? 64 : 128)) return keys;
   }
   return kMostKeys;
 }
