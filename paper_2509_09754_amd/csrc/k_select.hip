@@ -837,7 +837,6 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
 // interval's next 11 bits (nothing to do once it is decided); 4: counts; 5: write.  Digits of 11 bits because every launch
 // counts: a bin of the first histogram (19 bits) and one of the ends (22) are one key wide after two of them; a prepared
 // region has no histogram of the ends, and their 32 bits take the third.
-constexpr int kStepKeys = 32;
 constexpr int kStepBits = 11;
 constexpr int kStepBins = 1 << kStepBits;
 static_assert(next_hist_word(true) + 2 * kStepBins + (1 << (32 - 2 * kStepBits)) <= 3 * kSelBins &&
@@ -875,7 +874,7 @@ __device__ __forceinline__ void step_narrow(Interval& v, const unsigned int* __r
   __syncthreads();
 }
 
-template <int STEP>
+template <int STEP, int KP>
 __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch a) {
   const lava_select_problem pr = a.p[0];
   const int bx = (int)blockIdx.x, nb = (int)gridDim.x;
@@ -892,7 +891,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
   const long long out_off = pr.out_offset_dev ? (long long)*pr.out_offset_dev : 0;
   const float* __restrict__ scores = pr.scores + in_off;
   if (STEP < 5 && kept_total == 0) return;
-  const int wave_base = __builtin_amdgcn_readfirstlane((bx * kSelWaves + wave) * (64 * kStepKeys));
+  const int wave_base = __builtin_amdgcn_readfirstlane((bx * kSelWaves + wave) * (64 * KP));
   Interval v = {0u, 0u, 0u, 0u, 0u};
   if (STEP >= 1 && kept_total > 0) {
     unsigned int pk[3];
@@ -904,16 +903,16 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
     for (int l = 0; l < (STEP < 4 ? STEP - 1 : 3) && !decided(v); ++l) step_narrow(v, step_hist + l * kStepBins, sh);
     if (STEP <= 3 && decided(v)) return;
   }
-  unsigned int key[kStepKeys];
-  load_keys<kStepKeys>(scores, wave_base, total, key);
+  unsigned int key[KP];
+  load_keys<KP>(scores, wave_base, total, key);
   if constexpr (STEP == 0) {
     sh.hist[threadIdx.x] = sh.list[threadIdx.x] = 0u;
     __syncthreads();
-    count_first<kStepKeys>(key, sh.hist, sh.list);
+    count_first<KP>(key, sh.hist, sh.list);
     lds_done();
     __syncthreads();
     unsigned int c = sh.hist[threadIdx.x];
-    if (threadIdx.x == 0) c -= missing<kStepKeys>(bx, total);
+    if (threadIdx.x == 0) c -= missing<KP>(bx, total);
     if (c) __hip_atomic_fetch_add(&hist[threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int of_end = sh.list[threadIdx.x];
     if (of_end) __hip_atomic_fetch_add(&hist[kLevelBins + threadIdx.x], of_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -923,7 +922,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
     __syncthreads();
     const unsigned int shift = step_shift(v), base = lds_offset(bins);
 #pragma unroll
-    for (int j = 0; j < kStepKeys; ++j) {
+    for (int j = 0; j < KP; ++j) {
       const unsigned int rel = key[j] - v.lo;
       count_row(rel <= v.width, base + 4u * (rel >> shift));
     }
@@ -938,7 +937,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
     if constexpr (STEP == 4) {
       unsigned int gt = 0u, eq = 0u;
 #pragma unroll
-      for (int j = 0; j < kStepKeys; ++j) {
+      for (int j = 0; j < KP; ++j) {
         gt += (unsigned int)__popcll(__ballot(key[j] > t.T));
         eq += t.ties ? (unsigned int)__popcll(__ballot(key[j] == t.T)) : 0u;
       }
@@ -960,7 +959,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_step_kernel(const SelectBatch
       gt = wave_sums(sh.wave, 0).total;
       eq = wave_sums(sh.wave2, 0).total;
       __syncthreads();
-      write_survivors<kStepKeys>(key, 0xffffffffu, scores, wave_base, total, n_heads, t, gt, eq, kept_total, pr.budget, false, bx == 0,
+      write_survivors<KP>(key, 0xffffffffu, scores, wave_base, total, n_heads, t, gt, eq, kept_total, pr.budget, false, bx == 0,
                                  sh, pr.head_counts, pr.head_offsets, pr.kept_idx + out_off,
                                  pr.kept_scores ? pr.kept_scores + out_off : nullptr);
     }
@@ -1082,13 +1081,23 @@ int32_t launch_select_batch(int n_heads, int n_problems, const lava_select_probl
       with_keys(keys, [&](auto kp) { hipLaunchKernelGGL(sel_fused_kernel<decltype(kp)::value>, grid, block, 0, s, a); });
     } else {                                               // a single problem wider than the device allows
       ProfScope ps(KID_SEL_STEPS, s);
-      const dim3 grid((unsigned)workgroups_for(a.p[0].total_entries, kStepKeys));
-      if (!a.p[0].primed) hipLaunchKernelGGL(sel_step_kernel<0>, grid, block, 0, s, a);
-      hipLaunchKernelGGL(sel_step_kernel<1>, grid, block, 0, s, a);
-      hipLaunchKernelGGL(sel_step_kernel<2>, grid, block, 0, s, a);
-      if (a.p[0].primed) hipLaunchKernelGGL(sel_step_kernel<3>, grid, block, 0, s, a);   // its end bins are 32 bits wide
-      hipLaunchKernelGGL(sel_step_kernel<4>, grid, block, 0, s, a);
-      hipLaunchKernelGGL(sel_step_kernel<5>, grid, block, 0, s, a);
+      // Keys per lane: 32, which read a problem in few workgroups, where those still fill three quarters of the device's
+      // compute units, else 16 (budget n/100 and n/4, us: 4 M 49.5 and 56.7 with 32, 44.3 and 48.6 with 16; 8 M, prepared,
+      // 48.7 and 63.4, 49.5 and 66.0; 16 M within 2 % of each other 118 and 131, 132 and 144).
+      const int64_t total = a.p[0].total_entries;
+      const bool wide = workgroups_for(total, 32) * 4 >= 3 * (int64_t)sweep_device_wgs();
+      auto steps = [&](auto kp) {
+        constexpr int KP = decltype(kp)::value;
+        const dim3 grid((unsigned)workgroups_for(total, KP));
+        if (!a.p[0].primed) hipLaunchKernelGGL((sel_step_kernel<0, KP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((sel_step_kernel<1, KP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((sel_step_kernel<2, KP>), grid, block, 0, s, a);
+        if (a.p[0].primed) hipLaunchKernelGGL((sel_step_kernel<3, KP>), grid, block, 0, s, a);   // its end bins are 32 bits wide
+        hipLaunchKernelGGL((sel_step_kernel<4, KP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((sel_step_kernel<5, KP>), grid, block, 0, s, a);
+      };
+      if (wide) steps(std::integral_constant<int, 32>{});
+      else steps(std::integral_constant<int, 16>{});
     }
     const int32_t st = launch_status();
     if (st != LAVA_OK) return st;
