@@ -143,7 +143,7 @@ int32_t lava_window_scores(const lava_layer_desc* desc, int32_t batch, const int
 /*
  * lava_window_scores that also prepares the workspace of the selection which will rank the scores it
  * writes (Alg. 1 runs the two back to back): while the final scores are still in registers the score
- * kernels count the selection's first radix digit, so that the selection needs neither its clearing
+ * kernels count the selection's first histogram, so that the selection needs neither its clearing
  * launch nor its first pass over the scores nor the grid-wide wait behind that pass.  Results of both
  * calls are unchanged bit for bit.
  *

@@ -20,7 +20,7 @@ enum KernelId : int {
   KID_PREPASS,        // value-row norms and window softmax statistics in one launch
   KID_POOLSTAT,       // max-pool, value factor, +inf window entries, entropy statistic
   KID_SEL_INIT,       // selection: clear histograms and counters
-  KID_SEL_FUSED,      // selection: radix select + ordered write in one launch
+  KID_SEL_FUSED,      // selection: threshold + ordered write in one launch
   KID_SEL_STEPS,      // selection: the same phases as separate launches (very large inputs)
   KID_COMPACT,        // K/V row gather
   KID_BUDGETS,        // layer budgets on the device

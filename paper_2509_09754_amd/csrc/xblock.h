@@ -18,11 +18,16 @@
 //    with ld_dev* (or device-scope atomic adds on both sides, as for histograms).  A plain store to
 //    such a buffer may sit in the writer's L2 past the ticket; a plain load may hit a stale line.
 //    Published buffers in this library: the statistic partials (ent_part), the statistics partials
-//    of the persistent sweep and its unit / completion words, the selection's histograms, published
-//    counts, state words and head_counts of a prepared selection.
+//    of the persistent sweep and its unit / completion words; of the selection the histograms, the
+//    segments of keys, the exchange words (one per workgroup), the state words and, if prepared, head_counts.
+//  * The selection's segments and exchange words: every wavefront drains its stores to the workgroup's
+//    segment, a workgroup barrier follows, then one lane stores the word with the segment's length and
+//    the epoch; whoever has seen the epoch finds the keys.  Segment and word are written again in a
+//    later epoch only behind a grid-wide wait, at which every workgroup arrives after it has read all
+//    words of the epoch before (whose keys nobody reads: a segment was too small for them).
 //  * Counters and tickets must be zero before the launch that uses them: they are cleared by an
 //    EARLIER kernel of the same call on the same stream (the value-norm / statistics launch, the
-//    selection's init kernel) or by the same kernel before a grid-wide wait that every workgroup passes;
+//    selection's init kernel, a cascade step's plan kernel) or by the same kernel before a grid-wide wait that every workgroup passes;
 //    never by a memset node (a caller may capture the calls in a graph).
 //  * Stress test: tests/test_gpu_parity.py runs launches of over a thousand workgroups thirty times and
 //    requires the bits of the first run every time.

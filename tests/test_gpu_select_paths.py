@@ -128,7 +128,7 @@ def test_prepared_equals_plain(lava, n):
 
 @pytest.mark.parametrize("kind", ["narrow", "tiny", "huge", "signed", "equal"])
 def test_select_step_launches(lava, kind):
-    """Two digits behind a bin of the first histogram, three behind its end bins, none where all keys are equal."""
+    """Two digits behind a bin of the first histogram or of its end bins' one, none where all keys are equal."""
     n, nh = 3_400_000, 4
     print(f"select step launches {kind}", flush=True)
     s = flat(kind, n, 11)
