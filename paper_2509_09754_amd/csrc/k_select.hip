@@ -125,29 +125,32 @@ __device__ __forceinline__ int segment_start(const int64_t* __restrict__ seg_off
 // the scores and the flat order inside a wavefront is row by row, lane by lane: positions are bit counts
 // of ballots, nothing goes through LDS.  Entries beyond the end get key 0, which no entry has: the one score
 // whose image it is, the NaN with all bits set, gets 1, so that it is ranked like any other (NaN is no valid score,
-// but a slot counted and not written would be an index from nowhere for the gather behind the selection).
+// but a slot counted and not written would be an index from nowhere for the gather behind the selection).  One loop maps
+// the keys of complete and of partly filled wavefronts: a loop in either branch cost 4 us of a 16-sequence batch.
 template <int KP>
 __device__ __forceinline__ void load_keys(const float* __restrict__ scores, int wave_base, int total,
                                           unsigned int (&key)[KP]) {
   const int lane = (int)(threadIdx.x & 63);
-  auto ranked = [](unsigned int bits) -> unsigned int {
-    const unsigned int k = score_key(__uint_as_float(bits));
-    return k > 1u ? k : 1u;
-  };
-  if (span_complete(wave_base, 64 * KP, total)) {   // uniform; all loads in flight before the first use
+  const bool complete = span_complete(wave_base, 64 * KP, total);
+  if (complete) {                                   // uniform; all loads in flight before the first use
     const float* __restrict__ src = scores + wave_base + lane;
 #pragma unroll
     for (int j = 0; j < KP; ++j) key[j] = __float_as_uint(src[64 * j]);
-#pragma unroll
-    for (int j = 0; j < KP; ++j) key[j] = ranked(key[j]);
   } else {
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
       const int p = wave_base + lane + 64 * j;
       key[j] = p < total ? __float_as_uint(scores[p]) : 0u;
     }
+  }
 #pragma unroll
-    for (int j = 0; j < KP; ++j) key[j] = wave_base + lane + 64 * j < total ? ranked(key[j]) : 0u;
+  for (int j = 0; j < KP; ++j) {
+    const unsigned int k = score_key(__uint_as_float(key[j]));
+    key[j] = k > 1u ? k : 1u;
+  }
+  if (!complete) {
+#pragma unroll
+    for (int j = 0; j < KP; ++j) key[j] = wave_base + lane + 64 * j < total ? key[j] : 0u;
   }
 }
 static_assert(kMaxHeads <= 64, "one lane per head");
