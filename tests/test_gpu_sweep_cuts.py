@@ -87,3 +87,31 @@ def test_split_group(lava, n, kind):
     got = scores.cpu().numpy().reshape(64, n)[:, : n - 8].astype(np.float64)
     mask = want > 1e-30 * want.max()
     assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
+
+
+def test_split_group_fill_is_no_sweep(lava):
+    """The attention score's fill launch writes a float per token and head (2 MB here), the score kernel reads a row of 128:
+    cleared by one or two workgroups the fill took longer than the scores (58 us of events against 48), by many 6."""
+    import ctypes
+    print("split group: time of the fill", flush=True)
+    hq, hkv, n = 28, 4, 131072
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(h, m, 128, device="cuda", generator=g).bfloat16() for h, m in ((hq, 32), (hkv, n), (hkv, n)))
+    desc = lava.LayerDesc.make(hq, hkv, 128, 32, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION)
+    ws = torch.empty(lava.lava_window_scores_workspace_bytes(desc, 1, n), dtype=torch.uint8, device="cuda")
+    names = [lava.lib.lava_prof_kernel_name(i) for i in range(lava.lib.lava_prof_kernel_count())]
+    best = {b"vnorm": 1e9, b"scores": 1e9}
+    try:
+        for _ in range(8):
+            lava.lib.lava_prof_enable(1), lava.lib.lava_prof_reset()
+            lava.lava_window_scores(desc, [n], q, k, v, workspace=ws)
+            torch.cuda.synchronize()
+            for name in best:
+                ms, launches = ctypes.c_double(), ctypes.c_int64()
+                lava.lib.lava_prof_read(names.index(name), ctypes.byref(ms), ctypes.byref(launches))
+                assert launches.value == 1
+                best[name] = min(best[name], ms.value)
+    finally:
+        lava.lib.lava_prof_enable(0), lava.lib.lava_prof_reset()
+    print(best, flush=True)
+    assert best[b"vnorm"] < 0.5 * best[b"scores"]
