@@ -72,8 +72,10 @@ constexpr int kTileKeys = 32;        // keys per MFMA tile
 constexpr int kMaxChunkHeads = 4;    // query heads a wavefront keeps in registers
 
 struct SweepPlan {
-  int chunk_heads;     // GT: row blocks (32 window rows of one head) per chunk (<= kMaxChunkHeads; <= 2 for f32 with d_h 128)
-  int n_chunks;        // ceil(G * blocks per head / GT)
+  int chunk_heads;     // GT: row blocks (32 window rows of one head) per chunk (<= kMaxChunkHeads; <= 2 for f32)
+  int wg_chunks;       // chunks a workgroup handles, each by its own wavefronts: 2 where the group has two, 4 for three or
+                       // four of f32, else 1
+  int n_chunks;        // workgroups a group is split over: chunks / wg_chunks
   int blocks_x;        // workgroups along the key axis per (KV head, chunk)
   int tiles_per_block; // key tiles per workgroup
   int vnorm_blocks;    // workgroups per KV head of the value-norm kernel
@@ -91,7 +93,7 @@ int sweep_blocks_per_head(const lava_layer_desc& d);   // 32-row blocks a head's
 
 // Workspace of lava_window_scores for one sequence (all offsets 256-byte aligned).
 struct ScoreWorkspace {
-  size_t off_stat_part;   // float2 [H_kv*n_chunks][blocks_x][GT*32]  (row max, row sum)
+  size_t off_stat_part;   // float2 [H_kv*n_chunks][blocks_x][wg_chunks*GT*32]  (row max, row sum)
   size_t off_vnorm_part;  // float  [H_kv][vnorm_blocks]
   size_t off_sraw;        // float  [H_kv][N']  group-max of window-mean attention
   size_t off_ent_part;    // double2[pool blocks]  partial (S, T)

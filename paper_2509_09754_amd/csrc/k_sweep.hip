@@ -81,6 +81,21 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Maximum over the wavefront's lanes, in every lane, of values that are not negative.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max_f32(float x) {
+  return fmaxf(x, __uint_as_float((unsigned int)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, ROWS, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max_f32(float x) {
+  x = dpp_max_f32<0x111, 0xf>(x);
+  x = dpp_max_f32<0x112, 0xf>(x);
+  x = dpp_max_f32<0x114, 0xf>(x);
+  x = dpp_max_f32<0x118, 0xf>(x);
+  x = dpp_max_f32<0x142, 0xa>(x);
+  x = dpp_max_f32<0x143, 0xc>(x);
+  return __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
+
 // Layer statistic from per-lane partial sums S = sum s, T = sum s ln s (fp64): fixed-order reduction
 // over lanes, wavefronts and, by the last workgroup to arrive, workgroups; then
 // e = (ln S - T / S) / n_entries  (Eq. 4-5 in closed form).  Contains workgroup barriers.  Returns true in
@@ -191,27 +206,89 @@ __device__ __forceinline__ void plan_budgets(const BudgetPlanArgs& plan, const P
     for (int i = lane; i < n; i += 64) out_b[i] = -1;
 }
 
+// One tile of keys (its fragments in kf) into a wavefront's running statistics: per head of the chunk this lane's
+// maximum of the raw dot products of its query row (lane % 32) and the sum of exp2((dot - max) * c2) over the keys it
+// has seen (the two lane halves see different keys of the same rows).
+template <int DT, int D, int GT>
+__device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], long long tile, long long n, int w, int bph,
+                                           float c2, const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
+                                           float (&m_run)[GT], float (&z_run)[GT]) {
+  const int r = lane & 31, half = lane >> 5;
+  const long long key0 = tile * kTileKeys;
+  // 32-bit inputs: all heads' products at once (the split of the keys is shared); bf16: head by head, so that
+  // the next head's matrix instructions run beside this head's exponentials
+  f32x16 all[DT == LAVA_F32 ? GT : 1];
+  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, true>(kf, qf, q_finite, all);
+  auto head_dots = [&](int t) -> f32x16 {
+    if constexpr (DT == LAVA_F32) return all[t];
+    else return dot_tile<D, true>(kf, qf[t]);
+  };
+  if (key0 + kTileKeys - 1 <= n - w) {
+    // every row sees every key of the tile: straight-line code
+    f32x16 acc = head_dots(0);
+#pragma unroll
+    for (int t = 0; t < GT; ++t) {
+      f32x16 nxt = acc;
+      if (t + 1 < GT) nxt = head_dots(t + 1);
+      float tmax = fmaxf(acc[0], acc[1]);
+#pragma unroll
+      for (int v = 2; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
+      const float mn = fmaxf(m_run[t], tmax);
+      const float mc = mn * c2;
+      float zs = 0.0f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) zs += fast_exp2(fmaf(acc[v], c2, -mc));
+      z_run[t] = z_run[t] * fast_exp2((m_run[t] - mn) * c2) + zs;   // exp2(-inf) = 0 on the first tile
+      m_run[t] = mn;
+      acc = nxt;
+    }
+  } else {
+    // tile touches the window or the end of the sequence: mask what a row may not see
+    const int rel0 = (int)(key0 - (n - w));                // position of the tile's first key relative to N - w
+#pragma unroll
+    for (int t = 0; t < GT; ++t) {
+      // window row of this lane in block t (a chunk starts at an even block when heads have two blocks);
+      // row rr sees relative positions <= min(rr, w - 1)
+      const int rr = r + ((bph == 2 && (t & 1)) ? 32 : 0);
+      const int row_limit = rr < w - 1 ? rr : w - 1;
+      f32x16 acc = head_dots(t);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (rel0 + 8 * (v / 4) + 4 * half + (v % 4) > row_limit) acc[v] = -INFINITY;
+      float tmax = acc[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
+      if (tmax > -INFINITY) {
+        const float mn = fmaxf(m_run[t], tmax);
+        const float mc = mn * c2;
+        float zs = 0.0f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zs += fast_exp2(fmaf(acc[v], c2, -mc));
+        const float f = (m_run[t] == mn) ? 1.0f : fast_exp2((m_run[t] - mn) * c2);
+        z_run[t] = z_run[t] * f + zs;
+        m_run[t] = mn;
+      }
+    }
+  }
+}
+
 // The statistics sweep of one wavefront: tiles first, first + WAVES, ... (cnt of them) of the head
-// at kg, whose first STAGES - 1 tiles have already been requested into `ring`.  Returns, per head of
-// the chunk, this lane's running maximum of the raw dot products of its query row (lane % 32) and
-// the sum of exp2((dot - max) * c2) over the keys this lane saw (the two lane halves see different
-// keys of the same rows).  The assignment of tiles to wavefronts is static: the sums depend on the
-// order, and results must not depend on timing.  Tile `it` sits in ring slot (it + slot0) % STAGES
-// (slot0 != 0 when another sweep of the same wavefront used the ring just before and requested these tiles).
+// at kg, whose first STAGES - 1 tiles have already been requested into `ring`.  The assignment of tiles to
+// wavefronts is static: the sums depend on the order, and results must not depend on timing.  Tile `it` sits in ring
+// slot (it + slot0) % STAGES (slot0 != 0 when another sweep of the same wavefront used the ring just before and
+// requested these tiles).
 template <int DT, int D, int GT, int WAVES, int STAGES>
 __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const FragReader<DT, D>& frags,
                                             const char* __restrict__ kg, long long n, int w, int bph, float c2,
                                             long long first, int cnt, u32x4* ring,
-                                            const u32x4 (&qf)[GT][Tile<DT, D>::kSteps], int lane,
+                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
                                             float (&m_run)[GT], float (&z_run)[GT], int slot0 = 0) {
   using T = Tile<DT, D>;
   static_assert((STAGES & (STAGES - 1)) == 0, "ring slots are taken modulo a power of two");
 #pragma unroll
   for (int t = 0; t < GT; ++t) { m_run[t] = -INFINITY; z_run[t] = 0.0f; }
-  const int r = lane & 31, half = lane >> 5;
   const unsigned int ring_addr = lds_addr(ring);
   for (int it = 0; it < cnt; ++it) {
-    const long long tile = first + (long long)it * WAVES;
     const int ahead = it + STAGES - 1;
     if (ahead < cnt)
       dma.issue(kg, first + (long long)ahead * WAVES, n, lane, ring + ((ahead + slot0) % STAGES) * T::kTileChunks);
@@ -219,63 +296,14 @@ __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const Fra
     wait_tile<DT, D>(younger);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + ((it + slot0) % STAGES) * T::kTileBytes, kf);
-
-    const long long key0 = tile * kTileKeys;
-    if (key0 + kTileKeys - 1 <= n - w) {
-      // every row sees every key of the tile: straight-line code, the next head's MFMAs are
-      // independent of this head's exponentials
-      f32x16 acc = dot_tile<DT, D, true>(kf, qf[0]);
-#pragma unroll
-      for (int t = 0; t < GT; ++t) {
-        f32x16 nxt = acc;
-        if (t + 1 < GT) nxt = dot_tile<DT, D, true>(kf, qf[t + 1]);
-        float tmax = fmaxf(acc[0], acc[1]);
-#pragma unroll
-        for (int v = 2; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
-        const float mn = fmaxf(m_run[t], tmax);
-        const float mc = mn * c2;
-        float zs = 0.0f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) zs += fast_exp2(fmaf(acc[v], c2, -mc));
-        z_run[t] = z_run[t] * fast_exp2((m_run[t] - mn) * c2) + zs;   // exp2(-inf) = 0 on the first tile
-        m_run[t] = mn;
-        acc = nxt;
-      }
-    } else {
-      // tile touches the window or the end of the sequence: mask what a row may not see
-      const int rel0 = (int)(key0 - (n - w));                // position of the tile's first key relative to N - w
-#pragma unroll
-      for (int t = 0; t < GT; ++t) {
-        // window row of this lane in block t (a chunk starts at an even block when heads have two blocks);
-        // row rr sees relative positions <= min(rr, w - 1)
-        const int rr = r + ((bph == 2 && (t & 1)) ? 32 : 0);
-        const int row_limit = rr < w - 1 ? rr : w - 1;
-        f32x16 acc = dot_tile<DT, D, true>(kf, qf[t]);
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (rel0 + 8 * (v / 4) + 4 * half + (v % 4) > row_limit) acc[v] = -INFINITY;
-        float tmax = acc[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
-        if (tmax > -INFINITY) {
-          const float mn = fmaxf(m_run[t], tmax);
-          const float mc = mn * c2;
-          float zs = 0.0f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) zs += fast_exp2(fmaf(acc[v], c2, -mc));
-          const float f = (m_run[t] == mn) ? 1.0f : fast_exp2((m_run[t] - mn) * c2);
-          z_run[t] = z_run[t] * f + zs;
-          m_run[t] = mn;
-        }
-      }
-    }
+    stats_tile<DT, D, GT>(kf, first + (long long)it * WAVES, n, w, bph, c2, qf, q_finite, lane, m_run, z_run);
   }
 }
 
-// Merge of the two lane halves (same row, different keys), then of the wavefronts in wavefront order.
-// Thread (head * 32 + row) of the workgroup returns true and the merged (max, sum) of its row.
-// Contains a workgroup barrier.
-template <int GT, int WAVES>
+// Merge of the two lane halves (same row, different keys), then of a chunk's wavefronts in wavefront order.
+// Thread (head * 32 + row) of the workgroup, heads counted through its NC chunks, returns true and the merged
+// (max, sum) of its row.  Contains a workgroup barrier.
+template <int GT, int WAVES, int NC>
 __device__ __forceinline__ bool stats_merge_waves(float (&m_run)[GT], float (&z_run)[GT], float c2, int lane, int wave,
                                                   float2 (*s_red)[kMaxChunkHeads * 32], float2& out) {
   const int r = lane & 31, half = lane >> 5;
@@ -287,13 +315,15 @@ __device__ __forceinline__ bool stats_merge_waves(float (&m_run)[GT], float (&z_
     if (half == 0) s_red[wave][t * 32 + r] = make_float2(m_run[t], z_run[t]);
   }
   __syncthreads();
-  if (threadIdx.x >= GT * 32) return false;
-  float m = -INFINITY, z = 0.0f;
+  constexpr int kPerChunk = WAVES / NC;                      // wavefronts of a chunk
+  static_assert(NC * GT <= WAVES * 2, "a thread per row");
+  if (threadIdx.x >= NC * GT * 32) return false;
+  const int first_wave = NC == 1 ? 0 : (int)(threadIdx.x / (GT * 32)) * kPerChunk, row = (int)(threadIdx.x % (GT * 32));
+  float2 p[kPerChunk];
 #pragma unroll
-  for (int wv = 0; wv < WAVES; ++wv) {
-    const float2 p = s_red[wv][threadIdx.x];
-    merge_stat(m, z, p.x, p.y, c2);
-  }
+  for (int wv = 0; wv < kPerChunk; ++wv) p[wv] = s_red[first_wave + wv][row];
+  float m = -INFINITY, z = 0.0f;
+  merge_stats<kPerChunk>(p, c2, m, z);
   out = make_float2(m, z);
   return true;
 }
@@ -370,25 +400,25 @@ static_assert(kMaxSeqPerLaunch <= 64, "one lane per sequence");
 // The value-norm sweep of one wavefront: tiles first, first + WAVES, ... (cnt of them) of the head at
 // vg, whose first STAGES - 1 tiles have already been requested into `ring`.  Returns this lane's maximum
 // over its rows (row lane % 32 of every tile) of sum_c |V[row, c]|; with token_norm the rows' own norms
-// also go to row_norm (indexed by position).  CHAIN: as the ring drains, the first STAGES - 1 tiles
-// of the same numbers at `next` (the head's keys) are requested into the slots that follow, so that the
-// statistics sweep continues without a gap: its tile `it` is in slot (cnt + it) % STAGES.
-template <int DT, int D, int WAVES, int STAGES, bool CHAIN>
+// also go to row_norm (indexed by position).  CHAIN > 0: as the ring drains, the first STAGES - 1 of the tiles
+// next_first, next_first + CHAIN, ... (next_cnt of them) at `next` (the head's keys) are requested into the slots
+// that follow, so that the statistics sweep continues without a gap: its tile `it` is in slot (cnt + it) % STAGES.
+template <int DT, int D, int WAVES, int STAGES, int CHAIN>
 __device__ __forceinline__ float vnorm_tiles(const TileDma<DT, D>& dma, const FragReader<DT, D>& frags,
                                              const char* __restrict__ vg, const char* __restrict__ next, long long n,
-                                             long long first, int cnt, u32x4* ring, int lane, bool token_norm,
-                                             float* __restrict__ row_norm) {
+                                             long long first, int cnt, long long next_first, int next_cnt, u32x4* ring,
+                                             int lane, bool token_norm, float* __restrict__ row_norm) {
   using T = Tile<DT, D>;
   static_assert((STAGES & (STAGES - 1)) == 0, "ring slots are taken modulo a power of two");
   const unsigned int ring_addr = lds_addr(ring);
-  const int total = CHAIN ? 2 * cnt : cnt;                   // tiles this wavefront requests through the ring
+  const int total = CHAIN > 0 ? cnt + next_cnt : cnt;        // tiles this wavefront requests through the ring
   float best = 0.0f;
   for (int it = 0; it < cnt; ++it) {
     const int ahead = it + STAGES - 1;
     if (ahead < cnt)
       dma.issue(vg, first + (long long)ahead * WAVES, n, lane, ring + (ahead % STAGES) * T::kTileChunks);
-    else if (CHAIN && ahead < total)
-      dma.issue(next, first + (long long)(ahead - cnt) * WAVES, n, lane, ring + (ahead % STAGES) * T::kTileChunks);
+    else if (CHAIN > 0 && ahead < total)
+      dma.issue(next, next_first + (long long)(ahead - cnt) * CHAIN, n, lane, ring + (ahead % STAGES) * T::kTileChunks);
     const int younger = total - 1 - it < STAGES - 1 ? total - 1 - it : STAGES - 1;
     wait_tile<DT, D>(younger);
     // each lane sums the half row it holds (row lane % 32; rows past n repeat row n - 1), the two
@@ -398,7 +428,7 @@ __device__ __forceinline__ float vnorm_tiles(const TileDma<DT, D>& dma, const Fr
     float s = 0.0f;
 #pragma unroll
     for (int j = 0; j < T::kSteps; ++j) s = abs_sum16<DT>(f[j], s);
-    s += __shfl_xor(s, 32);
+    s = add_halves(s);
     best = fmaxf(best, s);
     if (token_norm) {                                          // uniform: the rows' own norms, for the pooling step
       const long long row = (first + (long long)it * WAVES) * kTileKeys + (lane & 31);
@@ -419,7 +449,9 @@ __device__ __forceinline__ float vnorm_tiles(const TileDma<DT, D>& dma, const Fr
 // L1 norms (what vnorm_kernel does in a launch of its own, cut here like the statistics: vnorm_blocks ==
 // blocks_x), through the same ring, and runs on into the keys without draining it.  One launch instead of
 // two: one start-up and one tail for both streams.  Workgroup (0, 0) also clears what vnorm_kernel clears.
-template <int DT, int D, int GT, int W, bool VN>
+//
+// NC: chunks of the group a workgroup handles, each by its own kWaves / NC wavefronts (SweepPlan::wg_chunks).
+template <int DT, int D, int GT, int W, bool VN, int NC>
 __global__ void __launch_bounds__((Shape<DT, D, W>::kThreads), (Shape<DT, D, W>::kMinWaves))
 stats_kernel(const SweepArgs a) {
   using T = Tile<DT, D>;
@@ -438,9 +470,12 @@ stats_kernel(const SweepArgs a) {
   __shared__ float2 s_red[kWaves][kMaxChunkHeads * 32];   // [wave][head*32+row]
 
   const int lane = threadIdx.x & 63, wave = wave_index();
-  const int g = u.y / n_chunks, chunk = u.y % n_chunks;
-  const int h0 = g * G + chunk * GT;
-  const int nh = (G - chunk * GT) < GT ? (G - chunk * GT) : GT;
+  constexpr int kPerChunk = kWaves / NC;                       // wavefronts of a chunk
+  const int wave_chunk = wave / kPerChunk, wave_in_chunk = wave % kPerChunk;
+  const int g = u.y / n_chunks, chunk = NC == 1 ? u.y % n_chunks : wave_chunk;
+  const int head0 = NC > 2 && chunk * GT >= G ? G - 1 : chunk * GT;   // three chunks of four: the last one repeats a head, unused
+  const int h0 = g * G + head0;
+  const int nh = (G - head0) < GT ? (G - head0) : GT;
   const char* kg = reinterpret_cast<const char*>(k) + (long long)g * n * T::kRowBytes;
 
   TileDma<DT, D> dma;
@@ -453,17 +488,18 @@ stats_kernel(const SweepArgs a) {
   long long t_end = t_begin + tiles_per_block;
   if (t_end > n_tiles) t_end = n_tiles;
 
-  // this wavefront's tiles: t_begin + wave, + kWaves, ...; ring of kStages buffers, kStages-1 tiles ahead
-  const long long first = t_begin + wave;
-  const int cnt = first < t_end ? (int)((t_end - first + kWaves - 1) / kWaves) : 0;
+  // this wavefront's key tiles: t_begin + its index in the chunk, + kPerChunk, ...; ring of kStages buffers,
+  // kStages-1 tiles ahead.  Value tiles go round all wavefronts.
+  const long long first = t_begin + wave_in_chunk;
+  const int cnt = first < t_end ? (int)((t_end - first + kPerChunk - 1) / kPerChunk) : 0;
   u32x4* ring = s_tile[wave][0];
-  const bool with_v = VN && chunk == 0;                        // uniform
-  const char* first_stream = kg;
+  const bool with_v = VN && (NC > 1 || chunk == 0);            // uniform
+  const long long first_v = t_begin + wave;
+  const int cnt_v = with_v && first_v < t_end ? (int)((t_end - first_v + kWaves - 1) / kWaves) : 0;
+  const char* vg = nullptr;
   if constexpr (VN) {
-    if (with_v) {
-      const u32x4* __restrict__ v = static_cast<const u32x4*>(a.v) + (long long)a.H_kv * sq.tok * T::kCpr;
-      first_stream = reinterpret_cast<const char*>(v) + (long long)g * n * T::kRowBytes;
-    }
+    const u32x4* __restrict__ v = static_cast<const u32x4*>(a.v) + (long long)a.H_kv * sq.tok * T::kCpr;
+    vg = reinterpret_cast<const char*>(v) + (long long)g * n * T::kRowBytes;
     if (u.x == 0 && u.y == 0) {
       uint32_t* __restrict__ counters = reinterpret_cast<uint32_t*>(a.ws + sq.ws_off + a.off_counter);
       const int n_counter_words = kCtlUnitA + a.H_kv * sq.blocks_x;
@@ -471,19 +507,30 @@ stats_kernel(const SweepArgs a) {
       clear_selection_region(a, (int)u.z, Shape<DT, D, W>::kThreads);
     }
   }
-  // VN: the query rows, once per workgroup, into the last stage of the first GT wavefronts' rings, ahead of the
-  // first tiles
-  static_assert(!VN || kWaves >= GT, "one staging buffer per head");
+  // VN: the query rows, once per workgroup, ahead of the first tiles: a chunk's heads into the last stage of its
+  // wavefronts' rings, or, where it has fewer wavefronts than heads, into all stages (the first tiles then wait
+  // until the rows are read).
+  constexpr int kQSlots = GT <= kPerChunk ? 1 : GT / kPerChunk;    // heads a wavefront stages
+  static_assert(kQSlots <= kStages, "one staging buffer per head");
+  constexpr bool kQFirst = kQSlots > 1;
+  auto q_buffer = [&](int t) { return s_tile[wave_chunk * kPerChunk + t / kQSlots][kStages - 1 - t % kQSlots]; };
   if constexpr (VN) {
-    if (wave < GT) request_q<DT, D>(dma, q_win, h0, nh, wave, w, a.bph, lane, ring + (kStages - 1) * T::kTileChunks);
-  }
-  // with the value rows first, the ring holds both streams in turn: the wavefront's cnt value tiles, then
-  // its cnt key tiles (a wavefront with few tiles already requests keys here)
 #pragma unroll
-  for (int p = 0; p < kStages - 1; ++p) {
-    if (p < cnt) dma.issue(first_stream, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
-    else if (with_v && p < 2 * cnt) dma.issue(kg, first + (long long)(p - cnt) * kWaves, n, lane, ring + p * T::kTileChunks);
+    for (int i = 0; i < kQSlots; ++i) {
+      const int t = wave_in_chunk * kQSlots + i;
+      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, w, a.bph, lane, q_buffer(t));
+    }
   }
+  // with the value rows first, the ring holds both streams in turn: the wavefront's cnt_v value tiles, then
+  // its cnt key tiles (a wavefront with few tiles already requests keys here)
+  auto first_tiles = [&]() {
+#pragma unroll
+    for (int p = 0; p < kStages - 1; ++p) {
+      if (p < cnt_v) dma.issue(vg, first_v + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
+      else if (p < cnt_v + cnt) dma.issue(kg, first + (long long)(p - cnt_v) * kPerChunk, n, lane, ring + p * T::kTileChunks);
+    }
+  };
+  if constexpr (!(VN && kQFirst)) first_tiles();
   // VN: the value rows, which need no query rows, come first, so the wavefronts have drifted apart again by the
   // time the keys begin.  Every wavefront fetching its own copy of the query rows (eight times the traffic on lines
   // all workgroups want at once, and a wait for the first tiles as well) began the sweep 7.3 us after the
@@ -493,41 +540,49 @@ stats_kernel(const SweepArgs a) {
   // overlap.  (Staging was measured slower there: the wavefronts leave the barrier in step and the sweep loses
   // more than the set-up gains.)  Both are in before the loop: otherwise the compiler, which cannot count
   // the ring's loads across iterations, waits for everything in flight before each tile's products.
-  u32x4 qf[GT][T::kSteps];
+  u32x4 qf[GT][kQVec<DT, D>];
+  bool q_finite = true;
   if constexpr (VN) {
     int young = 0;
+    if constexpr (!kQFirst) {
 #pragma unroll
-    for (int p = 0; p < kStages - 1; ++p) young += (p < cnt || (with_v && p < 2 * cnt)) ? 1 : 0;
-    if (wave < GT) wait_tile<DT, D>(young);
+      for (int p = 0; p < kStages - 1; ++p) young += p < cnt_v + cnt ? 1 : 0;
+    }
+    if (wave_in_chunk * kQSlots < GT) wait_tile<DT, D>(young);
     wave_barrier();
 #pragma unroll
-    for (int t = 0; t < GT; ++t) frags.read(lds_addr(&s_tile[t][kStages - 1][0]), qf[t]);
+    for (int t = 0; t < GT; ++t) {
+      u32x4 raw[T::kSteps];
+      frags.read(lds_addr(q_buffer(t)), raw);
+      q_finite &= make_q<DT, D>(raw, qf[t]);
+    }
     wave_barrier();
+    if constexpr (kQFirst) first_tiles();
   } else {
-    load_q<DT, D, GT>(q_win, h0, nh, w, a.bph, lane, qf);
+    q_finite = load_q<DT, D, GT>(q_win, h0, nh, w, a.bph, lane, qf);
     wait_vmcnt<0>();
   }
+  q_finite = __ballot(!q_finite) == 0ull;
   float v_best = 0.0f;
   int slot0 = 0;
   if constexpr (VN) {
     if (with_v) {
-      v_best = vnorm_tiles<DT, D, kWaves, kStages, true>(dma, frags, first_stream, kg, n, first, cnt, ring, lane,
-                                                         a.token_norm != 0,
-                                                         a.scores + (long long)a.H_kv * sq.tok + (long long)g * n);
-      slot0 = cnt % kStages;
+      v_best = vnorm_tiles<DT, D, kWaves, kStages, kPerChunk>(
+          dma, frags, vg, kg, n, first_v, cnt_v, first, cnt, ring, lane, a.token_norm != 0,
+          a.scores + (long long)a.H_kv * sq.tok + (long long)g * n);
+      slot0 = cnt_v % kStages;
     }
   }
   float m_run[GT], z_run[GT];
-  stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, lane, m_run, z_run,
-                                          slot0);
+  stats_tiles<DT, D, GT, kPerChunk, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+                                             z_run, slot0);
   if constexpr (VN) {
     __shared__ float s_vmax[kWaves];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v_best = fmaxf(v_best, __shfl_xor(v_best, off));
+    v_best = wave_max_f32(v_best);
     if (lane == 0) s_vmax[wave] = v_best;                      // read after the barrier of the merge below
     float2 mine;
-    const bool owner = stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, s_red, mine);
-    if (owner) stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (GT * 32) + threadIdx.x] = mine;
+    const bool owner = stats_merge_waves<GT, kWaves, NC>(m_run, z_run, c2, lane, wave, s_red, mine);
+    if (owner) stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (NC * GT * 32) + threadIdx.x] = mine;
     if (with_v && threadIdx.x == 0) {
       float m = s_vmax[0];
 #pragma unroll
@@ -538,8 +593,8 @@ stats_kernel(const SweepArgs a) {
     if (with_v) clear_raw_scores(a, sq, g, t_begin, t_end, Shape<DT, D, W>::kThreads);
   } else {
     float2 mine;
-    if (stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, s_red, mine))
-      stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (GT * 32) + threadIdx.x] = mine;
+    if (stats_merge_waves<GT, kWaves, NC>(m_run, z_run, c2, lane, wave, s_red, mine))
+      stat_part[((long long)(unsigned int)(u.y * sq.blocks_x + u.x)) * (NC * GT * 32) + threadIdx.x] = mine;
   }
 }
 
@@ -605,7 +660,7 @@ __device__ __forceinline__ void digit0_flush(unsigned int* bins, unsigned int ru
 // written by other workgroups of the SAME launch (device-scope stores), so they are read with device-scope
 // loads.  `part` points at partial 0 of the head's (chunk's) rows.  LDS is accessed by instruction here, so that
 // tiles requested before stay in flight; the caller synchronises afterwards.
-template <int GT, int WAVES>
+template <int GT, int WAVES>                                  // GT: heads of all chunks of the workgroup
 struct Merge {
   static constexpr int kRows = GT * 32;
   static constexpr bool kSplit = WAVES >= 2 * GT;             // wavefronts GT .. merge, the others fetch query rows
@@ -633,8 +688,7 @@ __device__ __forceinline__ void merge_partials(int merger, const float2* __restr
       else
         x[u] = make_float2(-INFINITY, 0.0f);
     }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) merge_stat(m, z, x[u].x, x[u].y, c2);
+    merge_stats<16>(x, c2, m, z);
   }
   lds_write64(lds_addr(s_merge) + (unsigned int)(slice * kRows + row) * 8u, make_float2(m, z));
 }
@@ -666,21 +720,74 @@ __device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict_
   lds_write32(lds_addr(s_bias) + (unsigned int)merger * 4u, bias);
 }
 
+// Raw score of this lane's key (lane % 32 of the tile whose fragments are in kf): maximum over the chunk's heads of the
+// window mean of the attention.  bias_addr: LDS address of the chunk's biases, + 16 for the upper lane half (rows held by
+// a lane in result register v: 8 * (v / 4) + 4 * half + v % 4 -> four float4 per head).
+template <int DT, int D, int GT>
+__device__ __forceinline__ float score_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], float c2, unsigned int bias_addr,
+                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int bph) {
+  float best = 0.0f, pair = 0.0f;
+  f32x16 all[DT == LAVA_F32 ? GT : 1];
+  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, false>(kf, qf, q_finite, all);
+  auto head_dots = [&](int t) -> f32x16 {
+    if constexpr (DT == LAVA_F32) return all[t];
+    else return dot_tile<D, false>(kf, qf[t]);
+  };
+  f32x16 acc = head_dots(0);
+#pragma unroll
+  for (int t = 0; t < GT; ++t) {
+    f32x16 nxt = acc;
+    if (t + 1 < GT) nxt = head_dots(t + 1);
+    float ps = 0.0f;
+    u32x4 bb[4];                       // biases of rows 8*jj + 4*half + 0..3 of head t
+    lds_read128x4_strided<32>(bias_addr + t * 128, bb[0], bb[1], bb[2], bb[3]);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      ps += fast_exp2(fmaf(acc[4 * jj + 0], c2, -__uint_as_float(bb[jj].x)));
+      ps += fast_exp2(fmaf(acc[4 * jj + 1], c2, -__uint_as_float(bb[jj].y)));
+      ps += fast_exp2(fmaf(acc[4 * jj + 2], c2, -__uint_as_float(bb[jj].z)));
+      ps += fast_exp2(fmaf(acc[4 * jj + 3], c2, -__uint_as_float(bb[jj].w)));
+    }
+    ps = add_halves(ps);
+    if (bph == 2) {                    // uniform: a head's window mean is the sum over its two row blocks
+      if (t & 1) best = fmaxf(best, pair + ps);
+      else pair = ps;
+    } else {
+      best = fmaxf(best, ps);
+    }
+    acc = nxt;
+  }
+  return best;
+}
+
+// This lane's raw score into a tile's place in the span of raw scores; JOIN: as a maximum.  The lane's slot is formed
+// from the lane counter instead of living in a register across the loop, which has none to spare.
+template <bool JOIN>
+__device__ __forceinline__ void span_put(unsigned int tile_at, float score) {
+  unsigned int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  if (l < 32u) {
+    if constexpr (JOIN) lds_max32(tile_at + l * 4u, score);
+    else lds_write32(tile_at + l * 4u, score);
+  }
+}
+
 // The score sweep of one wavefront over the jobs of its workgroup: the workgroup's own tiles
 // t_begin .. t_end - 1, then (FUSED) the pooling halo, i.e. the tile before and the tile after the
 // span.  fifo[] holds the jobs this wavefront has already requested into its ring (the first
 // STAGES - 1 are fixed); the rest are taken from the shared counter *next_job as wavefronts become
 // free, because the wavefronts of a workgroup do not run at the same speed.  Which wavefront
 // computes a tile does not change its result, so the scores stay deterministic.
-// FUSED: raw scores go to s_span (position p of the prefix at s_span[p - (t_begin - 1) * 32]);
+// FUSED: raw scores go to s_span (position p of the prefix at s_span[p - (t_begin - 1) * 32]; SHARED_SPAN: as a
+// maximum, joined with what the wavefronts of the group's other chunk find);
 // otherwise to raw_head[position] (atomic maximum when the group is split over workgroups).
-template <int DT, int D, int GT, int WAVES, int STAGES, bool FUSED>
+template <int DT, int D, int GT, int WAVES, int STAGES, bool FUSED, bool SHARED_SPAN>
 __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const FragReader<DT, D>& frags,
                                              const char* __restrict__ kg, long long n, long long n_prefix, float c2,
                                              long long t_begin, long long t_end, int n_own, bool halo_left,
                                              bool halo_right, int n_jobs, int (&fifo)[STAGES], u32x4* ring,
                                              unsigned int* next_job, const float* s_bias, float* s_span,
-                                             const u32x4 (&qf)[GT][Tile<DT, D>::kSteps], int lane,
+                                             const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
                                              float* __restrict__ raw_head, int n_chunks, int bph) {
   using T = Tile<DT, D>;
   auto job_tile = [&](int j) -> long long {
@@ -691,7 +798,6 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
   const int half = lane >> 5;
   const unsigned int ring_addr = lds_addr(ring);
   const unsigned int next_job_addr = lds_addr(next_job);
-  // rows held by this lane in result register v: 8 * (v / 4) + 4 * half + v % 4 -> four float4 per head
   const unsigned int bias_addr = lds_addr(s_bias) + half * 16;
   const unsigned int span_base = lds_addr(s_span);
 
@@ -733,38 +839,9 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
     if constexpr (!FUSED) store_result(pend_key, pend);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + (it % STAGES) * T::kTileBytes, kf);
-
-    float best = 0.0f, pair = 0.0f;
-    f32x16 acc = dot_tile<DT, D, false>(kf, qf[0]);
-#pragma unroll
-    for (int t = 0; t < GT; ++t) {
-      f32x16 nxt = acc;
-      if (t + 1 < GT) nxt = dot_tile<DT, D, false>(kf, qf[t + 1]);
-      float ps = 0.0f;
-      u32x4 bb[4];                       // biases of rows 8*jj + 4*half + 0..3 of head t
-      lds_read128x4_strided<32>(bias_addr + t * 128, bb[0], bb[1], bb[2], bb[3]);
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        ps += fast_exp2(fmaf(acc[4 * jj + 0], c2, -__uint_as_float(bb[jj].x)));
-        ps += fast_exp2(fmaf(acc[4 * jj + 1], c2, -__uint_as_float(bb[jj].y)));
-        ps += fast_exp2(fmaf(acc[4 * jj + 2], c2, -__uint_as_float(bb[jj].z)));
-        ps += fast_exp2(fmaf(acc[4 * jj + 3], c2, -__uint_as_float(bb[jj].w)));
-      }
-      ps += __shfl_xor(ps, 32);
-      if (bph == 2) {                    // uniform: a head's window mean is the sum over its two row blocks
-        if (t & 1) best = fmaxf(best, pair + ps);
-        else pair = ps;
-      } else {
-        best = fmaxf(best, ps);
-      }
-      acc = nxt;
-    }
+    const float best = score_tile<DT, D, GT>(kf, c2, bias_addr, qf, q_finite, bph);
     if constexpr (FUSED) {
-      // the lane's slot in the span is formed here from the lane counter instead of living in a register
-      // across the loop, which has none to spare
-      unsigned int l;
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-      if (l < 32u) lds_write32(span_base + (unsigned int)(tile - t_begin + 1) * (kTileKeys * 4) + l * 4u, best);
+      span_put<SHARED_SPAN>(span_base + (unsigned int)(tile - t_begin + 1) * (kTileKeys * 4), best);
     } else {
       pend = best;
       pend_key = (int)(tile * kTileKeys) + (lane & 31);
@@ -791,8 +868,7 @@ __device__ __forceinline__ void scores_finish(const PoolArgs& pa, float vb, int 
   if (count_digits && wave == 0)
     for (int i = threadIdx.x; i < kSelDigit0Bins; i += 64) bins[i] = 0u;
   unsigned int run_digit = 0u, run_len = 0u;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) vb = fmaxf(vb, __shfl_xor(vb, off));
+  vb = wave_max_f32(vb);
   if ((threadIdx.x & 63) == 0) s_vb[wave] = vb;
   lds_reads_done();                      // this wavefront's span entries are written
   __syncthreads();                       // s_span complete, s_vb visible
@@ -892,7 +968,7 @@ __device__ __forceinline__ void scores_finish(const PoolArgs& pa, float vb, int 
   }
 }
 
-template <int DT, int D, int GT, bool FUSED, int W>
+template <int DT, int D, int GT, bool FUSED, int W, int NC>
 __global__ void __launch_bounds__((Shape<DT, D, W>::kThreads), (Shape<DT, D, W>::kMinWaves))
 scores_kernel(const SweepArgs a) {
   using T = Tile<DT, D>;
@@ -926,13 +1002,18 @@ scores_kernel(const SweepArgs a) {
   constexpr int kWaves = Shape<DT, D, W>::kWaves;
   constexpr int kStages = Shape<DT, D, W>::kStages;
   __shared__ u32x4 s_tile[kWaves][kStages][T::kTileChunks];
-  __shared__ __attribute__((aligned(16))) float s_bias[GT * 32];
+  __shared__ __attribute__((aligned(16))) float s_bias[NC * GT * 32];
   __shared__ __attribute__((aligned(16))) float s_span[FUSED ? (Shape<DT, D, W>::kFusedTiles + 2) * kTileKeys : 4];   // raw scores of the span + halo tiles
 
   const int lane = threadIdx.x & 63, wave = wave_index();
-  const int g = u.y / n_chunks, chunk = u.y % n_chunks;
-  const int h0 = g * G + chunk * GT;
-  const int nh = (G - chunk * GT) < GT ? (G - chunk * GT) : GT;
+  static_assert(NC == 1 || FUSED, "several chunks in a workgroup finish the scores there");
+  constexpr int kPerChunk = kWaves / NC;                       // wavefronts of a chunk
+  const int wave_chunk = wave / kPerChunk, wave_in_chunk = wave % kPerChunk;
+  const int g = u.y / n_chunks, chunk = NC == 1 ? u.y % n_chunks : wave_chunk;
+  const int head0 = NC > 2 && chunk * GT >= G ? G - 1 : chunk * GT;   // three chunks of four: the last one repeats a head, unused
+  const int h0 = g * G + head0;
+  const int nh = (G - head0) < GT ? (G - head0) : GT;
+  const int wg_h0 = NC == 1 ? h0 : g * G, wg_nh = NC == 1 ? nh : G;   // heads of the workgroup
   const char* kg = reinterpret_cast<const char*>(k) + (long long)g * n * T::kRowBytes;
   const long long n_prefix = n - w;
 
@@ -943,11 +1024,11 @@ scores_kernel(const SweepArgs a) {
   }
 
   constexpr int kThreads = Shape<DT, D, W>::kThreads;
-  using M = Merge<GT, kWaves>;
+  using M = Merge<NC * GT, kWaves>;
   __shared__ float2 s_merge[M::kSlices * M::kRows];
 
-  __shared__ unsigned int s_next_job;
-  if (threadIdx.x == 0) s_next_job = kWaves * (kStages - 1);   // published by the barriers below
+  __shared__ unsigned int s_next_job[NC];
+  if (threadIdx.x < NC) s_next_job[threadIdx.x] = kPerChunk * (kStages - 1);   // published by the barriers below
   TileDma<DT, D> dma;
   dma.init(lane);
   FragReader<DT, D> frags;
@@ -960,7 +1041,8 @@ scores_kernel(const SweepArgs a) {
   // tile after the span.  The first kStages - 1 jobs of every wavefront are fixed; the rest are taken
   // from a shared counter as wavefronts become free, because the wavefronts of a workgroup do not
   // run at the same speed (two share each SIMD and the older one wins the arbitration).  Which
-  // wavefront computes a tile does not change its result, so the scores stay deterministic.
+  // wavefront computes a tile does not change its result, so the scores stay deterministic.  With two chunks
+  // the workgroup has each job twice, once for the wavefronts of either chunk.
   const int n_own = t_begin < t_end ? (int)(t_end - t_begin) : 0;
   const bool halo_left = FUSED && n_own > 0 && t_begin > 0;
   const bool halo_right = FUSED && n_own > 0 && t_end < n_tiles;
@@ -972,42 +1054,68 @@ scores_kernel(const SweepArgs a) {
   int fifo[kStages];                                            // jobs requested and not yet computed; -1: none
 #pragma unroll
   for (int p = 0; p < kStages; ++p) {
-    const int j = wave + p * kWaves;
+    const int j = wave_in_chunk + p * kPerChunk;
     fifo[p] = (p < kStages - 1 && j < n_jobs) ? j : -1;
   }
   u32x4* ring = s_tile[wave][0];
+  if constexpr (NC > 1)                                         // published by the barriers below
+    for (int i = threadIdx.x; i < (n_own + 2) * kTileKeys; i += kThreads) lds_write32(lds_addr(s_span) + i * 4u, 0.0f);
   // Set-up: the first wavefronts request the query rows into the last stage of their rings (idle until the loop
   // starts) while the others merge the normalisers of every (head, row), from the statistics partials or the
   // caller's log-sum-exp; then everybody requests first tiles.  Loads return in order and the compiler cannot
   // count the conditional ones, so what is waited for goes out ahead of the tiles: with the tiles first and
   // the query rows copied through registers the loop began 7.2 us after the workgroup, of which 4.5 were the
   // first tiles' way (131072 tokens), and the device idled until the second ones arrived.
-  static_assert(kWaves >= GT, "one staging buffer per head");
-  const int merger = M::kSplit ? (int)threadIdx.x - GT * 64 : (int)threadIdx.x;
-  if (lse != nullptr)
-    bias_of_lse<GT>(merger, lse, nh, h0, w, a.bph, s_bias);
-  else
-    merge_partials<GT, kWaves, false>(merger, stat_part + (long long)u.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
-  asm volatile("" ::: "memory");
-  if (wave < GT) request_q<DT, D>(dma, q_win, h0, nh, wave, w, a.bph, lane, ring + (kStages - 1) * T::kTileChunks);
-  int young = 0;
+  // (Where a chunk has fewer wavefronts than heads, the query rows take every stage and the first tiles wait.)
+  constexpr int kQSlots = GT <= kPerChunk ? 1 : GT / kPerChunk;    // heads a wavefront stages
+  static_assert(kQSlots <= kStages, "one staging buffer per head");
+  constexpr bool kQFirst = kQSlots > 1;
+  auto q_buffer = [&](int t) { return s_tile[wave_chunk * kPerChunk + t / kQSlots][kStages - 1 - t % kQSlots]; };
+  const auto request_rows = [&]() {
 #pragma unroll
-  for (int p = 0; p < kStages - 1; ++p)
-    if (fifo[p] >= 0) {
-      dma.issue(kg, job_tile(fifo[p]), n, lane, ring + p * T::kTileChunks);
-      ++young;
+    for (int i = 0; i < kQSlots; ++i) {
+      const int t = wave_in_chunk * kQSlots + i;
+      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, w, a.bph, lane, q_buffer(t));
     }
-  if (wave < GT) wait_tile<DT, D>(young);
-  wave_barrier();
-  if (lse == nullptr) write_bias<GT, kWaves>(s_merge, nh, h0, w, a.bph, c2, s_bias);
-  u32x4 qf[GT][T::kSteps];
+    asm volatile("" ::: "memory");
+  };
+  if constexpr (!M::kSplit) request_rows();                     // ahead of the partials, whose wait covers both
+  const int merger = M::kSplit ? (int)threadIdx.x - NC * GT * 64 : (int)threadIdx.x;
+  if (lse != nullptr)
+    bias_of_lse<NC * GT>(merger, lse, wg_nh, wg_h0, w, a.bph, s_bias);
+  else
+    merge_partials<NC * GT, kWaves, false>(merger, stat_part + (long long)u.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
+  asm volatile("" ::: "memory");
+  if constexpr (M::kSplit) request_rows();
+  int young = 0;
+  auto first_tiles = [&]() {
 #pragma unroll
-  for (int t = 0; t < GT; ++t) frags.read(lds_addr(&s_tile[t][kStages - 1][0]), qf[t]);
+    for (int p = 0; p < kStages - 1; ++p)
+      if (fifo[p] >= 0) {
+        dma.issue(kg, job_tile(fifo[p]), n, lane, ring + p * T::kTileChunks);
+        ++young;
+      }
+  };
+  if constexpr (!kQFirst) first_tiles();
+  if (wave_in_chunk * kQSlots < GT) wait_tile<DT, D>(young);
   wave_barrier();
+  if (lse == nullptr) write_bias<NC * GT, kWaves>(s_merge, wg_nh, wg_h0, w, a.bph, c2, s_bias);
+  u32x4 qf[GT][kQVec<DT, D>];
+  bool q_finite = true;
+#pragma unroll
+  for (int t = 0; t < GT; ++t) {
+    u32x4 raw[T::kSteps];
+    frags.read(lds_addr(q_buffer(t)), raw);
+    q_finite &= make_q<DT, D>(raw, qf[t]);
+  }
+  q_finite = __ballot(!q_finite) == 0ull;
+  wave_barrier();
+  if constexpr (kQFirst) first_tiles();
 
-  scores_tiles<DT, D, GT, kWaves, kStages, FUSED>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
-                                                  halo_right, n_jobs, fifo, ring, &s_next_job, s_bias, s_span,
-                                                  qf, lane, s_raw + (long long)g * n_prefix, n_chunks, a.bph);
+  scores_tiles<DT, D, GT, kPerChunk, kStages, FUSED, (NC > 1)>(
+      dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left, halo_right, n_jobs, fifo, ring,
+      &s_next_job[NC == 1 ? 0 : wave_chunk], s_bias + (NC == 1 ? 0 : wave_chunk * GT * 32), s_span, qf, q_finite, lane,
+      s_raw + (long long)g * n_prefix, n_chunks, a.bph);
   if constexpr (FUSED) {
     __shared__ float s_vb[kWaves];
     __shared__ double s_s[kWaves], s_t[kWaves];
@@ -1096,12 +1204,18 @@ sweep_kernel(const SweepArgs a) {
     }
   };
   // `younger`: key tiles this wavefront has requested since q_request
-  auto q_commit = [&](u32x4 (&qf)[GT][T::kSteps], int younger) {
+  auto q_commit = [&](u32x4 (&qf)[GT][kQVec<DT, D>], int younger) -> bool {
     if (wave < GT) wait_tile<DT, D>(younger);
     __syncthreads();
+    bool finite = true;
 #pragma unroll
-    for (int t = 0; t < GT; ++t) frags.read(lds_addr(&sm.tile[t][kStages - 1][0]), qf[t]);
+    for (int t = 0; t < GT; ++t) {
+      u32x4 raw[T::kSteps];
+      frags.read(lds_addr(&sm.tile[t][kStages - 1][0]), raw);
+      finite &= make_q<DT, D>(raw, qf[t]);
+    }
     __syncthreads();
+    return __ballot(!finite) == 0ull;
   };
   auto seq_of_unit = [&](int u) {
     int si = 0;
@@ -1150,14 +1264,16 @@ sweep_kernel(const SweepArgs a) {
 #pragma unroll
       for (int p = 0; p < kStages - 1; ++p)
         if (p < cnt) dma.issue(kg, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
-      u32x4 qf[GT][T::kSteps];
-      load_q<DT, D, GT>(static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + si) * a.H * w * T::kCpr, g * G,
-                        G < GT ? G : GT, w, a.bph, lane, qf);
+      u32x4 qf[GT][kQVec<DT, D>];
+      bool q_finite = load_q<DT, D, GT>(static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + si) * a.H * w * T::kCpr, g * G,
+                                        G < GT ? G : GT, w, a.bph, lane, qf);
       wait_vmcnt<0>();
+      q_finite = __ballot(!q_finite) == 0ull;
       float m_run[GT], z_run[GT];
-      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, lane, m_run, z_run);
+      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+                                              z_run);
       float2 mine;
-      if (stats_merge_waves<GT, kWaves>(m_run, z_run, c2, lane, wave, sm.red, mine))
+      if (stats_merge_waves<GT, kWaves, 1>(m_run, z_run, c2, lane, wave, sm.red, mine))
         st_dev_f2(&stat_part[((long long)g * sq.blocks_x + bx) * kRows + threadIdx.x], mine.x, mine.y);
       // published: the partials are device-visible before the head's completion count moves.  The unit's
       // word goes to "done" (2); should a helper and the owner both have run the unit (their partials are
@@ -1216,8 +1332,8 @@ sweep_kernel(const SweepArgs a) {
         dma.issue(kg, job_tile(fifo[p]), n, lane, ring + p * T::kTileChunks);
         ++primed;
       }
-    u32x4 qf[GT][T::kSteps];
-    q_commit(qf, primed);
+    u32x4 qf[GT][kQVec<DT, D>];
+    const bool q_finite = q_commit(qf, primed);
 
     // The head's statistics.  A wait that lasts looks for statistics units of this head nobody has
     // claimed (their owners are not resident yet); one is then run above and this unit set up again.
@@ -1275,9 +1391,9 @@ sweep_kernel(const SweepArgs a) {
     write_bias<GT, kWaves>(sm.sc.merge, G < GT ? G : GT, g * G, w, a.bph, c2, sm.bias);
     lds_reads_done();
     __syncthreads();
-    scores_tiles<DT, D, GT, kWaves, kStages, true>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
+    scores_tiles<DT, D, GT, kWaves, kStages, true, false>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
                                                    halo_right, n_jobs, fifo, ring, &sm.next_job, sm.bias, sm.sc.span,
-                                                   qf, lane, nullptr, 1, 1);
+                                                   qf, q_finite, lane, nullptr, 1, 1);
     scores_finish<kThreads>(pa, vb, g, n, n_prefix, w, t_begin, t_end, n_tiles, sm.sc.span, sm.vb, sm.ss, sm.st,
                             &sm.last, (unsigned int)(sq.blocks_x * H_kv), (unsigned int)(g * sq.blocks_x + bx), H_kv,
                             bx == 0, wave, reinterpret_cast<unsigned int*>(&sm.tile[0][0][0]));
@@ -1340,7 +1456,7 @@ vnorm_kernel(const SweepArgs a) {
 #pragma unroll
   for (int p = 0; p < kStages - 1; ++p)
     if (p < cnt) dma.issue(vg, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
-  const float best = vnorm_tiles<DT, D, kWaves, kStages, false>(dma, frags, vg, nullptr, n, first, cnt, ring, lane,
+  const float best = vnorm_tiles<DT, D, kWaves, kStages, 0>(dma, frags, vg, nullptr, n, first, cnt, 0, 0, ring, lane,
                                                                  a.token_norm != 0, row_norm + (long long)g * n);
   clear_raw_scores(a, sq, g, t_begin, t_end, VShape<DT, D>::kThreads);
   float wave_best = best;
@@ -1456,10 +1572,17 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   SweepPlan p;
   const int G = (d.n_q_heads / d.n_kv_heads) * sweep_blocks_per_head(d);   // row blocks of 32 window rows per group
   int gt = kMaxChunkHeads;
-  if (d.dtype == LAVA_F32 && d.head_dim == 128) gt = 2;
+  if (d.dtype == LAVA_F32) gt = 2;     // query rows as three bf16 parts
   p.chunk_heads = G < gt ? G : gt;     // even whenever heads have two blocks: a head's blocks stay in one chunk
   if (p.chunk_heads == 3) p.chunk_heads = 4;   // kernels are built for 1, 2 and 4 heads per chunk
-  p.n_chunks = (G + p.chunk_heads - 1) / p.chunk_heads;
+  const int chunks = (G + p.chunk_heads - 1) / p.chunk_heads;
+  // A group of two chunks (f32: up to four) is swept by one workgroup, each chunk by a share of its wavefronts: the
+  // scores meet in its LDS and it finishes them.  Split over workgroups they meet in memory, where they have to be
+  // cleared first, and a pooling launch finishes them (28 heads on 4, 21013 tokens: 51.0 us a layer, in one workgroup
+  // 49.3; and the sequences of a batch then share their launches).  More chunks would leave a wavefront or
+  // less to each.
+  p.wg_chunks = chunks == 2 ? 2 : d.dtype != LAVA_F32 ? 1 : chunks > 2 && chunks <= 4 ? 4 : 1;
+  p.n_chunks = p.wg_chunks > 1 ? 1 : chunks;
   p.narrow = narrow && sweep_has_narrow_shape(d);
   const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
   // One resident workgroup per slot of the device (one per CU for the wide shape, two for the
@@ -1544,7 +1667,7 @@ ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n) {
   ScoreWorkspace w;
   size_t off = 0;
   w.off_stat_part = off;
-  off += align_up(sizeof(float2) * (size_t)d.n_kv_heads * p.n_chunks * p.blocks_x_bound * p.chunk_heads * 32);
+  off += align_up(sizeof(float2) * (size_t)d.n_kv_heads * p.n_chunks * p.wg_chunks * p.blocks_x_bound * p.chunk_heads * 32);
   w.off_vnorm_part = off;
   off += align_up(sizeof(float) * (size_t)d.n_kv_heads * p.vnorm_blocks_bound);
   w.off_sraw = off;          // only a group split into chunks goes through raw scores in memory
@@ -1607,21 +1730,26 @@ float sweep_exp2_scale(const lava_layer_desc& d) {
   return scale * kLog2e;
 }
 
-// Dispatch over (dtype, head_dim, heads per chunk).
+// Dispatch over (dtype, head_dim, heads per chunk, chunks per workgroup: several only of the largest).
 #define LAVA_SWEEP_DISPATCH(CALL)                                                   \
   do {                                                                              \
     const int gt = p.chunk_heads;                                                   \
     if (d.dtype == LAVA_BF16 && d.head_dim == 128) {                                \
-      if (gt == 4) CALL(LAVA_BF16, 128, 4); else if (gt == 2) CALL(LAVA_BF16, 128, 2); \
-      else CALL(LAVA_BF16, 128, 1);                                                 \
+      if (p.wg_chunks == 2) CALL(LAVA_BF16, 128, 4, 2);                             \
+      else if (gt == 4) CALL(LAVA_BF16, 128, 4, 1);                                 \
+      else if (gt == 2) CALL(LAVA_BF16, 128, 2, 1); else CALL(LAVA_BF16, 128, 1, 1); \
     } else if (d.dtype == LAVA_BF16 && d.head_dim == 64) {                          \
-      if (gt == 4) CALL(LAVA_BF16, 64, 4); else if (gt == 2) CALL(LAVA_BF16, 64, 2); \
-      else CALL(LAVA_BF16, 64, 1);                                                  \
+      if (p.wg_chunks == 2) CALL(LAVA_BF16, 64, 4, 2);                              \
+      else if (gt == 4) CALL(LAVA_BF16, 64, 4, 1);                                  \
+      else if (gt == 2) CALL(LAVA_BF16, 64, 2, 1); else CALL(LAVA_BF16, 64, 1, 1);  \
     } else if (d.dtype == LAVA_F32 && d.head_dim == 64) {                           \
-      if (gt == 4) CALL(LAVA_F32, 64, 4); else if (gt == 2) CALL(LAVA_F32, 64, 2);  \
-      else CALL(LAVA_F32, 64, 1);                                                   \
+      if (p.wg_chunks == 4) CALL(LAVA_F32, 64, 2, 4);                               \
+      else if (p.wg_chunks == 2) CALL(LAVA_F32, 64, 2, 2);                          \
+      else if (gt == 2) CALL(LAVA_F32, 64, 2, 1); else CALL(LAVA_F32, 64, 1, 1);    \
     } else if (d.dtype == LAVA_F32 && d.head_dim == 128) {                          \
-      if (gt == 2) CALL(LAVA_F32, 128, 2); else CALL(LAVA_F32, 128, 1);             \
+      if (p.wg_chunks == 4) CALL(LAVA_F32, 128, 2, 4);                              \
+      else if (p.wg_chunks == 2) CALL(LAVA_F32, 128, 2, 2);                         \
+      else if (gt == 2) CALL(LAVA_F32, 128, 2, 1); else CALL(LAVA_F32, 128, 1, 1);  \
     } else {                                                                        \
       return LAVA_ERR_SHAPE;                                                        \
     }                                                                               \
@@ -1631,17 +1759,17 @@ int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
                      bool with_vnorm, hipStream_t s) {
   const dim3 grid(a.n_units);
   ProfScope ps(with_vnorm ? KID_PREPASS : KID_STATS, s);
-#define LAVA_STATS_W(DTV, DV, GTV, WV)                                                                             \
+#define LAVA_STATS_W(DTV, DV, GTV, WV, NCV)                                                                        \
   do {                                                                                                             \
     if (with_vnorm)                                                                                                \
-      hipLaunchKernelGGL((stats_kernel<DTV, DV, GTV, WV, true>), grid, dim3(Shape<DTV, DV, WV>::kThreads), 0, s, a); \
+      hipLaunchKernelGGL((stats_kernel<DTV, DV, GTV, WV, true, NCV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), 0, s, a); \
     else                                                                                                           \
-      hipLaunchKernelGGL((stats_kernel<DTV, DV, GTV, WV, false>), grid, dim3(Shape<DTV, DV, WV>::kThreads), 0, s, a); \
+      hipLaunchKernelGGL((stats_kernel<DTV, DV, GTV, WV, false, NCV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), 0, s, a); \
   } while (0)
-#define LAVA_STATS(DTV, DV, GTV)                                               \
+#define LAVA_STATS(DTV, DV, GTV, NCV)                                          \
   do {                                                                         \
-    if (Shape<DTV, DV, 4>::kNarrow && p.narrow) LAVA_STATS_W(DTV, DV, GTV, (Shape<DTV, DV, 4>::kNarrow ? 4 : 8)); \
-    else LAVA_STATS_W(DTV, DV, GTV, 8);                                        \
+    if (Shape<DTV, DV, 4>::kNarrow && p.narrow) LAVA_STATS_W(DTV, DV, GTV, (Shape<DTV, DV, 4>::kNarrow ? 4 : 8), NCV); \
+    else LAVA_STATS_W(DTV, DV, GTV, 8, NCV);                                        \
   } while (0)
   LAVA_SWEEP_DISPATCH(LAVA_STATS);
 #undef LAVA_STATS
@@ -1650,14 +1778,14 @@ int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
 }
 
 int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s) {
-  if (!p.fused_pool || a.lse != nullptr || a.bph != 1) return LAVA_ERR_INVALID_ARG;
+  if (!p.fused_pool || p.wg_chunks != 1 || a.lse != nullptr || a.bph != 1) return LAVA_ERR_INVALID_ARG;
   // persistent workgroups: as many as the device keeps resident for this shape, at most one per unit
   const int slots = compute_units() * ((p.narrow && sweep_has_narrow_shape(d)) ? 2 : 1);
   const dim3 grid(a.n_units < slots ? a.n_units : slots);
   ProfScope ps(KID_SWEEP, s);
 #define LAVA_SWEEP_W(DTV, DV, GTV, WV) \
   hipLaunchKernelGGL((sweep_kernel<DTV, DV, GTV, WV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), 0, s, a)
-#define LAVA_SWEEP(DTV, DV, GTV)                                               \
+#define LAVA_SWEEP(DTV, DV, GTV, NCV)                                          \
   do {                                                                         \
     if (Shape<DTV, DV, 4>::kNarrow && p.narrow) LAVA_SWEEP_W(DTV, DV, GTV, (Shape<DTV, DV, 4>::kNarrow ? 4 : 8)); \
     else LAVA_SWEEP_W(DTV, DV, GTV, 8);                                        \
@@ -1671,19 +1799,19 @@ int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
 int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s) {
   const dim3 grid(a.n_units);
   ProfScope ps(KID_SCORES, s);
-#define LAVA_SCORES_W(DTV, DV, GTV, WV)                                                                     \
+#define LAVA_SCORES_W(DTV, DV, GTV, WV, NCV)                                                                \
   do {                                                                                                      \
     if (p.fused_pool)                                                                                       \
-      hipLaunchKernelGGL((scores_kernel<DTV, DV, GTV, true, WV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), \
+      hipLaunchKernelGGL((scores_kernel<DTV, DV, GTV, true, WV, NCV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), \
                          0, s, a);                                                                          \
     else                                                                                                    \
-      hipLaunchKernelGGL((scores_kernel<DTV, DV, GTV, false, WV>), grid, dim3(Shape<DTV, DV, WV>::kThreads), \
+      hipLaunchKernelGGL((scores_kernel<DTV, DV, GTV, false, WV, 1>), grid, dim3(Shape<DTV, DV, WV>::kThreads), \
                          0, s, a);                                                                          \
   } while (0)
-#define LAVA_SCORES(DTV, DV, GTV)                                               \
+#define LAVA_SCORES(DTV, DV, GTV, NCV)                                          \
   do {                                                                          \
-    if (Shape<DTV, DV, 4>::kNarrow && p.narrow) LAVA_SCORES_W(DTV, DV, GTV, (Shape<DTV, DV, 4>::kNarrow ? 4 : 8)); \
-    else LAVA_SCORES_W(DTV, DV, GTV, 8);                                        \
+    if (Shape<DTV, DV, 4>::kNarrow && p.narrow) LAVA_SCORES_W(DTV, DV, GTV, (Shape<DTV, DV, 4>::kNarrow ? 4 : 8), NCV); \
+    else LAVA_SCORES_W(DTV, DV, GTV, 8, NCV);                                        \
   } while (0)
   LAVA_SWEEP_DISPATCH(LAVA_SCORES);
 #undef LAVA_SCORES

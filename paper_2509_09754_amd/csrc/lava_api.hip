@@ -262,7 +262,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     // Statistics and scores: two launches, or (when the caller's tuning asks for it, all heads of a group
     // fit one workgroup and the statistics pass is needed) one persistent launch that runs both passes.
     // The persistent launch measured a few per cent slower on this device, so it is not the default.
-    const bool persistent = together && lse == nullptr && a.bph == 1 && tuning().sweep_schedule == 2;
+    const bool persistent = together && plan_max.wg_chunks == 1 && lse == nullptr && a.bph == 1 && tuning().sweep_schedule == 2;
     // Value norms: a launch of their own, or, where a statistics launch follows anyway, inside it (its
     // workgroups sweep the value rows of their span before the keys: one launch fewer).  Measured: a gain
     // for one sequence per launch (4 % of the whole path at 32K tokens, none at 128K), a loss of about 3 %

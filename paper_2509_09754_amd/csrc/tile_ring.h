@@ -28,13 +28,17 @@ template <int DT> struct Elem;
 template <> struct Elem<LAVA_BF16> { static constexpr int kBytes = 2; };
 template <> struct Elem<LAVA_F32> { static constexpr int kBytes = 4; };
 
-// acc += A(16 bytes of k) x B(16 bytes of k).  Both operands use the same lane -> k mapping, so
+// acc += A(8 values of k) x B(8 values of k).  Both operands use the same lane -> k mapping, so
 // any fixed assignment of a row's elements to (step, lane half) gives the full dot product.
+__device__ __forceinline__ f32x16 mfma_bf16(const u32x4& a, const u32x4& b, f32x16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+
+// the same over 16 bytes of either type, 32-bit values through the 32-bit instructions
 template <int DT>
 __device__ __forceinline__ f32x16 mfma_chunk(const u32x4& a, const u32x4& b, f32x16 acc) {
   if constexpr (DT == LAVA_BF16) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+    return mfma_bf16(a, b, acc);
   } else {
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
@@ -45,6 +49,12 @@ __device__ __forceinline__ f32x16 mfma_chunk(const u32x4& a, const u32x4& b, f32
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// x of this lane + x of lane ^ 32, without a trip through the LDS unit
+__device__ __forceinline__ float add_halves(float x) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
 
 #define LAVA_GLOBAL_AS __attribute__((address_space(1)))
 #define LAVA_LDS_AS __attribute__((address_space(3)))
@@ -65,6 +75,18 @@ __device__ __forceinline__ void merge_stat(float& m, float& z, float m2, float z
   const float f1 = (m == mn) ? 1.0f : fast_exp2((m - mn) * c2);
   const float f2 = (m2 == mn) ? 1.0f : fast_exp2((m2 - mn) * c2);
   z = z * f1 + z2 * f2;
+  m = mn;
+}
+
+// (m, z) (+) p[0] (+) ... (+) p[N - 1], the maximum first: N independent exponentials instead of a chain of them.
+template <int N>
+__device__ __forceinline__ void merge_stats(const float2 (&p)[N], float c2, float& m, float& z) {
+  float mn = m;
+#pragma unroll
+  for (int i = 0; i < N; ++i) mn = fmaxf(mn, p[i].x);
+  z *= m == mn ? 1.0f : fast_exp2((m - mn) * c2);
+#pragma unroll
+  for (int i = 0; i < N; ++i) z += p[i].y * (p[i].x == mn ? 1.0f : fast_exp2((p[i].x - mn) * c2));
   m = mn;
 }
 
@@ -270,6 +292,11 @@ __device__ __forceinline__ void lds_write32(unsigned int a, float x) {
   asm volatile("ds_write_b32 %0, %1" : : "v"(a), "v"(x) : "memory");
 }
 
+// *a = max(*a, x) for values that are not negative, which order as integers
+__device__ __forceinline__ void lds_max32(unsigned int a, float x) {
+  asm volatile("ds_max_u32 %0, %1" : : "v"(a), "v"(x) : "memory");
+}
+
 // Per-lane addresses of a tile's MFMA operand fragments: lane l holds row l % 32 and, at step j,
 // the row's 16-byte chunk 2j + l/32 (stored at slot chunk ^ (row & 7)).
 template <int DT, int D>
@@ -312,23 +339,93 @@ struct FragReader {
 // handled as `bph` (1 or 2) row blocks of 32: block index hb = head * bph + block, rows block * 32 ..
 // Everything up to the point where a head's window rows are summed treats a row block as a head.
 //
+// Query rows as a wavefront keeps them for a sweep: the 16-byte chunks of FragReader (bf16), or for every pair of
+// chunks their three bf16 parts (f32, see split8).
+template <int DT, int D> constexpr int kQVec = DT == LAVA_BF16 ? Tile<DT, D>::kSteps : Tile<DT, D>::kSteps / 2 * 3;
+
+// 32-bit values as sums of three bf16: x = hi + mid + lo, exactly (8 + 8 + 8 bits; hi is cut, so that it never
+// overflows, the others are rounded).  `a` and `b`: four values each.
+__device__ __forceinline__ unsigned int pack_bf16(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+__device__ __forceinline__ float bf16_low(unsigned int u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf16_high(unsigned int u) { return __uint_as_float(u & 0xffff0000u); }
+__device__ __forceinline__ void split8(const u32x4& a, const u32x4& b, u32x4& hi, u32x4& mid, u32x4& lo) {
+  const unsigned int x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const unsigned int x0 = x[2 * i], x1 = x[2 * i + 1];
+    hi[i] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+    const float r0 = __uint_as_float(x0) - bf16_high(x0), r1 = __uint_as_float(x1) - bf16_high(x1);
+    mid[i] = pack_bf16(r0, r1);
+    lo[i] = pack_bf16(r0 - bf16_low(mid[i]), r1 - bf16_high(mid[i]));
+  }
+}
+__device__ __forceinline__ float abs_max8(const u32x4& a, const u32x4& b, float m) {
+  const unsigned int x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) m = fmaxf(fmaxf(m, fabsf(__uint_as_float(x[i]))), fabsf(__uint_as_float(x[i + 1])));
+  return m;
+}
+
+// A head's query rows from their chunks.  Returns true if every value is finite (f32: the parts of the others would
+// not add up to them, so an infinite value or a NaN is its first part, the rest zero, and dot_tiles goes another way).
+template <int DT, int D>
+__device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], u32x4 (&q)[kQVec<DT, D>]) {
+  if constexpr (DT == LAVA_BF16) {
+#pragma unroll
+    for (int j = 0; j < Tile<DT, D>::kSteps; ++j) q[j] = raw[j];
+    return true;
+  } else {
+    float sum = 0.0f;                                            // an infinity or NaN leaves a NaN in its second part
+#pragma unroll
+    for (int j = 0; j < Tile<DT, D>::kSteps; j += 2) {
+      split8(raw[j], raw[j + 1], q[j / 2 * 3], q[j / 2 * 3 + 1], q[j / 2 * 3 + 2]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum += fabsf(bf16_low(q[j / 2 * 3 + 1][i])) + fabsf(bf16_high(q[j / 2 * 3 + 1][i]));
+    }
+    const bool finite = sum == sum;
+    if (__ballot(!finite) != 0ull) {                             // uniform, rare
+#pragma unroll
+      for (int j = 0; j < Tile<DT, D>::kSteps * 4; ++j) {
+        const unsigned int x = raw[j / 4][j % 4], shift = 16 * (j & 1);
+        if ((x & 0x7f800000u) == 0x7f800000u) {
+          u32x4* part = &q[j / 8 * 3];
+          const int at = j % 8 / 2;
+          if (x & 0x007fffffu) part[0][at] |= 0x0040u << shift;
+          part[1][at] &= ~(0xffffu << shift);
+          part[2][at] &= ~(0xffffu << shift);
+        }
+      }
+    }
+    return finite;
+  }
+}
+
 // Query fragments of the chunk's row blocks hb0 .. hb0 + nh - 1, one copy per wavefront straight from
-// global memory: row r = lane % 32 of the block (zero beyond the window or the chunk).
+// global memory: row r = lane % 32 of the block (zero beyond the window or the chunk).  Returns this lane's share of
+// "all finite".
 template <int DT, int D, int GT>
-__device__ __forceinline__ void load_q(const u32x4* __restrict__ qg, int hb0, int nh, int w, int bph, int lane,
-                                       u32x4 (&qf)[GT][Tile<DT, D>::kSteps]) {
+__device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, int nh, int w, int bph, int lane,
+                                       u32x4 (&qf)[GT][kQVec<DT, D>]) {
   using T = Tile<DT, D>;
   const int r = lane & 31, half = lane >> 5;
+  bool finite = true;
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
     const int head = (hb0 + t) / bph, row = ((hb0 + t) % bph) * 32 + r;
+    u32x4 raw[T::kSteps];
 #pragma unroll
     for (int j = 0; j < T::kSteps; ++j) {
       u32x4 x = u32x4{0u, 0u, 0u, 0u};
       if (t < nh && row < w) x = qg[((long long)head * w + row) * T::kCpr + 2 * j + half];
-      qf[t][j] = x;
+      raw[j] = x;
     }
+    finite &= make_q<DT, D>(raw, qf[t]);
   }
+  return finite;
 }
 
 // Row block hb of the chunk hb0 .. hb0 + nh - 1 as a tile in LDS, requested with direct-to-LDS loads by one
@@ -343,14 +440,74 @@ __device__ __forceinline__ void request_q(const TileDma<DT, D>& dma, const u32x4
 }
 
 // One head's 32 x 32 block of raw dot products: keys x rows (KEYS_AS_ROWS) or rows x keys.
-template <int DT, int D, bool KEYS_AS_ROWS>
-__device__ __forceinline__ f32x16 dot_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps],
-                                           const u32x4 (&qh)[Tile<DT, D>::kSteps]) {
+template <int D, bool KEYS_AS_ROWS>
+__device__ __forceinline__ f32x16 dot_tile(const u32x4 (&kf)[Tile<LAVA_BF16, D>::kSteps],
+                                           const u32x4 (&qh)[Tile<LAVA_BF16, D>::kSteps]) {
   f32x16 acc = {0};
 #pragma unroll
-  for (int j = 0; j < Tile<DT, D>::kSteps; ++j)
-    acc = KEYS_AS_ROWS ? mfma_chunk<DT>(kf[j], qh[j], acc) : mfma_chunk<DT>(qh[j], kf[j], acc);
+  for (int j = 0; j < Tile<LAVA_BF16, D>::kSteps; ++j)
+    acc = KEYS_AS_ROWS ? mfma_bf16(kf[j], qh[j], acc) : mfma_bf16(qh[j], kf[j], acc);
   return acc;
+}
+
+// The same for 32-bit inputs and all heads of a chunk at once.  The 32-bit matrix instruction has a sixteenth of the
+// bf16 rate, so values are taken as three bf16 parts and six of the nine products summed, the small ones first: what is
+// left out (mid*lo, lo*mid, lo*lo) is below 2^-24 of a product of the values.  Bound by the vector unit: a tile of 32
+// keys and 128 values takes 48 bf16 instructions of 32 cycles per head (32-bit: 64 of 64 cycles), the split 350
+// vector instructions of 5 cycles, shared by two heads (more do not fit the registers).  Layer of 9001 tokens, 32 heads
+// on 8: 86.9 -> 75.5 us, error of the scores against 64 bits 1.0e-6 -> 6.2e-7; 1024 tokens of 64 values, 8 heads on 2:
+// 35.0 -> 32.0 us, 5.1e-7 -> 3.1e-7.  Tiles or queries with infinities or NaN go through the 32-bit instructions,
+// query rows put together again.
+template <int D, int GT, bool KEYS_AS_ROWS>
+__device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::kSteps],
+                                          const u32x4 (&qf)[GT][kQVec<LAVA_F32, D>], bool q_finite, f32x16 (&acc)[GT]) {
+  constexpr int kPairs = Tile<LAVA_F32, D>::kSteps / 2;
+  float top = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kPairs; ++j) top = abs_max8(kf[2 * j], kf[2 * j + 1], top);
+#pragma unroll
+  for (int t = 0; t < GT; ++t) acc[t] = f32x16{0};
+  auto mul = [&](int t, const u32x4& k, const u32x4& q) {
+    acc[t] = KEYS_AS_ROWS ? mfma_bf16(k, q, acc[t]) : mfma_bf16(q, k, acc[t]);
+  };
+  if (q_finite && __ballot(!(top < INFINITY)) == 0ull) {
+    u32x4 hi[kPairs];
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+      u32x4 mid, lo;
+      split8(kf[2 * j], kf[2 * j + 1], hi[j], mid, lo);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, lo, qf[t][3 * j]);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j + 2]);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, mid, qf[t][3 * j + 1]);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, mid, qf[t][3 * j]);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j + 1]);
+    }
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j)
+#pragma unroll
+      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2 * kPairs; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < GT; ++t) {
+          const int at = (j & 1) * 2 + i / 2;
+          unsigned int part[3] = {qf[t][j / 2 * 3][at], qf[t][j / 2 * 3 + 1][at], qf[t][j / 2 * 3 + 2][at]};
+          asm volatile("" : "+v"(part[0]), "+v"(part[1]), "+v"(part[2]));   // or they are put together ahead of the sweep's loop
+          const float q = (i & 1) ? (bf16_high(part[0]) + bf16_high(part[1])) + bf16_high(part[2])
+                                  : (bf16_low(part[0]) + bf16_low(part[1])) + bf16_low(part[2]);
+          const float k = __uint_as_float(kf[j][i]);
+          acc[t] = KEYS_AS_ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(k, q, acc[t], 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_32x32x2f32(q, k, acc[t], 0, 0, 0);
+        }
+  }
 }
 
 // Index of the wavefront inside its workgroup as a scalar, so that everything derived from it

@@ -1,0 +1,86 @@
+"""Groups whose query heads are swept in parts by the wavefronts of one workgroup (bf16: 5 to 8 heads, f32: 3 to 8), and
+32-bit products formed from bf16 parts."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle import lava_oracle as O
+from paper_2509_09754_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lava():
+    from paper_2509_09754_amd import lava as L
+    yield L
+    L.set_tuning()
+
+
+def scores_of(lava, shapes, layers, sweep_shape="auto"):
+    s = shapes[0]
+    desc = lava.LayerDesc.make(s.n_q_heads, s.n_kv_heads, s.head_dim, s.window, s.dtype)
+    q, k, v = (torch.cat([lava.to_device(x[i], s.dtype).reshape(-1) for x in layers]) for i in range(3))
+    lava.set_tuning(sweep_shape=sweep_shape)
+    out = lava.lava_window_scores(desc, [x.n for x in shapes], q, k, v)
+    torch.cuda.synchronize()
+    lava.set_tuning()
+    return [x.cpu().numpy().astype(np.float64) for x in out]
+
+
+def check(shapes, refs, out, tol=1e-5):
+    """fp32 sums (over d_h products, then over the keys of a row) of values exact to 2^-24: a few 1e-6 of a score."""
+    at = 0
+    for b, (s, want) in enumerate(zip(shapes, refs)):
+        got = out[0][at: at + s.n_kv_heads * s.n].reshape(s.n_kv_heads, s.n)
+        at += s.n_kv_heads * s.n
+        mask = want > 1e-30 * want.max()
+        assert np.max(np.abs(got[:, : s.n_prefix][mask] - want[mask]) / want[mask]) < tol
+        assert np.all(got[:, : s.n_prefix][want == 0] == 0)
+        assert np.all(np.isposinf(got[:, s.n_prefix:]))
+        e = O.layer_entropy(want)
+        assert abs(out[2][b] - e) <= 1e-4 * abs(e) + 2e-5 / want.size
+
+
+def shape_of(dtype, d, G, w, n):
+    return dataclasses.replace(synth.config(1, n=n, budget=0, heavy_count=4), n_q_heads=2 * G, n_kv_heads=2, head_dim=d,
+                               window=w, dtype=dtype)
+
+
+# every number of heads per part and of parts, a part with heads missing, windows of two row blocks; one tile per
+# wavefront, several, ragged ends; and the shape of two workgroups per compute unit
+@pytest.mark.parametrize("sweep_shape", ["wide", "narrow"])
+@pytest.mark.parametrize("dtype,d,G,w", [("bf16", 128, 5, 32), ("bf16", 128, 8, 7), ("bf16", 64, 6, 16), ("bf16", 128, 3, 33),
+                                         ("bf16", 128, 9, 32), ("f32", 64, 1, 8), ("f32", 64, 2, 8), ("f32", 64, 4, 32),
+                                         ("f32", 64, 5, 8), ("f32", 64, 3, 40), ("f32", 128, 1, 32), ("f32", 128, 4, 32),
+                                         ("f32", 128, 6, 20), ("f32", 128, 3, 40), ("f32", 128, 9, 8)])
+def test_groups_in_parts(lava, dtype, d, G, w, sweep_shape):
+    lengths = [w + 1, 333, 2085] if sweep_shape == "wide" else [2085, 333]
+    print(f"groups in parts {dtype} d{d} G{G} w{w} {sweep_shape} {lengths}", flush=True)
+    shapes = [shape_of(dtype, d, G, w, n) for n in lengths]
+    inps = [synth.gen_layer(s, 3 + i) for i, s in enumerate(shapes)]
+    refs = [O.lava_scores(*i.f64(), s.window, s.pool_kernel)[0] for s, i in zip(shapes, inps)]
+    check(shapes, refs, scores_of(lava, shapes, [(i.q_win, i.k, i.v) for i in inps], sweep_shape))
+
+
+@pytest.mark.parametrize("d,G", [(64, 4), (128, 4), (128, 1)])
+def test_32_bit_products_of_any_values(lava, d, G):
+    """Values over many magnitudes, the largest there are (no part may overflow) and infinities (a key that minus
+    infinity takes out of every softmax, in a tile of its own way through the kernel)."""
+    print(f"32-bit products of any values d{d} G{G}", flush=True)
+    s = shape_of("f32", d, G, 32, 700)
+    i = synth.gen_layer(s, 5)
+    q, k, v = (np.array(x, dtype=np.float32) for x in (i.q_win, i.k, i.v))
+    rng = np.random.Generator(np.random.PCG64(3))
+    k *= np.exp2(rng.integers(-20, 2, size=k.shape)).astype(np.float32)
+    q[..., 0] = np.abs(q[..., 0]) + 0.1
+    q[..., 1] = 0.0
+    k[0, 40, 0] = -np.inf
+    k[1, 300, 0] = -np.inf
+    k[:, 77, 1] = np.finfo(np.float32).max
+    k[:, 78, 1] = -np.finfo(np.float32).max
+    want = O.lava_scores(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), s.window, s.pool_kernel)[0]
+    assert np.isfinite(want).all()
+    check([s], [want], scores_of(lava, [s], [(q, k, v)]))
