@@ -37,7 +37,7 @@ def measured_traffic(workload):
             read_mib, write_mib = float(cells[3]), float(cells[4])
         except ValueError:
             continue
-        for kid in ("vnorm", "stats", "scores", "sweep", "sel_fused", "compact", "decode_merge", "decode"):
+        for kid in ("vnorm", "stats", "scores", "sweep", "sel_fused", "compact", "decode"):
             if cells[0].startswith(kid + "_kernel"):
                 # the statistics kernel that also sweeps the value rows is the launch the library times as "prepass"
                 name = "prepass" if kid == "stats" and cells[0].rstrip(">").endswith("true") else kid
@@ -281,7 +281,7 @@ def decode_batched(lava, synth, torch, np, sh, desc, dev, B, args, iters):
     torch.cuda.synchronize()
     prof = lava.prof_read()
     lava.prof_enable(False)
-    k_us = {n: 1e3 * prof[n][0] / max(prof[n][1], 1) for n in ("decode", "decode_merge")}
+    k_us = {n: 1e3 * prof[n][0] / max(prof[n][1], 1) for n in ("decode",)}
     bytes_b = 2 * batch * B * row_bytes
     return {"batch": batch, "rows_per_seq": B, "us": round(1e6 * t_batch, 2), "pools": n_pools,
             "algorithmic_bytes": bytes_b, "kernel_us": {n: round(v, 2) for n, v in k_us.items()},

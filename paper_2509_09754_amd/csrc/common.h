@@ -24,8 +24,7 @@ enum KernelId : int {
   KID_SEL_STEPS,      // selection: the same phases as separate launches (very large inputs)
   KID_COMPACT,        // K/V row gather
   KID_BUDGETS,        // layer budgets on the device
-  KID_DECODE,         // decode attention over the packed cache: per-unit partials
-  KID_DECODE_MERGE,   // decode attention: merge of the units of each head
+  KID_DECODE,         // decode attention over the packed cache
   KID_COUNT
 };
 
@@ -218,7 +217,7 @@ struct DecodePlan {
   int rows_per_unit;     // rows of one head a workgroup handles
   int group_pad;         // G rounded up to 1, 2, 4 or 8
   int64_t units_bound;   // units a sequence can have at most (grid.x)
-  size_t off_ml, off_acc, bytes;
+  size_t off_ml, off_acc, off_flags, bytes;
 };
 DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t rows_capacity, int64_t tail_len);
 int32_t launch_decode(const lava_layer_desc& d, int32_t batch, const void* q, const void* k_hat,

@@ -2,8 +2,9 @@
 // Sec. 3): one query token per sequence, the G query heads of a KV group share the group's
 // retained rows, which sit packed and variable-length per head as the selection wrote them.
 //
-//   decode_kernel   one workgroup per "unit" = up to C consecutive rows of one head (packed rows
-//                   first, then the rows appended since the eviction).  Each wavefront streams
+//   decode_kernel   one workgroup per "unit" = up to C rows of one head, counted in tiles of 32 rows (the head's
+//                   packed rows first, then the rows appended since the eviction: with units of their own, one
+//                   appended row cost every head a unit).  Each wavefront streams
 //                   32-row tiles: K through its private LDS ring (two tiles ahead), V straight
 //                   into registers (one tile ahead; a lane owns the same columns of every row, so
 //                   a row is one coalesced load and needs no LDS).  The step is latency-bound
@@ -15,15 +16,29 @@
 //                     output   acc[head][dims of this lane] += p[key][head] * V[key][dims]: the
 //                              probabilities go through LDS as fp32 and are broadcast per key;
 //                              V is never rounded or transposed
-//                   then the wavefronts' partial (max, sum, acc) are merged and written out.
-//   decode_merge    one workgroup per (sequence, KV head): merges the units of the head in unit
-//                   order (deterministic) and normalises.
+//                   then the wavefronts' partial (max, sum, acc) are merged.  A head of one unit is
+//                   finished there; otherwise the partial goes to the workspace, and the workgroup that
+//                   finds all partials of the head published merges them in unit order (deterministic)
+//                   and normalises.
+//
+// A unit's partial is published by a 64-bit flag in the workspace, which the caller hands over with any contents: a flag
+// counts only if it equals the call's tag, a number no other call of the process uses (a random start, counted on), and
+// whoever merges a head clears its flags, so that the same launch replayed from a graph starts without them.
+// There is no counter to clear ahead and no second launch (one layer of 8192 rows: 11.9 us with a merge launch, of
+// which it took 5).  Every workgroup stores its flag, waits until the store is visible to the device and then reads the
+// flags of its head: whichever store became visible last, its workgroup finds them all.  Should several, each writes
+// the same bits.  Nobody waits for another workgroup.
 //
 // The step is bound by HBM: 2 * d_h * elem bytes per retained row against 4 * G * d_h flop.
 #include <math.h>
+#include <unistd.h>
+
+#include <atomic>
+#include <chrono>
 
 #include "common.h"
 #include "tile_ring.h"
+#include "xblock.h"
 
 namespace lava {
 
@@ -79,11 +94,15 @@ struct DecodeArgs {
   const char* v_tail;
   long long tail_len, tail_capacity;
   int H, H_kv, G;
-  int rows_per_unit;               // C, a multiple of 32 * kDecWaves
+  int tiles_per_unit;              // C / 32, a multiple of kDecWaves
   int units_bound;                 // grid.x: units a sequence can have at most
   float c2;                        // softmax scale * log2 e
   float2* part_ml;                 // [batch][units_bound][GP]  (max in log2 units, sum)
   float* part_acc;                 // [batch][units_bound][GP][D]
+  unsigned long long* flags;       // [batch][units_bound]  == tag: the unit's partial is published
+  unsigned long long tag;
+  float* out;                      // [batch][H][D]
+  float* lse;                      // [batch][H] or null
 };
 
 __device__ __forceinline__ long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
@@ -98,17 +117,16 @@ __device__ __forceinline__ long long lane_value64(long long x, int lane) {
 }
 
 // The units of one sequence, found by every wavefront on its own with one coalesced load of the
-// head offsets: lane g holds head g.  Units are numbered head by head, each head's packed chunks
-// first, then its tail chunks.  Offsets a kernel may follow start at >= 0, never decrease and end
+// head offsets: lane g holds head g.  Units are numbered head by head.  Offsets a kernel may follow start at >= 0, never decrease and end
 // within the stated capacity; anything else makes `usable` false and nothing is read.
-// A decode step over one layer is two launches of dependent trips to memory; the map is on both chains, so its sums
-// and look-ups are lane moves and scalar reads, not shuffles (batch 1, 8192 rows: 13.5 -> 13.0 us for the step).
+// A decode step over one layer is a chain of dependent trips to memory with the map at its head, so its sums
+// and look-ups are lane moves and scalar reads, not shuffles.
 struct UnitMap {
   bool usable;
   unsigned int total;        // units of the sequence
   unsigned int incl;         // lane g: units of heads 0..g
   unsigned int cnt;          // lane g: units of head g
-  unsigned int packed;       // lane g: packed units of head g
+  unsigned int packed;       // lane g: tiles of head g's packed rows
   long long off, len;        // lane g: first packed row and number of packed rows of head g
 };
 
@@ -118,7 +136,7 @@ __device__ __forceinline__ unsigned int dpp_add(unsigned int x) {
 }
 
 __device__ __forceinline__ UnitMap map_units(const long long* __restrict__ offs, int n_heads, long long capacity,
-                                             int rows_per_unit, long long tail_len, int lane) {
+                                             int tiles_per_unit, long long tail_len, int lane) {
   UnitMap m;
   const bool head = lane < n_heads;
   const long long o = head ? offs[lane] : 0;
@@ -127,10 +145,10 @@ __device__ __forceinline__ UnitMap map_units(const long long* __restrict__ offs,
   m.usable = __ballot(bad) == 0ull;
   m.off = o;
   m.len = head && m.usable ? o_next - o : 0;
-  const unsigned int tail_units = tail_len > 0 ? (unsigned int)ceil_div(tail_len, rows_per_unit) : 0u;
-  // a usable length fits 31 bits (capacity < 2^31)
-  m.packed = ((unsigned int)m.len + (unsigned int)rows_per_unit - 1u) / (unsigned int)rows_per_unit;
-  m.cnt = head && m.usable ? m.packed + tail_units : 0u;
+  const unsigned int tail_tiles = (unsigned int)ceil_div(tail_len, kTileKeys);
+  // usable lengths fit 31 bits (capacity and tail < 2^31)
+  m.packed = ((unsigned int)m.len + kTileKeys - 1u) / kTileKeys;
+  m.cnt = head && m.usable ? (m.packed + tail_tiles + (unsigned int)tiles_per_unit - 1u) / (unsigned int)tiles_per_unit : 0u;
   unsigned int incl = m.cnt;                                 // inclusive sum over the lanes
   incl = dpp_add<0x111, 0xf>(incl);
   incl = dpp_add<0x112, 0xf>(incl);
@@ -141,6 +159,95 @@ __device__ __forceinline__ UnitMap map_units(const long long* __restrict__ offs,
   m.incl = incl;
   m.total = lane_value(incl, 63);
   return m;
+}
+
+// Merge of a head's `mine` units, whose partials start at ml / pa, by a workgroup that has seen all their flags, in unit
+// order.  Units are taken kMergeChunk at a time: their (max, sum) pairs go through LDS, every thread then
+// knows the chunk's maximum per head without a second trip to memory, and the loads of the partial
+// outputs of a whole chunk are independent of each other, so the time does not grow with the
+// number of units the way a loop of dependent round trips does.  Across chunks the running result is
+// rescaled as in the online softmax.
+constexpr int kMergeChunk = 32;
+template <int D, int GP>
+__device__ __forceinline__ void merge_units(const DecodeArgs& a, int b, int g, int mine, const float2* ml, const float* pa,
+                                            float2 (*s_ml)[GP]) {
+  constexpr int kPairs = GP * D / 2;                        // outputs in pairs: (t, e) and (t, e + 1)
+  constexpr int kOut = (kPairs + kDecThreads - 1) / kDecThreads;
+  float M[kOut], L[kOut];
+  float2 sum[kOut];
+#pragma unroll
+  for (int j = 0; j < kOut; ++j) { M[j] = -INFINITY; L[j] = 0.0f; sum[j] = make_float2(0.0f, 0.0f); }
+  for (int c0 = 0; c0 < mine; c0 += kMergeChunk) {
+    const int nu = mine - c0 < kMergeChunk ? mine - c0 : kMergeChunk;
+    float2 pv[kOut][16];                                     // the first sixteen units', on their way beside the pairs
+    auto load_units = [&](int u0) {
+#pragma unroll
+      for (int j = 0; j < kOut; ++j) {
+        const int idx = 2 * ((int)threadIdx.x + kDecThreads * j);
+        const float2* col = reinterpret_cast<const float2*>(pa + (long long)c0 * GP * D + idx);
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          pv[j][u] = idx < GP * D && u0 + u < nu ? ld_dev_f2(&col[(long long)(u0 + u) * (GP * D / 2)]) : make_float2(0.0f, 0.0f);
+      }
+    };
+    load_units(0);
+    for (int i = threadIdx.x; i < nu * GP; i += kDecThreads) s_ml[i / GP][i % GP] = ld_dev_f2(&ml[(long long)c0 * GP + i]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+      const int t = 2 * ((int)threadIdx.x + kDecThreads * j) / D;
+      if (t >= GP) continue;
+      float mc = s_ml[0][t].x;
+      for (int u = 1; u < nu; ++u) mc = fmaxf(mc, s_ml[u][t].x);
+      const float m_new = fmaxf(M[j], mc);                   // finite: a unit holds at least one row
+      const float keep = fast_exp2(M[j] - m_new);            // exp2(-inf) = 0 for the first chunk
+      M[j] = m_new;
+      L[j] *= keep;
+      sum[j].x *= keep;
+      sum[j].y *= keep;
+    }
+    for (int u0 = 0; u0 < nu; u0 += 16) {                    // sixteen independent loads per round trip
+      if (u0 > 0) load_units(u0);
+#pragma unroll
+      for (int j = 0; j < kOut; ++j) {
+        const int t = 2 * ((int)threadIdx.x + kDecThreads * j) / D;
+        if (t >= GP) continue;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {                       // unit order: the result does not depend on timing
+          if (u0 + u < nu) {
+            const float2 st = s_ml[u0 + u][t];
+            const float wgt = fast_exp2(st.x - M[j]);
+            L[j] += wgt * st.y;
+            sum[j].x += wgt * pv[j][u].x;
+            sum[j].y += wgt * pv[j][u].y;
+          }
+        }
+      }
+    }
+    __syncthreads();                                         // the next chunk overwrites s_ml
+  }
+#pragma unroll
+  for (int j = 0; j < kOut; ++j) {
+    const int idx = 2 * ((int)threadIdx.x + kDecThreads * j), t = idx / D, e = idx % D;
+    if (t >= a.G) continue;
+    const long long row = (long long)b * a.H + (long long)g * a.G + t;
+    a.out[row * D + e] = sum[j].x / L[j];
+    a.out[row * D + e + 1] = sum[j].y / L[j];
+    if (a.lse != nullptr && e == 0) a.lse[row] = (M[j] + log2f(L[j])) * 0.6931471805599453f;
+  }
+}
+
+// What the units do not write: zeros for heads without rows, NaN everywhere if the offsets cannot be followed.
+// By one workgroup of the sequence.
+template <int D>
+__device__ __forceinline__ void fill_heads(const DecodeArgs& a, int b, const UnitMap& um, bool bad) {
+  if (!bad && __ballot((int)(threadIdx.x & 63) < a.H_kv && um.cnt == 0u) == 0ull) return;   // the same in every wavefront
+  for (int g = 0; g < a.H_kv; ++g) {
+    if (!bad && lane_value(um.cnt, g) != 0u) continue;
+    const long long row0 = (long long)b * a.H + (long long)g * a.G;
+    for (int i = threadIdx.x; i < a.G * D; i += kDecThreads) a.out[row0 * D + i] = bad ? NAN : 0.0f;
+    if (a.lse != nullptr && (int)threadIdx.x < a.G) a.lse[row0 + threadIdx.x] = bad ? NAN : -INFINITY;
+  }
 }
 
 template <int DT, int D, int GP>
@@ -157,30 +264,26 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int b = blockIdx.y;
   const UnitMap um = map_units(a.head_offsets + (long long)b * (a.H_kv + 1), a.H_kv, a.rows_capacity,
-                               a.rows_per_unit, a.tail_len, lane);
-  if (!um.usable || blockIdx.x >= um.total) return;         // bad offsets (the merge reports them) or no such unit
+                               a.tiles_per_unit, a.tail_len, lane);
+  const bool bad = !um.usable || um.total > (unsigned int)a.units_bound;
+  if (blockIdx.x == 0) fill_heads<D>(a, b, um, bad);
+  if (bad || blockIdx.x >= um.total) return;                // uniform: nothing to follow, or no such unit
   const int g = __builtin_ctzll(__ballot(um.incl > blockIdx.x));
   const long long u = (long long)blockIdx.x - ((long long)lane_value(um.incl, g) - (long long)lane_value(um.cnt, g));
-  const long long packed_units = lane_value(um.packed, g);
+  const long long packed_tiles = lane_value(um.packed, g);
   const long long off_g = lane_value64(um.off, g), len_g = lane_value64(um.len, g);
-
-  const char* kb;
-  const char* vb;
-  long long n_rows;
-  if (u < packed_units) {
-    const long long base = (a.seq_base ? a.seq_base[b] : (long long)b * a.rows_capacity) + off_g +
-                           u * a.rows_per_unit;
-    n_rows = len_g - u * a.rows_per_unit;
-    kb = a.k_hat + base * T::kRowBytes;
-    vb = a.v_hat + base * T::kRowBytes;
-  } else {
-    const long long c = u - packed_units;
-    const long long base = ((long long)b * a.H_kv + g) * a.tail_capacity + c * a.rows_per_unit;
-    n_rows = a.tail_len - c * a.rows_per_unit;
-    kb = a.k_tail + base * T::kRowBytes;
-    vb = a.v_tail + base * T::kRowBytes;
-  }
-  if (n_rows > a.rows_per_unit) n_rows = a.rows_per_unit;
+  const long long tail_tiles = ceil_div(a.tail_len, kTileKeys);
+  const long long first_tile = u * a.tiles_per_unit;         // of the head's tiles: packed ones, then appended ones
+  const long long packed_at = ((a.seq_base ? a.seq_base[b] : (long long)b * a.rows_capacity) + off_g) * T::kRowBytes;
+  const long long tail_at = ((long long)b * a.H_kv + g) * a.tail_capacity * T::kRowBytes;
+  long long n_tiles = packed_tiles + tail_tiles - first_tile;
+  if (n_tiles > a.tiles_per_unit) n_tiles = a.tiles_per_unit;
+  // Tile i of this wavefront: which rows (of the packed ones or of the appended ones), as a tile index there, and how many
+  // rows there are
+  struct Src {
+    bool packed;
+    long long tile, rows;
+  };
 
   // This wavefront's tiles: wave, wave + kDecWaves, ...  Vector-memory operations complete in issue
   // order and the K ring is awaited by count, so the order below is part of the protocol:
@@ -188,24 +291,29 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
   using VRaw = typename RawBits<S::kBpl>::type;
   TileDma<DT, D> dma;
   dma.init(lane);
-  const long long n_tiles = ceil_div(n_rows, kTileKeys);
   const int cnt = wave < n_tiles ? (int)((n_tiles - wave + kDecWaves - 1) / kDecWaves) : 0;
   u32x4* ring = s_tile[wave][0];
   FragReader<DT, D> frags;
   frags.init_at(lane, lds_addr(ring));
   const unsigned int p_addr = lds_addr(&s_p[wave][0][0]);
+  auto source = [&](int i) -> Src {
+    const long long t = first_tile + wave + (long long)i * kDecWaves;
+    return t < packed_tiles ? Src{true, t, len_g} : Src{false, t - packed_tiles, a.tail_len};
+  };
   auto issue_k = [&](int i) {
-    dma.issue(kb, wave + (long long)i * kDecWaves, n_rows, lane, ring + (i % kStages) * T::kTileChunks);
+    const Src src = source(i);
+    dma.issue(src.packed ? a.k_hat + packed_at : a.k_tail + tail_at, src.tile, src.rows, lane, ring + (i % kStages) * T::kTileChunks);
   };
   const unsigned int v_lane = (unsigned int)lane * S::kBpl;   // a row is a uniform address plus this
   auto load_v = [&](VRaw (&dst)[kTileKeys], int i) {
-    const long long row0 = (wave + (long long)i * kDecWaves) * kTileKeys;
-    const char* p = vb + row0 * T::kRowBytes;
-    if (row0 + kTileKeys <= n_rows) {
+    const Src src = source(i);
+    const long long row0 = src.tile * kTileKeys;
+    const char* p = (src.packed ? a.v_hat + packed_at : a.v_tail + tail_at) + row0 * T::kRowBytes;
+    if (row0 + kTileKeys <= src.rows) {
 #pragma unroll
       for (int kk = 0; kk < kTileKeys; ++kk) dst[kk] = *reinterpret_cast<const VRaw*>(p + kk * T::kRowBytes + v_lane);
-    } else {                                                // rows beyond the unit repeat its last row
-      const int last = (int)(n_rows - 1 - row0);            // 0 .. 30, uniform
+    } else {                                                // rows beyond the last one repeat it
+      const int last = (int)(src.rows - 1 - row0);          // 0 .. 30, uniform
 #pragma unroll
       for (int kk = 0; kk < kTileKeys; ++kk)
         dst[kk] = *reinterpret_cast<const VRaw*>(p + (kk < last ? kk : last) * T::kRowBytes + v_lane);
@@ -239,7 +347,6 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
   // PAR = it % 2 is the ring stage of K_it
   auto step = [&](auto par, int it, VRaw (&v_cur)[kTileKeys], VRaw (&v_next)[kTileKeys]) {
     constexpr int PAR = decltype(par)::value;
-    const long long tile = wave + (long long)it * kDecWaves;
     // ---------------- K tile: logits, online softmax, probabilities to LDS
     {
       // everything older than V_it (32 loads) and, if it was requested, K_{it+1} has landed
@@ -256,7 +363,8 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
         x2 = mfma_chunk<DT>(kf[j + 1], qf[j + 1], x2);
       }
       x += x2;                                              // x[v]: key 8*(v/4) + 4*half + v%4, head col
-      const long long left = n_rows - tile * kTileKeys;     // rows of the unit from this tile on (uniform)
+      const Src src = source(it);
+      const long long left = src.rows - src.tile * kTileKeys;   // rows from this tile on (uniform)
       float mt = -INFINITY;
       if (left >= kTileKeys) {
 #pragma unroll
@@ -264,7 +372,7 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
           x[v] *= a.c2;
           mt = fmaxf(mt, x[v]);
         }
-      } else {                                              // the unit's last, partial tile
+      } else {                                              // a partial tile
         int h4 = 4 * half;
         asm volatile("" : "+v"(h4));                        // keeps this path's temporaries out of the hot loop
 #pragma unroll
@@ -353,113 +461,81 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
 #pragma unroll
     for (int e = 0; e < kDpl; ++e) s_acc[wave][t][lane * kDpl + e] = acc[t][e];
   __syncthreads();
+  const int mine = (int)lane_value(um.cnt, g);               // units of the head
   const long long slot = (long long)b * a.units_bound + blockIdx.x;
-  for (int idx = threadIdx.x; idx < GP * D; idx += kDecThreads) {
-    const int t = idx / D, e = idx % D;
+  constexpr int kPairs = GP * D / 2;
+#pragma unroll
+  for (int j = 0; j < (kPairs + kDecThreads - 1) / kDecThreads; ++j) {
+    const int idx = 2 * ((int)threadIdx.x + kDecThreads * j), t = idx / D, e = idx % D;
+    if (t >= GP) continue;
     float M = s_m[0][t];
 #pragma unroll
     for (int w2 = 1; w2 < kDecWaves; ++w2) M = fmaxf(M, s_m[w2][t]);
-    float sum = 0.0f;
+    float L = 0.0f;
+    float2 sum = make_float2(0.0f, 0.0f);
 #pragma unroll
-    for (int w2 = 0; w2 < kDecWaves; ++w2) sum += fast_exp2(s_m[w2][t] - M) * s_acc[w2][t][e];
-    a.part_acc[(slot * GP + t) * D + e] = sum;
-    if (e == 0) {
-      float L = 0.0f;
-#pragma unroll
-      for (int w2 = 0; w2 < kDecWaves; ++w2) L += fast_exp2(s_m[w2][t] - M) * s_l[w2][t];
-      a.part_ml[slot * GP + t] = make_float2(M, L);
+    for (int w2 = 0; w2 < kDecWaves; ++w2) {
+      const float wgt = fast_exp2(s_m[w2][t] - M);
+      L += wgt * s_l[w2][t];
+      sum.x += wgt * s_acc[w2][t][e];
+      sum.y += wgt * s_acc[w2][t][e + 1];
+    }
+    if (mine > 1) {
+      st_dev_f2(reinterpret_cast<float2*>(a.part_acc + slot * GP * D + idx), sum.x, sum.y);
+      if (e == 0) st_dev_f2(&a.part_ml[slot * GP + t], M, L);
+    } else if (t < a.G) {
+      const long long row = (long long)b * a.H + (long long)g * a.G + t;
+      a.out[row * D + e] = sum.x / L;
+      a.out[row * D + e + 1] = sum.y / L;
+      if (a.lse != nullptr && e == 0) a.lse[row] = (M + log2f(L)) * 0.6931471805599453f;
     }
   }
-}
-
-// One workgroup per (KV head, sequence): merge the head's units in unit order (deterministic).
-// Units are taken kMergeChunk at a time: their (max, sum) pairs go through LDS, every thread then
-// knows the chunk's maximum per head without a second trip to memory, and the loads of the partial
-// outputs of a whole chunk are independent of each other, so the kernel's time does not grow with the
-// number of units the way a loop of dependent round trips does.  Across chunks the running result is
-// rescaled as in the online softmax.
-constexpr int kMergeChunk = 32;
-template <int D, int GP>
-__global__ void __launch_bounds__(256) decode_merge_kernel(DecodeArgs a, float* __restrict__ out,
-                                                           float* __restrict__ lse) {
-  const int b = blockIdx.y, g = blockIdx.x;
-  const UnitMap um = map_units(a.head_offsets + (long long)b * (a.H_kv + 1), a.H_kv, a.rows_capacity,
-                               a.rows_per_unit, a.tail_len, (int)(threadIdx.x & 63));
-  const int mine = (int)lane_value(um.cnt, g);
-  const long long first = (long long)lane_value(um.incl, g) - mine;
-  const bool overflow = !um.usable || um.total > (unsigned int)a.units_bound;
-  const float2* ml = a.part_ml + ((long long)b * a.units_bound + first) * GP;
-  const float* pa = a.part_acc + ((long long)b * a.units_bound + first) * GP * D;
-  __shared__ float2 s_ml[kMergeChunk][GP];
-  constexpr int kOut = (GP * D + 255) / 256;                // outputs per thread: (t, e) = (idx / D, idx % D), idx = tid + 256 j
-  float M[kOut], L[kOut], sum[kOut];
-#pragma unroll
-  for (int j = 0; j < kOut; ++j) { M[j] = -INFINITY; L[j] = 0.0f; sum[j] = 0.0f; }
-  for (int c0 = 0; c0 < (overflow ? 0 : mine); c0 += kMergeChunk) {
-    const int nu = mine - c0 < kMergeChunk ? mine - c0 : kMergeChunk;
-    for (int i = threadIdx.x; i < nu * GP; i += 256) s_ml[i / GP][i % GP] = ml[(long long)c0 * GP + i];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kOut; ++j) {
-      const int idx = (int)threadIdx.x + 256 * j;
-      if (idx >= a.G * D) continue;
-      const int t = idx / D, e = idx % D;
-      float mc = s_ml[0][t].x;
-      for (int u = 1; u < nu; ++u) mc = fmaxf(mc, s_ml[u][t].x);
-      const float m_new = fmaxf(M[j], mc);                   // finite: a unit holds at least one row
-      const float keep = fast_exp2(M[j] - m_new);            // exp2(-inf) = 0 for the first chunk
-      float l_new = L[j] * keep, s_new = sum[j] * keep;
-      const float* col = pa + ((long long)c0 * GP + t) * D + e;
-      for (int u0 = 0; u0 < nu; u0 += 16) {                  // sixteen independent loads per round trip
-        float pv[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) pv[u] = u0 + u < nu ? col[(long long)(u0 + u) * GP * D] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {                       // unit order: the result does not depend on timing
-          if (u0 + u < nu) {
-            const float2 st = s_ml[u0 + u][t];
-            const float wgt = fast_exp2(st.x - m_new);
-            l_new += wgt * st.y;
-            s_new += wgt * pv[u];
-          }
-        }
-      }
-      M[j] = m_new;
-      L[j] = l_new;
-      sum[j] = s_new;
+  if (mine <= 1) return;
+  // ---------------- publish the unit; merge the head if all its units are published
+  drain_vmem();
+  __syncthreads();                                          // every thread's share of the partial is visible to the device
+  unsigned long long* flags = a.flags + slot - u;           // of the head's units
+  int* s_all = reinterpret_cast<int*>(&s_p[0][0][0]);
+  if (wave == 0) {
+    if (lane == 0) {
+      st_dev(&flags[u], a.tag);
+      drain_vmem();
     }
-    __syncthreads();                                         // the next chunk overwrites s_ml
+    bool all = true;
+    for (int i = lane; i < mine; i += 64) all &= ld_dev(&flags[i]) == a.tag;
+    const bool every = __ballot(!all) == 0ull;
+    if (lane == 0) *s_all = every ? 1 : 0;
   }
-#pragma unroll
-  for (int j = 0; j < kOut; ++j) {
-    const int idx = (int)threadIdx.x + 256 * j;
-    if (idx >= a.G * D) continue;
-    const int t = idx / D, e = idx % D;
-    float result = 0.0f, lse_v = -INFINITY;
-    if (overflow) {
-      result = lse_v = NAN;
-    } else if (mine > 0) {
-      result = sum[j] / L[j];
-      lse_v = (M[j] + log2f(L[j])) * 0.6931471805599453f;
-    }
-    out[((long long)b * a.H + (long long)g * a.G + t) * D + e] = result;
-    if (lse != nullptr && e == 0) lse[(long long)b * a.H + (long long)g * a.G + t] = lse_v;
-  }
+  __syncthreads();
+  if (*s_all == 0) return;
+  for (int i = threadIdx.x; i < mine; i += kDecThreads) st_dev(&flags[i], 0ull);
+  static_assert(sizeof(s_tile) >= kMergeChunk * GP * sizeof(float2), "the ring is the merge's buffer");
+  merge_units<D, GP>(a, b, g, mine, a.part_ml + (slot - u) * GP, a.part_acc + (slot - u) * GP * D,
+                     reinterpret_cast<float2 (*)[GP]>(&s_tile[0][0][0]));
 }
 
 template <int DT, int D, int GP>
-int32_t launch_one(const DecodeArgs& a, int batch, float* out, float* lse, hipStream_t s) {
-  {
-    ProfScope ps(KID_DECODE, s);
-    hipLaunchKernelGGL((decode_kernel<DT, D, GP>), dim3(a.units_bound, batch), dim3(kDecThreads), 0, s, a);
-  }
-  int32_t st = launch_status();
-  if (st != LAVA_OK) return st;
-  {
-    ProfScope ps(KID_DECODE_MERGE, s);
-    hipLaunchKernelGGL((decode_merge_kernel<D, GP>), dim3(a.H_kv, batch), dim3(256), 0, s, a, out, lse);
-  }
+int32_t launch_one(const DecodeArgs& a, int batch, hipStream_t s) {
+  ProfScope ps(KID_DECODE, s);
+  hipLaunchKernelGGL((decode_kernel<DT, D, GP>), dim3(a.units_bound, batch), dim3(kDecThreads), 0, s, a);
   return launch_status();
+}
+
+// A number that no other call of this process uses and that memory holds by chance once in 2^64 words: a mixed
+// counter (a bijection of 64 bits) from a start of its own in every process.
+unsigned long long mix64(unsigned long long x) {
+  x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+  x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+  return x ^ (x >> 31);
+}
+unsigned long long next_tag() {
+  static std::atomic<unsigned long long> next{
+      mix64((unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() ^
+            ((unsigned long long)getpid() << 40) ^ (unsigned long long)reinterpret_cast<uintptr_t>(&next))};
+  for (;;) {
+    const unsigned long long tag = mix64(next.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed));
+    if (tag != 0ull) return tag;                            // 0 is "not published"
+  }
 }
 
 int padded_group(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8; }
@@ -482,20 +558,22 @@ int device_cus() {
 DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t rows_capacity, int64_t tail_len) {
   DecodePlan p;
   const int64_t step = kTileKeys * kDecWaves;
-  const int64_t total = (int64_t)batch * (rows_capacity + (int64_t)d.n_kv_heads * tail_len);
-  // Rows per unit: the device holds two workgroups per compute unit at a time; the units should fill
-  // a whole number of such rounds, at least two (units differ in length, heads end in partial units,
-  // and only a second round lets the dispatcher even that out), with as few units as that allows
-  // (every unit pays its set-up and leaves a partial result to merge).  A head is expected to waste
-  // half a unit.  Measured on 64 x 8192 rows: 768 rows (two rounds) 60.7 us, 512 rows (two and a
-  // half) 62.7 us.
+  const int64_t tail_tiles = (tail_len + kTileKeys - 1) / kTileKeys;
+  const int64_t total = (int64_t)batch * (rows_capacity + (int64_t)d.n_kv_heads * tail_tiles * kTileKeys);
+  // Rows per unit: the device holds two workgroups per compute unit at a time; the units should fill whole rounds of
+  // those, with as few units as that allows (every unit pays its set-up and leaves a partial result to merge).
+  // A head is expected to waste half a unit.  One round if heads are then still cut into several units, which evens
+  // them out (16 x 8192 rows: 384 rows a unit, one round, 19.5 us, 256, two rounds, 22.4; 32 x 8192: 768, one round,
+  // 35.4, 384 38.1; one sequence of a million rows: 2048 109, 1024 122); otherwise at least two, so that the
+  // dispatcher can (64 x 8192 rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
   const int64_t resident = 2 * (int64_t)device_cus();
   const int64_t heads = (int64_t)batch * d.n_kv_heads;
   int64_t c = 16 * step;
-  for (int64_t rounds = 2; rounds <= 64; ++rounds) {
+  for (int64_t rounds = 1; rounds <= 64; ++rounds) {
     const int64_t room = rounds * resident - heads / 2;
     if (room <= 0) continue;
     c = ((total + room - 1) / room + step - 1) / step * step;
+    if (rounds == 1 && c > step && 4 * c * heads > 3 * total) continue;
     if (c <= 16 * step) break;
   }
   if (c < step) c = step;
@@ -503,13 +581,15 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   if (tuning().decode_rows_per_unit >= step) c = tuning().decode_rows_per_unit / step * step;   // caller's tuning
   p.rows_per_unit = (int)c;
   p.group_pad = padded_group(d.n_q_heads / d.n_kv_heads);
-  const int64_t tail_units = tail_len > 0 ? (tail_len + c - 1) / c : 0;
-  p.units_bound = (rows_capacity + c - 1) / c + d.n_kv_heads + d.n_kv_heads * tail_units;
+  // a head's last packed tile, and its last unit, may be partial
+  const int64_t tiles = (rows_capacity + kTileKeys - 1) / kTileKeys + d.n_kv_heads * (1 + tail_tiles);
+  p.units_bound = (tiles + c / kTileKeys - 1) / (c / kTileKeys) + d.n_kv_heads;
   if (p.units_bound < 1) p.units_bound = 1;
   const size_t slots = (size_t)batch * (size_t)p.units_bound * p.group_pad;
   p.off_ml = 0;
   p.off_acc = align_up(slots * sizeof(float2));
-  p.bytes = p.off_acc + align_up(slots * d.head_dim * sizeof(float));
+  p.off_flags = p.off_acc + align_up(slots * d.head_dim * sizeof(float));
+  p.bytes = p.off_flags + align_up((size_t)batch * (size_t)p.units_bound * sizeof(unsigned long long));
   return p;
 }
 
@@ -532,15 +612,19 @@ int32_t launch_decode(const lava_layer_desc& d, int32_t batch, const void* q, co
   a.H = d.n_q_heads;
   a.H_kv = d.n_kv_heads;
   a.G = d.n_q_heads / d.n_kv_heads;
-  a.rows_per_unit = p.rows_per_unit;
+  a.tiles_per_unit = p.rows_per_unit / kTileKeys;
   a.units_bound = (int)p.units_bound;
   const float scale = d.softmax_scale > 0.0f ? d.softmax_scale : 1.0f / sqrtf((float)d.head_dim);
   a.c2 = scale * kLog2e;
   a.part_ml = reinterpret_cast<float2*>(static_cast<char*>(ws) + p.off_ml);
   a.part_acc = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_acc);
+  a.flags = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + p.off_flags);
+  a.tag = next_tag();
+  a.out = out;
+  a.lse = lse;
 
 #define LAVA_DECODE_CASE(DT, D, GP) \
-  if (d.dtype == DT && d.head_dim == D && p.group_pad == GP) return launch_one<DT, D, GP>(a, batch, out, lse, s);
+  if (d.dtype == DT && d.head_dim == D && p.group_pad == GP) return launch_one<DT, D, GP>(a, batch, s);
 #define LAVA_DECODE_GROUPS(DT, D) \
   LAVA_DECODE_CASE(DT, D, 1) LAVA_DECODE_CASE(DT, D, 2) LAVA_DECODE_CASE(DT, D, 4) LAVA_DECODE_CASE(DT, D, 8)
   LAVA_DECODE_GROUPS(LAVA_BF16, 128)

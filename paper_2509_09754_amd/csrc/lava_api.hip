@@ -21,7 +21,7 @@ struct ProfState {
 
 const char* const kKernelNames[KID_COUNT] = {
     "vnorm", "stats", "scores", "sweep", "prepass", "poolstat", "sel_init", "sel_fused", "sel_steps", "compact", "budgets",
-    "decode", "decode_merge"};
+    "decode"};
 
 void prof_collect() {
   (void)hipDeviceSynchronize();
