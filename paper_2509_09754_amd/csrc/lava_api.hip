@@ -227,8 +227,11 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     int max_vb = 0;
     a.n_units = 0;
     SweepPlan plan = plan_max;
-    int64_t launch_tokens = 0;
-    for (int i = 0; i < a.n_seq; ++i) launch_tokens += seq_lens[b0 + i];
+    int64_t launch_tokens = 0, launch_tiles = 0;
+    for (int i = 0; i < a.n_seq; ++i) {
+      launch_tokens += seq_lens[b0 + i];
+      launch_tiles += (seq_lens[b0 + i] + kTileKeys - 1) / kTileKeys * d.n_kv_heads;
+    }
     // Several sequences whose workgroups do not all fit on the device at once: the narrow shape
     // (two workgroups per CU, out of phase) hides the per-workgroup set-up that a launch of
     // several rounds of one-per-CU workgroups would pay once per round.
@@ -264,11 +267,14 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     // The persistent launch measured a few per cent slower on this device, so it is not the default.
     const bool persistent = together && plan_max.wg_chunks == 1 && lse == nullptr && a.bph == 1 && tuning().sweep_schedule == 2;
     // Value norms: a launch of their own, or, where a statistics launch follows anyway, inside it (its
-    // workgroups sweep the value rows of their span before the keys: one launch fewer).  Measured: a gain
-    // for one sequence per launch (4 % of the whole path at 32K tokens, none at 128K), a loss of about 3 %
-    // for a launch of many sequences, whose value norms do better with their own, finer cut.
+    // workgroups sweep the value rows of their span before the keys: one launch and one start-up fewer; a launch
+    // of their own is cut finer).  Whole path, 8 KV heads, own launch -> inside: 2 x 1350 tokens 42.1 -> 34.6 us,
+    // 8 x 4000 84.0 -> 76.4, 16 x 8000 209 -> 193, 32 x 8000 384 -> 358, 28 x 16000 603 -> 601; then nothing (12
+    // sequences, 531 thousand tokens, 634) and a loss (16, 648 thousand tokens, 750 -> 756; 32 x 32768 1133 -> 1141):
+    // inside up to 512 key tiles per compute unit.
     const bool prepass = lse == nullptr && !persistent && d.score_kind != LAVA_SCORE_ATTENTION &&
-                         (tuning().sweep_schedule == 3 || (tuning().sweep_schedule == 0 && a.n_seq == 1));
+                         (tuning().sweep_schedule == 3 ||
+                          (tuning().sweep_schedule == 0 && (a.n_seq == 1 || launch_tiles <= 512 * (int64_t)sweep_device_wgs())));
     if (prepass) {
       for (int i = 0; i < a.n_seq; ++i) {
         a.s[i].vnorm_blocks = a.s[i].blocks_x;
