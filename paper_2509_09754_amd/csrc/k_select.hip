@@ -65,9 +65,10 @@ static_assert(kFlagWord + 2 * kFusedMaxBlocks <= 3 * kSelBins, "histogram area")
 struct SelectState {
   unsigned int barrier;      // arrivals at the grid barriers of the fused kernel (monotonic)
   unsigned int error;        // set when a wait gave up (results are then invalid)
-  unsigned int done;         // workgroups of the fused kernel that have written their results
+  unsigned int outcome;      // kOpen until the fused kernel's workgroups agree on kComplete or kFailed (see there)
   unsigned int reserved[5];
 };
+constexpr unsigned int kOpen = 0u, kComplete = 1u, kFailed = 2u;
 static_assert(sizeof(SelectState) == kSelStateWords * sizeof(unsigned int), "cleared word by word by the score kernels");
 
 SelectWorkspace make_select_workspace(int64_t total) { return select_layout(total); }
@@ -82,6 +83,7 @@ struct SelShared {
   unsigned int wave2[kSelWaves];
   unsigned int pick[3];
   unsigned int before[4];                   // handed from wavefront 0 to the workgroup
+  unsigned int failed;
 };
 
 // The keys that may still hold the threshold: lo .. lo + width.  `need` survivors must come from the
@@ -476,7 +478,7 @@ __device__ __forceinline__ void write_survivors(const unsigned int (&key)[KP], u
 
 // Grid-wide barrier of the fused kernel: all of its workgroups are resident (the host checks the
 // grid against the device's capacity), arrivals are counted monotonically, and the wait is
-// bounded: if it ever gives up, the error word is set and the kernel still runs to completion.
+// bounded: if it ever gives up, the outcome is failure and the kernel still runs to completion.
 __device__ __forceinline__ void grid_sync(SelectState* __restrict__ st, unsigned int round, unsigned int n_blocks,
                                           unsigned int spin_limit) {
   drain_vmem();
@@ -488,7 +490,7 @@ __device__ __forceinline__ void grid_sync(SelectState* __restrict__ st, unsigned
     while (ld_dev(&st->barrier) < target) {
       __builtin_amdgcn_s_sleep(2);
       if (++spins > spin_limit) {
-        st_dev(&st->error, 1u);
+        st_dev(&st->outcome, kFailed);       // still open: this workgroup's keys are not published yet
         break;
       }
     }
@@ -533,7 +535,7 @@ __global__ void __launch_bounds__(kSelThreads) sel_init_kernel(const SelectBatch
   if (threadIdx.x == 0) {
     st->barrier = 0u;
     st->error = 0u;
-    st->done = 0u;
+    st->outcome = kOpen;
   }
 }
 
@@ -613,6 +615,20 @@ __device__ __forceinline__ void fetch_list(const unsigned int* seg, unsigned int
   }
 }
 
+// What becomes of a selection whose waits are bounded: either every workgroup writes its survivors or every one writes
+// the mark no consumer can mistake for a selection (no survivors anywhere, counts -1).  The first proposal stands: a
+// workgroup that has seen the words of all others in the last exchange proposes completion, one whose wait is over its
+// limit failure; one that is outvoted by completion finds the words in place.  A wait before that fails while the outcome is
+// open, and its failure is visible before the word that the others wait for.  The answer is not needed before the survivors
+// are written, so it travels beside the rest of the selection.  (Marks written over the results by the workgroup that
+// finishes last, found by a ticket, were two trips to memory and two barriers at the end of every selection:
+// @@FIG@@.)  For wavefront 0; the outcome before the proposal, in lane 0.
+__device__ __forceinline__ unsigned int propose(SelectState* st, unsigned int outcome) {
+  unsigned int was = kOpen;
+  if ((threadIdx.x & 63) == 0) was = atomicCAS(&st->outcome, kOpen, outcome);
+  return was;
+}
+
 // The whole selection in one launch.
 template <int KP>
 __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectBatch a) {
@@ -651,6 +667,8 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
   if (primed && bx == 0 && threadIdx.x < (unsigned)n_heads)
     st_dev(reinterpret_cast<unsigned int*>(&pr.head_counts[threadIdx.x]), 0u);
 
+  bool failed = false;                               // wavefront 0: a wait gave up, here or elsewhere
+  unsigned int outcome = kOpen;                      // lane 0 of it: the outcome before this workgroup's proposal
   Threshold t = {0xffffffffu, 0u};                   // nothing survives
   unsigned int rows = 0u;                            // rows of this wavefront that may hold survivors
   unsigned int gt_before = 0u, eq_before = 0u;
@@ -724,14 +742,19 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
           if (lane == 0)
             st_dev(&flag[bx], ((unsigned long long)epoch << 48) | ((unsigned long long)above << 24) | inside);
           unsigned int gt = 0u, before = 0u, pos = 0u, over = 0u, spins = 0u;
-          bool gave_up = false;
+          bool patient = false;                        // the words are all there already: somebody has seen them
           for (unsigned int b0 = 0; b0 < nb; b0 += 64u) {
             const unsigned int b = b0 + (unsigned int)lane;
             unsigned long long x = 0ull;
             for (;;) {
               if (b < nb) x = ld_dev(&flag[b]);
               if (__all(b >= nb || (unsigned int)(x >> 48) >= epoch)) break;
-              if (gave_up || ++spins > a.spin_limit) { gave_up = true; break; }
+              if (failed) break;
+              if (!patient && ++spins > a.spin_limit) {
+                patient = __builtin_amdgcn_readfirstlane(propose(st, kFailed)) == kComplete;
+                failed = !patient;
+                if (failed) break;
+              }
               __builtin_amdgcn_s_sleep(1);
             }
             if (b >= nb || (unsigned int)(x >> 48) < epoch) x = 0ull;
@@ -745,8 +768,9 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
           gt = wave_sum(gt);
           before = wave_sum(before);
           over = __any(over != 0u) ? 1u : 0u;
+          // the last exchange: from here on nobody has to wait
+          if (!failed && !(want_keys && over != 0u)) outcome = propose(st, kComplete);
           if (lane == 0) {
-            if (gave_up) st_dev(&st->error, 1u);
             sh.seg_pos[nb] = pos;
             sh.before[0] = gt;
             sh.before[1] = before;
@@ -815,29 +839,20 @@ __global__ void __launch_bounds__(kSelThreads, 8) sel_fused_kernel(const SelectB
       break;
     }
   }
+  if (threadIdx.x == 0) sh.failed = failed || outcome == kFailed ? 1u : 0u;
   __syncthreads();                                   // sh.off; sh.wave / sh.wave2 are free
   const lava_select_problem& out = a.p[opaque(prob)];   // read again here: fewer scalars live until now
+  if (sh.failed != 0u) {                             // uniform over the problem's workgroups
+    if (threadIdx.x < (unsigned)n_heads) out.head_counts[threadIdx.x] = -1;
+    if (threadIdx.x <= (unsigned)n_heads) out.head_offsets[threadIdx.x] = 0;
+    if (threadIdx.x == 0) st_dev(&st->error, 1u);
+    if (threadIdx.x == 0 && out.error_dev != nullptr) *out.error_dev = 1;
+    return;
+  }
   const long long out_off = out.out_offset_dev ? (long long)*out.out_offset_dev : 0;
   write_survivors<KP>(key, rows, scores, wave_base, total, n_heads, t, gt_before, eq_before, kept_total, out.budget, alone,
                       bx == 0, sh, out.head_counts, out.head_offsets, out.kept_idx + out_off,
                       out.kept_scores ? out.kept_scores + out_off : nullptr);
-  if (alone) return;
-
-  // A wait that gave up leaves results computed from incomplete counts.  The workgroup that
-  // finishes last (every other one has completed its writes before taking its ticket) then replaces
-  // them by a mark no consumer can mistake for a selection: no survivors anywhere, counts -1.
-  drain_vmem();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned int tk = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sh.wave[0] = (tk + 1u == nb && ld_dev(&st->error) != 0u) ? 1u : 0u;
-  }
-  __syncthreads();
-  if (sh.wave[0] != 0u) {
-    if (threadIdx.x < (unsigned)n_heads) out.head_counts[threadIdx.x] = -1;
-    if (threadIdx.x <= (unsigned)n_heads) out.head_offsets[threadIdx.x] = 0;
-    if (threadIdx.x == 0 && out.error_dev != nullptr) *out.error_dev = 1;
-  }
 }
 
 // The same phases as separate launches (kernel boundaries take the place of the waits), for a problem
