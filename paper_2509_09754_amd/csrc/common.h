@@ -88,6 +88,8 @@ struct SweepPlan {
 SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens = 0, bool narrow = false);
 bool sweep_has_narrow_shape(const lava_layer_desc& d);
 int sweep_device_wgs();   // compute units of the current device
+int sweep_rows_per_head(const lava_layer_desc& d);     // rows a head has in a row block: 32, or 16 or 8 where heads share one
+int sweep_blocks_per_group(const lava_layer_desc& d);  // row blocks of a KV group
 int sweep_blocks_per_head(const lava_layer_desc& d);   // 32-row blocks a head's window rows take: 1 or 2
 
 // Workspace of lava_window_scores for one sequence (all offsets 256-byte aligned).
@@ -142,8 +144,9 @@ struct SweepArgs {
   float* layer_stat;         // [batch]
   char* ws;
   size_t off_stat_part, off_vnorm_part, off_sraw, off_ent_part, off_counter;   // inside a sequence's region
-  int H, H_kv, w, G, n_chunks, pool_half;   // G: row blocks of 32 window rows per KV group = (H / H_kv) * bph
+  int H, H_kv, w, G, n_chunks, pool_half;   // G: row blocks per KV group
   int bph;                   // row blocks per query head: 1 (w <= 32) or 2
+  int rph;                   // rows per query head in a block: 32, or 16 or 8 where heads share one
   int token_norm;            // value factor per token: vnorm leaves ||V[g, i]||_1 in scores[g][i], the pooling step multiplies by it
   float c2;
   int first_seq;             // index in the batch of s[0]

@@ -210,10 +210,10 @@ __device__ __forceinline__ void plan_budgets(const BudgetPlanArgs& plan, const P
 // maximum of the raw dot products of its query row (lane % 32) and the sum of exp2((dot - max) * c2) over the keys it
 // has seen (the two lane halves see different keys of the same rows).
 template <int DT, int D, int GT>
-__device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], long long tile, long long n, int w, int bph,
+__device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], long long tile, long long n, const RowMap& rm,
                                            float c2, const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
                                            float (&m_run)[GT], float (&z_run)[GT]) {
-  const int r = lane & 31, half = lane >> 5;
+  const int r = lane & (rm.rph - 1), half = lane >> 5, w = rm.w;   // r: window row, in the first block of two
   const long long key0 = tile * kTileKeys;
   // 32-bit inputs: all heads' products at once (the split of the keys is shared); bf16: head by head, so that
   // the next head's matrix instructions run beside this head's exponentials
@@ -249,7 +249,7 @@ __device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps
     for (int t = 0; t < GT; ++t) {
       // window row of this lane in block t (a chunk starts at an even block when heads have two blocks);
       // row rr sees relative positions <= min(rr, w - 1)
-      const int rr = r + ((bph == 2 && (t & 1)) ? 32 : 0);
+      const int rr = r + ((rm.bph == 2 && (t & 1)) ? 32 : 0);
       const int row_limit = rr < w - 1 ? rr : w - 1;
       f32x16 acc = head_dots(t);
 #pragma unroll
@@ -279,7 +279,7 @@ __device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps
 // requested these tiles).
 template <int DT, int D, int GT, int WAVES, int STAGES>
 __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const FragReader<DT, D>& frags,
-                                            const char* __restrict__ kg, long long n, int w, int bph, float c2,
+                                            const char* __restrict__ kg, long long n, const RowMap& rm, float c2,
                                             long long first, int cnt, u32x4* ring,
                                             const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
                                             float (&m_run)[GT], float (&z_run)[GT], int slot0 = 0) {
@@ -296,7 +296,7 @@ __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const Fra
     wait_tile<DT, D>(younger);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + ((it + slot0) % STAGES) * T::kTileBytes, kf);
-    stats_tile<DT, D, GT>(kf, first + (long long)it * WAVES, n, w, bph, c2, qf, q_finite, lane, m_run, z_run);
+    stats_tile<DT, D, GT>(kf, first + (long long)it * WAVES, n, rm, c2, qf, q_finite, lane, m_run, z_run);
   }
 }
 
@@ -382,6 +382,7 @@ __device__ __forceinline__ void wave_barrier() {
 struct Unit {
   int z, y, x;
 };
+__device__ __forceinline__ RowMap row_map(const SweepArgs& a) { return RowMap{a.H / a.H_kv, a.G, a.bph, a.rph, a.w}; }
 __device__ __forceinline__ Unit unit_of_block(const SweepArgs& a) {
   Unit u;
   u.z = 0;
@@ -459,6 +460,7 @@ stats_kernel(const SweepArgs a) {
   const SweepSeq sq = a.s[u.z];
   const long long n = sq.n;
   const int w = a.w, G = a.G, n_chunks = a.n_chunks, tiles_per_block = sq.tiles_per_block;
+  const RowMap rm = row_map(a);
   const float c2 = a.c2;
   const u32x4* __restrict__ q_win =
       static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + u.z) * a.H * w * T::kCpr;
@@ -518,7 +520,7 @@ stats_kernel(const SweepArgs a) {
 #pragma unroll
     for (int i = 0; i < kQSlots; ++i) {
       const int t = wave_in_chunk * kQSlots + i;
-      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, w, a.bph, lane, q_buffer(t));
+      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
     }
   }
   // with the value rows first, the ring holds both streams in turn: the wavefront's cnt_v value tiles, then
@@ -559,7 +561,7 @@ stats_kernel(const SweepArgs a) {
     wave_barrier();
     if constexpr (kQFirst) first_tiles();
   } else {
-    q_finite = load_q<DT, D, GT>(q_win, h0, nh, w, a.bph, lane, qf);
+    q_finite = load_q<DT, D, GT>(q_win, h0, nh, rm, lane, qf);
     wait_vmcnt<0>();
   }
   q_finite = __ballot(!q_finite) == 0ull;
@@ -574,7 +576,7 @@ stats_kernel(const SweepArgs a) {
     }
   }
   float m_run[GT], z_run[GT];
-  stats_tiles<DT, D, GT, kPerChunk, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+  stats_tiles<DT, D, GT, kPerChunk, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_finite, lane, m_run,
                                              z_run, slot0);
   if constexpr (VN) {
     __shared__ float s_vmax[kWaves];
@@ -696,27 +698,29 @@ __device__ __forceinline__ void merge_partials(int merger, const float2* __restr
 // Step 2: the slices are merged in slice order; bias = log2(row normaliser * w) in the exp2 domain,
 // +inf for padding rows (their exponentials vanish).  Thread t < kRows does row t.
 template <int GT, int WAVES>
-__device__ __forceinline__ void write_bias(const float2* s_merge, int nh, int h0, int w, int bph, float c2, const float* s_bias) {
+__device__ __forceinline__ void write_bias(const float2* s_merge, int nh, int h0, const RowMap& rm, float c2, const float* s_bias) {
   using M = Merge<GT, WAVES>;
   if (threadIdx.x >= M::kRows) return;
-  const int t = threadIdx.x >> 5, rr = ((h0 + t) % bph) * 32 + (int)(threadIdx.x & 31);   // block and window row
+  const int t = threadIdx.x >> 5;
   float m = -INFINITY, z = 0.0f;
 #pragma unroll
   for (int sl = 0; sl < M::kSlices; ++sl) {
     const float2 x = lds_read64(lds_addr(s_merge) + (unsigned int)(sl * M::kRows + (int)threadIdx.x) * 8u);
     merge_stat(m, z, x.x, x.y, c2);
   }
-  const float bias = t < nh && rr < w ? m * c2 + log2f(z) + log2f((float)w) : INFINITY;
+  const bool real = t < nh && row_at(rm, h0 + t, (int)(threadIdx.x & 31)).real;
+  const float bias = real ? m * c2 + log2f(z) + log2f((float)rm.w) : INFINITY;
   lds_write32(lds_addr(s_bias) + threadIdx.x * 4u, bias);
 }
 // ... or the bias of the caller's log-sum-exp, by merger t < kRows
 template <int GT>
-__device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict__ lse, int nh, int h0, int w, int bph,
+__device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict__ lse, int nh, int h0, const RowMap& rm,
                                             const float* s_bias) {
   if (merger < 0 || merger >= GT * 32) return;
-  const int t = merger >> 5, head = (h0 + t) / bph, rr = ((h0 + t) % bph) * 32 + (merger & 31);
+  const int t = merger >> 5;
+  const RowAt at = row_at(rm, h0 + t, merger & 31);
   float bias = INFINITY;
-  if (t < nh && rr < w) bias = lse[(long long)head * w + rr] * kLog2e + log2f((float)w);
+  if (t < nh && at.real) bias = lse[(long long)at.head * rm.w + at.row] * kLog2e + log2f((float)rm.w);
   lds_write32(lds_addr(s_bias) + (unsigned int)merger * 4u, bias);
 }
 
@@ -725,7 +729,7 @@ __device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict_
 // a lane in result register v: 8 * (v / 4) + 4 * half + v % 4 -> four float4 per head).
 template <int DT, int D, int GT>
 __device__ __forceinline__ float score_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], float c2, unsigned int bias_addr,
-                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int bph) {
+                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, const RowMap& rm) {
   float best = 0.0f, pair = 0.0f;
   f32x16 all[DT == LAVA_F32 ? GT : 1];
   if constexpr (DT == LAVA_F32) dot_tiles<D, GT, false>(kf, qf, q_finite, all);
@@ -738,18 +742,31 @@ __device__ __forceinline__ float score_tile(const u32x4 (&kf)[Tile<DT, D>::kStep
   for (int t = 0; t < GT; ++t) {
     f32x16 nxt = acc;
     if (t + 1 < GT) nxt = head_dots(t + 1);
-    float ps = 0.0f;
-    u32x4 bb[4];                       // biases of rows 8*jj + 4*half + 0..3 of head t
+    u32x4 bb[4];                       // biases of rows 8*jj + 4*half + 0..3 of block t
     lds_read128x4_strided<32>(bias_addr + t * 128, bb[0], bb[1], bb[2], bb[3]);
+    auto share = [&](float sum, int jj) {   // + the exponentials of four rows
+      sum += fast_exp2(fmaf(acc[4 * jj + 0], c2, -__uint_as_float(bb[jj].x)));
+      sum += fast_exp2(fmaf(acc[4 * jj + 1], c2, -__uint_as_float(bb[jj].y)));
+      sum += fast_exp2(fmaf(acc[4 * jj + 2], c2, -__uint_as_float(bb[jj].z)));
+      sum += fast_exp2(fmaf(acc[4 * jj + 3], c2, -__uint_as_float(bb[jj].w)));
+      return sum;
+    };
+    if constexpr (GT == 1) {             // the one case in which heads share a block (sweep_rows_per_head)
+      if (rm.rph == 8) {                 // uniform
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      ps += fast_exp2(fmaf(acc[4 * jj + 0], c2, -__uint_as_float(bb[jj].x)));
-      ps += fast_exp2(fmaf(acc[4 * jj + 1], c2, -__uint_as_float(bb[jj].y)));
-      ps += fast_exp2(fmaf(acc[4 * jj + 2], c2, -__uint_as_float(bb[jj].z)));
-      ps += fast_exp2(fmaf(acc[4 * jj + 3], c2, -__uint_as_float(bb[jj].w)));
+        for (int jj = 0; jj < 4; ++jj) best = fmaxf(best, add_halves(share(0.0f, jj)));
+        break;
+      }
+      if (rm.rph == 16) {
+        best = fmaxf(add_halves(share(share(0.0f, 0), 1)), add_halves(share(share(0.0f, 2), 3)));
+        break;
+      }
     }
+    float ps = 0.0f;
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) ps = share(ps, jj);
     ps = add_halves(ps);
-    if (bph == 2) {                    // uniform: a head's window mean is the sum over its two row blocks
+    if (rm.bph == 2) {                   // uniform: a head's window mean is the sum over its two row blocks
       if (t & 1) best = fmaxf(best, pair + ps);
       else pair = ps;
     } else {
@@ -788,7 +805,7 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
                                              bool halo_right, int n_jobs, int (&fifo)[STAGES], u32x4* ring,
                                              unsigned int* next_job, const float* s_bias, float* s_span,
                                              const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
-                                             float* __restrict__ raw_head, int n_chunks, int bph) {
+                                             float* __restrict__ raw_head, int n_chunks, const RowMap& rm) {
   using T = Tile<DT, D>;
   auto job_tile = [&](int j) -> long long {
     if (j < n_own) return t_begin + j;
@@ -839,7 +856,7 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
     if constexpr (!FUSED) store_result(pend_key, pend);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + (it % STAGES) * T::kTileBytes, kf);
-    const float best = score_tile<DT, D, GT>(kf, c2, bias_addr, qf, q_finite, bph);
+    const float best = score_tile<DT, D, GT>(kf, c2, bias_addr, qf, q_finite, rm);
     if constexpr (FUSED) {
       span_put<SHARED_SPAN>(span_base + (unsigned int)(tile - t_begin + 1) * (kTileKeys * 4), best);
     } else {
@@ -977,6 +994,7 @@ scores_kernel(const SweepArgs a) {
   const int seq = a.first_seq + (int)u.z;
   const long long n = sq.n;
   const int w = a.w, G = a.G, n_chunks = a.n_chunks, tiles_per_block = sq.tiles_per_block;
+  const RowMap rm = row_map(a);
   const int stat_blocks = sq.blocks_x;
   const float c2 = a.c2;
   const u32x4* __restrict__ q_win = static_cast<const u32x4*>(a.q_win) + (long long)seq * a.H * w * T::kCpr;
@@ -1075,14 +1093,14 @@ scores_kernel(const SweepArgs a) {
 #pragma unroll
     for (int i = 0; i < kQSlots; ++i) {
       const int t = wave_in_chunk * kQSlots + i;
-      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, w, a.bph, lane, q_buffer(t));
+      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
     }
     asm volatile("" ::: "memory");
   };
   if constexpr (!M::kSplit) request_rows();                     // ahead of the partials, whose wait covers both
   const int merger = M::kSplit ? (int)threadIdx.x - NC * GT * 64 : (int)threadIdx.x;
   if (lse != nullptr)
-    bias_of_lse<NC * GT>(merger, lse, wg_nh, wg_h0, w, a.bph, s_bias);
+    bias_of_lse<NC * GT>(merger, lse, wg_nh, wg_h0, rm, s_bias);
   else
     merge_partials<NC * GT, kWaves, false>(merger, stat_part + (long long)u.y * stat_blocks * M::kRows, stat_blocks, c2, s_merge);
   asm volatile("" ::: "memory");
@@ -1099,7 +1117,7 @@ scores_kernel(const SweepArgs a) {
   if constexpr (!kQFirst) first_tiles();
   if (wave_in_chunk * kQSlots < GT) wait_tile<DT, D>(young);
   wave_barrier();
-  if (lse == nullptr) write_bias<NC * GT, kWaves>(s_merge, wg_nh, wg_h0, w, a.bph, c2, s_bias);
+  if (lse == nullptr) write_bias<NC * GT, kWaves>(s_merge, wg_nh, wg_h0, rm, c2, s_bias);
   u32x4 qf[GT][kQVec<DT, D>];
   bool q_finite = true;
 #pragma unroll
@@ -1115,7 +1133,7 @@ scores_kernel(const SweepArgs a) {
   scores_tiles<DT, D, GT, kPerChunk, kStages, FUSED, (NC > 1)>(
       dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left, halo_right, n_jobs, fifo, ring,
       &s_next_job[NC == 1 ? 0 : wave_chunk], s_bias + (NC == 1 ? 0 : wave_chunk * GT * 32), s_span, qf, q_finite, lane,
-      s_raw + (long long)g * n_prefix, n_chunks, a.bph);
+      s_raw + (long long)g * n_prefix, n_chunks, rm);
   if constexpr (FUSED) {
     __shared__ float s_vb[kWaves];
     __shared__ double s_s[kWaves], s_t[kWaves];
@@ -1179,6 +1197,7 @@ sweep_kernel(const SweepArgs a) {
   __shared__ SweepSmem<DT, D, GT, W> sm;
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int w = a.w, G = a.G, H_kv = a.H_kv;
+  const RowMap rm = row_map(a);
   const float c2 = a.c2;
   uint32_t* __restrict__ ctl0 = reinterpret_cast<uint32_t*>(a.ws + a.s[0].ws_off + a.off_counter);
   TileDma<DT, D> dma;
@@ -1266,11 +1285,11 @@ sweep_kernel(const SweepArgs a) {
         if (p < cnt) dma.issue(kg, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
       u32x4 qf[GT][kQVec<DT, D>];
       bool q_finite = load_q<DT, D, GT>(static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + si) * a.H * w * T::kCpr, g * G,
-                                        G < GT ? G : GT, w, a.bph, lane, qf);
+                                        G < GT ? G : GT, rm, lane, qf);
       wait_vmcnt<0>();
       q_finite = __ballot(!q_finite) == 0ull;
       float m_run[GT], z_run[GT];
-      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, w, a.bph, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_finite, lane, m_run,
                                               z_run);
       float2 mine;
       if (stats_merge_waves<GT, kWaves, 1>(m_run, z_run, c2, lane, wave, sm.red, mine))
@@ -1388,12 +1407,12 @@ sweep_kernel(const SweepArgs a) {
                                      sm.sc.merge);
     lds_reads_done();
     __syncthreads();
-    write_bias<GT, kWaves>(sm.sc.merge, G < GT ? G : GT, g * G, w, a.bph, c2, sm.bias);
+    write_bias<GT, kWaves>(sm.sc.merge, G < GT ? G : GT, g * G, rm, c2, sm.bias);
     lds_reads_done();
     __syncthreads();
     scores_tiles<DT, D, GT, kWaves, kStages, true, false>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
                                                    halo_right, n_jobs, fifo, ring, &sm.next_job, sm.bias, sm.sc.span,
-                                                   qf, q_finite, lane, nullptr, 1, 1);
+                                                   qf, q_finite, lane, nullptr, 1, rm);
     scores_finish<kThreads>(pa, vb, g, n, n_prefix, w, t_begin, t_end, n_tiles, sm.sc.span, sm.vb, sm.ss, sm.st,
                             &sm.last, (unsigned int)(sq.blocks_x * H_kv), (unsigned int)(g * sq.blocks_x + bx), H_kv,
                             bx == 0, wave, reinterpret_cast<unsigned int*>(&sm.tile[0][0][0]));
@@ -1566,11 +1585,24 @@ int sweep_device_wgs() { return compute_units(); }
 
 int sweep_blocks_per_head(const lava_layer_desc& d) { return d.window > 32 ? 2 : 1; }
 
+int sweep_rows_per_head(const lava_layer_desc& d) {
+  // Heads share a block where one block then holds the group: kernels of more blocks would pay for the choice between
+  // two sums in their loop (131072 tokens, 32 heads on 8: 1 %), with little left to gain.
+  const int heads = d.n_q_heads / d.n_kv_heads;
+  if (heads == 2 && d.window <= 16) return 16;
+  return (heads == 3 || heads == 4) && d.window <= 8 ? 8 : 32;
+}
+
+int sweep_blocks_per_group(const lava_layer_desc& d) {
+  const int heads = d.n_q_heads / d.n_kv_heads, share = 32 / sweep_rows_per_head(d);
+  return (heads + share - 1) / share * sweep_blocks_per_head(d);
+}
+
 bool sweep_has_narrow_shape(const lava_layer_desc& d) { return !(d.dtype == LAVA_F32 && d.head_dim == 128); }
 
 SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens, bool narrow) {
   SweepPlan p;
-  const int G = (d.n_q_heads / d.n_kv_heads) * sweep_blocks_per_head(d);   // row blocks of 32 window rows per group
+  const int G = sweep_blocks_per_group(d);
   int gt = kMaxChunkHeads;
   if (d.dtype == LAVA_F32) gt = 2;     // query rows as three bf16 parts
   p.chunk_heads = G < gt ? G : gt;     // even whenever heads have two blocks: a head's blocks stay in one chunk
@@ -1778,7 +1810,7 @@ int32_t launch_stats(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
 }
 
 int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s) {
-  if (!p.fused_pool || p.wg_chunks != 1 || a.lse != nullptr || a.bph != 1) return LAVA_ERR_INVALID_ARG;
+  if (!p.fused_pool || p.wg_chunks != 1 || a.lse != nullptr || a.bph != 1 || a.rph != 32) return LAVA_ERR_INVALID_ARG;
   // persistent workgroups: as many as the device keeps resident for this shape, at most one per unit
   const int slots = compute_units() * ((p.narrow && sweep_has_narrow_shape(d)) ? 2 : 1);
   const dim3 grid(a.n_units < slots ? a.n_units : slots);

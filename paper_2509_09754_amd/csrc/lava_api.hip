@@ -213,7 +213,8 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
   a.H_kv = d.n_kv_heads;
   a.w = d.window;
   a.bph = sweep_blocks_per_head(d);
-  a.G = (d.n_q_heads / d.n_kv_heads) * a.bph;
+  a.rph = sweep_rows_per_head(d);
+  a.G = sweep_blocks_per_group(d);
   a.n_chunks = plan_max.n_chunks;
   a.pool_half = d.pool_kernel / 2;
   a.token_norm = d.score_kind == LAVA_SCORE_TOKEN_NORM ? 1 : 0;
@@ -265,7 +266,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     // Statistics and scores: two launches, or (when the caller's tuning asks for it, all heads of a group
     // fit one workgroup and the statistics pass is needed) one persistent launch that runs both passes.
     // The persistent launch measured a few per cent slower on this device, so it is not the default.
-    const bool persistent = together && plan_max.wg_chunks == 1 && lse == nullptr && a.bph == 1 && tuning().sweep_schedule == 2;
+    const bool persistent = together && plan_max.wg_chunks == 1 && lse == nullptr && a.bph == 1 && a.rph == 32 && tuning().sweep_schedule == 2;
     // Value norms: a launch of their own, or, where a statistics launch follows anyway, inside it (its
     // workgroups sweep the value rows of their span before the keys: one launch and one start-up fewer; a launch
     // of their own is cut finer).  Whole path, 8 KV heads, own launch -> inside: 2 x 1350 tokens 42.1 -> 34.6 us,

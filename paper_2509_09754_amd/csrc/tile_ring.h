@@ -335,10 +335,39 @@ struct FragReader {
   }
 };
 
-// The matrix cores take 32 query rows at a time, so a head whose window has more than 32 rows is
-// handled as `bph` (1 or 2) row blocks of 32: block index hb = head * bph + block, rows block * 32 ..
+// The matrix cores take 32 query rows at a time, a row block.  A head whose window has more than 32 rows is
+// handled as `bph` = 2 row blocks: block index hb = head * 2 + block, rows block * 32 ..; a group of two heads with
+// windows of at most 16 rows, or of up to four with at most 8, is one block, `rph` = 16 or 8 rows a head: with a block of
+// its own such a head pays matrix instructions, exponentials, normalisers and query rows for 32 (1024 tokens, 8 heads on
+// 2, 8 rows, f32: 32.0 -> 28.5 us a layer).
 // Everything up to the point where a head's window rows are summed treats a row block as a head.
-//
+struct RowMap {
+  int heads;     // query heads per KV group
+  int G;         // row blocks per KV group
+  int bph;       // row blocks per head: 1 or 2
+  int rph;       // rows per head in a block: 32, 16 or 8
+  int w;         // window rows
+};
+struct RowAt {
+  int head, row;   // query head of the layer, window row
+  bool real;       // the head exists and has that row
+};
+// Row r (0 .. 31) of row block hb, blocks counted through the KV groups.
+__device__ __forceinline__ RowAt row_at(const RowMap& m, int hb, int r) {
+  RowAt x;
+  if (m.rph == 32) {                                           // uniform
+    x.head = hb / m.bph;
+    x.row = (hb % m.bph) * 32 + r;
+    x.real = x.row < m.w;
+  } else {
+    const int g = hb / m.G, h = ((hb - g * m.G) * 32 + r) / m.rph;
+    x.head = g * m.heads + h;
+    x.row = r & (m.rph - 1);
+    x.real = h < m.heads && x.row < m.w;
+  }
+  return x;
+}
+
 // Query rows as a wavefront keeps them for a sweep: the 16-byte chunks of FragReader (bf16), or for every pair of
 // chunks their three bf16 parts (f32, see split8).
 template <int DT, int D> constexpr int kQVec = DT == LAVA_BF16 ? Tile<DT, D>::kSteps : Tile<DT, D>::kSteps / 2 * 3;
@@ -408,19 +437,19 @@ __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], 
 // global memory: row r = lane % 32 of the block (zero beyond the window or the chunk).  Returns this lane's share of
 // "all finite".
 template <int DT, int D, int GT>
-__device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, int nh, int w, int bph, int lane,
+__device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, int nh, const RowMap& rm, int lane,
                                        u32x4 (&qf)[GT][kQVec<DT, D>]) {
   using T = Tile<DT, D>;
   const int r = lane & 31, half = lane >> 5;
   bool finite = true;
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
-    const int head = (hb0 + t) / bph, row = ((hb0 + t) % bph) * 32 + r;
+    const RowAt at = row_at(rm, hb0 + t, r);
     u32x4 raw[T::kSteps];
 #pragma unroll
     for (int j = 0; j < T::kSteps; ++j) {
       u32x4 x = u32x4{0u, 0u, 0u, 0u};
-      if (t < nh && row < w) x = qg[((long long)head * w + row) * T::kCpr + 2 * j + half];
+      if (t < nh && at.real) x = qg[((long long)at.head * rm.w + at.row) * T::kCpr + 2 * j + half];
       raw[j] = x;
     }
     finite &= make_q<DT, D>(raw, qf[t]);
@@ -432,11 +461,26 @@ __device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, in
 // wavefront: no registers, and the block is read once per workgroup.  Rows beyond the window repeat its last
 // one, blocks beyond the chunk its last block: their results are masked or never used.
 template <int DT, int D>
-__device__ __forceinline__ void request_q(const TileDma<DT, D>& dma, const u32x4* __restrict__ qg, int hb0, int nh, int t, int w,
-                                          int bph, int lane, u32x4* buf) {
-  const int hb = hb0 + (t < nh ? t : nh - 1), head = hb / bph, row0 = (hb % bph) * 32;
-  const char* rows = reinterpret_cast<const char*>(qg) + ((long long)head * w + row0) * Tile<DT, D>::kRowBytes;
-  dma.issue_clamped(rows, 0, w - row0 < 32 ? w - row0 : 32, lane, buf);
+__device__ __forceinline__ void request_q(const TileDma<DT, D>& dma, const u32x4* __restrict__ qg, int hb0, int nh, int t,
+                                          const RowMap& rm, int lane, u32x4* buf) {
+  using T = Tile<DT, D>;
+  const int hb = hb0 + (t < nh ? t : nh - 1);
+  const char* q = reinterpret_cast<const char*>(qg);
+  if (rm.rph == 32) {                                          // uniform: one head's rows, which follow each other
+    const int head = hb / rm.bph, row0 = (hb % rm.bph) * 32;
+    dma.issue_clamped(q + ((long long)head * rm.w + row0) * T::kRowBytes, 0, rm.w - row0 < 32 ? rm.w - row0 : 32, lane, buf);
+    return;
+  }
+  const int g = hb / rm.G, h0 = (hb - g * rm.G) * (32 / rm.rph);
+#pragma unroll
+  for (int i = 0; i < T::kLoads; ++i) {
+    const int c = i * 64 + lane, r = c / T::kCpr, slot = c % T::kCpr;
+    int h = h0 + r / rm.rph, row = r & (rm.rph - 1);
+    h = h < rm.heads ? h : rm.heads - 1;
+    row = row < rm.w ? row : rm.w - 1;
+    const char* src = q + ((long long)(g * rm.heads + h) * rm.w + row) * T::kRowBytes + ((slot ^ (r & 7)) << 4);
+    __builtin_amdgcn_global_load_lds((const LAVA_GLOBAL_AS void*)src, (LAVA_LDS_AS void*)(buf + i * 64), 16, 0, 0);
+  }
 }
 
 // One head's 32 x 32 block of raw dot products: keys x rows (KEYS_AS_ROWS) or rows x keys.

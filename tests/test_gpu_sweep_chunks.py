@@ -1,5 +1,5 @@
-"""Groups whose query heads are swept in parts by the wavefronts of one workgroup (bf16: 5 to 8 heads, f32: 3 to 8), and
-32-bit products formed from bf16 parts."""
+"""Groups whose query heads are swept in parts by the wavefronts of one workgroup (bf16: 5 to 8 heads, f32: 3 to 8), heads with
+short windows that share a block of 32 rows, and 32-bit products formed from bf16 parts."""
 import dataclasses
 
 import numpy as np
@@ -19,12 +19,12 @@ def lava():
     L.set_tuning()
 
 
-def scores_of(lava, shapes, layers, sweep_shape="auto"):
+def scores_of(lava, shapes, layers, sweep_shape="auto", lse=None):
     s = shapes[0]
     desc = lava.LayerDesc.make(s.n_q_heads, s.n_kv_heads, s.head_dim, s.window, s.dtype)
     q, k, v = (torch.cat([lava.to_device(x[i], s.dtype).reshape(-1) for x in layers]) for i in range(3))
     lava.set_tuning(sweep_shape=sweep_shape)
-    out = lava.lava_window_scores(desc, [x.n for x in shapes], q, k, v)
+    out = lava.lava_window_scores(desc, [x.n for x in shapes], q, k, v, lse=lse)
     torch.cuda.synchronize()
     lava.set_tuning()
     return [x.cpu().numpy().astype(np.float64) for x in out]
@@ -49,13 +49,16 @@ def shape_of(dtype, d, G, w, n):
                                window=w, dtype=dtype)
 
 
-# every number of heads per part and of parts, a part with heads missing, windows of two row blocks; one tile per
-# wavefront, several, ragged ends; and the shape of two workgroups per compute unit
+# every number of heads per part and of parts, a part with heads missing, windows of two row blocks, two and four heads in a
+# block, blocks with heads missing; one tile per wavefront, several, ragged ends; and the shape of two workgroups per
+# compute unit
 @pytest.mark.parametrize("sweep_shape", ["wide", "narrow"])
 @pytest.mark.parametrize("dtype,d,G,w", [("bf16", 128, 5, 32), ("bf16", 128, 8, 7), ("bf16", 64, 6, 16), ("bf16", 128, 3, 33),
                                          ("bf16", 128, 9, 32), ("f32", 64, 1, 8), ("f32", 64, 2, 8), ("f32", 64, 4, 32),
                                          ("f32", 64, 5, 8), ("f32", 64, 3, 40), ("f32", 128, 1, 32), ("f32", 128, 4, 32),
-                                         ("f32", 128, 6, 20), ("f32", 128, 3, 40), ("f32", 128, 9, 8)])
+                                         ("f32", 128, 6, 20), ("f32", 128, 3, 40), ("f32", 128, 9, 8),
+                                         ("bf16", 128, 2, 8), ("bf16", 128, 2, 16), ("bf16", 128, 4, 8), ("bf16", 64, 3, 9),
+                                         ("bf16", 128, 16, 8), ("bf16", 64, 16, 16), ("f32", 128, 7, 5), ("f32", 64, 16, 1)])
 def test_groups_in_parts(lava, dtype, d, G, w, sweep_shape):
     lengths = [w + 1, 333, 2085] if sweep_shape == "wide" else [2085, 333]
     print(f"groups in parts {dtype} d{d} G{G} w{w} {sweep_shape} {lengths}", flush=True)
@@ -84,3 +87,18 @@ def test_32_bit_products_of_any_values(lava, d, G):
     want = O.lava_scores(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), s.window, s.pool_kernel)[0]
     assert np.isfinite(want).all()
     check([s], [want], scores_of(lava, [s], [(q, k, v)]))
+
+
+@pytest.mark.parametrize("dtype,d,G,w", [("bf16", 128, 4, 8), ("bf16", 64, 3, 16), ("f32", 64, 5, 7), ("f32", 128, 2, 12)])
+def test_heads_sharing_a_block_take_the_callers_log_sum_exp(lava, dtype, d, G, w):
+    print(f"heads sharing a block, caller's log-sum-exp, {dtype} d{d} G{G} w{w}", flush=True)
+    s = shape_of(dtype, d, G, w, 900)
+    i = synth.gen_layer(s, 8)
+    q, k, v = i.f64()
+    x = np.einsum("gtrd,gnd->gtrn", q.reshape(2, G, w, d), k) / np.sqrt(d)
+    x[..., s.n - w:][..., np.arange(w)[None, :] > np.arange(w)[:, None]] = -np.inf
+    m = x.max(-1, keepdims=True)
+    lse = (m + np.log(np.exp(x - m).sum(-1, keepdims=True))).reshape(2 * G, w)
+    want = O.lava_scores(q, k, v, s.window, s.pool_kernel)[0]
+    # the log-sum-exp is handed over in 32 bits: 6e-8 of a value around 10 is 6e-7 of a score
+    check([s], [want], scores_of(lava, [s], [(i.q_win, i.k, i.v)], lse=torch.from_numpy(lse.astype(np.float32)).cuda()))
