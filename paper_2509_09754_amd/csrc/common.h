@@ -145,6 +145,7 @@ struct SweepArgs {
   char* ws;
   size_t off_stat_part, off_vnorm_part, off_sraw, off_ent_part, off_counter;   // inside a sequence's region
   int H, H_kv, w, G, n_chunks, pool_half;   // G: row blocks per KV group
+  int heads;                 // query heads per KV group
   int bph;                   // row blocks per query head: 1 (w <= 32) or 2
   int rph;                   // rows per query head in a block: 32, or 16 or 8 where heads share one
   int token_norm;            // value factor per token: vnorm leaves ||V[g, i]||_1 in scores[g][i], the pooling step multiplies by it

@@ -382,7 +382,7 @@ __device__ __forceinline__ void wave_barrier() {
 struct Unit {
   int z, y, x;
 };
-__device__ __forceinline__ RowMap row_map(const SweepArgs& a) { return RowMap{a.H / a.H_kv, a.G, a.bph, a.rph, a.w}; }
+__device__ __forceinline__ RowMap row_map(const SweepArgs& a) { return RowMap{a.heads, a.G, a.bph, a.rph, a.w}; }
 __device__ __forceinline__ Unit unit_of_block(const SweepArgs& a) {
   Unit u;
   u.z = 0;
@@ -520,7 +520,7 @@ stats_kernel(const SweepArgs a) {
 #pragma unroll
     for (int i = 0; i < kQSlots; ++i) {
       const int t = wave_in_chunk * kQSlots + i;
-      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
+      if (t < GT) request_q<DT, D, NC * GT>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
     }
   }
   // with the value rows first, the ring holds both streams in turn: the wavefront's cnt_v value tiles, then
@@ -708,7 +708,7 @@ __device__ __forceinline__ void write_bias(const float2* s_merge, int nh, int h0
     const float2 x = lds_read64(lds_addr(s_merge) + (unsigned int)(sl * M::kRows + (int)threadIdx.x) * 8u);
     merge_stat(m, z, x.x, x.y, c2);
   }
-  const bool real = t < nh && row_at(rm, h0 + t, (int)(threadIdx.x & 31)).real;
+  const bool real = t < nh && row_at<GT>(rm, h0 + t, (int)(threadIdx.x & 31)).real;
   const float bias = real ? m * c2 + log2f(z) + log2f((float)rm.w) : INFINITY;
   lds_write32(lds_addr(s_bias) + threadIdx.x * 4u, bias);
 }
@@ -718,7 +718,7 @@ __device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict_
                                             const float* s_bias) {
   if (merger < 0 || merger >= GT * 32) return;
   const int t = merger >> 5;
-  const RowAt at = row_at(rm, h0 + t, merger & 31);
+  const RowAt at = row_at<GT>(rm, h0 + t, merger & 31);
   float bias = INFINITY;
   if (t < nh && at.real) bias = lse[(long long)at.head * rm.w + at.row] * kLog2e + log2f((float)rm.w);
   lds_write32(lds_addr(s_bias) + (unsigned int)merger * 4u, bias);
@@ -1093,7 +1093,7 @@ scores_kernel(const SweepArgs a) {
 #pragma unroll
     for (int i = 0; i < kQSlots; ++i) {
       const int t = wave_in_chunk * kQSlots + i;
-      if (t < GT) request_q<DT, D>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
+      if (t < GT) request_q<DT, D, NC * GT>(dma, q_win, h0, nh, t, rm, lane, q_buffer(t));
     }
     asm volatile("" ::: "memory");
   };

@@ -213,6 +213,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
   a.H_kv = d.n_kv_heads;
   a.w = d.window;
   a.bph = sweep_blocks_per_head(d);
+  a.heads = d.n_q_heads / d.n_kv_heads;
   a.rph = sweep_rows_per_head(d);
   a.G = sweep_blocks_per_group(d);
   a.n_chunks = plan_max.n_chunks;

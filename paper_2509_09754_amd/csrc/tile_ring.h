@@ -352,10 +352,12 @@ struct RowAt {
   int head, row;   // query head of the layer, window row
   bool real;       // the head exists and has that row
 };
-// Row r (0 .. 31) of row block hb, blocks counted through the KV groups.
+// Row r (0 .. 31) of row block hb, blocks counted through the KV groups.  BLOCKS: of the kernel's group; heads can share
+// a block only where that is the whole group (the choice costs the other kernels a us of set-up).
+template <int BLOCKS>
 __device__ __forceinline__ RowAt row_at(const RowMap& m, int hb, int r) {
   RowAt x;
-  if (m.rph == 32) {                                           // uniform
+  if (BLOCKS > 1 || m.rph == 32) {                             // uniform
     x.head = hb / m.bph;
     x.row = (hb % m.bph) * 32 + r;
     x.real = x.row < m.w;
@@ -444,7 +446,7 @@ __device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, in
   bool finite = true;
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
-    const RowAt at = row_at(rm, hb0 + t, r);
+    const RowAt at = row_at<GT>(rm, hb0 + t, r);
     u32x4 raw[T::kSteps];
 #pragma unroll
     for (int j = 0; j < T::kSteps; ++j) {
@@ -460,13 +462,13 @@ __device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, in
 // Row block hb of the chunk hb0 .. hb0 + nh - 1 as a tile in LDS, requested with direct-to-LDS loads by one
 // wavefront: no registers, and the block is read once per workgroup.  Rows beyond the window repeat its last
 // one, blocks beyond the chunk its last block: their results are masked or never used.
-template <int DT, int D>
+template <int DT, int D, int BLOCKS>
 __device__ __forceinline__ void request_q(const TileDma<DT, D>& dma, const u32x4* __restrict__ qg, int hb0, int nh, int t,
                                           const RowMap& rm, int lane, u32x4* buf) {
   using T = Tile<DT, D>;
   const int hb = hb0 + (t < nh ? t : nh - 1);
   const char* q = reinterpret_cast<const char*>(qg);
-  if (rm.rph == 32) {                                          // uniform: one head's rows, which follow each other
+  if (BLOCKS > 1 || rm.rph == 32) {                            // uniform: one head's rows, which follow each other
     const int head = hb / rm.bph, row0 = (hb % rm.bph) * 32;
     dma.issue_clamped(q + ((long long)head * rm.w + row0) * T::kRowBytes, 0, rm.w - row0 < 32 ? rm.w - row0 : 32, lane, buf);
     return;
