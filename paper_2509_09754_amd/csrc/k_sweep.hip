@@ -1632,11 +1632,11 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   int64_t tpb = (n_tiles + max_bx - 1) / max_bx;
   // Short sequences: spans so short that their tiles and the pooling halo's two are one round of the eight
   // wavefronts (4115 tokens, 8 heads: 16 tiles a workgroup 48.0 us a layer, 8: 44.6, 6: 44.3, 4: 45.4);
-  // 32-bit inputs, whose products take 16 times as long, half of that (1024 tokens, 2 heads: 16 tiles 69.5 us,
-  // 8: 52.0, 6: 48.0, 4: 44.2), or with d_h 64 two, whose four tiles with the halo are one for every SIMD, where the
-  // device has the workgroups for it (1024 tokens 39.1 -> 35.5 us, 4096 41.7 -> 40.1; three tiles, five with the
-  // halo, lose: 9000 tokens 44.5 -> 45.3).
-  const int64_t shortest = d.dtype != LAVA_F32 ? 6 : (d.head_dim == 64 && tpb <= 2 ? 2 : 4);
+  // 32-bit inputs, whose products take several times as long, four (1024 tokens, 2 heads: 16 tiles 69.5 us,
+  // 8: 52.0, 6: 48.0, 4: 44.2), or two where the device has the workgroups for it (d_h 64, 1024 tokens 39.1 -> 35.5 us,
+  // 4096 41.7 -> 40.1; d_h 128, 8 heads, 1000 tokens 47.7 -> 42.2, 2048 48.9 -> 44.5; three tiles, five with the
+  // halo, lose: d_h 64, 9000 tokens 44.5 -> 45.3).
+  const int64_t shortest = d.dtype != LAVA_F32 ? 6 : (tpb <= 2 ? 2 : 4);
   if (tpb < shortest) tpb = shortest;
   // all heads of a group in one workgroup -> the scores kernel can finish the scores itself, which
   // needs the workgroup's span of raw scores in LDS: a bounded number of tiles per workgroup
