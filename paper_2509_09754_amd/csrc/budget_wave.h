@@ -26,10 +26,24 @@ struct WaveSync {
   }
 };
 
+// Data-parallel-primitive moves (a shift inside rows of 16 lanes, then the last lane of one row to the next ones): as
+// shuffles, twelve trips through the LDS unit each, the sums were half of the routine (cascade plan of 8 layers 4.8 -> 4.0 us, eight steps 270 -> 260).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_add_i64(long long x) {
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)x, CTRL, ROWS, 0xf, false);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)((unsigned long long)x >> 32), CTRL, ROWS, 0xf, false);
+  return x + (long long)(((unsigned long long)hi << 32) | lo);
+}
 __device__ __forceinline__ long long wave_sum(long long x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-  return x;
+  x = dpp_add_i64<0x111, 0xf>(x);
+  x = dpp_add_i64<0x112, 0xf>(x);
+  x = dpp_add_i64<0x114, 0xf>(x);
+  x = dpp_add_i64<0x118, 0xf>(x);
+  x = dpp_add_i64<0x142, 0xa>(x);
+  x = dpp_add_i64<0x143, 0xc>(x);
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)x, 63);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)((unsigned long long)x >> 32), 63);
+  return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
 // The same routine run by the 64 lanes of one wavefront (the workgroup): every per-layer quantity
@@ -43,17 +57,17 @@ __device__ inline int allocate_budgets_wave(int lane, int n, const double* ed, l
                                             const long long* hi, long long* out, double* quota,
                                             long long* base, int* freel, double* frac, long long* state) {
 #pragma clang fp contract(off)
-  long long slo = 0, shi = 0, bad = 0;
+  long long slo = 0, shi = 0;
+  bool bad = false;
   for (int i = lane; i < n; i += 64) {
-    if (lo[i] > hi[i] || lo[i] < 0) bad = 1;
+    if (lo[i] > hi[i] || lo[i] < 0) bad = true;
     slo += lo[i];
     shi += hi[i];
     freel[i] = i;
   }
-  bad = wave_sum(bad);
   slo = wave_sum(slo);
   shi = wave_sum(shi);
-  if (bad != 0 || slo > total || shi < total) return 1;
+  if (__ballot(bad) != 0ull || slo > total || shi < total) return 1;
   Sync::sync();
   int nf = n;
   long long remaining = total;
@@ -103,21 +117,19 @@ __device__ inline int allocate_budgets_wave(int lane, int n, const double* ed, l
       }
     }
     Sync::sync();
-    long long excess = 0, deficit = 0, n_over = 0, n_under = 0;
+    long long excess = 0, deficit = 0;
+    bool over = false, under = false;
     for (int j = lane; j < nf; j += 64) {
       const int i = freel[j];
-      if (base[j] > hi[i]) { excess += base[j] - hi[i]; ++n_over; }
-      if (base[j] < lo[i]) { deficit += lo[i] - base[j]; ++n_under; }
+      if (base[j] > hi[i]) { excess += base[j] - hi[i]; over = true; }
+      if (base[j] < lo[i]) { deficit += lo[i] - base[j]; under = true; }
     }
-    excess = wave_sum(excess);
-    deficit = wave_sum(deficit);
-    n_over = wave_sum(n_over);
-    n_under = wave_sum(n_under);
-    if (n_over == 0 && n_under == 0) {
+    const bool any_over = __ballot(over) != 0ull, any_under = __ballot(under) != 0ull;
+    if (!any_over && !any_under) {
       for (int j = lane; j < nf; j += 64) out[freel[j]] = base[j];
       break;
     }
-    const bool pin_over = n_over > 0 && excess >= deficit;
+    const bool pin_over = any_over && wave_sum(excess) >= wave_sum(deficit);
     if (lane == 0) {
       int keep = 0;
       long long rest = remaining;

@@ -168,31 +168,33 @@ __global__ void __launch_bounds__(64) cascade_plan_kernel(int n_layers, int n_he
     return;
   }
   __shared__ BudgetScratch sc;
+  __shared__ long long s_out[kMaxLayers];               // the budgets: read again here, which through memory is another trip
   // the in-place gather later in the same step meets at a grid-wide barrier: its counter starts at zero
   if (gather_sync != nullptr) {
     gather_sync[threadIdx.x] = 0u;
     gather_sync[64 + threadIdx.x] = 0u;
   }
+  // rows held by this lane's first layer: on their way beside the statistics
+  long long held_first = hi;
+  if ((int)threadIdx.x + 1 < n_layers) held_first = (long long)head_offsets_cur[(long long)threadIdx.x * (n_heads + 1) + n_heads];
   for (int i = threadIdx.x; i < n_layers; i += 64) {
     sc.ed[i] = (double)e[i];
     sc.lo[i] = lo;
     sc.hi[i] = hi;
   }
   __syncthreads();
-  long long* out_b = reinterpret_cast<long long*>(out);
-  const int bad = allocate_budgets_wave<BlockSync>((int)threadIdx.x, n_layers, sc.ed, total, sc.lo, sc.hi, out_b, sc.quota, sc.base, sc.freel,
+  const int bad = allocate_budgets_wave<BlockSync>((int)threadIdx.x, n_layers, sc.ed, total, sc.lo, sc.hi, s_out, sc.quota, sc.base, sc.freel,
                                         sc.frac, sc.state);
-  if (bad)
-    for (int i = threadIdx.x; i < n_layers; i += 64) out_b[i] = -1;
   __syncthreads();
   for (int t = threadIdx.x; t < n_layers; t += 64) {
     long long held = hi;
     if (t + 1 < n_layers) {
-      held = (long long)head_offsets_cur[(long long)t * (n_heads + 1) + n_heads];
+      held = t < 64 ? held_first : (long long)head_offsets_cur[(long long)t * (n_heads + 1) + n_heads];
       held = held < 0 ? 0 : held;
     }
     const long long cap = held < bound ? held : bound;
-    long long kept = out_b[t];
+    long long kept = bad ? -1 : s_out[t];
+    out[t] = kept;
     kept = kept < 0 ? 0 : (kept < cap ? kept : cap);
     sc.base[t] = kept;
   }
