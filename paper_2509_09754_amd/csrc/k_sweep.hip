@@ -211,14 +211,14 @@ __device__ __forceinline__ void plan_budgets(const BudgetPlanArgs& plan, const P
 // has seen (the two lane halves see different keys of the same rows).
 template <int DT, int D, int GT>
 __device__ __forceinline__ void stats_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], long long tile, long long n, const RowMap& rm,
-                                           float c2, const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
+                                           float c2, const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_parts, int lane,
                                            float (&m_run)[GT], float (&z_run)[GT]) {
   const int r = lane & (rm.rph - 1), half = lane >> 5, w = rm.w;   // r: window row, in the first block of two
   const long long key0 = tile * kTileKeys;
   // 32-bit inputs: all heads' products at once (the split of the keys is shared); bf16: head by head, so that
   // the next head's matrix instructions run beside this head's exponentials
   f32x16 all[DT == LAVA_F32 ? GT : 1];
-  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, true>(kf, qf, q_finite, all);
+  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, true>(kf, qf, q_parts, all);
   auto head_dots = [&](int t) -> f32x16 {
     if constexpr (DT == LAVA_F32) return all[t];
     else return dot_tile<D, true>(kf, qf[t]);
@@ -281,7 +281,7 @@ template <int DT, int D, int GT, int WAVES, int STAGES>
 __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const FragReader<DT, D>& frags,
                                             const char* __restrict__ kg, long long n, const RowMap& rm, float c2,
                                             long long first, int cnt, u32x4* ring,
-                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
+                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_parts, int lane,
                                             float (&m_run)[GT], float (&z_run)[GT], int slot0 = 0) {
   using T = Tile<DT, D>;
   static_assert((STAGES & (STAGES - 1)) == 0, "ring slots are taken modulo a power of two");
@@ -296,7 +296,7 @@ __device__ __forceinline__ void stats_tiles(const TileDma<DT, D>& dma, const Fra
     wait_tile<DT, D>(younger);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + ((it + slot0) % STAGES) * T::kTileBytes, kf);
-    stats_tile<DT, D, GT>(kf, first + (long long)it * WAVES, n, rm, c2, qf, q_finite, lane, m_run, z_run);
+    stats_tile<DT, D, GT>(kf, first + (long long)it * WAVES, n, rm, c2, qf, q_parts, lane, m_run, z_run);
   }
 }
 
@@ -543,7 +543,7 @@ stats_kernel(const SweepArgs a) {
   // more than the set-up gains.)  Both are in before the loop: otherwise the compiler, which cannot count
   // the ring's loads across iterations, waits for everything in flight before each tile's products.
   u32x4 qf[GT][kQVec<DT, D>];
-  bool q_finite = true;
+  bool q_parts = true;
   if constexpr (VN) {
     int young = 0;
     if constexpr (!kQFirst) {
@@ -556,15 +556,15 @@ stats_kernel(const SweepArgs a) {
     for (int t = 0; t < GT; ++t) {
       u32x4 raw[T::kSteps];
       frags.read(lds_addr(q_buffer(t)), raw);
-      q_finite &= make_q<DT, D>(raw, qf[t]);
+      q_parts &= make_q<DT, D>(raw, qf[t]);
     }
     wave_barrier();
     if constexpr (kQFirst) first_tiles();
   } else {
-    q_finite = load_q<DT, D, GT>(q_win, h0, nh, rm, lane, qf);
+    q_parts = load_q<DT, D, GT>(q_win, h0, nh, rm, lane, qf);
     wait_vmcnt<0>();
   }
-  q_finite = __ballot(!q_finite) == 0ull;
+  q_parts = __ballot(!q_parts) == 0ull;
   float v_best = 0.0f;
   int slot0 = 0;
   if constexpr (VN) {
@@ -576,7 +576,7 @@ stats_kernel(const SweepArgs a) {
     }
   }
   float m_run[GT], z_run[GT];
-  stats_tiles<DT, D, GT, kPerChunk, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+  stats_tiles<DT, D, GT, kPerChunk, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_parts, lane, m_run,
                                              z_run, slot0);
   if constexpr (VN) {
     __shared__ float s_vmax[kWaves];
@@ -729,10 +729,10 @@ __device__ __forceinline__ void bias_of_lse(int merger, const float* __restrict_
 // a lane in result register v: 8 * (v / 4) + 4 * half + v % 4 -> four float4 per head).
 template <int DT, int D, int GT>
 __device__ __forceinline__ float score_tile(const u32x4 (&kf)[Tile<DT, D>::kSteps], float c2, unsigned int bias_addr,
-                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, const RowMap& rm) {
+                                            const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_parts, const RowMap& rm) {
   float best = 0.0f, pair = 0.0f;
   f32x16 all[DT == LAVA_F32 ? GT : 1];
-  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, false>(kf, qf, q_finite, all);
+  if constexpr (DT == LAVA_F32) dot_tiles<D, GT, false>(kf, qf, q_parts, all);
   auto head_dots = [&](int t) -> f32x16 {
     if constexpr (DT == LAVA_F32) return all[t];
     else return dot_tile<D, false>(kf, qf[t]);
@@ -804,7 +804,7 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
                                              long long t_begin, long long t_end, int n_own, bool halo_left,
                                              bool halo_right, int n_jobs, int (&fifo)[STAGES], u32x4* ring,
                                              unsigned int* next_job, const float* s_bias, float* s_span,
-                                             const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_finite, int lane,
+                                             const u32x4 (&qf)[GT][kQVec<DT, D>], bool q_parts, int lane,
                                              float* __restrict__ raw_head, int n_chunks, const RowMap& rm) {
   using T = Tile<DT, D>;
   auto job_tile = [&](int j) -> long long {
@@ -856,7 +856,7 @@ __device__ __forceinline__ void scores_tiles(const TileDma<DT, D>& dma, const Fr
     if constexpr (!FUSED) store_result(pend_key, pend);
     u32x4 kf[T::kSteps];
     frags.read(ring_addr + (it % STAGES) * T::kTileBytes, kf);
-    const float best = score_tile<DT, D, GT>(kf, c2, bias_addr, qf, q_finite, rm);
+    const float best = score_tile<DT, D, GT>(kf, c2, bias_addr, qf, q_parts, rm);
     if constexpr (FUSED) {
       span_put<SHARED_SPAN>(span_base + (unsigned int)(tile - t_begin + 1) * (kTileKeys * 4), best);
     } else {
@@ -1119,20 +1119,20 @@ scores_kernel(const SweepArgs a) {
   wave_barrier();
   if (lse == nullptr) write_bias<NC * GT, kWaves>(s_merge, wg_nh, wg_h0, rm, c2, s_bias);
   u32x4 qf[GT][kQVec<DT, D>];
-  bool q_finite = true;
+  bool q_parts = true;
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
     u32x4 raw[T::kSteps];
     frags.read(lds_addr(q_buffer(t)), raw);
-    q_finite &= make_q<DT, D>(raw, qf[t]);
+    q_parts &= make_q<DT, D>(raw, qf[t]);
   }
-  q_finite = __ballot(!q_finite) == 0ull;
+  q_parts = __ballot(!q_parts) == 0ull;
   wave_barrier();
   if constexpr (kQFirst) first_tiles();
 
   scores_tiles<DT, D, GT, kPerChunk, kStages, FUSED, (NC > 1)>(
       dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left, halo_right, n_jobs, fifo, ring,
-      &s_next_job[NC == 1 ? 0 : wave_chunk], s_bias + (NC == 1 ? 0 : wave_chunk * GT * 32), s_span, qf, q_finite, lane,
+      &s_next_job[NC == 1 ? 0 : wave_chunk], s_bias + (NC == 1 ? 0 : wave_chunk * GT * 32), s_span, qf, q_parts, lane,
       s_raw + (long long)g * n_prefix, n_chunks, rm);
   if constexpr (FUSED) {
     __shared__ float s_vb[kWaves];
@@ -1226,15 +1226,15 @@ sweep_kernel(const SweepArgs a) {
   auto q_commit = [&](u32x4 (&qf)[GT][kQVec<DT, D>], int younger) -> bool {
     if (wave < GT) wait_tile<DT, D>(younger);
     __syncthreads();
-    bool finite = true;
+    bool parts = true;
 #pragma unroll
     for (int t = 0; t < GT; ++t) {
       u32x4 raw[T::kSteps];
       frags.read(lds_addr(&sm.tile[t][kStages - 1][0]), raw);
-      finite &= make_q<DT, D>(raw, qf[t]);
+      parts &= make_q<DT, D>(raw, qf[t]);
     }
     __syncthreads();
-    return __ballot(!finite) == 0ull;
+    return __ballot(!parts) == 0ull;
   };
   auto seq_of_unit = [&](int u) {
     int si = 0;
@@ -1284,12 +1284,12 @@ sweep_kernel(const SweepArgs a) {
       for (int p = 0; p < kStages - 1; ++p)
         if (p < cnt) dma.issue(kg, first + (long long)p * kWaves, n, lane, ring + p * T::kTileChunks);
       u32x4 qf[GT][kQVec<DT, D>];
-      bool q_finite = load_q<DT, D, GT>(static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + si) * a.H * w * T::kCpr, g * G,
+      bool q_parts = load_q<DT, D, GT>(static_cast<const u32x4*>(a.q_win) + (long long)(a.first_seq + si) * a.H * w * T::kCpr, g * G,
                                         G < GT ? G : GT, rm, lane, qf);
       wait_vmcnt<0>();
-      q_finite = __ballot(!q_finite) == 0ull;
+      q_parts = __ballot(!q_parts) == 0ull;
       float m_run[GT], z_run[GT];
-      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_finite, lane, m_run,
+      stats_tiles<DT, D, GT, kWaves, kStages>(dma, frags, kg, n, rm, c2, first, cnt, ring, qf, q_parts, lane, m_run,
                                               z_run);
       float2 mine;
       if (stats_merge_waves<GT, kWaves, 1>(m_run, z_run, c2, lane, wave, sm.red, mine))
@@ -1352,7 +1352,7 @@ sweep_kernel(const SweepArgs a) {
         ++primed;
       }
     u32x4 qf[GT][kQVec<DT, D>];
-    const bool q_finite = q_commit(qf, primed);
+    const bool q_parts = q_commit(qf, primed);
 
     // The head's statistics.  A wait that lasts looks for statistics units of this head nobody has
     // claimed (their owners are not resident yet); one is then run above and this unit set up again.
@@ -1412,7 +1412,7 @@ sweep_kernel(const SweepArgs a) {
     __syncthreads();
     scores_tiles<DT, D, GT, kWaves, kStages, true, false>(dma, frags, kg, n, n_prefix, c2, t_begin, t_end, n_own, halo_left,
                                                    halo_right, n_jobs, fifo, ring, &sm.next_job, sm.bias, sm.sc.span,
-                                                   qf, q_finite, lane, nullptr, 1, rm);
+                                                   qf, q_parts, lane, nullptr, 1, rm);
     scores_finish<kThreads>(pa, vb, g, n, n_prefix, w, t_begin, t_end, n_tiles, sm.sc.span, sm.vb, sm.ss, sm.st,
                             &sm.last, (unsigned int)(sq.blocks_x * H_kv), (unsigned int)(g * sq.blocks_x + bx), H_kv,
                             bx == 0, wave, reinterpret_cast<unsigned int*>(&sm.tile[0][0][0]));

@@ -394,6 +394,7 @@ __device__ __forceinline__ void split8(const u32x4& a, const u32x4& b, u32x4& hi
     lo[i] = pack_bf16(r0 - bf16_low(mid[i]), r1 - bf16_high(mid[i]));
   }
 }
+// A NaN does not count.
 __device__ __forceinline__ float abs_max8(const u32x4& a, const u32x4& b, float m) {
   const unsigned int x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
@@ -401,8 +402,14 @@ __device__ __forceinline__ float abs_max8(const u32x4& a, const u32x4& b, float 
   return m;
 }
 
-// A head's query rows from their chunks.  Returns true if every value is finite (f32: the parts of the others would
-// not add up to them, so an infinite value or a NaN is its first part, the rest zero, and dot_tiles goes another way).
+// Products of parts stand for products of values where both are below this: no part, product of parts or sum of 128
+// products overflows, which with parts of either sign would give a NaN for a product that is infinite (a key that the
+// type's lowest value masks, a query of 2^24 and more), and a last part that is lost below the type's smallest values
+// (2^-133) is less than 2^-73 of a logit.
+constexpr float kPartsLimit = 1152921504606846976.0f;            // 2^60
+
+// A head's query rows from their chunks.  Returns true if products of their parts may be used (f32; the parts add up to
+// the value either way: of an infinity or NaN, which has no others, the first part is the value and the rest zero).
 template <int DT, int D>
 __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], u32x4 (&q)[kQVec<DT, D>]) {
   if constexpr (DT == LAVA_BF16) {
@@ -410,15 +417,14 @@ __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], 
     for (int j = 0; j < Tile<DT, D>::kSteps; ++j) q[j] = raw[j];
     return true;
   } else {
-    float sum = 0.0f;                                            // an infinity or NaN leaves a NaN in its second part
+    float top = 0.0f;
 #pragma unroll
     for (int j = 0; j < Tile<DT, D>::kSteps; j += 2) {
+      top = abs_max8(raw[j], raw[j + 1], top);
       split8(raw[j], raw[j + 1], q[j / 2 * 3], q[j / 2 * 3 + 1], q[j / 2 * 3 + 2]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sum += fabsf(bf16_low(q[j / 2 * 3 + 1][i])) + fabsf(bf16_high(q[j / 2 * 3 + 1][i]));
     }
-    const bool finite = sum == sum;
-    if (__ballot(!finite) != 0ull) {                             // uniform, rare
+    const bool parts = top < kPartsLimit;
+    if (__ballot(!parts) != 0ull) {                              // uniform, rare
 #pragma unroll
       for (int j = 0; j < Tile<DT, D>::kSteps * 4; ++j) {
         const unsigned int x = raw[j / 4][j % 4], shift = 16 * (j & 1);
@@ -431,19 +437,19 @@ __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], 
         }
       }
     }
-    return finite;
+    return parts;
   }
 }
 
 // Query fragments of the chunk's row blocks hb0 .. hb0 + nh - 1, one copy per wavefront straight from
 // global memory: row r = lane % 32 of the block (zero beyond the window or the chunk).  Returns this lane's share of
-// "all finite".
+// "products of parts may be used".
 template <int DT, int D, int GT>
 __device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, int nh, const RowMap& rm, int lane,
                                        u32x4 (&qf)[GT][kQVec<DT, D>]) {
   using T = Tile<DT, D>;
   const int r = lane & 31, half = lane >> 5;
-  bool finite = true;
+  bool parts = true;
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
     const RowAt at = row_at<GT>(rm, hb0 + t, r);
@@ -454,9 +460,9 @@ __device__ __forceinline__ bool load_q(const u32x4* __restrict__ qg, int hb0, in
       if (t < nh && at.real) x = qg[((long long)at.head * rm.w + at.row) * T::kCpr + 2 * j + half];
       raw[j] = x;
     }
-    finite &= make_q<DT, D>(raw, qf[t]);
+    parts &= make_q<DT, D>(raw, qf[t]);
   }
-  return finite;
+  return parts;
 }
 
 // Row block hb of the chunk hb0 .. hb0 + nh - 1 as a tile in LDS, requested with direct-to-LDS loads by one
@@ -502,11 +508,11 @@ __device__ __forceinline__ f32x16 dot_tile(const u32x4 (&kf)[Tile<LAVA_BF16, D>:
 // keys and 128 values takes 48 bf16 instructions of 32 cycles per head (32-bit: 64 of 64 cycles), the split 350
 // vector instructions of 5 cycles, shared by two heads (more do not fit the registers).  Layer of 9001 tokens, 32 heads
 // on 8: 86.9 -> 75.5 us, error of the scores against 64 bits 1.0e-6 -> 6.2e-7; 1024 tokens of 64 values, 8 heads on 2:
-// 35.0 -> 32.0 us, 5.1e-7 -> 3.1e-7.  Tiles or queries with infinities or NaN go through the 32-bit instructions,
-// query rows put together again.
+// 35.0 -> 32.0 us, 5.1e-7 -> 3.1e-7.  Tiles or queries with large values or infinities (kPartsLimit) go through the
+// 32-bit instructions, query rows put together again; a NaN's parts are NaN.
 template <int D, int GT, bool KEYS_AS_ROWS>
 __device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::kSteps],
-                                          const u32x4 (&qf)[GT][kQVec<LAVA_F32, D>], bool q_finite, f32x16 (&acc)[GT]) {
+                                          const u32x4 (&qf)[GT][kQVec<LAVA_F32, D>], bool q_parts, f32x16 (&acc)[GT]) {
   constexpr int kPairs = Tile<LAVA_F32, D>::kSteps / 2;
   float top = 0.0f;
 #pragma unroll
@@ -516,7 +522,7 @@ __device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::k
   auto mul = [&](int t, const u32x4& k, const u32x4& q) {
     acc[t] = KEYS_AS_ROWS ? mfma_bf16(k, q, acc[t]) : mfma_bf16(q, k, acc[t]);
   };
-  if (q_finite && __ballot(!(top < INFINITY)) == 0ull) {
+  if (q_parts && __ballot(!(top < kPartsLimit)) == 0ull) {
     u32x4 hi[kPairs];
 #pragma unroll
     for (int j = 0; j < kPairs; ++j) {
@@ -547,8 +553,9 @@ __device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::k
           const int at = (j & 1) * 2 + i / 2;
           unsigned int part[3] = {qf[t][j / 2 * 3][at], qf[t][j / 2 * 3 + 1][at], qf[t][j / 2 * 3 + 2][at]};
           asm volatile("" : "+v"(part[0]), "+v"(part[1]), "+v"(part[2]));   // or they are put together ahead of the sweep's loop
-          const float q = (i & 1) ? (bf16_high(part[0]) + bf16_high(part[1])) + bf16_high(part[2])
-                                  : (bf16_low(part[0]) + bf16_low(part[1])) + bf16_low(part[2]);
+          // the second and third part first: the second one rounds, and with the first would overflow at the largest values
+          const float q = (i & 1) ? bf16_high(part[0]) + (bf16_high(part[1]) + bf16_high(part[2]))
+                                  : bf16_low(part[0]) + (bf16_low(part[1]) + bf16_low(part[2]));
           const float k = __uint_as_float(kf[j][i]);
           acc[t] = KEYS_AS_ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(k, q, acc[t], 0, 0, 0)
                                 : __builtin_amdgcn_mfma_f32_32x32x2f32(q, k, acc[t], 0, 0, 0);

@@ -102,3 +102,36 @@ def test_heads_sharing_a_block_take_the_callers_log_sum_exp(lava, dtype, d, G, w
     want = O.lava_scores(q, k, v, s.window, s.pool_kernel)[0]
     # the log-sum-exp is handed over in 32 bits: 6e-8 of a value around 10 is 6e-7 of a score
     check([s], [want], scores_of(lava, [s], [(i.q_win, i.k, i.v)], lse=torch.from_numpy(lse.astype(np.float32)).cuda()))
+
+
+@pytest.mark.parametrize("big_q", [1.0, 2.0**10, 2.0**25, 2.0**70])
+@pytest.mark.parametrize("d,G,w", [(64, 4, 32), (128, 4, 32), (128, 1, 7)])
+def test_32_bit_products_that_overflow(lava, d, G, w, big_q):
+    """Keys masked by the type's lowest value (or near it) against queries of any size: the product is the lowest value or
+    minus infinity, the key's weight zero and the other keys' weights what they are without it.  No part of a value and no
+    product of parts may overflow to the other side."""
+    print(f"32-bit products that overflow d{d} G{G} w{w} query {big_q}", flush=True)
+    s = shape_of("f32", d, G, w, 700)
+    i = synth.gen_layer(s, 6)
+    q, k, v = (np.array(x, dtype=np.float32) for x in (i.q_win, i.k, i.v))
+    top = np.finfo(np.float32).max
+    q[..., 1] = np.float32(big_q)
+    k[..., 1] = 0.0
+    for row, x in ((40, -top), (77, -top * np.float32(0.5020)), (300, -top * np.float32(0.9980))):
+        k[:, row, 1] = x
+    want = O.lava_scores(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), s.window, s.pool_kernel)[0]
+    assert np.isfinite(want).all()
+    check([s], [want], scores_of(lava, [s], [(q, k, v)]))
+
+
+def test_32_bit_queries_of_the_largest_value(lava):
+    """A query row with the largest value, put together again from its parts for the 32-bit instructions."""
+    print("32-bit queries of the largest value", flush=True)
+    s = shape_of("f32", 128, 2, 32, 700)
+    i = synth.gen_layer(s, 7)
+    q, k, v = (np.array(x, dtype=np.float32) for x in (i.q_win, i.k, i.v))
+    q[..., 1] = np.finfo(np.float32).max
+    k[..., 1] = 0.0
+    k[:, 5, 1] = 2.0**-128                                       # times the query: 1 - 2^-24
+    want = O.lava_scores(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), s.window, s.pool_kernel)[0]
+    check([s], [want], scores_of(lava, [s], [(q, k, v)]))
