@@ -374,8 +374,9 @@ __device__ __forceinline__ RowAt row_at(const RowMap& m, int hb, int r) {
 // chunks their three bf16 parts (f32, see split8).
 template <int DT, int D> constexpr int kQVec = DT == LAVA_BF16 ? Tile<DT, D>::kSteps : Tile<DT, D>::kSteps / 2 * 3;
 
-// 32-bit values as sums of three bf16: x = hi + mid + lo, exactly (8 + 8 + 8 bits; hi is cut, so that it never
-// overflows, the others are rounded).  `a` and `b`: four values each.
+// 32-bit values as sums of three bf16: x = hi + mid + lo, exactly (8 + 8 + 8 bits, each part what is nearest to what
+// the parts before it leave; 32-bit products of such parts: Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019).  `a` and `b`: four values each.
 __device__ __forceinline__ unsigned int pack_bf16(float lo, float hi) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -387,11 +388,30 @@ __device__ __forceinline__ void split8(const u32x4& a, const u32x4& b, u32x4& hi
   const unsigned int x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const unsigned int x0 = x[2 * i], x1 = x[2 * i + 1];
-    hi[i] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
-    const float r0 = __uint_as_float(x0) - bf16_high(x0), r1 = __uint_as_float(x1) - bf16_high(x1);
+    const float x0 = __uint_as_float(x[2 * i]), x1 = __uint_as_float(x[2 * i + 1]);
+    hi[i] = pack_bf16(x0, x1);
+    const float r0 = x0 - bf16_low(hi[i]), r1 = x1 - bf16_high(hi[i]);
     mid[i] = pack_bf16(r0, r1);
     lo[i] = pack_bf16(r0 - bf16_low(mid[i]), r1 - bf16_high(mid[i]));
+  }
+}
+// The same for any values: hi is cut instead, so that it does not overflow, and infinities and NaN are a first part only.
+__device__ __forceinline__ void split8_any(const u32x4& a, const u32x4& b, u32x4& hi, u32x4& mid, u32x4& lo) {
+  const unsigned int x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    unsigned int h[2];
+    float r[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const unsigned int u = x[2 * i + e];
+      const bool special = (u & 0x7f800000u) == 0x7f800000u;
+      h[e] = (u & 0xffff0000u) | (special && (u & 0x007fffffu) != 0u ? 0x00400000u : 0u);   // a NaN stays one
+      r[e] = special ? 0.0f : __uint_as_float(u) - __uint_as_float(h[e]);
+    }
+    hi[i] = __builtin_amdgcn_perm(h[1], h[0], 0x07060302u);
+    mid[i] = pack_bf16(r[0], r[1]);
+    lo[i] = pack_bf16(r[0] - bf16_low(mid[i]), r[1] - bf16_high(mid[i]));
   }
 }
 // A NaN does not count.
@@ -401,15 +421,14 @@ __device__ __forceinline__ float abs_max8(const u32x4& a, const u32x4& b, float 
   for (int i = 0; i < 8; i += 2) m = fmaxf(fmaxf(m, fabsf(__uint_as_float(x[i]))), fabsf(__uint_as_float(x[i + 1])));
   return m;
 }
-
 // Products of parts stand for products of values where both are below this: no part, product of parts or sum of 128
 // products overflows, which with parts of either sign would give a NaN for a product that is infinite (a key that the
-// type's lowest value masks, a query of 2^24 and more), and a last part that is lost below the type's smallest values
-// (2^-133) is less than 2^-73 of a logit.
+// type's lowest value masks, a query of 2^24 and more), and a part that is lost below the smallest normal values (2^-126)
+// changes a product by less than 2^-66.
 constexpr float kPartsLimit = 1152921504606846976.0f;            // 2^60
 
 // A head's query rows from their chunks.  Returns true if products of their parts may be used (f32; the parts add up to
-// the value either way: of an infinity or NaN, which has no others, the first part is the value and the rest zero).
+// the value either way).
 template <int DT, int D>
 __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], u32x4 (&q)[kQVec<DT, D>]) {
   if constexpr (DT == LAVA_BF16) {
@@ -419,23 +438,16 @@ __device__ __forceinline__ bool make_q(const u32x4 (&raw)[Tile<DT, D>::kSteps], 
   } else {
     float top = 0.0f;
 #pragma unroll
-    for (int j = 0; j < Tile<DT, D>::kSteps; j += 2) {
-      top = abs_max8(raw[j], raw[j + 1], top);
-      split8(raw[j], raw[j + 1], q[j / 2 * 3], q[j / 2 * 3 + 1], q[j / 2 * 3 + 2]);
-    }
+    for (int j = 0; j < Tile<DT, D>::kSteps; j += 2) top = abs_max8(raw[j], raw[j + 1], top);
     const bool parts = top < kPartsLimit;
-    if (__ballot(!parts) != 0ull) {                              // uniform, rare
+    if (__ballot(!parts) == 0ull) {                              // uniform
 #pragma unroll
-      for (int j = 0; j < Tile<DT, D>::kSteps * 4; ++j) {
-        const unsigned int x = raw[j / 4][j % 4], shift = 16 * (j & 1);
-        if ((x & 0x7f800000u) == 0x7f800000u) {
-          u32x4* part = &q[j / 8 * 3];
-          const int at = j % 8 / 2;
-          if (x & 0x007fffffu) part[0][at] |= 0x0040u << shift;
-          part[1][at] &= ~(0xffffu << shift);
-          part[2][at] &= ~(0xffffu << shift);
-        }
-      }
+      for (int j = 0; j < Tile<DT, D>::kSteps; j += 2)
+        split8(raw[j], raw[j + 1], q[j / 2 * 3], q[j / 2 * 3 + 1], q[j / 2 * 3 + 2]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < Tile<DT, D>::kSteps; j += 2)
+        split8_any(raw[j], raw[j + 1], q[j / 2 * 3], q[j / 2 * 3 + 1], q[j / 2 * 3 + 2]);
     }
     return parts;
   }
@@ -503,46 +515,64 @@ __device__ __forceinline__ f32x16 dot_tile(const u32x4 (&kf)[Tile<LAVA_BF16, D>:
 }
 
 // The same for 32-bit inputs and all heads of a chunk at once.  The 32-bit matrix instruction has a sixteenth of the
-// bf16 rate, so values are taken as three bf16 parts and six of the nine products summed, the small ones first: what is
-// left out (mid*lo, lo*mid, lo*lo) is below 2^-24 of a product of the values.  Bound by the vector unit: a tile of 32
-// keys and 128 values takes 48 bf16 instructions of 32 cycles per head (32-bit: 64 of 64 cycles), the split 350
-// vector instructions of 5 cycles, shared by two heads (more do not fit the registers).  Layer of 9001 tokens, 32 heads
-// on 8: 86.9 -> 75.5 us, error of the scores against 64 bits 1.0e-6 -> 6.2e-7; 1024 tokens of 64 values, 8 heads on 2:
-// 35.0 -> 32.0 us, 5.1e-7 -> 3.1e-7.  Tiles or queries with large values or infinities (kPartsLimit) go through the
-// 32-bit instructions, query rows put together again; a NaN's parts are NaN.
+// bf16 rate, so values are taken as three bf16 parts and six of the nine products summed: hi*hi on its own, the small
+// ones together, and then the two sums, by an addition that rounds to nearest where the matrix unit cuts.  What is left
+// out (mid*lo, lo*mid, lo*lo) is below 0.99 * 2^-24 of a product of the values.  Error of the logits against 64 bits, in
+// 2^-24 of the logit, where one channel makes the row (all roundings add up): largest 2.0, rms 0.45; 32-bit instructions
+// 1.3 and 0.44 (hi cut instead of rounded and one sum: 5.2 and 0.60; with mid*lo and lo*mid: 1.3 and 0.44, sweeps 12 %
+// longer).  Of the scores of normally distributed rows of 128 channels: largest 1.0e-6, rms 3.4e-7; 32-bit instructions
+// 2.4e-6 and 3.9e-7.
+// Bound by the vector unit: a tile of 32 keys and 128 values takes 48 bf16 instructions of 32 cycles per head (32-bit:
+// 64 of 64 cycles), the split 350 vector instructions of 5 cycles, shared by two heads (more do not fit the registers).
+// Scores of a layer of 9001 tokens, 32 heads on 8: 72.7 -> 61.6 us; 1024 tokens of 64 values, 8 heads on 2: 22.8 -> 16.5.
+// Tiles or queries with large values or infinities (kPartsLimit) go through the 32-bit instructions, query rows put
+// together again; a NaN's parts are NaN.
 template <int D, int GT, bool KEYS_AS_ROWS>
-__device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::kSteps],
+__device__ __forceinline__ void dot_tiles(const u32x4 (&kf_in)[Tile<LAVA_F32, D>::kSteps],
                                           const u32x4 (&qf)[GT][kQVec<LAVA_F32, D>], bool q_parts, f32x16 (&acc)[GT]) {
   constexpr int kPairs = Tile<LAVA_F32, D>::kSteps / 2;
+  u32x4 kf[2 * kPairs];
+#pragma unroll
+  for (int j = 0; j < 2 * kPairs; ++j) kf[j] = kf_in[j];
   float top = 0.0f;
 #pragma unroll
   for (int j = 0; j < kPairs; ++j) top = abs_max8(kf[2 * j], kf[2 * j + 1], top);
 #pragma unroll
   for (int t = 0; t < GT; ++t) acc[t] = f32x16{0};
-  auto mul = [&](int t, const u32x4& k, const u32x4& q) {
-    acc[t] = KEYS_AS_ROWS ? mfma_bf16(k, q, acc[t]) : mfma_bf16(q, k, acc[t]);
+  auto mul = [&](const u32x4& k, const u32x4& q, f32x16& sum) {
+    sum = KEYS_AS_ROWS ? mfma_bf16(k, q, sum) : mfma_bf16(q, k, sum);
   };
   if (q_parts && __ballot(!(top < kPartsLimit)) == 0ull) {
     u32x4 hi[kPairs];
+    f32x16 small[GT];
+#pragma unroll
+    for (int t = 0; t < GT; ++t) small[t] = f32x16{0};
 #pragma unroll
     for (int j = 0; j < kPairs; ++j) {
       u32x4 mid, lo;
       split8(kf[2 * j], kf[2 * j + 1], hi[j], mid, lo);
+      // the next pair's split begins here: with all of them in front of the products the query rows leave the vector
+      // registers and are copied back for every tile (160 moves, 5 % of the time)
+      if (j + 1 < kPairs) asm volatile("" : "+v"(kf[2 * j + 2]), "+v"(kf[2 * j + 3]), "+v"(hi[j]), "+v"(mid), "+v"(lo));
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, lo, qf[t][3 * j]);
+      for (int t = 0; t < GT; ++t) mul(lo, qf[t][3 * j], small[t]);
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j + 2]);
+      for (int t = 0; t < GT; ++t) mul(hi[j], qf[t][3 * j + 2], small[t]);
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, mid, qf[t][3 * j + 1]);
+      for (int t = 0; t < GT; ++t) mul(mid, qf[t][3 * j + 1], small[t]);
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, mid, qf[t][3 * j]);
+      for (int t = 0; t < GT; ++t) mul(mid, qf[t][3 * j], small[t]);
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j + 1]);
+      for (int t = 0; t < GT; ++t) mul(hi[j], qf[t][3 * j + 1], small[t]);
     }
 #pragma unroll
     for (int j = 0; j < kPairs; ++j)
 #pragma unroll
-      for (int t = 0; t < GT; ++t) mul(t, hi[j], qf[t][3 * j]);
+      for (int t = 0; t < GT; ++t) mul(hi[j], qf[t][3 * j], acc[t]);
+#pragma unroll
+    for (int t = 0; t < GT; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[t][v] += small[t][v];
   } else {
 #pragma unroll
     for (int j = 0; j < 2 * kPairs; ++j)
@@ -553,7 +583,7 @@ __device__ __forceinline__ void dot_tiles(const u32x4 (&kf)[Tile<LAVA_F32, D>::k
           const int at = (j & 1) * 2 + i / 2;
           unsigned int part[3] = {qf[t][j / 2 * 3][at], qf[t][j / 2 * 3 + 1][at], qf[t][j / 2 * 3 + 2][at]};
           asm volatile("" : "+v"(part[0]), "+v"(part[1]), "+v"(part[2]));   // or they are put together ahead of the sweep's loop
-          // the second and third part first: the second one rounds, and with the first would overflow at the largest values
+          // the second and third part first: with the first, the second one could overflow at the largest values
           const float q = (i & 1) ? bf16_high(part[0]) + (bf16_high(part[1]) + bf16_high(part[2]))
                                   : bf16_low(part[0]) + (bf16_low(part[1]) + bf16_low(part[2]));
           const float k = __uint_as_float(kf[j][i]);

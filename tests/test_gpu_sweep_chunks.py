@@ -135,3 +135,31 @@ def test_32_bit_queries_of_the_largest_value(lava):
     k[:, 5, 1] = 2.0**-128                                       # times the query: 1 - 2^-24
     want = O.lava_scores(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), s.window, s.pool_kernel)[0]
     check([s], [want], scores_of(lava, [s], [(q, k, v)]))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_32_bit_products_of_one_channel(lava, d):
+    """Rows whose logit is one product (an outlier channel), with mantissas that make the left-out products of parts as
+    large as they get, of one sign.  Against a key whose product has one digit and no error, a logit is off by at most
+    0.99 * 2^-24 of it for what is left out and 2^-24 for the rounding of the sum; 0.25 * 2^-24 for the exponential and the
+    score (half a unit each in 32 bits, of a logit of about 256)."""
+    print(f"32-bit products of one channel d{d}", flush=True)
+    heads, n = 16, 1201
+    rng = np.random.Generator(np.random.PCG64(9))
+    q, k, v = np.zeros((heads, 1, d), np.float32), np.zeros((heads, n, d), np.float32), np.ones((heads, n, d), np.float32)
+    for h, bits in enumerate([0x3f80fe80, 0x3f807f40, 0x3f803f40, 0x3f817f40] * (heads // 4)):
+        x = np.uint32(bits).view(np.float32)
+        at = int(rng.integers(d))
+        q[h, 0, at] = 16 * x
+        k[h, :, at] = 16 + 16 * rng.random(n) / 128
+        k[h, 100:400, at] = 16 * x
+        k[h, 0, at] = 16.0
+    desc = lava.LayerDesc.make(heads, heads, d, 1, "f32", pool_kernel=1, softmax_scale=1.0)
+    scores, _, _ = lava.lava_window_scores(desc, [n], *(lava.to_device(x, "f32") for x in (q, k, v)))
+    torch.cuda.synchronize()
+    got = scores.cpu().numpy().reshape(heads, n)[:, : n - 1].astype(np.float64)
+    logits = (q.astype(np.float64) @ k.astype(np.float64).transpose(0, 2, 1))[:, 0, : n - 1]
+    err = np.log(got / got[:, :1]) - (logits - logits[:, :1])
+    worst = float(np.max(np.abs(err) / logits)) * 2.0**24
+    print(f"   worst {worst:.2f} * 2^-24 of the logit", flush=True)
+    assert worst < 0.99 + 1.0 + 0.25
