@@ -758,7 +758,8 @@ __device__ __forceinline__ float score_tile(const u32x4 (&kf)[Tile<DT, D>::kStep
         break;
       }
       if (rm.rph == 16) {
-        best = fmaxf(add_halves(share(share(0.0f, 0), 1)), add_halves(share(share(0.0f, 2), 3)));
+        best = fmaxf(best, add_halves(share(share(0.0f, 0), 1)));   // a NaN does not count, so the score stays a number
+        best = fmaxf(best, add_halves(share(share(0.0f, 2), 3)));
         break;
       }
     }

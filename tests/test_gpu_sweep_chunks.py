@@ -163,3 +163,32 @@ def test_32_bit_products_of_one_channel(lava, d):
     worst = float(np.max(np.abs(err) / logits)) * 2.0**24
     print(f"   worst {worst:.2f} * 2^-24 of the logit", flush=True)
     assert worst < 0.99 + 1.0 + 0.25
+
+
+@pytest.mark.parametrize("what", ["nan key", "inf key", "inf query", "nan window"])
+@pytest.mark.parametrize("dtype,d,G,w", [("bf16", 128, 2, 16), ("bf16", 64, 2, 9), ("f32", 64, 2, 16), ("f32", 128, 2, 5), ("bf16", 128, 4, 8),
+                                         ("f32", 64, 3, 8)])
+def test_heads_sharing_a_block_with_values_that_are_not_finite(lava, dtype, d, G, w, what):
+    """A head whose attention is not a number takes no part in its group's maximum, and a group of such heads scores zero,
+    whether its heads share a row block or not: the same heads twice in the group, too many for one block, give the same
+    scores."""
+    print(f"heads sharing a block, {what}, {dtype} d{d} G{G} w{w}", flush=True)
+    s = shape_of(dtype, d, G, w, 900)
+    i = synth.gen_layer(s, 12)
+    q, k, v = (lava.to_device(x, dtype).clone() for x in (i.q_win, i.k, i.v))
+    if what == "nan key":
+        k[0, 50, 3] = float("nan")
+    elif what == "inf key":
+        k[0, 50, 3], k[1, 60, 4] = float("inf"), float("-inf")
+    elif what == "inf query":
+        q[0, 1, 5] = float("inf")
+    else:
+        k[0, s.n - 1, 3] = float("nan")                          # seen by the last window row alone
+    twice = torch.cat([x.repeat(2, 1, 1) for x in q.view(2, G, w, d)])
+    out = []
+    for heads, x in ((G, q), (2 * G, twice)):
+        desc = lava.LayerDesc.make(2 * heads, 2, d, w, dtype)
+        out.append([t.cpu().numpy() for t in lava.lava_window_scores(desc, [s.n], x.contiguous(), k, v)])
+    assert not np.isnan(out[0][0]).any()
+    for got, want in zip(*out):
+        np.testing.assert_allclose(got, want, rtol=1e-5)
