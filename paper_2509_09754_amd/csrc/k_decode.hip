@@ -562,10 +562,14 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   const int64_t total = (int64_t)batch * (rows_capacity + (int64_t)d.n_kv_heads * tail_tiles * kTileKeys);
   // Rows per unit: the device holds two workgroups per compute unit at a time; the units should fill whole rounds of
   // those, with as few units as that allows (every unit pays its set-up and leaves a partial result to merge).
-  // A head is expected to waste half a unit.  One round if heads are then still cut into several units, which evens
-  // them out (16 x 8192 rows: 384 rows a unit, one round, 19.5 us, 256, two rounds, 22.4; 32 x 8192: 768, one round,
-  // 35.4, 384 38.1; one sequence of a million rows: 2048 109, 1024 122); otherwise at least two, so that the
-  // dispatcher can (64 x 8192 rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
+  // A head is expected to waste half a unit.  One round if heads are then still cut, 1.33 units a head or more on average,
+  // which evens them out (16 x 8192 rows: 384 rows a unit, one round, 19.5 us, 256, two rounds, 22.4; 32 x 8192, on the
+  // line: 768, one round, 35.4, 384 38.1), and its units are no longer than 1280 rows: the last ones end unevenly by as
+  // much (20 x 32768: 1536, one round, 80.0, 768, two, 67.7; 16 x 32768: 1280, one round, 48.7, 640 52.8); with d_h 64, of
+  // which four workgroups share a compute unit, so that one round of two leaves half the wavefronts out, 384 rows (24 x
+  // 8192: 512, one round, 19.2, 256 17.9; 32 x 8192: 768 23.6, 384 20.6).  Otherwise at least two rounds, so that the dispatcher
+  // can even them out (64 x 8192 rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
+  const int64_t one_round = d.head_dim == 64 && d.dtype == LAVA_BF16 ? 384 : 1280;
   const int64_t resident = 2 * (int64_t)device_cus();
   const int64_t heads = (int64_t)batch * d.n_kv_heads;
   int64_t c = 16 * step;
@@ -573,7 +577,7 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
     const int64_t room = rounds * resident - heads / 2;
     if (room <= 0) continue;
     c = ((total + room - 1) / room + step - 1) / step * step;
-    if (rounds == 1 && c > step && 4 * c * heads > 3 * total) continue;
+    if (rounds == 1 && c > step && (4 * c * heads > 3 * total || c > one_round)) continue;
     if (c <= 16 * step) break;
   }
   if (c < step) c = step;
