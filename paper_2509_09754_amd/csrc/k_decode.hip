@@ -564,13 +564,15 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   // those, with as few units as that allows (every unit pays its set-up and leaves a partial result to merge).
   // A head is expected to waste half a unit.  One round if heads are then still cut, 1.33 units a head or more on average,
   // which evens them out (16 x 8192 rows: 384 rows a unit, one round, 19.5 us, 256, two rounds, 22.4; 32 x 8192, on the
-  // line: 768, one round, 35.4, 384 38.1), and its units are no longer than 1280 rows or an eighth of a head: the last ones
+  // line: 768, one round, 35.4, 384 38.1), and its units are no longer than 1280 rows or a quarter of a head: the last ones
   // end unevenly by as much (20 x 32768: 1536, one round, 80.0, 768, two, 67.7; 16 x 32768: 1280, one round, 48.7, 640
-  // 52.8; one sequence of a million rows, 8 heads: 2048, one round, 109, 1024 122); with d_h 64, of
-  // which four workgroups share a compute unit, so that one round of two leaves half the wavefronts out, 384 rows (24 x
-  // 8192: 512, one round, 19.2, 256 17.9; 32 x 8192: 768 23.6, 384 20.6).  Otherwise at least two rounds, so that the dispatcher
-  // can even them out (64 x 8192 rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
-  const int64_t one_round = d.head_dim == 64 && d.dtype == LAVA_BF16 ? 384 : 1280;
+  // 52.8; 8 x 100000, 4 KV heads: 1792, one round, 88.8, 896 99.0; one sequence of a million rows: 2048, one round, 109,
+  // 1024 122).  bf16 with d_h 64, of which four workgroups share a compute unit, so that one round of two leaves half the
+  // wavefronts out: 384 rows or an eighth of a head (24 x 8192: 512, one round, 19.2, 256 17.9; 32 x 8192: 768 23.6, 384
+  // 20.6; 8 x 100000: 51.7 and 47.7).  Otherwise at least two rounds, so that the dispatcher can even them out (64 x 8192
+  // rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
+  const bool small = d.head_dim == 64 && d.dtype == LAVA_BF16;
+  const int64_t one_round = small ? 384 : 1280, per_head = small ? 8 : 4;
   const int64_t resident = 2 * (int64_t)device_cus();
   const int64_t heads = (int64_t)batch * d.n_kv_heads;
   int64_t c = 16 * step;
@@ -578,7 +580,7 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
     const int64_t room = rounds * resident - heads / 2;
     if (room <= 0) continue;
     c = ((total + room - 1) / room + step - 1) / step * step;
-    if (rounds == 1 && c > step && (4 * c * heads > 3 * total || (c > one_round && 8 * c * heads > total))) continue;
+    if (rounds == 1 && c > step && (4 * c * heads > 3 * total || (c > one_round && per_head * c * heads > total))) continue;
     if (c <= 16 * step) break;
   }
   if (c < step) c = step;
