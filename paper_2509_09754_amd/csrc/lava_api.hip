@@ -429,8 +429,9 @@ static int32_t check_compact_problem(const lava_layer_desc& d, const lava_compac
     return LAVA_ERR_INVALID_ARG;
   if (!aligned16(p.k_src) || !aligned16(p.v_src) || !aligned16(p.k_out) || !aligned16(p.v_out))
     return LAVA_ERR_INVALID_ARG;
+  // no more rows can survive than there are; with an output offset the capacity is the whole pool's, which others share
   const int64_t rows = p.src_offsets ? p.src_rows : (int64_t)d.n_kv_heads * p.src_rows;
-  if (p.capacity > rows) return LAVA_ERR_BUDGET;
+  if (p.capacity > rows && p.out_offset_dev == nullptr) return LAVA_ERR_BUDGET;
   return LAVA_OK;
 }
 

@@ -339,6 +339,8 @@ def test_batch_select_and_compact_argument_errors():
     assert cmp([okc, okc]) == lava.LAVA_OK                                          # capacities 0: nothing launched
     assert cmp([okc, cchanged(capacity=8 * 1024 + 1)]) == lava.LAVA_ERR_BUDGET      # dense source: H_kv * n rows
     assert cmp([okc, cchanged(src_offsets=0x10000, capacity=1025)]) == lava.LAVA_ERR_BUDGET   # packed source: pool rows
+    # with an output offset the capacity is a pool's that several layers share; accepted, so the next row's error is told
+    assert cmp([cchanged(capacity=8 * 1024 + 1, out_offset_dev=0x10000), cchanged(k_out=None)]) == lava.LAVA_ERR_INVALID_ARG
     assert cmp([okc, cchanged(k_out=None)]) == lava.LAVA_ERR_INVALID_ARG
     assert cmp([okc, cchanged(k_src=0x10008)]) == lava.LAVA_ERR_INVALID_ARG         # rows move as 16-byte words
     assert cmp([okc, cchanged(src_rows=0)]) == lava.LAVA_ERR_INVALID_ARG

@@ -161,3 +161,43 @@ def test_config3_full_stack_cascade_equals_single_shot_equals_oracle(lava, in_pl
         assert len(mine & theirs) >= 0.999 * b_min, l
         assert np.all(np.diff(r_offs) >= w)                                   # Eq. 1: the window is always kept
     say(f"   least kept-set overlap with the oracle's own selection: {least:.5f}")
+
+
+def test_pool_larger_than_any_layer(lava):
+    """Short layers packed into one pool: every compaction is told the pool's rows, more than its own layer has."""
+    say("stack: a pool larger than any of its layers")
+    L, n, hkv, d, w, total = 5, 96, 2, 64, 8, 5 * 100
+    dense = hkv * n
+    assert total > dense
+    inps = [synth.gen_layer(synth.LayerShape(8, hkv, d, n, w, "bf16", 0, heavy_count=4), 60 + t) for t in range(L)]
+    desc = lava.LayerDesc.make(8, hkv, d, w, "bf16")
+    k, v = (torch.stack([lava.to_device(getattr(i, x), "bf16") for i in inps]) for x in ("k", "v"))
+    rng = np.random.Generator(np.random.PCG64(8))
+    scores = rng.random((L, hkv, n)).astype(np.float32)
+    scores[:, :, n - w:] = np.inf
+    scores_dev = torch.from_numpy(scores).cuda()
+    budgets = [60, 140, dense, 16, 92]
+    assert sum(budgets) == total
+    first = torch.tensor(np.concatenate([[0], np.cumsum(budgets)]), dtype=torch.int64, device="cuda")
+    budgets_dev = torch.tensor(budgets, dtype=torch.int64, device="cuda")
+    counts = torch.empty(L, hkv, dtype=torch.int32, device="cuda")
+    offs = torch.empty(L, hkv + 1, dtype=torch.int64, device="cuda")
+    idx, pos = (torch.empty(total, dtype=torch.int32, device="cuda") for _ in range(2))
+    k_hat, v_hat = (torch.empty(total, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    sel, cmp = [], []
+    for t in range(L):
+        sel.append(lava.select_problem(scores_dev[t], dense, counts[t], offs[t], idx, budget_dev=budgets_dev[t: t + 1],
+                                       out_offset_dev=first[t: t + 1]))
+        cmp.append(lava.compact_problem(desc, n, k[t].view(-1, d), v[t].view(-1, d), offs[t], idx, total, k_hat, v_hat, pos_out=pos,
+                                        out_offset_dev=first[t: t + 1]))
+    lava.lava_select_topk_batch(hkv, sel, dense)
+    lava.lava_compact_batch(desc, cmp)
+    torch.cuda.synchronize()
+    uniform = np.arange(hkv + 1) * n
+    kh, vh, pos, at = lava.to_host_bits(k_hat), lava.to_host_bits(v_hat), pos.cpu().numpy(), 0
+    for t in range(L):
+        rc, ro, ri, _ = O.select_topk(scores[t].astype(np.float64).ravel(), uniform, budgets[t])
+        end = at + budgets[t]
+        assert np.array_equal(offs[t].cpu().numpy(), ro) and np.array_equal(pos[at:end], ri)
+        assert np.array_equal(kh[at:end], O.compact(inps[t].k, ro, ri)) and np.array_equal(vh[at:end], O.compact(inps[t].v, ro, ri))
+        at = end
