@@ -73,7 +73,7 @@ constexpr int kMaxChunkHeads = 4;    // query heads a wavefront keeps in registe
 struct SweepPlan {
   int chunk_heads;     // GT: row blocks (32 window rows of one head) per chunk (<= kMaxChunkHeads; <= 2 for f32)
   int wg_chunks;       // chunks a workgroup handles, each by its own wavefronts: 2 where the group has two, 4 for three or
-                       // four of f32, else 1
+                       // four of f32, else (and where the sequence has its group apart) 1
   int n_chunks;        // workgroups a group is split over: chunks / wg_chunks
   int blocks_x;        // workgroups along the key axis per (KV head, chunk)
   int tiles_per_block; // key tiles per workgroup
@@ -84,8 +84,10 @@ struct SweepPlan {
   bool narrow;         // 4-wavefront workgroups, two per CU (launches of several rounds of workgroups)
 };
 // batch_tokens: tokens of all sequences that share the launches (0 or n: the sequence is alone);
-// narrow: ask for the two-per-CU shape (ignored where the kernels have only one shape)
-SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens = 0, bool narrow = false);
+// narrow: ask for the two-per-CU shape (ignored where the kernels have only one shape);
+// apart: a chunk per workgroup also where one could handle them all (sweep_apart)
+SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens, bool narrow, bool apart);
+bool sweep_apart(const lava_layer_desc& d, int batch, int64_t n, bool statistics);
 bool sweep_has_narrow_shape(const lava_layer_desc& d);
 int sweep_device_wgs();   // compute units of the current device
 int sweep_rows_per_head(const lava_layer_desc& d);     // rows a head has in a row block: 32, or 16 or 8 where heads share one
@@ -101,7 +103,7 @@ struct ScoreWorkspace {
   size_t off_counter;     // uint32 "last workgroup done" tickets
   size_t bytes;
 };
-ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n);
+ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n, bool apart);
 int pool_blocks(const lava_layer_desc& d, int64_t n);
 
 int32_t launch_vnorm(const lava_layer_desc& d, int64_t n, const void* v, float* vnorm_part,
@@ -176,7 +178,7 @@ int32_t launch_sweep(const lava_layer_desc& d, const SweepArgs& a, const SweepPl
 // not fused (a group split into chunks): one sequence per launch, raw scores to the region's s_raw
 int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, const SweepPlan& p, hipStream_t s);
 float sweep_exp2_scale(const lava_layer_desc& d);
-int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const float* s_raw,
+int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const SweepPlan& p, const float* s_raw,
                         const float* vnorm_part, int vnorm_blocks, float* scores, float* vbar,
                         float* layer_stat, double2* ent_part, uint32_t* counters, unsigned int* sel_hist0,
                         const BudgetPlanArgs& plan, int plan_seq, hipStream_t s);

@@ -1601,20 +1601,48 @@ int sweep_blocks_per_group(const lava_layer_desc& d) {
 
 bool sweep_has_narrow_shape(const lava_layer_desc& d) { return !(d.dtype == LAVA_F32 && d.head_dim == 128); }
 
-SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens, bool narrow) {
-  SweepPlan p;
+static int sweep_chunk_heads(const lava_layer_desc& d) {
   const int G = sweep_blocks_per_group(d);
-  int gt = kMaxChunkHeads;
-  if (d.dtype == LAVA_F32) gt = 2;     // query rows as three bf16 parts
-  p.chunk_heads = G < gt ? G : gt;     // even whenever heads have two blocks: a head's blocks stay in one chunk
-  if (p.chunk_heads == 3) p.chunk_heads = 4;   // kernels are built for 1, 2 and 4 heads per chunk
-  const int chunks = (G + p.chunk_heads - 1) / p.chunk_heads;
-  // A group of two chunks (f32: up to four) is swept by one workgroup, each chunk by a share of its wavefronts: the
-  // scores meet in its LDS and it finishes them.  Split over workgroups they meet in memory, where they have to be
-  // cleared first, and a pooling launch finishes them (28 heads on 4, 21013 tokens: 51.0 us a layer, in one workgroup
-  // 49.3; and the sequences of a batch then share their launches).  More chunks would leave a wavefront or
-  // less to each.
-  p.wg_chunks = chunks == 2 ? 2 : d.dtype != LAVA_F32 ? 1 : chunks > 2 && chunks <= 4 ? 4 : 1;
+  const int gt = d.dtype == LAVA_F32 ? 2 : kMaxChunkHeads;   // f32: query rows as three bf16 parts
+  const int heads = G < gt ? G : gt;   // even whenever heads have two blocks: a head's blocks stay in one chunk
+  return heads == 3 ? 4 : heads;       // kernels are built for 1, 2 and 4 heads per chunk
+}
+
+static int sweep_chunks(const lava_layer_desc& d) {
+  const int heads = sweep_chunk_heads(d);
+  return (sweep_blocks_per_group(d) + heads - 1) / heads;
+}
+
+// A group of two chunks (f32: up to four) can be swept by one workgroup, each chunk by a share of its wavefronts: the
+// scores meet in its LDS and it finishes them, and the sequences of a batch share their launches (f32, d_h 128, 8 heads on
+// 2, 8 x 1000 tokens: 42 us, one sequence after the other 205).  Apart, a workgroup for each chunk, the scores meet in
+// memory, where they have to be cleared first, and a pooling launch finishes them; but a chunk has all wavefronts of a
+// workgroup and a short sequence twice or four times the workgroups.  A sequence alone has its group apart where the device
+// has few tiles a compute unit (scores and selection, in one workgroup -> apart):
+//   two chunks, from 1 tile (below it a span is one round of a chunk's wavefronts, make_sweep_plan) to 10: bf16, d_h 128,
+//     40 heads on 8, 9001 tokens 45.9 -> 44.2 us, 14000 51.0 -> 51.5; 10 on 2, 32768 45.7 -> 43.1, 65536 55.8 -> 56.3;
+//     f32, d_h 64, 32 on 8, 9001 50.9 -> 48.0, 20000 68.5 -> 71.4; not where the caller's log-sum-exp leaves one sweep of
+//     the two (bf16, d_h 128, 28 on 4, 9001 28.7 -> 29.8);
+//   f32 with d_h 128, of four wavefronts a workgroup, two chunks, up to 5: 8 on 2, 1024 34.9 -> 34.0, 20000 60.7 -> 58.3; 32
+//     on 8, 9001 72.9 -> 74.7;
+//   three, always (a fourth repeats a head in one workgroup): 12 on 2, 1024 44.7 -> 34.2; 48 on 8, 40000 315 -> 277;
+//   four, up to 20: 16 on 2, 1024 44.9 -> 34.5, 40000 110 -> 102; 64 on 8, 20000 175.4 -> 174.5, 40000 316 -> 331.
+// (f32 with d_h 64 and more chunks: the same time either way.)
+bool sweep_apart(const lava_layer_desc& d, int batch, int64_t n, bool statistics) {
+  if (batch > 1) return false;
+  const int chunks = sweep_chunks(d);
+  const int64_t tiles = (n + kTileKeys - 1) / kTileKeys * d.n_kv_heads, cus = compute_units();
+  if (d.dtype == LAVA_F32 && d.head_dim == 128)
+    return chunks == 3 || (chunks == 2 && tiles <= 5 * cus) || (chunks == 4 && tiles <= 20 * cus);
+  return statistics && chunks == 2 && tiles > cus && tiles <= 10 * cus;
+}
+
+SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens, bool narrow, bool apart) {
+  SweepPlan p;
+  p.chunk_heads = sweep_chunk_heads(d);
+  const int chunks = sweep_chunks(d);
+  // more chunks would leave a wavefront or less to each
+  p.wg_chunks = apart ? 1 : chunks == 2 ? 2 : d.dtype != LAVA_F32 ? 1 : chunks > 2 && chunks <= 4 ? 4 : 1;
   p.n_chunks = p.wg_chunks > 1 ? 1 : chunks;
   p.narrow = narrow && sweep_has_narrow_shape(d);
   const int64_t n_tiles = (n + kTileKeys - 1) / kTileKeys;
@@ -1636,8 +1664,9 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   // 32-bit inputs, whose products take several times as long, four (1024 tokens, 2 heads: 16 tiles 69.5 us,
   // 8: 52.0, 6: 48.0, 4: 44.2), or two where the device has the workgroups for it (d_h 64, 1024 tokens 39.1 -> 35.5 us,
   // 4096 41.7 -> 40.1; d_h 128, 8 heads, 1000 tokens 47.7 -> 42.2, 2048 48.9 -> 44.5; three tiles, five with the
-  // halo, lose: d_h 64, 9000 tokens 44.5 -> 45.3).
-  const int64_t shortest = d.dtype != LAVA_F32 ? 6 : (tpb <= 2 ? 2 : 4);
+  // halo, lose: d_h 64, 9000 tokens 44.5 -> 45.3); and two for the four wavefronts of each of two chunks (bf16, d_h 128,
+  // 16 heads on 2, 1024 tokens, scores alone: 21.2 -> 17.6 us, three tiles 18.9).
+  const int64_t shortest = d.dtype != LAVA_F32 ? (p.wg_chunks == 2 ? 2 : 6) : (tpb <= 2 ? 2 : 4);
   if (tpb < shortest) tpb = shortest;
   // all heads of a group in one workgroup -> the scores kernel can finish the scores itself, which
   // needs the workgroup's span of raw scores in LDS: a bounded number of tiles per workgroup
@@ -1695,8 +1724,8 @@ static size_t ent_blocks(const lava_layer_desc& d, int64_t n, const SweepPlan& p
   return pool > sweep ? pool : sweep;
 }
 
-ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n) {
-  const SweepPlan p = make_sweep_plan(d, n);
+ScoreWorkspace make_score_workspace(const lava_layer_desc& d, int64_t n, bool apart) {
+  const SweepPlan p = make_sweep_plan(d, n, 0, false, apart);
   ScoreWorkspace w;
   size_t off = 0;
   w.off_stat_part = off;
@@ -1852,12 +1881,12 @@ int32_t launch_scores(const lava_layer_desc& d, const SweepArgs& a, const SweepP
   return launch_status();
 }
 
-int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const float* s_raw,
+int32_t launch_poolstat(const lava_layer_desc& d, int64_t n, const SweepPlan& p, const float* s_raw,
                         const float* vnorm_part, int vnorm_blocks, float* scores, float* vbar,
                         float* layer_stat, double2* ent_part, uint32_t* counters, unsigned int* sel_hist0,
                         const BudgetPlanArgs& plan, int plan_seq, hipStream_t s) {
   const int64_t fine = (n + kPoolThreads * 4 - 1) / (kPoolThreads * 4);
-  const bool four = (size_t)fine <= ent_blocks(d, n, make_sweep_plan(d, n));
+  const bool four = (size_t)fine <= ent_blocks(d, n, p);
   const dim3 grid(four ? (unsigned)fine : (unsigned)pool_blocks(d, n), d.n_kv_heads), block(kPoolThreads);
   ProfScope ps(KID_POOLSTAT, s);
 #define LAVA_POOLSTAT(PER)                                                                                        \

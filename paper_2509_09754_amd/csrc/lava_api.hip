@@ -138,10 +138,12 @@ size_t lava_window_scores_workspace_bytes(const lava_layer_desc* desc, int32_t b
   // never shrinks with the length)
   const int64_t max_n = total_tokens - (int64_t)(batch - 1) * (desc->window + 1);
   if (max_n <= desc->window) return 0;
-  const size_t region = make_score_workspace(*desc, max_n).bytes;
-  // sequences of a batch are swept together, each in its own region; when a KV group has to be
-  // split into chunks they are processed one after another and share one region
-  return make_sweep_plan(*desc, max_n).fused_pool ? region * (size_t)batch : region;
+  // Sequences of a batch are swept together, each in its own region; when a KV group has to be
+  // split into chunks they are processed one after another and share one region.  Which of the two a sequence alone
+  // gets depends on its length (sweep_apart): room for either.
+  const size_t region = make_score_workspace(*desc, max_n, false).bytes, apart = make_score_workspace(*desc, max_n, true).bytes;
+  const size_t need = make_sweep_plan(*desc, max_n, 0, false, false).fused_pool ? region * (size_t)batch : region;
+  return need > apart ? need : apart;
 }
 
 // lava_window_scores, optionally preparing a selection workspace (select_ws != null) for the selections
@@ -169,9 +171,10 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     if (seq_lens[b] > max_n) max_n = seq_lens[b];
   }
   const lava_layer_desc& d = *desc;
-  const SweepPlan plan_max = make_sweep_plan(d, max_n);
-  const ScoreWorkspace region = make_score_workspace(d, max_n);
-  const bool together = plan_max.fused_pool;                 // property of the descriptor, not of the length
+  const bool apart = sweep_apart(d, batch, max_n, lse == nullptr);
+  const SweepPlan plan_max = make_sweep_plan(d, max_n, 0, false, apart);
+  const ScoreWorkspace region = make_score_workspace(d, max_n, apart);
+  const bool together = plan_max.fused_pool;                 // of a batch: a property of the descriptor, not of the lengths
   const size_t need = together ? region.bytes * (size_t)batch : region.bytes;
   if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 ||
       workspace_bytes < need)
@@ -241,7 +244,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     if (a.n_seq > 1) {
       int64_t wide_wgs = 0;
       for (int i = 0; i < a.n_seq; ++i)
-        wide_wgs += (int64_t)make_sweep_plan(d, seq_lens[b0 + i], launch_tokens).blocks_x * d.n_kv_heads * plan_max.n_chunks;
+        wide_wgs += (int64_t)make_sweep_plan(d, seq_lens[b0 + i], launch_tokens, false, apart).blocks_x * d.n_kv_heads * plan_max.n_chunks;
       narrow = wide_wgs > sweep_device_wgs();
     }
     if (tuning().sweep_shape == 1) narrow = false;           // forced by the caller's tuning
@@ -250,7 +253,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     plan_launch.narrow = narrow && sweep_has_narrow_shape(d);
     for (int i = 0; i < a.n_seq; ++i) {
       const int64_t n = seq_lens[b0 + i];
-      plan = make_sweep_plan(d, n, launch_tokens, narrow);
+      plan = make_sweep_plan(d, n, launch_tokens, narrow, apart);
       SweepSeq& sq = a.s[i];
       sq.n = n;
       sq.tok = tok;
@@ -303,7 +306,7 @@ static int32_t window_scores(const lava_layer_desc* desc, int32_t batch, const i
     if (!together) {                                         // one sequence: `plan` is its plan
       const SweepSeq& sq = a.s[0];
       char* reg = a.ws + sq.ws_off;
-      st = launch_poolstat(d, sq.n, reinterpret_cast<const float*>(reg + a.off_sraw),
+      st = launch_poolstat(d, sq.n, plan, reinterpret_cast<const float*>(reg + a.off_sraw),
                            reinterpret_cast<const float*>(reg + a.off_vnorm_part), sq.vnorm_blocks,
                            scores + (size_t)d.n_kv_heads * sq.tok, vbar + (size_t)b0 * d.n_kv_heads,
                            layer_stat + b0, reinterpret_cast<double2*>(reg + a.off_ent_part),

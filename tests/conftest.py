@@ -29,3 +29,20 @@ def tuning():
     from paper_2509_09754_amd import lava
     yield lava.set_tuning
     lava.set_tuning()
+
+
+@pytest.fixture
+def launches():
+    """launches(call): what the call returns, and how often it launched each kernel of the library."""
+    import torch
+    from paper_2509_09754_amd import lava
+
+    def count(call):
+        lava.prof_enable(True), lava.prof_reset()
+        try:
+            out = call()
+            torch.cuda.synchronize()
+            return out, {name: n for name, (_, n) in lava.prof_read().items()}
+        finally:
+            lava.prof_enable(False), lava.prof_reset()
+    return count

@@ -89,6 +89,45 @@ def test_split_group(lava, n, kind):
     assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
 
 
+# either side of the lines between which a sequence alone has its group's parts in workgroups of their own (tiles of 32 keys, of
+# all heads, a compute unit, of which there are 256)
+@pytest.mark.parametrize("dtype,d,G,n,apart", [("bf16", 128, 5, 128, 0), ("bf16", 64, 8, 129, 1), ("bf16", 128, 6, 1280, 1),
+                                               ("bf16", 64, 5, 1281, 0), ("f32", 64, 3, 129, 1), ("f32", 64, 4, 1281, 0),
+                                               ("f32", 64, 6, 500, 0), ("f32", 128, 4, 10, 1), ("f32", 128, 3, 640, 1),
+                                               ("f32", 128, 4, 641, 0), ("f32", 128, 5, 40, 1), ("f32", 128, 6, 2561, 1),
+                                               ("f32", 128, 8, 2560, 1), ("f32", 128, 7, 2561, 0)])
+@pytest.mark.parametrize("kind", ["lava", "lse", "attention"])
+def test_sequence_alone_and_its_groups_parts(lava, dtype, d, G, n, apart, kind, launches):
+    """A sequence alone and as one of a batch of two: the same scores, to the order of their sums, wherever the parts meet.
+    The workspace of the longer length does for the shorter one."""
+    print(f"parts of a group, {dtype} d{d} G{G} n={n} {kind}", flush=True)
+    hkv, w = 64, 9
+    s = synth.LayerShape(G * hkv, hkv, d, n, w, dtype, 0, heavy_count=1)
+    i = synth.gen_layer(s, n)
+    desc = lava.LayerDesc.make(G * hkv, hkv, d, w, dtype, score_kind=lava.LAVA_SCORE_ATTENTION if kind == "attention" else lava.LAVA_SCORE_LAVA)
+    q, k, v = (lava.to_device(a, dtype) for a in (i.q_win, i.k, i.v))
+    lse = torch.from_numpy(O.window_lse(*i.f64()[:2]).astype(np.float32)).cuda() if kind == "lse" else None
+    need = lava.lava_window_scores_workspace_bytes(desc, 1, n + 1)
+    assert need >= lava.lava_window_scores_workspace_bytes(desc, 1, n)
+    buf = torch.full((need + 4096,), 0x7E, dtype=torch.uint8, device="cuda")
+    (one, vbar, stat), count = launches(lambda: lava.lava_window_scores(desc, [n], q, k, v, lse=lse, workspace=buf[:need]))
+    if kind == "lse" and not (dtype == "f32" and d == 128):
+        apart = 0                                                # one sweep
+    assert count["poolstat"] == apart and bool((buf[need:] == 0x7E).all())
+    twice = [torch.cat([x.reshape(-1)] * 2) for x in (q, k, v)]
+    (two, vbar2, stat2), count = launches(lambda: lava.lava_window_scores(
+        desc, [n, n], *twice, lse=None if lse is None else torch.cat([lse.reshape(-1)] * 2).view(2 * G * hkv, w)))
+    assert count["poolstat"] == 0
+    for b in range(2):
+        np.testing.assert_allclose(two.view(2, -1)[b].cpu().numpy(), one.cpu().numpy().ravel(), rtol=1e-5)
+        assert torch.equal(vbar2[b], vbar[0])
+        np.testing.assert_allclose(stat2[b].cpu().numpy(), stat[0].cpu().numpy(), rtol=1e-4)
+    want = O.lava_scores(*i.f64(), w, 7, use_value_norm=kind != "attention")[0]
+    got = one.cpu().numpy().reshape(hkv, n)[:, : n - w].astype(np.float64)
+    mask = want > 1e-30 * want.max()
+    assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
+
+
 def test_split_group_fill_is_no_sweep(lava):
     """The attention score's fill launch writes a float per token and head (2 MB here), the score kernel reads a row of 128:
     cleared by one or two workgroups the fill took longer than the scores (58 us of events against 48), by many 6."""
