@@ -191,6 +191,44 @@ def test_select_marks_its_outputs_when_a_bounded_wait_gives_up(lava, tuning):
     assert int(err[0]) == 1                                 # the error word is the caller's to clear
 
 
+@pytest.mark.parametrize("polls", [1, 2, 4, 8, 64])
+def test_prepared_selection_whose_wait_is_over_its_limit(lava, polls, tuning):
+    """A prepared selection has one exchange between workgroups and no barrier before it: whether it completes is decided
+    by the first workgroup that has seen all words or whose wait is over its limit, set here from the host.  Every run ends,
+    and leaves either the selection or the mark in all outputs, and the status that goes with it."""
+    sh = synth.config(2, n=16384 + 5, budget=8 * 500)
+    Hkv, n, B = sh.n_kv_heads, sh.n, sh.budget
+    inp = synth.gen_layer(sh, 21)
+    desc = lava.LayerDesc.make(sh.n_q_heads, Hkv, sh.head_dim, sh.window, sh.dtype)
+    q, k, v = (lava.to_device(a, sh.dtype) for a in (inp.q_win, inp.k, inp.v))
+    ws = torch.empty(lava.lava_select_workspace_bytes(Hkv * n), dtype=torch.uint8, device="cuda")
+    want, marked = None, 0
+    for run in range(24):
+        scores, _, _ = lava.lava_window_scores(desc, [n], q, k, v, select_workspace=ws)
+        if want is None:
+            want = [x.cpu().numpy() for x in lava.lava_select_topk(Hkv, scores, B)]
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        counts = torch.full((Hkv,), 3, dtype=torch.int32, device="cuda")
+        offs = torch.full((Hkv + 1,), 5, dtype=torch.int64, device="cuda")
+        idx = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+        kept = torch.full((B,), -7.0, dtype=torch.float32, device="cuda")
+        prob = [lava.select_problem(scores, B, counts, offs, idx, kept, error_dev=err, primed=True)]
+        tuning(barrier_spin_limit=polls)
+        lava.lava_select_topk_batch(Hkv, prob, Hkv * n, workspace=ws)
+        tuning()
+        torch.cuda.synchronize()
+        if lava.lava_select_batch_status(ws, 1, Hkv * n) == lava.LAVA_OK:
+            assert int(err[0]) == 0
+            for x, y in zip((counts, offs, idx, kept), want):
+                assert np.array_equal(x.cpu().numpy(), y), run
+        else:
+            marked += 1
+            assert int(err[0]) == 1
+            assert counts.cpu().tolist() == [-1] * Hkv and offs.cpu().tolist() == [0] * (Hkv + 1), run
+            assert bool((idx == -7).all()) and bool((kept == -7.0).all())
+    say(f"prepared selection, {polls} polls: {marked} of 24 runs marked")
+
+
 def test_select_status_reports_ok(lava):
     say("select status")
     sc = torch.from_numpy(synth.random_scores(4, 5000, 23).ravel()).cuda()
@@ -275,14 +313,23 @@ SCORE_CASES = [
     ("bf16-G16", synth.LayerShape(32, 2, 128, 2100, 32, "bf16", 300)),
     ("bf16-G12-w64-d64", synth.LayerShape(24, 2, 64, 1300, 64, "bf16", 300)),
     ("w64-prefix-of-one", synth.LayerShape(8, 2, 64, 64 + 1, 64, "f32", 2 * 64 + 1, heavy_count=0)),
+    # two heads of 17 to 32 rows each, several spans: the persistent kernel of two row blocks
+    ("bf16-G2-w20", synth.LayerShape(8, 4, 128, 4000 + 3, 20, "bf16", 400)),
+    ("bf16-G2-w32-d64", synth.LayerShape(4, 2, 64, 3000, 32, "bf16", 400)),
+    ("f32-G2-w32", synth.LayerShape(4, 2, 128, 1700 + 5, 32, "f32", 400)),
+    ("f32-G2-w17-d64", synth.LayerShape(8, 4, 64, 2900, 17, "f32", 400)),
 ]
+# one workgroup has the whole group in one part, one row block a head, and heads do not share a block
+PERSISTENT = {"cfg2-small", "bf16-mha", "bf16-G3", "f32-d128-mha", "bf16-G2-w20", "bf16-G2-w32-d64", "f32-G2-w32",
+              "f32-G2-w17-d64"}
 
 
 @pytest.mark.parametrize("name,sh", SCORE_CASES, ids=[c[0] for c in SCORE_CASES])
-def test_window_scores_vs_oracle(lava, name, sh, tuning):
+def test_window_scores_vs_oracle(lava, name, sh, tuning, launches):
     """Every case under the three schedules of the sweeps (one launch per pass; value norms, then one
-    persistent launch for statistics and scores; value norms inside the statistics launch): each against the
-    oracle, and all against each other bit for bit (the same tiles are combined in the same order)."""
+    persistent launch for statistics and scores, where the shape has one; value norms inside the statistics
+    launch): each against the oracle, and all against each other bit for bit (the same tiles are combined in
+    the same order)."""
     say(f"scores {name}: {sh}")
     for seed in (0, 1):
         inp = synth.gen_layer(sh, seed)
@@ -292,7 +339,8 @@ def test_window_scores_vs_oracle(lava, name, sh, tuning):
         outs = {}
         for schedule in ("persistent", "prepass", "separate"):
             tuning(sweep_schedule=schedule)
-            _, _, got, vbar, stat = run_scores(lava, inp)
+            (_, _, got, vbar, stat), count = launches(lambda: run_scores(lava, inp))
+            assert count["sweep"] == (1 if schedule == "persistent" and name in PERSISTENT else 0), (schedule, count)
             compare_scores(sh, got, ref_s, vbar, ref_vbar, stat, ref_e)
             outs[schedule] = (got, vbar, stat)
         b = outs["separate"]
@@ -631,14 +679,21 @@ PRIMED_CASES = [
     ("cfg2-9k-narrow", synth.config(2, n=9000 + 5, budget=8 * 64), "narrow", "separate"),
     ("cfg2-9k-narrow-prepass", synth.config(2, n=9000 + 5, budget=8 * 64), "narrow", "prepass"),
     ("cfg2-20k-persistent", synth.config(2, n=20000 + 13, budget=8 * 300), "auto", "persistent"),
-    ("bf16-G8-two-chunks", synth.LayerShape(16, 2, 128, 2100, 32, "bf16", 300), "auto", "auto"),
+    ("bf16-G8-two-chunks", synth.LayerShape(16, 2, 128, 2100, 32, "bf16", 300), "auto", "auto"),   # in one workgroup
+    ("f32-G4-d64-two-chunks", synth.LayerShape(8, 2, 64, 1111, 32, "f32", 300), "auto", "auto"),
+    ("f32-G6-d64-three-chunks", synth.LayerShape(12, 2, 64, 1111, 32, "f32", 300), "auto", "separate"),
+    ("bf16-G9-split", synth.LayerShape(18, 2, 128, 2100, 32, "bf16", 300), "auto", "auto"),         # over workgroups
+    ("bf16-G7-split-by-length", synth.LayerShape(14, 2, 128, 6000, 32, "bf16", 300), "auto", "auto"),
+    ("f32-G6-split-by-length", synth.LayerShape(12, 2, 128, 1300, 32, "f32", 300), "auto", "auto"),
+    ("bf16-G12-w64-d64-split", synth.LayerShape(24, 2, 64, 1300, 64, "bf16", 300), "auto", "prepass"),
+    ("f32-G16-d64-split", synth.LayerShape(32, 2, 64, 1300, 32, "f32", 300), "auto", "separate"),
     ("f32-d128-G4", synth.LayerShape(8, 2, 128, 1111, 32, "f32", 300), "auto", "auto"),
     ("tiny-prefix", synth.LayerShape(8, 2, 64, 8 + 3, 8, "f32", 2 * 8 + 2, heavy_count=0), "auto", "auto"),
 ]
 
 
 @pytest.mark.parametrize("name,sh,shape,schedule", PRIMED_CASES, ids=[c[0] for c in PRIMED_CASES])
-def test_scores_that_prepare_their_selection(lava, name, sh, shape, schedule, tuning):
+def test_scores_that_prepare_their_selection(lava, name, sh, shape, schedule, tuning, launches):
     """lava_window_scores_primed + lava_select_topk_primed against the plain pair: the scores, the statistic and
     every output of the selection are identical bit for bit (the prepared histogram is the one the selection
     would have built), for several budgets, with the LAVa score and the per-token value-norm score; and
@@ -655,7 +710,8 @@ def test_scores_that_prepare_their_selection(lava, name, sh, shape, schedule, tu
         ws = torch.full((max(lava.lava_select_workspace_bytes(Hkv * n), 256),), 0xAB, dtype=torch.uint8, device="cuda")
         for budget in (Hkv * sh.window, sh.budget, Hkv * n - 1):
             want = lava.lava_select_topk(Hkv, s0, budget)
-            s1, vb1, e1 = lava.lava_window_scores(desc, [n], q, k, v, select_workspace=ws)
+            (s1, vb1, e1), count = launches(lambda: lava.lava_window_scores(desc, [n], q, k, v, select_workspace=ws))
+            assert count["poolstat"] == (1 if "split" in name else 0 if "chunks" in name else count["poolstat"])
             got = lava.lava_select_topk(Hkv, s1, budget, workspace=ws, primed=True)
             torch.cuda.synchronize()
             assert torch.equal(s0.view(torch.int32), s1.view(torch.int32)) and torch.equal(vb0, vb1) and torch.equal(e0, e1)
@@ -709,6 +765,10 @@ PLANNED_CASES = [
     ("cfg2-9k-5-layers", [synth.config(2, n=9000 + 5, budget=8 * 64)], 5, "auto"),
     ("cfg2-9k-128-layers-persistent", [synth.config(2, n=9000 + 5, budget=8 * 64)], 128, "persistent"),
     ("G8-two-chunks-7-layers", [synth.LayerShape(16, 2, 128, 2100, 32, "bf16", 300)], 7, "auto"),
+    ("G16-7-layers-split", [synth.LayerShape(32, 2, 128, 2100, 32, "bf16", 300)], 7, "auto"),
+    ("f32-G6-one-sequence-split", [synth.LayerShape(12, 2, 128, 1111, 32, "f32", 300)], 3, "auto"),
+    ("f32-G6-batch-of-2-three-chunks", [synth.LayerShape(12, 2, 128, n, 32, "f32", 300) for n in (400, 1111)], 3, "auto"),
+    ("G9-w40-batch-of-2-split", [synth.LayerShape(18, 2, 64, n, 40, "bf16", 300) for n in (900, 1500 + 7)], 3, "auto"),
     ("ragged-batch-of-3", [synth.config(2, n=n, budget=8 * 64) for n in (4096, 1500 + 3, 7000 + 11)], 4, "auto"),
     # more sequences than one sweep launch takes: the second launch's sequences use their own rows of the plan
     ("batch-of-40-short", [synth.config(2, n=300 + 23 * i, budget=8 * 40) for i in range(40)], 3, "auto"),
@@ -716,7 +776,7 @@ PLANNED_CASES = [
 
 
 @pytest.mark.parametrize("name,shapes,n_layers,schedule", PLANNED_CASES, ids=[c[0] for c in PLANNED_CASES])
-def test_scores_that_also_form_the_budgets(lava, name, shapes, n_layers, schedule, tuning):
+def test_scores_that_also_form_the_budgets(lava, name, shapes, n_layers, schedule, tuning, launches):
     """lava_window_scores_planned: scores, statistic and the prepared selection are those of the plain calls
     bit for bit, column `layer` of the statistics table receives the statistic, and the budgets equal what
     lava_layer_budgets returns for the same tables on the device, on the host, and the oracle's rule;
@@ -732,8 +792,8 @@ def test_scores_that_also_form_the_budgets(lava, name, shapes, n_layers, schedul
     k = torch.cat([lava.to_device(i.k, sh0.dtype).reshape(-1) for i in inps])
     v = torch.cat([lava.to_device(i.v, sh0.dtype).reshape(-1) for i in inps])
     lens = [s.n for s in shapes]
-    s0, vb0, e0 = lava.lava_window_scores(desc, lens, q, k, v)
-    torch.cuda.synchronize()
+    (s0, vb0, e0), count = launches(lambda: lava.lava_window_scores(desc, lens, q, k, v))
+    assert count["poolstat"] == (batch if "split" in name else 0)
     e_new = e0.cpu().numpy()
     for trial, layer in enumerate(sorted({0, n_layers // 2, n_layers - 1})):
         # statistics of the other layers around this one's, bounds that pin some layers on either side

@@ -67,22 +67,25 @@ def test_batch_of_whole_rounds(lava):
     check(shapes, inps, run(lava, desc, shapes, inps))
 
 
+# 5 heads a group: its parts meet in one workgroup or, with 8 tiles a compute unit, in memory; 9: always in memory
+@pytest.mark.parametrize("heads", [5, 9])
 @pytest.mark.parametrize("n", [40, 1024 + 8, 2049 + 8, 8000, 8500])
 @pytest.mark.parametrize("kind", ["lava", "lse", "attention"])
-def test_split_group(lava, n, kind):
-    """A group swept in two parts: the raw scores the parts join start from zero whichever kernel is the call's first
+def test_split_group(lava, n, kind, heads, launches):
+    """A group swept in parts: the raw scores the parts join start from zero whichever kernel is the call's first
     (statistics, value norms, the fill of the attention score), also in a workspace full of large floats, and the
     pooling launch takes 4 or 8 entries per thread (8 where 64 heads leave the workspace few partials)."""
-    print(f"split group {kind} n={n}", flush=True)
-    s = synth.LayerShape(320, 64, 64, n, 8, "bf16", 0, heavy_count=64)
+    print(f"split group {kind} n={n} {heads} heads", flush=True)
+    hq = 64 * heads
+    s = synth.LayerShape(hq, 64, 64, n, 8, "bf16", 0, heavy_count=64)
     i = synth.gen_layer(s, n)
-    desc = lava.LayerDesc.make(320, 64, 64, 8, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION if kind == "attention" else lava.LAVA_SCORE_LAVA)
+    desc = lava.LayerDesc.make(hq, 64, 64, 8, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION if kind == "attention" else lava.LAVA_SCORE_LAVA)
     q, k, v = (lava.to_device(a, "bf16") for a in (i.q_win, i.k, i.v))
     lse = torch.from_numpy(O.window_lse(*i.f64()[:2]).astype(np.float32)).cuda() if kind == "lse" else None
     need = lava.lava_window_scores_workspace_bytes(desc, 1, n)
     ws = torch.full((need,), 0x7E, dtype=torch.uint8, device="cuda")
-    scores, _, _ = lava.lava_window_scores(desc, [n], q, k, v, lse=lse, workspace=ws)
-    torch.cuda.synchronize()
+    (scores, _, _), count = launches(lambda: lava.lava_window_scores(desc, [n], q, k, v, lse=lse, workspace=ws))
+    assert count["poolstat"] == (1 if heads == 9 or (n == 1024 + 8 and kind != "lse") else 0)
     want = O.lava_scores(*i.f64(), 8, 7, use_value_norm=kind != "attention")[0]
     got = scores.cpu().numpy().reshape(64, n)[:, : n - 8].astype(np.float64)
     mask = want > 1e-30 * want.max()
@@ -128,17 +131,21 @@ def test_sequence_alone_and_its_groups_parts(lava, dtype, d, G, n, apart, kind, 
     assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
 
 
-def test_split_group_fill_is_no_sweep(lava):
+# 36 on 4 heads: the group is split and its raw scores are cleared; 28 on 4: nothing to clear
+@pytest.mark.parametrize("hq", [28, 36])
+def test_split_group_fill_is_no_sweep(lava, hq, launches):
     """The attention score's fill launch writes a float per token and head (2 MB here), the score kernel reads a row of 128:
     cleared by one or two workgroups the fill took longer than the scores (58 us of events against 48), by many 6."""
     import ctypes
     print("split group: time of the fill", flush=True)
-    hq, hkv, n = 28, 4, 131072
+    hkv, n = 4, 131072
     g = torch.Generator(device="cuda").manual_seed(1)
     q, k, v = (torch.randn(h, m, 128, device="cuda", generator=g).bfloat16() for h, m in ((hq, 32), (hkv, n), (hkv, n)))
     desc = lava.LayerDesc.make(hq, hkv, 128, 32, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION)
     ws = torch.empty(lava.lava_window_scores_workspace_bytes(desc, 1, n), dtype=torch.uint8, device="cuda")
     names = [lava.lib.lava_prof_kernel_name(i) for i in range(lava.lib.lava_prof_kernel_count())]
+    _, count = launches(lambda: lava.lava_window_scores(desc, [n], q, k, v, workspace=ws))
+    assert count["poolstat"] == (1 if hq == 36 else 0)
     best = {b"vnorm": 1e9, b"scores": 1e9}
     try:
         for _ in range(8):

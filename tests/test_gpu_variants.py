@@ -49,14 +49,18 @@ TOKEN_NORM_CASES = [
     ("cfg1", synth.config(1), None),
     ("cfg2-4k", synth.config(2, n=4096 + 77), None),
     ("cfg2-9k-narrow", synth.config(2, n=9000 + 5), "narrow"),
-    ("bf16-G8-two-chunks", synth.LayerShape(16, 2, 128, 2100, 32, "bf16", 300), None),
+    ("bf16-G8-two-chunks", synth.LayerShape(16, 2, 128, 2100, 32, "bf16", 300), None),     # both in one workgroup
+    ("bf16-G16-split", synth.LayerShape(32, 2, 128, 2100, 32, "bf16", 300), None),         # over workgroups
+    ("f32-G9-d64-split", synth.LayerShape(18, 2, 64, 1700, 32, "f32", 300), None),
+    ("f32-G6-d64-three-chunks", synth.LayerShape(12, 2, 64, 1111, 32, "f32", 300), None),
+    ("bf16-G7-split-by-length", synth.LayerShape(14, 2, 128, 6000, 32, "bf16", 300), None),
     ("f32-d128", synth.LayerShape(8, 2, 128, 1111, 32, "f32", 300), None),
     ("bf16-d64-pool3", synth.LayerShape(8, 4, 64, 3000, 16, "bf16", 400, pool_kernel=3), None),
 ]
 
 
 @pytest.mark.parametrize("name,sh,shape", TOKEN_NORM_CASES, ids=[c[0] for c in TOKEN_NORM_CASES])
-def test_token_norm_score(lava, name, sh, shape, tuning):
+def test_token_norm_score(lava, name, sh, shape, tuning, launches):
     say(f"variant: per-token value-norm score, {name}")
     if shape:
         tuning(sweep_shape=shape)
@@ -64,8 +68,8 @@ def test_token_norm_score(lava, name, sh, shape, tuning):
     desc = lava.LayerDesc.make(sh.n_q_heads, sh.n_kv_heads, sh.head_dim, sh.window, sh.dtype,
                                pool_kernel=sh.pool_kernel, score_kind=lava.LAVA_SCORE_TOKEN_NORM)
     q, k, v = (lava.to_device(a, sh.dtype) for a in (inp.q_win, inp.k, inp.v))
-    scores, vbar, stat = lava.lava_window_scores(desc, [sh.n], q, k, v)
-    torch.cuda.synchronize()
+    (scores, vbar, stat), count = launches(lambda: lava.lava_window_scores(desc, [sh.n], q, k, v))
+    assert count["poolstat"] == (1 if "split" in name else 0 if "chunks" in name else count["poolstat"])
     qf, kf, vf = inp.f64()
     want, want_vbar = O.token_norm_scores(qf, kf, vf, sh.window, sh.pool_kernel)
     got = scores.cpu().numpy().reshape(sh.n_kv_heads, sh.n)
