@@ -93,11 +93,15 @@ typedef struct lava_tuning {
   int32_t sweep_shape;          /* 0 library's choice, 1 wide (one workgroup per compute unit),
                                    2 narrow (two per compute unit), where the kernels have both */
   int32_t sweep_workgroups;     /* workgroups a sweep launch aims for, 1..65536                */
-  int32_t sweep_schedule;       /* 0 library's choice (today: 3 for a launch of one sequence, else
-                                   1), 1 three launches (value norms, statistics, scores), 2 value
-                                   norms, then one persistent launch for statistics and scores
-                                   where the shape allows it, 3 value norms inside the statistics
-                                   launch, then scores.  All give bit-identical results          */
+  int32_t sweep_schedule;       /* 0 library's choice (today: 3 for a launch of one sequence, and of
+                                   several with up to 512 tiles of 32 keys, all KV heads counted, per
+                                   compute unit, else 1), 1 three launches (value norms, statistics,
+                                   scores), 2 value norms, then one persistent launch for statistics
+                                   and scores where the shape allows it (window <= 32; bf16: G <= 4,
+                                   f32: G <= 2; not groups of two heads with window <= 16 or of three
+                                   and four with window <= 8; no caller's log-sum-exp; other calls run
+                                   as 1), 3 value norms inside the statistics launch, then scores.
+                                   All give bit-identical results                                 */
   int32_t decode_rows_per_unit; /* rows of one head per decode work unit, 128..8192            */
   int32_t barrier_spin_limit;   /* polls of a grid-wide wait before it gives up (default 2^18) */
   int32_t sweep_orphan_units;   /* testing aid for the persistent sweep: the owners leave every n-th
@@ -467,7 +471,11 @@ int32_t lava_cascade_step(const lava_layer_desc* desc, int32_t layer, int64_t n,
                           int64_t total_budget, lava_cascade_state* state, int64_t* budgets,
                           void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Bytes of device workspace lava_decode_attention needs.  Returns 0 for invalid arguments. */
+/* Bytes of device workspace lava_decode_attention needs for exactly these arguments; 0 for invalid ones.
+ * Not a bound for smaller ones: a step is cut into units by what fills the device, so the size goes up and
+ * down (by up to a factor of two) as the batch, rows_capacity or tail_len grows.  A workspace for many steps
+ * has the largest size over the values it will see; one that is too small is refused
+ * (LAVA_ERR_WORKSPACE). */
 size_t lava_decode_workspace_bytes(const lava_layer_desc* desc, int32_t batch, int64_t rows_capacity,
                                    int64_t tail_len);
 

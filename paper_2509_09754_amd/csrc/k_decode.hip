@@ -522,7 +522,8 @@ int32_t launch_one(const DecodeArgs& a, int batch, hipStream_t s) {
 }
 
 // A number that no other call of this process uses and that memory holds by chance once in 2^64 words: a mixed
-// counter (a bijection of 64 bits) from a start of its own in every process.
+// counter (a bijection of 64 bits) from a start of its own in every process.  The mixing and the counter's step are
+// those of SplitMix64 (Steele, Lea, Flood, "Fast splittable pseudorandom number generators", 2014).
 unsigned long long mix64(unsigned long long x) {
   x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
   x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;

@@ -19,18 +19,30 @@
 //    such a buffer may sit in the writer's L2 past the ticket; a plain load may hit a stale line.
 //    Published buffers in this library: the statistic partials (ent_part), the statistics partials
 //    of the persistent sweep and its unit / completion words; of the selection the histograms, the
-//    segments of keys, the exchange words (one per workgroup), the state words and, if prepared, head_counts.
+//    segments of keys, the exchange words (one per workgroup), the state words (the outcome among them)
+//    and, if prepared, head_counts; of a decode step the units' partials (part_ml, part_acc) and flags.
 //  * The selection's segments and exchange words: every wavefront drains its stores to the workgroup's
 //    segment, a workgroup barrier follows, then one lane stores the word with the segment's length and
 //    the epoch; whoever has seen the epoch finds the keys.  Segment and word are written again in a
 //    later epoch only behind a grid-wide wait, at which every workgroup arrives after it has read all
 //    words of the epoch before (whose keys nobody reads: a segment was too small for them).
-//  * Counters and tickets must be zero before the launch that uses them: they are cleared by an
+//  * The selection's outcome: one word, open at first, moved once and by compare-and-swap alone to "complete"
+//    (by whoever has seen all words of the last exchange) or "failed" (by whoever's wait is over its
+//    limit); a workgroup that finds it decided the other way follows, and one outvoted by completion goes on
+//    to read the words, which are then all in place.  A grid-wide wait that gives up stores "failed"
+//    directly: its workgroup has not published its word of the exchange, so nobody can have proposed completion.
+//  * The decode step's flags: a unit's partials are stored, the workgroup drains them (every wavefront, then a
+//    barrier), one lane stores the flag, DRAINS AGAIN and only then reads the flags of the head.  Of any
+//    two workgroups the one whose flag became visible later therefore reads both, so at least one workgroup of a head
+//    finds all its flags.  The workspace may hold anything: a flag counts only if it equals the call's
+//    tag, which no other call uses, and is cleared by whoever merges the head.
+//  * Counters, tickets and the outcome (the decode step has none of them) must be zero before the launch that uses them: they are cleared by an
 //    EARLIER kernel of the same call on the same stream (the value-norm / statistics launch, the
 //    selection's init kernel, a cascade step's plan kernel) or by the same kernel before a grid-wide wait that every workgroup passes;
 //    never by a memset node (a caller may capture the calls in a graph).
-//  * Stress test: tests/test_gpu_parity.py runs launches of over a thousand workgroups thirty times and
-//    requires the bits of the first run every time.
+//  * Stress tests: tests/test_gpu_parity.py runs launches of over a thousand workgroups thirty times and
+//    requires the bits of the first run every time, and prepared selections whose waits are limited to
+//    a few polls; tests/test_gpu_decode_units.py replays decode steps over workspaces of any contents.
 #pragma once
 
 #include <hip/hip_runtime.h>
