@@ -96,6 +96,7 @@ struct DecodeArgs {
   int H, H_kv, G;
   int tiles_per_unit;              // C / 32, a multiple of kDecWaves
   int units_bound;                 // grid.x: units a sequence can have at most
+  int turns;                       // the sequences take turns in the order of the workgroups
   float c2;                        // softmax scale * log2 e
   float2* part_ml;                 // [batch][units_bound][GP]  (max in log2 units, sum)
   float* part_acc;                 // [batch][units_bound][GP][D]
@@ -262,14 +263,23 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
   __shared__ float s_m[kDecWaves][GP], s_l[kDecWaves][GP];
 
   const int lane = threadIdx.x & 63, wave = wave_index();
-  const int b = blockIdx.y;
+  // Sequences take turns, their first units before their second ones: the workgroups without a unit then come last, and the
+  // others spread evenly over the XCDs, which get every eighth workgroup each (turned by one from unit to unit, or
+  // a batch of eight would have a sequence's units on one XCD).
+  unsigned int unit = blockIdx.x;
+  int b = blockIdx.y;
+  if (a.turns) {                                            // uniform
+    const unsigned int id = blockIdx.y * gridDim.x + blockIdx.x, n = gridDim.y;
+    unit = id / n;
+    b = (int)((id % n + unit % n) % n);
+  }
   const UnitMap um = map_units(a.head_offsets + (long long)b * (a.H_kv + 1), a.H_kv, a.rows_capacity,
                                a.tiles_per_unit, a.tail_len, lane);
   const bool bad = !um.usable || um.total > (unsigned int)a.units_bound;
-  if (blockIdx.x == 0) fill_heads<D>(a, b, um, bad);
-  if (bad || blockIdx.x >= um.total) return;                // uniform: nothing to follow, or no such unit
-  const int g = __builtin_ctzll(__ballot(um.incl > blockIdx.x));
-  const long long u = (long long)blockIdx.x - ((long long)lane_value(um.incl, g) - (long long)lane_value(um.cnt, g));
+  if (unit == 0u) fill_heads<D>(a, b, um, bad);
+  if (bad || unit >= um.total) return;                      // uniform: nothing to follow, or no such unit
+  const int g = __builtin_ctzll(__ballot(um.incl > unit));
+  const long long u = (long long)unit - ((long long)lane_value(um.incl, g) - (long long)lane_value(um.cnt, g));
   const long long packed_tiles = lane_value(um.packed, g);
   const long long off_g = lane_value64(um.off, g), len_g = lane_value64(um.len, g);
   const long long tail_tiles = ceil_div(a.tail_len, kTileKeys);
@@ -462,7 +472,7 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
     for (int e = 0; e < kDpl; ++e) s_acc[wave][t][lane * kDpl + e] = acc[t][e];
   __syncthreads();
   const int mine = (int)lane_value(um.cnt, g);               // units of the head
-  const long long slot = (long long)b * a.units_bound + blockIdx.x;
+  const long long slot = (long long)b * a.units_bound + unit;
   constexpr int kPairs = GP * D / 2;
 #pragma unroll
   for (int j = 0; j < (kPairs + kDecThreads - 1) / kDecThreads; ++j) {
@@ -622,6 +632,7 @@ int32_t launch_decode(const lava_layer_desc& d, int32_t batch, const void* q, co
   a.G = d.n_q_heads / d.n_kv_heads;
   a.tiles_per_unit = p.rows_per_unit / kTileKeys;
   a.units_bound = (int)p.units_bound;
+  a.turns = batch > 1 && p.units_bound * batch < (int64_t)1 << 32 ? 1 : 0;
   const float scale = d.softmax_scale > 0.0f ? d.softmax_scale : 1.0f / sqrtf((float)d.head_dim);
   a.c2 = scale * kLog2e;
   a.part_ml = reinterpret_cast<float2*>(static_cast<char*>(ws) + p.off_ml);

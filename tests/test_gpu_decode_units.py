@@ -90,3 +90,21 @@ def test_replays_on_changing_heads(lava):
         c.check(di)
         c.run()                                                # an ordinary call in between, on the same workspace
         c.check(di)
+
+
+@pytest.mark.parametrize("batch", [2, 3, 8, 16, 33])
+def test_sequences_take_turns(lava, batch):
+    """Sequences of very different length, some with nothing, one of them alone with many units: every unit of every sequence is
+    done by one workgroup, whatever the batch."""
+    print(f"decode units: {batch} sequences in turn", flush=True)
+    H, Hkv, d = 8, 2, 64
+    rows = [(0, 1, 130, 700, 40)[i % 5] for i in range(batch)]
+    rows[batch // 2] = 3000
+    lava.set_tuning(decode_rows_per_unit=128)
+    di = synth.gen_decode(H, Hkv, d, "bf16", rows, 4, tail_len=33, tail_capacity=40)
+    c = Call(lava, di, H, Hkv, d)
+    lava.set_tuning(decode_rows_per_unit=128)
+    for _ in range(2):
+        c.run()
+        c.check(di)
+    lava.set_tuning()
