@@ -571,31 +571,35 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   const int64_t step = kTileKeys * kDecWaves;
   const int64_t tail_tiles = (tail_len + kTileKeys - 1) / kTileKeys;
   const int64_t total = (int64_t)batch * (rows_capacity + (int64_t)d.n_kv_heads * tail_tiles * kTileKeys);
-  // Rows per unit: the device holds two workgroups per compute unit at a time; the units should fill whole rounds of
-  // those, with as few units as that allows (every unit pays its set-up and leaves a partial result to merge).
-  // A head is expected to waste half a unit.  One round if heads are then still cut, 1.33 units a head or more on average,
-  // which evens them out (16 x 8192 rows: 384 rows a unit, one round, 19.5 us, 256, two rounds, 22.4; 32 x 8192, on the
-  // line: 768, one round, 35.4, 384 38.1), and its units are no longer than 1280 rows or a quarter of a head: the last ones
-  // end unevenly by as much (20 x 32768: 1536, one round, 80.0, 768, two, 67.7; 16 x 32768: 1280, one round, 48.7, 640
-  // 52.8; 8 x 100000, 4 KV heads: 1792, one round, 88.8, 896 99.0; one sequence of a million rows: 2048, one round, 109,
-  // 1024 122).  bf16 with d_h 64, of which four workgroups share a compute unit, so that one round of two leaves half the
-  // wavefronts out: 384 rows or an eighth of a head (24 x 8192: 512, one round, 19.2, 256 17.9; 32 x 8192: 768 23.6, 384
-  // 20.6; 8 x 100000: 51.7 and 47.7).  Otherwise at least two rounds, so that the dispatcher can even them out (64 x 8192
-  // rows: 768, two rounds, 63.8 us, 2048, one round, 73.8).
+  // Rows per unit: the units should fill whole rounds of the workgroups the device holds at a time (two per compute unit; one
+  // with rows of 512 bytes, whose ring takes 128 KB of LDS), with as few units as that allows (every unit pays its set-up and
+  // leaves a partial result to merge).  A head is expected to waste half a unit; a sequence of one head wastes what it does.
+  // One round (12 x 32768 rows on 8 KV heads: 896 rows a unit, one round, 40.8 us, 512, two, 44.1; f32 128.2 -> 95.9 with
+  // 896, which is two rounds there) if its units are no longer than one and a half heads (of 256 rows, two: 32 KV heads, 12 x
+  // 4096: 10.2, with 128 14.4) and no longer than 1280 rows or a quarter of a head: the last ones end unevenly by as much
+  // (7 heads a group, 24 x 32768: 1920, one round, 104.7, 896, two, 94.3).
+  // bf16 with d_h 64, of which four workgroups share a compute unit, so that one round of two leaves half the wavefronts
+  // out: 256 rows or an eighth of a head (4 KV heads, 16 x 8192: 384, one round, 16.2, 256, two, 15.5).
+  // Heads of many units are merged by one workgroup each, about 0.11 us a unit, where 128 more rows in a unit are 1.6 us: no
+  // fewer than the root of 8 rows a head (one head of 32768 rows: 128 39.3, 512 23.4; of 100000: 256 61.9, 896 35.7).
   const bool small = d.head_dim == 64 && d.dtype == LAVA_BF16;
-  const int64_t one_round = small ? 384 : 1280, per_head = small ? 8 : 4;
-  const int64_t resident = 2 * (int64_t)device_cus();
+  const int64_t one_round = small ? 256 : 1280, per_head = small ? 8 : 4, most = 16 * step;
+  const int64_t resident = (d.head_dim == 128 && d.dtype == LAVA_F32 ? 1 : 2) * (int64_t)device_cus();
   const int64_t heads = (int64_t)batch * d.n_kv_heads;
-  int64_t c = 16 * step;
-  for (int64_t rounds = 1; rounds <= 64; ++rounds) {
-    const int64_t room = rounds * resident - heads / 2;
-    if (room <= 0) continue;
-    c = ((total + room - 1) / room + step - 1) / step * step;
-    if (rounds == 1 && c > step && (4 * c * heads > 3 * total || (c > one_round && per_head * c * heads > total))) continue;
-    if (c <= 16 * step) break;
+  const auto units = [&](int64_t rows) {
+    if (d.n_kv_heads == 1) return batch * ((rows_capacity + tail_tiles * kTileKeys + rows - 1) / rows);
+    return total / rows + heads / 2;
+  };
+  int64_t rounds = (units(most) + resident - 1) / resident, c;
+  if (rounds < 1) rounds = 1;
+  for (;; ++rounds) {
+    for (c = step; c < most && units(c) > rounds * resident; c += step) {}
+    if (rounds > 1 || c == step || (c == 2 * step && c * heads <= 2 * total) ||
+        (2 * c * heads <= 3 * total && (c <= one_round || per_head * c * heads <= total)))
+      break;
   }
-  if (c < step) c = step;
-  if (c > 16 * step) c = 16 * step;
+  const int64_t merged = (int64_t)(sqrt(8.0 * (double)total / (double)heads) / step + 0.5) * step;
+  if (c < merged) c = merged < most ? merged : most;
   if (tuning().decode_rows_per_unit >= step) c = tuning().decode_rows_per_unit / step * step;   // caller's tuning
   p.rows_per_unit = (int)c;
   p.group_pad = padded_group(d.n_q_heads / d.n_kv_heads);
