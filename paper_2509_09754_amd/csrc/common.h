@@ -222,7 +222,8 @@ int32_t launch_compact_inplace(const lava_layer_desc& d, int n_layers, const int
 struct DecodePlan {
   int rows_per_unit;     // rows of one head a workgroup handles
   int group_pad;         // G rounded up to 1, 2, 4 or 8
-  int64_t units_bound;   // units a sequence can have at most (grid.x)
+  int64_t units_bound;   // units a sequence can have at most
+  bool turns;            // sequences take turns in the order of the workgroups
   size_t off_ml, off_acc, off_flags, bytes;
 };
 DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t rows_capacity, int64_t tail_len);

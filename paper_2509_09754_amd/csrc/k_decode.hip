@@ -95,8 +95,9 @@ struct DecodeArgs {
   long long tail_len, tail_capacity;
   int H, H_kv, G;
   int tiles_per_unit;              // C / 32, a multiple of kDecWaves
-  int units_bound;                 // grid.x: units a sequence can have at most
-  int turns;                       // the sequences take turns in the order of the workgroups
+  int units_bound;                 // units a sequence can have at most
+  int turns;                       // grid: 1 [batch][units_bound], the sequences take turns; 0 [units_bound][batch]
+  unsigned int turn_shift, turn_mask;   // unit u of sequence b is in place b - ((u >> shift) & mask) of the sequences' turn
   float c2;                        // softmax scale * log2 e
   float2* part_ml;                 // [batch][units_bound][GP]  (max in log2 units, sum)
   float* part_acc;                 // [batch][units_bound][GP][D]
@@ -264,14 +265,14 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
 
   const int lane = threadIdx.x & 63, wave = wave_index();
   // Sequences take turns, their first units before their second ones: the workgroups without a unit then come last, and the
-  // others spread evenly over the XCDs, which get every eighth workgroup each (turned by one from unit to unit, or
-  // a batch of eight would have a sequence's units on one XCD).
+  // others spread evenly over the XCDs, which get every eighth workgroup each (turned from unit to unit where the number of
+  // sequences would have a sequence's units on few of the XCDs).
   unsigned int unit = blockIdx.x;
   int b = blockIdx.y;
   if (a.turns) {                                            // uniform
-    const unsigned int id = blockIdx.y * gridDim.x + blockIdx.x, n = gridDim.y;
-    unit = id / n;
-    b = (int)((id % n + unit % n) % n);
+    unit = blockIdx.y;
+    b = (int)blockIdx.x + (int)((unit >> a.turn_shift) & a.turn_mask);
+    if (b >= (int)gridDim.x) b -= (int)gridDim.x;
   }
   const UnitMap um = map_units(a.head_offsets + (long long)b * (a.H_kv + 1), a.H_kv, a.rows_capacity,
                                a.tiles_per_unit, a.tail_len, lane);
@@ -527,7 +528,7 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DecodeArgs a) {
 template <int DT, int D, int GP>
 int32_t launch_one(const DecodeArgs& a, int batch, hipStream_t s) {
   ProfScope ps(KID_DECODE, s);
-  hipLaunchKernelGGL((decode_kernel<DT, D, GP>), dim3(a.units_bound, batch), dim3(kDecThreads), 0, s, a);
+  hipLaunchKernelGGL((decode_kernel<DT, D, GP>), a.turns ? dim3(batch, a.units_bound) : dim3(a.units_bound, batch), dim3(kDecThreads), 0, s, a);
   return launch_status();
 }
 
@@ -607,6 +608,13 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   const int64_t tiles = (rows_capacity + kTileKeys - 1) / kTileKeys + d.n_kv_heads * (1 + tail_tiles);
   p.units_bound = (tiles + c / kTileKeys - 1) / (c / kTileKeys) + d.n_kv_heads;
   if (p.units_bound < 1) p.units_bound = 1;
+  // Sequences take turns (48 x 8192 rows on 2 KV heads, 487 units for 512 places: 60.5 us one sequence after the other, 46.3
+  // in turn; f32, d_h 128, 100 x 1024 on 1, two units and two idle workgroups a sequence: 50.7 and 34.6), but for several
+  // rounds that end with a sixteenth of the places free, where few workgroups are idle: there is nothing to gain then, and
+  // rows at the same distance in every sequence are read together (64 x 8192, 939 units: 65.1 and 67.2).
+  const int64_t filled = units(c), last = (filled + resident - 1) / resident;
+  const bool even = last > 1 && 16 * filled <= 15 * last * resident && 4 * filled >= 3 * batch * p.units_bound;
+  p.turns = batch > 1 && !even && p.units_bound <= 65535;     // the units are the grid's y then
   const size_t slots = (size_t)batch * (size_t)p.units_bound * p.group_pad;
   p.off_ml = 0;
   p.off_acc = align_up(slots * sizeof(float2));
@@ -636,7 +644,12 @@ int32_t launch_decode(const lava_layer_desc& d, int32_t batch, const void* q, co
   a.G = d.n_q_heads / d.n_kv_heads;
   a.tiles_per_unit = p.rows_per_unit / kTileKeys;
   a.units_bound = (int)p.units_bound;
-  a.turns = batch > 1 && p.units_bound * batch < (int64_t)1 << 32 ? 1 : 0;
+  a.turns = p.turns ? 1 : 0;
+  // A workgroup's place among those of its unit and all before it, modulo 8, is its XCD.  An odd batch moves a sequence on by
+  // itself; an even one of eight and more by one place a unit; two, four and six cover their XCDs first.
+  const unsigned int even = (unsigned int)batch & (0u - (unsigned int)batch);   // largest power of two that divides it
+  a.turn_shift = batch >= 8 || even == 1u ? 0u : even == 2u ? 2u : 1u;
+  a.turn_mask = even == 1u ? 0u : batch >= 8 ? 7u : even - 1u;
   const float scale = d.softmax_scale > 0.0f ? d.softmax_scale : 1.0f / sqrtf((float)d.head_dim);
   a.c2 = scale * kLog2e;
   a.part_ml = reinterpret_cast<float2*>(static_cast<char*>(ws) + p.off_ml);

@@ -92,18 +92,22 @@ def test_replays_on_changing_heads(lava):
         c.check(di)
 
 
-@pytest.mark.parametrize("batch", [2, 3, 8, 16, 33])
-def test_sequences_take_turns(lava, batch):
+# numbers of sequences that are turned by one a unit, after two or four units, and not at all; one round of 512 workgroups (in
+# turn) and two that are not full (one after the other)
+@pytest.mark.parametrize("units", [510, 760])
+@pytest.mark.parametrize("batch", [2, 3, 4, 6, 8, 9, 16, 33])
+def test_sequences_take_turns(lava, batch, units):
     """Sequences of very different length, some with nothing, one of them alone with many units: every unit of every sequence is
     done by one workgroup, whatever the batch."""
-    print(f"decode units: {batch} sequences in turn", flush=True)
+    print(f"decode units: {batch} sequences in turn, {units} units", flush=True)
     H, Hkv, d = 8, 2, 64
-    rows = [(0, 1, 130, 700, 40)[i % 5] for i in range(batch)]
-    rows[batch // 2] = 3000
+    # capacity / 128 + 1 (two appended tiles a head) + 1 (half a unit a head) units a sequence are expected
+    cap = (units // batch - 2) * 128
+    rows = [min((0, 1, 130, 700, 40)[i % 5], cap) for i in range(batch)]
+    rows[batch // 2] = cap - 40
     lava.set_tuning(decode_rows_per_unit=128)
-    di = synth.gen_decode(H, Hkv, d, "bf16", rows, 4, tail_len=33, tail_capacity=40)
+    di = synth.gen_decode(H, Hkv, d, "bf16", rows, 4, rows_capacity=cap, tail_len=33, tail_capacity=40)
     c = Call(lava, di, H, Hkv, d)
-    lava.set_tuning(decode_rows_per_unit=128)
     for _ in range(2):
         c.run()
         c.check(di)
