@@ -585,7 +585,8 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   // fewer than the root of 8 rows a head (one head of 32768 rows: 128 39.3, 512 23.4; of 100000: 256 61.9, 896 35.7).
   const bool small = d.head_dim == 64 && d.dtype == LAVA_BF16;
   const int64_t one_round = small ? 256 : 1280, per_head = small ? 8 : 4, most = 16 * step;
-  const int64_t resident = (d.head_dim == 128 && d.dtype == LAVA_F32 ? 1 : 2) * (int64_t)device_cus();
+  const bool one_per_cu = d.head_dim == 128 && d.dtype == LAVA_F32;
+  const int64_t resident = (one_per_cu ? 1 : 2) * (int64_t)device_cus();
   const int64_t heads = (int64_t)batch * d.n_kv_heads;
   const auto units = [&](int64_t rows) {
     if (d.n_kv_heads == 1) return batch * ((rows_capacity + tail_tiles * kTileKeys + rows - 1) / rows);
@@ -609,11 +610,12 @@ DecodePlan make_decode_plan(const lava_layer_desc& d, int32_t batch, int64_t row
   p.units_bound = (tiles + c / kTileKeys - 1) / (c / kTileKeys) + d.n_kv_heads;
   if (p.units_bound < 1) p.units_bound = 1;
   // Sequences take turns (48 x 8192 rows on 2 KV heads, 487 units for 512 places: 60.5 us one sequence after the other, 46.3
-  // in turn; f32, d_h 128, 100 x 1024 on 1, two units and two idle workgroups a sequence: 50.7 and 34.6), but for several
-  // rounds that end with a sixteenth of the places free, where few workgroups are idle: there is nothing to gain then, and
-  // rows at the same distance in every sequence are read together (64 x 8192, 939 units: 65.1 and 67.2).
+  // in turn; f32, d_h 128, 100 x 1024 on 1, two units and two idle workgroups a sequence: 63 and 36), unless two workgroups
+  // share a compute unit, few are idle and a sixteenth of the last round's places is free: there is little to gain then, and
+  // rows at the same distance in every sequence are read together (64 x 8192, 939 units: 64.6 and 66.7; 16 x 8192, 405: 20.3
+  // and 20.9).
   const int64_t filled = units(c), last = (filled + resident - 1) / resident;
-  const bool even = last > 1 && 16 * filled <= 15 * last * resident && 4 * filled >= 3 * batch * p.units_bound;
+  const bool even = !one_per_cu && 16 * filled <= 15 * last * resident && 10 * filled >= 7 * batch * p.units_bound;
   p.turns = batch > 1 && !even && p.units_bound <= 65535;     // the units are the grid's y then
   const size_t slots = (size_t)batch * (size_t)p.units_bound * p.group_pad;
   p.off_ml = 0;
