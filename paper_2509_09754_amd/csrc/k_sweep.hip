@@ -1672,29 +1672,33 @@ SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tok
   // needs the workgroup's span of raw scores in LDS: a bounded number of tiles per workgroup
   p.fused_pool = p.n_chunks == 1;
   const int64_t fused_cap = p.narrow ? kFusedTilesNarrow : kFusedTilesWide;
+  // workgroups that fill whole rounds of `wgs` with spans of at most `cap` tiles
+  const auto whole_rounds = [](int64_t tiles, int64_t cap, int64_t wgs) { return (tiles + cap * wgs - 1) / (cap * wgs) * wgs; };
+  const int64_t own_tiles = n_tiles * d.n_kv_heads;
   // bounds that hold for either shape, alone or in a batch, and never shrink when n grows: a
   // workspace sized for the longest sequence of a batch must also hold the (differently split)
   // partials of every shorter one
-  int64_t bx_alone = 2 * device_wgs / ((int64_t)d.n_kv_heads * p.n_chunks);
-  if (target_wgs / ((int64_t)d.n_kv_heads * p.n_chunks) > bx_alone) bx_alone = target_wgs / ((int64_t)d.n_kv_heads * p.n_chunks);
-  if (bx_alone < 1) bx_alone = 1;
-  const int64_t capped = (n_tiles + kFusedTilesNarrow - 1) / kFusedTilesNarrow;
-  p.blocks_x_bound = (int)(bx_alone > capped ? bx_alone : capped);
+  const int64_t forced = tuning().sweep_workgroups, heads_chunks = (int64_t)d.n_kv_heads * p.n_chunks;
+  int64_t bound = (2 * device_wgs > target_wgs ? 2 * device_wgs : target_wgs) / heads_chunks;
+  if (bound < 1) bound = 1;
+  const auto at_least = [&](int64_t x) { if (bound < x) bound = x; };
+  at_least((n_tiles + kFusedTilesNarrow - 1) / kFusedTilesNarrow);
+  if (p.fused_pool) {
+    at_least(whole_rounds(own_tiles, kFusedTilesWide, forced > 0 ? forced : device_wgs) / d.n_kv_heads);
+    at_least(whole_rounds(own_tiles, kFusedTilesNarrow, forced > 0 ? forced : 2 * device_wgs) / d.n_kv_heads);
+  }
+  p.blocks_x_bound = (int)bound;
   if (p.fused_pool && tpb > fused_cap) {
-    tpb = fused_cap;
-    if (shared) {
-      // Several rounds of workgroups: the batch as a whole is cut into as many workgroups as fill whole
-      // rounds, instead of longest spans whose last round leaves half the device idle (32 sequences of 32768
-      // tokens: 2816 workgroups of up to 96 tiles, 5.5 rounds of 512, 1310 us for the whole stack; 3072 of 86,
-      // 6 rounds, 1290 us).
-      const int64_t all = (batch_tokens + kTileKeys - 1) / kTileKeys * d.n_kv_heads;
-      const int64_t rounds = (all + fused_cap * target_wgs - 1) / (fused_cap * target_wgs);
-      const int64_t fewest = (n_tiles + fused_cap - 1) / fused_cap;
-      int64_t bx = n_tiles * rounds * target_wgs / all;
-      if (bx > p.blocks_x_bound) bx = p.blocks_x_bound;      // what the workspace holds; at least `fewest`
-      if (bx < fewest) bx = fewest;
-      tpb = (n_tiles + bx - 1) / bx;
-    }
+    // Several rounds of workgroups: the launch as a whole is cut into as many workgroups as fill whole
+    // rounds, instead of longest spans whose last round leaves half the device idle (32 sequences of 32768
+    // tokens: 2816 workgroups of up to 96 tiles, 5.5 rounds of 512, 1310 us for the whole stack; 3072 of 86,
+    // 6 rounds, 1290 us; one of 270000, 28 heads on 4, scores alone: 264 of 128 tiles 368 us, 512 of 66 245).
+    const int64_t all = shared ? (batch_tokens + kTileKeys - 1) / kTileKeys * d.n_kv_heads : own_tiles;
+    const int64_t fewest = (n_tiles + fused_cap - 1) / fused_cap;
+    int64_t bx = n_tiles * whole_rounds(all, fused_cap, target_wgs) / all;
+    if (bx > p.blocks_x_bound) bx = p.blocks_x_bound;        // what the workspace holds; at least `fewest`
+    if (bx < fewest) bx = fewest;
+    tpb = (n_tiles + bx - 1) / bx;
   }
   p.tiles_per_block = (int)tpb;
   p.blocks_x = (int)((n_tiles + tpb - 1) / tpb);

@@ -161,3 +161,54 @@ def test_split_group_fill_is_no_sweep(lava, hq, launches):
         lava.lib.lava_prof_enable(0), lava.lib.lava_prof_reset()
     print(best, flush=True)
     assert best[b"vnorm"] < 0.5 * best[b"scores"]
+
+
+# two to four rounds of few workgroups (spans of at most 128 tiles of 32 keys, narrow 96), one chunk and several
+@pytest.mark.parametrize("dtype,d,hq,hkv,wgs,n", [("bf16", 64, 5, 1, 1, 128 * 32 + 1), ("bf16", 128, 4, 2, 2, 4500), ("f32", 64, 8, 1, 1, 7000),
+                                                  ("bf16", 64, 3, 1, 3, 3 * 4096 + 40), ("f32", 128, 2, 1, 1, 3 * 4096 + 1),
+                                                  ("bf16", 128, 6, 3, 2, 4096 + 50)])
+@pytest.mark.parametrize("shape", ["wide", "narrow"])
+@pytest.mark.parametrize("schedule", ["separate", "persistent", "prepass"])
+def test_sequence_alone_of_several_rounds(lava, dtype, d, hq, hkv, wgs, n, shape, schedule, tuning):
+    """A sequence alone whose spans are longer than a workgroup holds is cut into whole rounds of workgroups: the scores are the
+    oracle's, and the workspace of that length holds the partials."""
+    print(f"several rounds, {dtype} d{d} {hq} on {hkv}, {wgs} workgroups, n={n} {shape} {schedule}", flush=True)
+    s = synth.LayerShape(hq, hkv, d, n, 17, dtype, 0, heavy_count=32)
+    i = synth.gen_layer(s, n)
+    tuning(sweep_workgroups=wgs, sweep_shape=shape, sweep_schedule=schedule)
+    desc = lava.LayerDesc.make(hq, hkv, d, 17, dtype)
+    need = lava.lava_window_scores_workspace_bytes(desc, 1, n)
+    buf = torch.full((need + 4096,), 0x7E, dtype=torch.uint8, device="cuda")
+    q, k, v = (lava.to_device(a, dtype) for a in (i.q_win, i.k, i.v))
+    scores, _, _ = lava.lava_window_scores(desc, [n], q, k, v, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x7E).all())
+    want = O.lava_scores(*i.f64(), 17, 7)[0]
+    got = scores.cpu().numpy().reshape(hkv, n)[:, : n - 17].astype(np.float64)
+    mask = want > 1e-30 * want.max()
+    assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,n", [("bf16", 128, 28, 4, 270000), ("bf16", 128, 32, 8, 140000), ("f32", 128, 32, 8, 140000)])
+def test_sequence_alone_fills_its_rounds(lava, dtype, d, hq, hkv, n, tuning):
+    """Just more spans than the device takes at a time: the library's own cut against one of two full rounds, events around
+    the scores.  A last round that is nearly empty takes 1.3 to 1.5 times as long (368 us against 255, 228 against 177, 888 against
+    582)."""
+    print(f"rounds of a sequence alone, {dtype} {hq} on {hkv}, {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v = (torch.randn(h, m, d, device="cuda", generator=g).to(dt) for h, m in ((hq, 32), (hkv, n), (hkv, n)))
+    desc = lava.LayerDesc.make(hq, hkv, d, 32, dtype)
+    best = {}
+    for wgs in (0, 512):
+        tuning(sweep_workgroups=wgs)
+        ws = torch.empty(lava.lava_window_scores_workspace_bytes(desc, 1, n), dtype=torch.uint8, device="cuda")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            lava.lava_window_scores(desc, [n], q, k, v, workspace=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best[wgs] = min(best.get(wgs, 1e9), a.elapsed_time(b))
+    print(best, flush=True)
+    assert best[0] < 1.12 * best[512]
