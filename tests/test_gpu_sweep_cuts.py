@@ -212,3 +212,25 @@ def test_sequence_alone_fills_its_rounds(lava, dtype, d, hq, hkv, n, tuning):
             best[wgs] = min(best.get(wgs, 1e9), a.elapsed_time(b))
     print(best, flush=True)
     assert best[0] < 1.12 * best[512]
+
+
+def test_ragged_batch_of_one_round(lava):
+    """32-bit sequences of d_h 128 whose shares of the device, rounded up, are a few workgroups more than it has: the batch takes
+    little longer than one of equal lengths and as many tokens (254 us and 234), and not a second round (437)."""
+    print("ragged 32-bit batch of one round", flush=True)
+    hq, hkv, d = 12, 2, 128
+    lens = [35828, 21654, 34808, 42833]
+    desc, best = lava.LayerDesc.make(hq, hkv, d, 32, "f32"), {}
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(m * d, device="cuda", generator=g) for m in (4 * hq * 32, hkv * sum(lens), hkv * sum(lens)))
+    for name, ls in (("ragged", lens), ("equal", [33781, 33781, 33781, 33780])):
+        ws = torch.empty(lava.lava_window_scores_workspace_bytes(desc, 4, sum(ls)), dtype=torch.uint8, device="cuda")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            lava.lava_window_scores(desc, ls, q, k, v, workspace=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best[name] = min(best.get(name, 1e9), a.elapsed_time(b))
+    print(best, flush=True)
+    assert best["ragged"] < 1.35 * best["equal"]
