@@ -1620,9 +1620,15 @@ static int sweep_chunks(const lava_layer_desc& d) {
 // workgroup and a short sequence twice or four times the workgroups.  A sequence alone has its group apart where the device
 // has few tiles a compute unit (scores and selection, in one workgroup -> apart):
 //   two chunks, from 1 tile (below it a span is one round of a chunk's wavefronts, make_sweep_plan) to 10: bf16, d_h 128,
-//     40 heads on 8, 9001 tokens 45.9 -> 44.2 us, 14000 51.0 -> 51.5; 10 on 2, 32768 45.7 -> 43.1, 65536 55.8 -> 56.3;
-//     f32, d_h 64, 32 on 8, 9001 50.9 -> 48.0, 20000 68.5 -> 71.4; not where the caller's log-sum-exp leaves one sweep of
-//     the two (bf16, d_h 128, 28 on 4, 9001 28.7 -> 29.8);
+//     40 heads on 8, 9001 tokens 45.9 -> 44.2 us, 14000 51.0 -> 51.5; f32, d_h 64, 32 on 8, 9001 50.9 -> 48.0, 20000 68.5 ->
+//     71.4; bf16 to 20 where the KV heads are two and to 28 where there is one (the more workgroups a head has, the more
+//     partial statistics each of them merges): scores alone, d_h 128, 12 tiles 40.3 -> 38.0 and 43.6 -> 39.3, at 20 and 28
+//     the same; the attention score of one head to 56, since no value rows hide that (28 tiles 63.5 -> 60.3);
+//   bf16, two chunks, from 128 on, where spans kept in LDS need several rounds of workgroups: the attention score (40 on 8,
+//     204800 tokens, d_h 128 286.6 -> 260.3, d_h 64 191.6 -> 178.5; with d_h 128 from 56: 64 tiles 96.5 -> 95.0, 127 169.6 -> 163.6),
+//     the caller's log-sum-exp (135 tiles 155.2 -> 147.7; with d_h 128 from 72: 100 tiles 126.4 -> 112.9, d_h 64 68.7 -> 72.6; below
+//     that never: 28 on 4, 9001 28.7 -> 29.8), and one or two KV heads (135 tiles, d_h 64 192 -> 167 and 174 -> 164); not the other
+//     scores of more heads (40 on 8, 204800 tokens, d_h 128 354.6 -> 379.8);
 //   f32 with d_h 128, of four wavefronts a workgroup, two chunks, up to 5: 8 on 2, 1024 34.9 -> 34.0, 20000 60.7 -> 58.3; 32
 //     on 8, 9001 72.9 -> 74.7;
 //   three, always (a fourth repeats a head in one workgroup): 12 on 2, 1024 44.7 -> 34.2; 48 on 8, 40000 315 -> 277;
@@ -1634,7 +1640,14 @@ bool sweep_apart(const lava_layer_desc& d, int batch, int64_t n, bool statistics
   const int64_t tiles = (n + kTileKeys - 1) / kTileKeys * d.n_kv_heads, cus = compute_units();
   if (d.dtype == LAVA_F32 && d.head_dim == 128)
     return chunks == 3 || (chunks == 2 && tiles <= 5 * cus) || (chunks == 4 && tiles <= 20 * cus);
-  return statistics && chunks == 2 && tiles > cus && tiles <= 10 * cus;
+  if (chunks != 2) return false;
+  if (d.dtype == LAVA_F32) return statistics && tiles > cus && tiles <= 10 * cus;
+  if (!statistics) return tiles > (d.head_dim == 128 ? 72 : 128) * cus;
+  const bool attention = d.score_kind == LAVA_SCORE_ATTENTION;
+  const int64_t few = d.n_kv_heads == 1 ? (attention ? 56 : 28) : d.n_kv_heads == 2 ? 20 : 10;
+  if (tiles <= few * cus) return tiles > cus;
+  if (attention) return tiles > (d.head_dim == 128 ? 56 : 128) * cus;
+  return d.n_kv_heads <= 2 && tiles > 128 * cus;
 }
 
 SweepPlan make_sweep_plan(const lava_layer_desc& d, int64_t n, int64_t batch_tokens, bool narrow, bool apart) {

@@ -131,7 +131,36 @@ def test_sequence_alone_and_its_groups_parts(lava, dtype, d, G, n, apart, kind, 
     assert np.max(np.abs(got[mask] - want[mask]) / want[mask]) < 1e-5
 
 
-# 36 on 4 heads: the group is split and its raw scores are cleared; 28 on 4: nothing to clear
+# the lines that depend on the number of KV heads and on the score
+@pytest.mark.parametrize("d,hkv,n,kind,apart", [(64, 1, 229376, "lava", 1), (64, 1, 229377, "lava", 0), (128, 2, 81920, "lava", 1),
+                                                (128, 2, 81921, "lava", 0), (128, 1, 229377, "attention", 1), (64, 1, 458753, "attention", 0),
+                                                (128, 8, 57344, "attention", 0), (128, 8, 57345, "attention", 1), (128, 8, 73728, "lse", 0),
+                                                (128, 8, 73729, "lse", 1), (64, 8, 131072, "lse", 0), (64, 8, 131073, "lse", 1),
+                                                (64, 8, 131072, "attention", 0), (64, 8, 131073, "attention", 1), (64, 2, 524288, "lava", 0),
+                                                (64, 2, 524289, "lava", 1), (64, 8, 131073, "lava", 0)])
+def test_long_sequence_alone_and_its_groups_parts(lava, d, hkv, n, kind, apart, launches):
+    """A long sequence alone and beside a short one: the same scores, to the order of their sums, wherever the parts meet."""
+    print(f"parts of a group, d{d} on {hkv} n={n} {kind}", flush=True)
+    G, w, short = 5, 9, 10
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *shape: torch.randn(*shape, device="cuda", generator=g).bfloat16().reshape(-1)
+    q, k, v = rand(2, G * hkv, w, d), rand(hkv, n, d), rand(hkv, n, d)
+    desc = lava.LayerDesc.make(G * hkv, hkv, d, w, "bf16", score_kind=lava.LAVA_SCORE_ATTENTION if kind == "attention" else lava.LAVA_SCORE_LAVA)
+    lse = torch.full((2 * G * hkv, w), 13.0, device="cuda") if kind == "lse" else None
+    need = lava.lava_window_scores_workspace_bytes(desc, 1, n)
+    buf = torch.full((need + 4096,), 0x7E, dtype=torch.uint8, device="cuda")
+    (one, vbar, stat), count = launches(lambda: lava.lava_window_scores(
+        desc, [n], q[: q.numel() // 2], k, v, lse=None if lse is None else lse[: G * hkv], workspace=buf[:need]))
+    assert count["poolstat"] == apart and bool((buf[need:] == 0x7E).all())
+    k2, v2 = torch.cat([k, rand(hkv, short, d)]), torch.cat([v, rand(hkv, short, d)])
+    (two, vbar2, stat2), count = launches(lambda: lava.lava_window_scores(desc, [n, short], q, k2, v2, lse=lse))
+    assert count["poolstat"] == 0
+    torch.testing.assert_close(two[: hkv * n], one, rtol=1e-5, atol=0)
+    assert torch.equal(vbar2[0], vbar[0])
+    torch.testing.assert_close(stat2[0], stat[0], rtol=1e-4, atol=0)
+
+
+# a group split by the length of its sequence, and one that is always split: both clear raw scores
 @pytest.mark.parametrize("hq", [28, 36])
 def test_split_group_fill_is_no_sweep(lava, hq, launches):
     """The attention score's fill launch writes a float per token and head (2 MB here), the score kernel reads a row of 128:
@@ -145,7 +174,7 @@ def test_split_group_fill_is_no_sweep(lava, hq, launches):
     ws = torch.empty(lava.lava_window_scores_workspace_bytes(desc, 1, n), dtype=torch.uint8, device="cuda")
     names = [lava.lib.lava_prof_kernel_name(i) for i in range(lava.lib.lava_prof_kernel_count())]
     _, count = launches(lambda: lava.lava_window_scores(desc, [n], q, k, v, workspace=ws))
-    assert count["poolstat"] == (1 if hq == 36 else 0)
+    assert count["poolstat"] == 1
     best = {b"vnorm": 1e9, b"scores": 1e9}
     try:
         for _ in range(8):
